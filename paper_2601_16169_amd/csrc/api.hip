@@ -118,9 +118,11 @@ static void space_release_device(sqd_space* sp) {
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     sp->diag = sp->ua = nullptr;
-    sp->ab_grp = sp->ab_chunk_pair = sp->ab_rev = sp->kh_tile_off = sp->kh_pairs = sp->kh_map = nullptr;
+    sp->ab_grp = nullptr;
+    sp->ab_chunk_pair = sp->ab_rev = sp->kh_tile_off = sp->kh_pairs = sp->kh_map = nullptr;
     sp->ab_row_order = nullptr;
-    sp->abs_grp = sp->abs_src = nullptr;
+    sp->abs_grp = nullptr;
+    sp->abs_src = nullptr;
     sp->abs_G = sp->abs_nchunks = 0;
     sp->win_P = nullptr;
     sp->win_P_bytes = 0;
@@ -390,7 +392,7 @@ static int build_space_impl(sqd_ctx* ctx, int nalpha, int nbeta, int nw, const u
         return rc;
     }
     ctx->spaces.push_back(sp);
-    if ((rc = sqd_build_values(ctx, sp)) || (rc = sqd_ensure_diag(ctx, sp))) {
+    if ((rc = sqd_alloc_cross_tables(ctx, sp)) || (rc = sqd_build_values(ctx, sp)) || (rc = sqd_ensure_diag(ctx, sp))) {
         sqd_space_free(sp);
         return rc;
     }

@@ -163,7 +163,10 @@ __global__ void __launch_bounds__(256) kb_gather(const bdesc* __restrict__ D, co
         if (d.st->done) continue;
         const T* Y = (const T*)(sizeof(T) == 8 ? (const void*)d.Y64 : (const void*)d.Y32);
         T* S = (T*)(sizeof(T) == 8 ? (void*)d.sout : (void*)d.S32);
-        gather_row<T>(Y, S, d.nb, d.ab64.ldy, d.ab64.bperm, d.a_off, d.a_order[units[u].y], row);
+        const ab_table& tab = aba(d, T()).tab;
+        const gather_args<T> a{Y, d.nb, tab.nslots, tab.perm, d.a_off, S, nullptr, nullptr, nullptr, nullptr};
+        gather_row<T>(a, d.a_order[units[u].y], 1, row);
+        if (STAGED) __syncthreads();
     }
 }
 
@@ -760,7 +763,6 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
         part += d.nblk;
         d.ntx = (int)nblk(d.nb, 64);
         d.nty = (int)nblk(d.na, 64);
-        const int64_t ldy = (int64_t)B.nslices * 64;
         want((void**)&d.V, sizeof(double) * d.n * mmax);
         want((void**)&d.AV, sizeof(double) * d.n * mmax);
         want((void**)&d.T, sizeof(double) * d.n);
@@ -768,13 +770,13 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
         want((void**)&d.sout, sizeof(double) * d.n);
         want((void**)&d.Ct, sizeof(double) * d.n);
         want((void**)&d.Yt, sizeof(double) * d.n);
-        want((void**)&d.Y64, sizeof(double) * (A.nnz_s * ldy + 1));
+        want((void**)&d.Y64, sizeof(double) * (A.nnz_s * B.ab64.nslots + 1));
         if (mixed) {
             want((void**)&d.c32, sizeof(float) * d.n);
             want((void**)&d.Ct32, sizeof(float) * d.n);
             want((void**)&d.Yt32, sizeof(float) * d.n);
             want((void**)&d.S32, sizeof(float) * d.n);
-            want((void**)&d.Y32, sizeof(float) * (A.nnz_s * ldy + 1));
+            want((void**)&d.Y32, sizeof(float) * (A.nnz_s * B.ab32.nslots + 1));
         }
         for (int j = 0; j < d.nblk; ++j) vec.push_back(make_int2(b, j));
         for (int t = 0; t < d.ntx * d.nty; ++t) tr.push_back(make_int2(b, t));
@@ -831,7 +833,6 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
         const spin_tables& A = sp->sp[0];
         const spin_tables& B = sp->sp[1];
         bdesc& d = p.host[b];
-        const int64_t ldy = (int64_t)B.nslices * 64;
         d.diag = sp->diag;
         d.out = vecs[b];
         d.noise = nullptr;
@@ -839,22 +840,16 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
         d.a_order = sp->ab_row_order;
         d.st = p.states + b;
         // same-spin: BB on C (rows alpha, columns beta, diagonal fused), AA on C^T
-        d.aa64 = ss_args<double>{d.Ct, d.Yt, B.n, A.n, A.perm_ss, A.nslices, A.sl_s_off, A.sl_d_off, A.sell_s_pk,
-                                 A.sell_s_v64, A.sell_d_nbr, A.sell_d_v64, B.str, B.nw, nullptr, 0};
-        d.bb64 = ss_args<double>{d.cin, d.sout, A.n, B.n, B.perm_ss, B.nslices, B.sl_s_off, B.sl_d_off, B.sell_s_pk,
-                                 B.sell_s_v64, B.sell_d_nbr, B.sell_d_v64, A.str, A.nw, sp->diag, 1};
-        d.aa32 = ss_args<float>{d.Ct32, d.Yt32, B.n, A.n, A.perm_ss, A.nslices, A.sl_s_off, A.sl_d_off, A.sell_s_pk,
-                                A.sell_s_v32, A.sell_d_nbr, A.sell_d_v32, B.str, B.nw, nullptr, 0};
-        d.bb32 = ss_args<float>{d.c32, d.S32, A.n, B.n, B.perm_ss, B.nslices, B.sl_s_off, B.sl_d_off, B.sell_s_pk,
-                                B.sell_s_v32, B.sell_d_nbr, B.sell_d_v32, A.str, A.nw, nullptr, 1};
+        d.aa64 = ss_args<double>{d.Ct, d.Yt, B.n, A.n, A.ss64, B.ws64, B.str, B.nw, nullptr, 0};
+        d.bb64 = ss_args<double>{d.cin, d.sout, A.n, B.n, B.ss64, A.ws64, A.str, A.nw, sp->diag, 1};
+        d.aa32 = ss_args<float>{d.Ct32, d.Yt32, B.n, A.n, A.ss32, B.ws32, B.str, B.nw, nullptr, 0};
+        d.bb32 = ss_args<float>{d.c32, d.S32, A.n, B.n, B.ss32, A.ws32, A.str, A.nw, nullptr, 1};
         const bool src = !cls2[b] && p.GS;
-        const int* grp = src ? sp->abs_grp : sp->ab_grp;
+        const int2* grp = src ? sp->abs_grp : sp->ab_grp;
         const int* cpair = src ? nullptr : sp->ab_chunk_pair;
         d.abs_src = src ? sp->abs_src : nullptr;
-        d.ab64 = abg_args<double>{d.cin, d.Y64, B.n, ldy, grp, cpair, A.s_pk, B.perm_ab, B.nslices, B.sl_ab_off,
-                                  B.sell_ab_pk};
-        d.ab32 = abg_args<float>{d.c32, d.Y32, B.n, ldy, grp, cpair, A.s_pk, B.perm_ab, B.nslices, B.sl_ab_off,
-                                 B.sell_ab_pk};
+        d.ab64 = abg_args<double>{d.cin, d.Y64, B.n, grp, cpair, B.ab64};
+        d.ab32 = abg_args<float>{d.c32, d.Y32, B.n, grp, cpair, B.ab32};
     }
     if (!ctx->batch_count_host &&
         hipHostMalloc((void**)&ctx->batch_count_host, sizeof(int), hipHostMallocDefault) != hipSuccess) {

@@ -120,8 +120,7 @@ k_same_spin(ss_args<T> a, const T* __restrict__ jk, int norb, const int* __restr
 template <typename T, int KC, int MAXJ>
 __global__ void __launch_bounds__(1024)
 k_ab_direct(const T* __restrict__ C, T* __restrict__ S, int64_t na, int64_t nb, const int* __restrict__ a_off,
-            const uint32_t* __restrict__ a_pk, const int* __restrict__ bperm, int nbslices,
-            const int* __restrict__ bsl_off, const uint32_t* __restrict__ bs_pk, const T* __restrict__ V, int norb,
+            const uint32_t* __restrict__ a_pk, ab_table tab, const T* __restrict__ V, int norb,
             const int* __restrict__ skip) {
     if (skip && *skip) return;
     extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -160,8 +159,7 @@ k_ab_direct(const T* __restrict__ C, T* __restrict__ S, int64_t na, int64_t nb, 
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) {
             const int sl = slice_base + j * nw + wave;
-            if (sl < nbslices) {
-                const int c0 = bsl_off[sl], c1 = bsl_off[sl + 1];
+            if (sl < tab.nslices) {
                 T a = acc[j];
                 auto one = [&](uint32_t e) {
                     const int nbr = (int)(e & SQD_NBR_MASK);
@@ -174,23 +172,18 @@ k_ab_direct(const T* __restrict__ C, T* __restrict__ S, int64_t na, int64_t nb, 
                     for (int k = 0; k < KC; ++k) t += vr[k] * cr[k];
                     a += (e >> 31) ? -t : t;
                 };
-                int col = c0;
-                for (; col + 8 <= c1; col += 8) {   // eight table entries in flight
-                    uint32_t b8[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) b8[u] = bs_pk[(int64_t)(col + u) * 64 + lane];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) one(b8[u]);
+                const uint4* p = reinterpret_cast<const uint4*>(tab.ent) + (int64_t)tab.blk[sl] * 64 + lane;
+                int left = tab.cols[sl];
+                uint4 x1 = p[0];
+                for (; left > 0; left -= 4) {   // the next four entries in flight
+                    const uint4 x = x1;
+                    p += 64;
+                    x1 = *p;   // (the table holds one block past the last)
+                    one(x.x);
+                    if (left > 1) one(x.y);
+                    if (left > 2) one(x.z);
+                    if (left > 3) one(x.w);
                 }
-                if (col + 4 <= c1) {
-                    uint32_t b4[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) b4[u] = bs_pk[(int64_t)(col + u) * 64 + lane];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) one(b4[u]);
-                    col += 4;
-                }
-                for (; col < c1; ++col) one(bs_pk[(int64_t)col * 64 + lane]);
                 acc[j] = a;
             }
         }
@@ -198,8 +191,8 @@ k_ab_direct(const T* __restrict__ C, T* __restrict__ S, int64_t na, int64_t nb, 
 #pragma unroll
     for (int j = 0; j < MAXJ; ++j) {
         const int sl = slice_base + j * nw + wave;
-        if (sl < nbslices) {
-            const int tb = bperm[sl * 64 + lane];
+        if (sl < tab.nslices) {
+            const int tb = tab.perm[tab.slot[sl] + lane];
             if (tb < nb) {
                 const int64_t o = ia * nb + tb;
                 S[o] += acc[j];
@@ -231,18 +224,29 @@ k_ab_srcgrouped(abg_args<T> a, const int* __restrict__ chunk_src, const T* __res
     abs_block<T, GS>(a, chunk_src, V, norb, blockIdx.x, lds_raw);
 }
 
-// sigma[ia][perm(p)] += sum_{e = a_off[ia]}^{a_off[ia+1]-1} Y[e][p] (gather_row),
-// one workgroup per alpha row; STAGED: the row is assembled in LDS first.
-template <typename T, bool STAGED>
+// ---------------------------------------------------------------- all terms in one launch
+// Row blocks of the beta-beta term (into bb.Y), then of the alpha-alpha term
+// (into aa.Y), then the chunks of the alpha-beta term (into ab.Y): the terms
+// write buffers of their own and run together; the gather adds them.
+template <typename T, int R, int G>
 __global__ void __launch_bounds__(1024)
-k_ab_gather(const T* __restrict__ Y, T* __restrict__ S, int64_t na, int64_t nb, int64_t ldy,
-            const int* __restrict__ bperm, const int* __restrict__ a_off, const int* __restrict__ order,
-            const int* __restrict__ skip) {
+k_sigma_terms(ss_args<T> bb, ss_args<T> aa, abg_args<T> ab, int n_bb, int n_aa, const T* __restrict__ jk,
+              const T* __restrict__ V, int norb, const int* __restrict__ skip) {
     if (skip && *skip) return;
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    T* row = STAGED ? reinterpret_cast<T*>(lds_raw) : nullptr;
-    for (int64_t k = blockIdx.x; k < na; k += gridDim.x)
-        gather_row<T>(Y, S, nb, ldy, bperm, a_off, order[k], row);
+    const int k = blockIdx.x;
+    if (k < n_bb) ss_block<T, R>(bb, jk, norb, k, lds_raw);
+    else if (k < n_bb + n_aa) ss_block<T, R>(aa, jk, norb, k - n_bb, lds_raw);
+    else abg_block<T, G>(ab, V, norb, k - n_bb - n_aa, lds_raw);
+}
+
+// Rows of sigma from Y (gather_row), heaviest first; STAGED: assembled in LDS.
+template <typename T, bool STAGED>
+__global__ void __launch_bounds__(1024)
+k_ab_gather(gather_args<T> a, int ng, const int* __restrict__ order, const int* __restrict__ skip) {
+    if (skip && *skip) return;
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    gather_row<T>(a, order[blockIdx.x], ng, STAGED ? reinterpret_cast<T*>(lds_raw) : nullptr);
 }
 
 // Longest alpha-beta output row assembled in LDS by the gather (larger rows are
@@ -317,6 +321,17 @@ bool use_window(sqd_ctx* ctx, int64_t nrows, int64_t ncols, int norb, size_t es)
     return lds4 > (size_t)ctx->max_lds && nrows >= 2;
 }
 
+template <typename T>
+const sell_table<T>& same_spin_table(const spin_tables& t) {
+    if constexpr (sizeof(T) == 8) return t.ss64;
+    else return t.ss32;
+}
+template <typename T>
+const T* cross_table(const spin_tables& t) {
+    if constexpr (sizeof(T) == 8) return t.ws64;
+    else return t.ws32;
+}
+
 // colmajor: X and Y hold the transposes (the alpha-alpha term read from C and
 // added into sigma directly).
 // The alpha-alpha term runs column-major on C (no transposes) when a staged
@@ -326,17 +341,17 @@ bool use_window(sqd_ctx* ctx, int64_t nrows, int64_t ncols, int norb, size_t es)
 // pieces: no change; FP32 with 2 rows of the 2.56e8 workload, 8-byte pieces:
 // alpha-alpha with its transposes 17.1 ms, in place 20.8 ms); otherwise the
 // transposes around the row-major kernel.
-bool aa_in_place(sqd_ctx* ctx, int64_t nb, int64_t na, int norb, size_t es) {
-    if (use_window(ctx, nb, na, norb, es)) return true;
+bool aa_in_place(sqd_ctx* ctx, int64_t nb, int64_t na, int norb, size_t es, bool windows) {
+    if (windows && use_window(ctx, nb, na, norb, es)) return true;
     return (size_t)pick_rows(ctx, nb, na, norb, es) * es >= 64;
 }
 
 template <typename T>
 int launch_same_spin(sqd_ctx* ctx, sqd_space* sp, const T* X, T* Y, int64_t nrows, int64_t ncols,
                      const spin_tables& col, const spin_tables& row, const T* jk, int norb, const double* diag,
-                     int accumulate, const int* skip, const char* timer_name, int colmajor = 0) {
+                     int accumulate, const int* skip, const char* timer_name, bool windows, int colmajor = 0) {
     const size_t es = sizeof(T);
-    if (use_window(ctx, nrows, ncols, norb, es)) {
+    if (windows && use_window(ctx, nrows, ncols, norb, es)) {
         // the windowed kernel ends in slot order, so the diagonal (scattered
         // reads of diag and X there) goes in the coalesced pass that places
         // its output, or in one of its own (2.56e8 workload: beta-beta with
@@ -363,11 +378,8 @@ int launch_same_spin(sqd_ctx* ctx, sqd_space* sp, const T* X, T* Y, int64_t nrow
     int nw = ctx->tune[SQD_TUNE_SS_WAVES] ? ctx->tune[SQD_TUNE_SS_WAVES]
                                           : ((R == 8 || lds > (size_t)ctx->max_lds / 2) ? 16 : 8);
     const dim3 grid(nblk(nrows, R)), block(64 * nw);
-    const T* sv = nullptr; const T* dv = nullptr;
-    if constexpr (sizeof(T) == 8) { sv = (const T*)col.sell_s_v64; dv = (const T*)col.sell_d_v64; }
-    else { sv = (const T*)col.sell_s_v32; dv = (const T*)col.sell_d_v32; }
-    ss_args<T> args{X, Y, nrows, ncols, col.perm_ss, col.nslices, col.sl_s_off, col.sl_d_off, col.sell_s_pk, sv,
-                    col.sell_d_nbr, dv, row.str, row.nw, diag, accumulate, colmajor};
+    ss_args<T> args{X, Y, nrows, ncols, same_spin_table<T>(col), cross_table<T>(row), row.str, row.nw, diag,
+                    accumulate, colmajor};
     prof_scope ps(ctx, timer_name);
 #define SQD_SS_LAUNCH(RR)                                                                                    \
     case RR:                                                                                                 \
@@ -394,8 +406,9 @@ int launch_ab_direct(sqd_ctx* ctx, const sqd_space* sp, const T* C, T* S, const 
     if (KC == 0) return sqd_fail(ctx, SQD_E_LIMIT, "alpha-beta source row does not fit in LDS");
     int nw = ctx->tune[SQD_TUNE_AB_WAVES] ? ctx->tune[SQD_TUNE_AB_WAVES] : 8;
     // fewer waves when there are few slices
-    while (nw > 4 && (int64_t)nw * 2 > B.nslices && ctx->tune[SQD_TUNE_AB_WAVES] == 0) nw >>= 1;
-    const int groups = (B.nslices + nw * kAbMaxJ - 1) / (nw * kAbMaxJ);
+    const ab_table& tab = B.ab32;   // whole rows: a lane keeps its target across the passes
+    while (nw > 4 && (int64_t)nw * 2 > tab.nslices && ctx->tune[SQD_TUNE_AB_WAVES] == 0) nw >>= 1;
+    const int groups = (tab.nslices + nw * kAbMaxJ - 1) / (nw * kAbMaxJ);
     const size_t lds = ((size_t)(B.n + 1) + (size_t)sp->norb * sp->norb) * KC * es;
     const dim3 grid((unsigned)A.n, (unsigned)groups), block(64 * nw);
     prof_scope ps(ctx, sizeof(T) == 8 ? "k_ab_direct<double>" : "k_ab_direct<float>");
@@ -403,8 +416,7 @@ int launch_ab_direct(sqd_ctx* ctx, const sqd_space* sp, const T* C, T* S, const 
     case KK:                                                                                                 \
         set_lds(k_ab_direct<T, KK, kAbMaxJ>, (int)lds);                                                      \
         hipLaunchKernelGGL((k_ab_direct<T, KK, kAbMaxJ>), grid, block, lds, ctx->stream, C, S, A.n, B.n,   \
-                           A.s_off, A.s_pk, B.perm_ab, B.nslices, B.sl_ab_off, B.sell_ab_pk, V, sp->norb,  \
-                           skip);                                                                            \
+                           A.s_off, A.s_pk, tab, V, sp->norb, skip);                                         \
         break;
     switch (KC) {
         SQD_AB_LAUNCH(1)
@@ -460,11 +472,13 @@ int ensure_ab_groups_impl(sqd_ctx* ctx, sqd_space* sp, int G) {
     const int npair = sp->norb * sp->norb;
     std::vector<std::vector<int>> by(npair);
     for (int64_t e = 0; e < A.nnz_s; ++e) by[(pk[e] >> SQD_PAIR_SHIFT) & SQD_PAIR_MASK].push_back((int)e);
-    std::vector<int> grp, cp;
+    std::vector<int2> grp;
+    std::vector<int> cp;
     for (int p = 0; p < npair; ++p) {
         const auto& v = by[p];
         for (size_t k = 0; k < v.size(); k += G) {
-            for (int r = 0; r < G; ++r) grp.push_back(k + r < v.size() ? v[k + r] : -1);
+            for (int r = 0; r < G; ++r)
+                grp.push_back(k + r < v.size() ? make_int2(v[k + r], (int)pk[v[k + r]]) : make_int2(-1, 0));
             cp.push_back(p);
         }
     }
@@ -472,10 +486,10 @@ int ensure_ab_groups_impl(sqd_ctx* ctx, sqd_space* sp, int G) {
     if (sp->ab_chunk_pair) { (void)hipFree(sp->ab_chunk_pair); sp->ab_chunk_pair = nullptr; }
     int rc;
     if ((rc = ensure_ab_row_order(ctx, sp))) return rc;
-    if ((rc = sqd_alloc(ctx, (void**)&sp->ab_grp, sizeof(int) * (grp.size() + 1), &sp->bytes))) return rc;
+    if ((rc = sqd_alloc(ctx, (void**)&sp->ab_grp, sizeof(int2) * (grp.size() + 1), &sp->bytes))) return rc;
     if ((rc = sqd_alloc(ctx, (void**)&sp->ab_chunk_pair, sizeof(int) * (cp.size() + 1), &sp->bytes))) return rc;
     if (!grp.empty()) {
-        SQD_HIP(ctx, hipMemcpy(sp->ab_grp, grp.data(), sizeof(int) * grp.size(), hipMemcpyHostToDevice));
+        SQD_HIP(ctx, hipMemcpy(sp->ab_grp, grp.data(), sizeof(int2) * grp.size(), hipMemcpyHostToDevice));
         SQD_HIP(ctx, hipMemcpy(sp->ab_chunk_pair, cp.data(), sizeof(int) * cp.size(), hipMemcpyHostToDevice));
     }
     sp->ab_G = G;
@@ -518,21 +532,23 @@ int ensure_ab_source_groups(sqd_ctx* ctx, sqd_space* sp, int G) {
         SQD_HIP(ctx, hipMemcpy(pk.data(), A.s_pk, sizeof(uint32_t) * A.nnz_s, hipMemcpyDeviceToHost));
     std::vector<std::vector<int>> by(A.n);
     for (int64_t e = 0; e < A.nnz_s; ++e) by[pk[e] & SQD_NBR_MASK].push_back((int)e);
-    std::vector<int> grp, cs;
+    std::vector<int2> grp;
+    std::vector<int> cs;
     for (int64_t j = 0; j < A.n; ++j) {
         const auto& v = by[j];
         for (size_t k = 0; k < v.size(); k += G) {
-            for (int r = 0; r < G; ++r) grp.push_back(k + r < v.size() ? v[k + r] : -1);
+            for (int r = 0; r < G; ++r)
+                grp.push_back(k + r < v.size() ? make_int2(v[k + r], (int)pk[v[k + r]]) : make_int2(-1, 0));
             cs.push_back((int)j);
         }
     }
     if (sp->abs_grp) { (void)hipFree(sp->abs_grp); sp->abs_grp = nullptr; }
     if (sp->abs_src) { (void)hipFree(sp->abs_src); sp->abs_src = nullptr; }
     int rc;
-    if ((rc = sqd_alloc(ctx, (void**)&sp->abs_grp, sizeof(int) * (grp.size() + 1), &sp->bytes))) return rc;
+    if ((rc = sqd_alloc(ctx, (void**)&sp->abs_grp, sizeof(int2) * (grp.size() + 1), &sp->bytes))) return rc;
     if ((rc = sqd_alloc(ctx, (void**)&sp->abs_src, sizeof(int) * (cs.size() + 1), &sp->bytes))) return rc;
     if (!grp.empty()) {
-        SQD_HIP(ctx, hipMemcpy(sp->abs_grp, grp.data(), sizeof(int) * grp.size(), hipMemcpyHostToDevice));
+        SQD_HIP(ctx, hipMemcpy(sp->abs_grp, grp.data(), sizeof(int2) * grp.size(), hipMemcpyHostToDevice));
         SQD_HIP(ctx, hipMemcpy(sp->abs_src, cs.data(), sizeof(int) * cs.size(), hipMemcpyHostToDevice));
     }
     sp->abs_G = G;
@@ -540,21 +556,115 @@ int ensure_ab_source_groups(sqd_ctx* ctx, sqd_space* sp, int G) {
     return SQD_OK;
 }
 
+// The sliced singles a product of this element size walks.
+const ab_table& ab_tab(const spin_tables& t, size_t es) { return es == sizeof(double) ? t.ab64 : t.ab32; }
+
 // Y bytes of the grouped alpha-beta path (0 if it is not to be used).
 size_t ab_grouped_bytes(sqd_ctx* ctx, const sqd_space* sp, size_t es) {
     const int variant = ctx->tune[SQD_TUNE_AB_VARIANT];
     if (variant == 2) return 0;
     if (ab_group_size(ctx, sp) == 0 && !ab_use_source_groups(ctx, sp)) return 0;
-    const size_t bytes = (size_t)sp->sp[0].nnz_s * (size_t)sp->sp[1].nslices * 64 * es;
+    const size_t bytes = (size_t)sp->sp[0].nnz_s * (size_t)ab_tab(sp->sp[1], es).nslots * es;
     const size_t cap = (size_t)64 << 30;   // keep the intermediate below 64 GiB
     if (variant == 0 && bytes > cap) return 0;
     return bytes + 256;
 }
 
 template <typename T>
+int launch_ab_gather(sqd_ctx* ctx, sqd_space* sp, const gather_args<T>& a, const int* skip) {
+    const int64_t na = sp->sp[0].n;
+    if (na == 0 || a.nb == 0) return SQD_OK;
+    prof_scope ps(ctx, sizeof(T) == 8 ? "k_ab_gather<double>" : "k_ab_gather<float>");
+    // measured on MI355X (4.0e6-determinant workload): up to 1024 threads per
+    // row for FP64, 512 for FP32, one per two slots; FP64 rows shorter than
+    // half of that (whose sums may be split) take as many groups as fit
+    const int most = sizeof(T) == 8 ? 1024 : 512;
+    const int per = (int)std::min<int64_t>(most, (a.nslots / 2 + 63) / 64 * 64);
+    const int64_t row_bytes = a.nb * (int64_t)sizeof(T);
+    if (row_bytes <= std::min<int64_t>(kGatherStageBytes, (int64_t)ctx->max_lds)) {
+        const int ng = sizeof(T) == 8 ? std::min(8, most / per) : 1;
+        set_lds(k_ab_gather<T, true>, (int)(ng * row_bytes));
+        hipLaunchKernelGGL((k_ab_gather<T, true>), dim3((unsigned)na), dim3(per * ng), (size_t)(ng * row_bytes),
+                           ctx->stream, a, ng, sp->ab_row_order, skip);
+    } else {
+        hipLaunchKernelGGL((k_ab_gather<T, false>), dim3((unsigned)na), dim3(per), 0, ctx->stream, a, 1,
+                           sp->ab_row_order, skip);
+    }
+    SQD_HIP(ctx, hipGetLastError());
+    return SQD_OK;
+}
+
+// Shape of the one-launch product: R rows per same-spin workgroup, G singles
+// per alpha-beta workgroup (R = 0: not taken).
+struct fused_shape { int R = 0, G = 0, waves = 0; size_t lds = 0; };
+
+// Where all three terms run in one launch and the gather ends the product.
+// Separate launches leave the chip half empty at the end of each (a term of
+// sigma on 1200 strings per spin has 300 row blocks for 256 compute units) and
+// cost a launch and its latency each, and the alpha-alpha term two transposes.
+// Measured on MI355X, whole sigma, us, before / now with n strings per spin
+// (norb 8 to 36): FP64 n = 70: 39 / 11, 1237 x 731: 229 / 109, 1900: 443 / 403,
+// 2600: 965 / 785, 3600: 1870 / 1504 (four rows and singles per workgroup, with
+// eight waves while two workgroups fit a compute unit, else sixteen: 1500: 254
+// against 273, 2600: 826 against 785); 4300: 3704 / 2712, 5500: 6097 / 4478,
+// 8800: 14836 / 12844 (two rows; the windowed kernel before).  FP32, whose
+// rows are half as long: n = 1500: 218 / 149, 2000: 423 / 389, 3600: 1463 /
+// 1093, 4300: 2413 / 2171 with four rows, eight waves while four workgroups fit
+// (2000: 391 against 419; 2600: 540 against 508); beyond 100 KiB the separate
+// launches win (5500: 3523 against 3486, 5500 x 300: 348 against 595, 7000:
+// 5443 against 6775 with two rows).
+fused_shape fused_pick(sqd_ctx* ctx, const sqd_space* sp, size_t es, unsigned mask, int ab_path) {
+    fused_shape f;
+    constexpr unsigned kOff = SQD_TERM_AA | SQD_TERM_BB | SQD_TERM_AB;
+    if ((mask & kOff) != kOff || ab_path != SQD_AB_DIRECT) return f;
+    for (int key : {SQD_TUNE_SS_ROWS, SQD_TUNE_SS_WAVES, SQD_TUNE_SS_WINDOW, SQD_TUNE_AB_VARIANT, SQD_TUNE_AB_GROUP,
+                    SQD_TUNE_AB_WAVES})
+        if (ctx->tune[key]) return f;   // a kernel chosen by the caller
+    const size_t n2 = (size_t)sp->norb * sp->norb, lim = (size_t)ctx->max_lds;
+    const size_t cols = (size_t)std::max(sp->sp[0].n, sp->sp[1].n) + 1;
+    auto bytes = [&](int k) { return std::max((cols + n2) * k, ((size_t)sp->sp[1].n + 1) * k + n2) * es; };
+    if (bytes(4) <= (es == sizeof(double) ? lim : lim * 5 / 8)) f.R = 4;
+    else if (es == sizeof(double) && bytes(2) <= lim) f.R = 2;
+    f.G = f.R;
+    f.lds = f.R ? bytes(f.R) : 0;
+    f.waves = f.lds <= lim / (es == sizeof(double) ? 2 : 4) ? 8 : 16;
+    return f;
+}
+
+template <typename T>
+int launch_fused(sqd_ctx* ctx, sqd_space* sp, const fused_shape& f, const T* C, T* S, T* S2, T* Y, const T* jk,
+                 const T* V, const double* diag, const double* c64, double* out64, const int* skip) {
+    const spin_tables& A = sp->sp[0];
+    const spin_tables& B = sp->sp[1];
+    int rc;
+    if ((rc = ensure_ab_groups_impl(ctx, sp, f.G))) return rc;
+    const ab_table& tab = ab_tab(B, sizeof(T));
+    ss_args<T> bb{C, S, A.n, B.n, same_spin_table<T>(B), cross_table<T>(A), A.str, A.nw, nullptr, 0, 0};
+    ss_args<T> aa{C, S2, B.n, A.n, same_spin_table<T>(A), cross_table<T>(B), B.str, B.nw, nullptr, 0, 1};
+    abg_args<T> ab{C, Y, B.n, sp->ab_grp, sp->ab_chunk_pair, tab};
+    const int n_bb = (int)nblk(A.n, f.R), n_aa = (int)nblk(B.n, f.R);
+    {
+        prof_scope ps(ctx, sizeof(T) == 8 ? "k_sigma_terms<double>" : "k_sigma_terms<float>");
+        const dim3 grid(n_bb + n_aa + sp->ab_nchunks), block(64 * f.waves);
+        auto launch = [&](auto k) {
+            constexpr int K = decltype(k)::value;
+            set_lds(k_sigma_terms<T, K, K>, (int)f.lds);
+            hipLaunchKernelGGL((k_sigma_terms<T, K, K>), grid, block, f.lds, ctx->stream, bb, aa, ab, n_bb, n_aa, jk,
+                               V, sp->norb, skip);
+        };
+        if (f.R == 4) launch(std::integral_constant<int, 4>());
+        else launch(std::integral_constant<int, 2>());
+        SQD_HIP(ctx, hipGetLastError());
+    }
+    return launch_ab_gather<T>(ctx, sp, gather_args<T>{Y, B.n, tab.nslots, tab.perm, A.s_off, S, S2, diag, c64, out64},
+                               skip);
+}
+
+template <typename T>
 int launch_ab_grouped(sqd_ctx* ctx, sqd_space* sp, const T* C, T* S, T* Y, const T* V, const int* skip) {
     const spin_tables& A = sp->sp[0];
     const spin_tables& B = sp->sp[1];
+    const ab_table& tab = ab_tab(B, sizeof(T));
     int rc;
     if (ab_use_source_groups(ctx, sp)) {
         const int GS = ab_source_group_size(ctx, sp);
@@ -562,8 +672,7 @@ int launch_ab_grouped(sqd_ctx* ctx, sqd_space* sp, const T* C, T* S, T* Y, const
         if (sp->abs_nchunks > 0) {
             const size_t lds = ((size_t)(B.n + 1) + (size_t)GS * sp->norb * sp->norb) * sizeof(T);
             const int nw = ctx->tune[SQD_TUNE_AB_WAVES] ? ctx->tune[SQD_TUNE_AB_WAVES] : 16;
-            abg_args<T> args{C, Y, B.n, (int64_t)B.nslices * 64, sp->abs_grp, nullptr, A.s_pk, B.perm_ab,
-                             B.nslices, B.sl_ab_off, B.sell_ab_pk};
+            abg_args<T> args{C, Y, B.n, sp->abs_grp, nullptr, tab};
             prof_scope ps(ctx, sizeof(T) == 8 ? "k_ab_srcgrouped<double>" : "k_ab_srcgrouped<float>");
 #define SQD_ABS_LAUNCH(GG)                                                                                    \
     case GG:                                                                                                  \
@@ -588,8 +697,7 @@ int launch_ab_grouped(sqd_ctx* ctx, sqd_space* sp, const T* C, T* S, T* Y, const
         // share each table entry (G <= 2: the loop is latency-bound)
         const int nw = ctx->tune[SQD_TUNE_AB_WAVES] ? ctx->tune[SQD_TUNE_AB_WAVES]
                                                     : ((sizeof(T) == 8 || G <= 2) ? 16 : 8);
-        abg_args<T> args{C, Y, B.n, (int64_t)B.nslices * 64, sp->ab_grp, sp->ab_chunk_pair, A.s_pk, B.perm_ab,
-                         B.nslices, B.sl_ab_off, B.sell_ab_pk};
+        abg_args<T> args{C, Y, B.n, sp->ab_grp, sp->ab_chunk_pair, tab};
         prof_scope ps(ctx, sizeof(T) == 8 ? "k_ab_grouped<double>" : "k_ab_grouped<float>");
 #define SQD_ABG_LAUNCH(GG)                                                                                   \
     case GG:                                                                                                 \
@@ -606,24 +714,8 @@ int launch_ab_grouped(sqd_ctx* ctx, sqd_space* sp, const T* C, T* S, T* Y, const
 #undef SQD_ABG_LAUNCH
     }
     }
-    const unsigned gx = (unsigned)std::min<int64_t>(A.n, 1 << 20);
-    prof_scope ps(ctx, sizeof(T) == 8 ? "k_ab_gather<double>" : "k_ab_gather<float>");
-    const int64_t ldy = (int64_t)B.nslices * 64;
-    const int64_t row_bytes = B.n * (int64_t)sizeof(T);
-    if (A.n == 0 || B.n == 0) return SQD_OK;
-    // measured on MI355X (4.0e6-determinant workload): 1024 threads per row
-    // for FP64, 512 for FP32
-    const dim3 gblock(sizeof(T) == 8 ? 1024 : 512);
-    if (row_bytes <= std::min<int64_t>(kGatherStageBytes, (int64_t)ctx->max_lds)) {
-        set_lds(k_ab_gather<T, true>, (int)row_bytes);
-        hipLaunchKernelGGL((k_ab_gather<T, true>), dim3(gx), gblock, (size_t)row_bytes, ctx->stream, Y, S, A.n,
-                           B.n, ldy, B.perm_ab, A.s_off, sp->ab_row_order, skip);
-    } else {
-        hipLaunchKernelGGL((k_ab_gather<T, false>), dim3(gx), gblock, 0, ctx->stream, Y, S, A.n, B.n, ldy,
-                           B.perm_ab, A.s_off, sp->ab_row_order, skip);
-    }
-    SQD_HIP(ctx, hipGetLastError());
-    return SQD_OK;
+    return launch_ab_gather<T>(ctx, sp, gather_args<T>{Y, B.n, tab.nslots, tab.perm, A.s_off, S, nullptr, nullptr,
+                                                       nullptr, nullptr}, skip);
 }
 
 }  // namespace
@@ -666,6 +758,10 @@ int sqd_sigma_auto_path(sqd_ctx* ctx, const sqd_space* sp, int precision) {
 bool sqd_sigma_prepared(sqd_ctx* ctx, const sqd_space* sp, int precision, unsigned mask, int ab_path) {
     if (sp->values_version != ctx->ham_version || sp->diag_version != ctx->ham_version) return false;
     const size_t es0 = precision == SQD_FP64 ? 8 : 4;
+    if (ab_path == SQD_AB_AUTO) ab_path = sqd_sigma_auto_path(ctx, sp, precision);
+    const fused_shape fused = fused_pick(ctx, sp, es0, mask, ab_path);
+    if (fused.R && ab_grouped_bytes(ctx, sp, es0))
+        return sp->ab_grp != nullptr && sp->ab_G == fused.G && sp->ab_row_order != nullptr;
     for (int spin = 0; spin < 2; ++spin) {   // windowed same-spin tables of either spin
         if (!(mask & (spin == 0 ? SQD_TERM_AA : SQD_TERM_BB))) continue;
         const spin_tables& col = sp->sp[spin].alias ? sp->sp[0] : sp->sp[spin];
@@ -687,11 +783,19 @@ bool sqd_sigma_prepared(sqd_ctx* ctx, const sqd_space* sp, int precision, unsign
     return sp->ab_grp != nullptr && sp->ab_G == ab_group_size(ctx, sp) && sp->ab_row_order != nullptr;
 }
 
+// The windowed tables, cross-spin table and scratch of a spin exist.
+static bool window_built(sqd_ctx* ctx, const sqd_space* sp, int spin, const spin_tables& col, const spin_tables& row) {
+    const int W = sqd_window_count(ctx, sp->sp[spin].n);
+    return W != 0 && col.win_W == W && row.wg64 && (W == 1 || sp->win_P_bytes >= sqd_window_scratch_bytes(sp));
+}
+
 // True when the arrays that a space's first product builds exist for a
 // product with these arguments: the diagonal, and for same-spin rows too long
 // to stage four whole the windowed tables of the column spin, the cross-spin
 // table of the row spin and the partial-sum scratch.  (Their values may still
-// be stale: those are refreshed in place.)
+// be stale: those are refreshed in place.)  A first product in one launch
+// builds no windowed tables; the no-allocation product then stages whole rows,
+// which fit where the one launch was taken.
 bool sqd_space_built_for(sqd_ctx* ctx, const sqd_space* sp, int precision, unsigned mask) {
     if (!sp->diag || !sp->ua) return false;
     const size_t es = precision == SQD_FP64 ? 8 : 4;
@@ -700,8 +804,8 @@ bool sqd_space_built_for(sqd_ctx* ctx, const sqd_space* sp, int precision, unsig
         const spin_tables& col = sp->sp[spin].alias ? sp->sp[0] : sp->sp[spin];
         const spin_tables& row = sp->sp[1 - spin].alias ? sp->sp[0] : sp->sp[1 - spin];
         if (use_window(ctx, sp->sp[1 - spin].n, sp->sp[spin].n, sp->norb, es)) {
-            const int W = sqd_window_count(ctx, sp->sp[spin].n);
-            if (W == 0 || col.win_W != W || !row.wg64 || (W > 1 && sp->win_P_bytes < sqd_window_scratch_bytes(sp)))
+            if (!window_built(ctx, sp, spin, col, row) &&
+                !(sp->fused_terms[precision == SQD_FP64 ? 0 : 1] & (spin == 0 ? SQD_TERM_AA : SQD_TERM_BB)))
                 return false;
         }
     }
@@ -743,6 +847,16 @@ int sqd_sigma_impl(sqd_ctx* ctx, sqd_space* sp, const double* c, double* sigma, 
     const int norb = sp->norb;
     if (ab_path == SQD_AB_AUTO) ab_path = sqd_sigma_auto_path(ctx, sp, precision);
     const double* diag = (mask & SQD_TERM_DIAG) ? sp->diag : nullptr;
+    const fused_shape fused = fused_pick(ctx, sp, precision == SQD_FP64 ? 8 : 4, mask, ab_path);
+    // the windowed same-spin kernel, where the dispatch takes it; without an
+    // allocation only on tables that exist
+    auto win = [&](int spin) {
+        if (!ext_scratch) return true;
+        const spin_tables& col = sp->sp[spin].alias ? sp->sp[0] : sp->sp[spin];
+        const spin_tables& row = sp->sp[1 - spin].alias ? sp->sp[0] : sp->sp[1 - spin];
+        return window_built(ctx, sp, spin, col, row);
+    };
+    const bool win_aa = win(0), win_bb = win(1);
     const unsigned g = nblk(dim, 256);
     const dim3 tgrid(nblk(nb, 64), nblk(na, 64)), tgridT(nblk(na, 64), nblk(nb, 64));
     if (precision == SQD_FP64) {
@@ -758,20 +872,25 @@ int sqd_sigma_impl(sqd_ctx* ctx, sqd_space* sp, const double* c, double* sigma, 
         // the columns of C and adds into sigma (row-staged kernel with eight
         // rows, and the windowed kernel through its placing pass), or comes
         // back through a coalesced transpose that adds
+        if (fused.R && ybytes) {
+            sp->fused_terms[0] |= mask;
+            return launch_fused<double>(ctx, sp, fused, c, sigma, Ct, Yab, ctx->jk64, ctx->eri, diag, c, nullptr,
+                                        skip);
+        }
         bool written = false;
         if (mask & SQD_TERM_BB) {
             if ((rc = launch_same_spin<double>(ctx, sp, c, sigma, na, nb, B, A, ctx->jk64, norb, diag, 0, skip,
-                                               "k_same_spin<double>[bb]")))
+                                               "k_same_spin<double>[bb]", win_bb)))
                 return rc;
             written = true;
         } else if (diag) {
             hipLaunchKernelGGL(k_diag_apply, dim3(g), dim3(256), 0, ctx->stream, diag, c, sigma, dim, 0, skip);
             written = true;
         }
-        if ((mask & SQD_TERM_AA) && aa_in_place(ctx, nb, na, norb, 8)) {
+        if ((mask & SQD_TERM_AA) && aa_in_place(ctx, nb, na, norb, 8, win_aa)) {
             // beta rows read from the columns of C, added into sigma
             if ((rc = launch_same_spin<double>(ctx, sp, c, sigma, nb, na, A, B, ctx->jk64, norb, nullptr,
-                                               written ? 1 : 0, skip, "k_same_spin<double>[aa]", 1)))
+                                               written ? 1 : 0, skip, "k_same_spin<double>[aa]", win_aa, 1)))
                 return rc;
             written = true;
         } else if (mask & SQD_TERM_AA) {
@@ -781,7 +900,7 @@ int sqd_sigma_impl(sqd_ctx* ctx, sqd_space* sp, const double* c, double* sigma, 
                                    nb, skip);
             }
             if ((rc = launch_same_spin<double>(ctx, sp, Ct, Yt, nb, na, A, B, ctx->jk64, norb, nullptr, 0, skip,
-                                               "k_same_spin<double>[aa]"))) return rc;
+                                               "k_same_spin<double>[aa]", win_aa))) return rc;
             {
                 prof_scope pt(ctx, "k_transpose<double>");
                 if (written)
@@ -821,16 +940,20 @@ int sqd_sigma_impl(sqd_ctx* ctx, sqd_space* sp, const double* c, double* sigma, 
         hipLaunchKernelGGL((k_convert<double, float>), dim3(g), dim3(256), 0, ctx->stream, c, C32, dim, skip);
         Cin = C32;
     }
+    if (fused.R && ybytes) {
+        sp->fused_terms[1] |= mask;
+        return launch_fused<float>(ctx, sp, fused, Cin, S32, Ct32, Yab, ctx->jk32, ctx->eri32, diag, c, sigma, skip);
+    }
     bool written = false;
     if (mask & SQD_TERM_BB) {
         if ((rc = launch_same_spin<float>(ctx, sp, Cin, S32, na, nb, B, A, ctx->jk32, norb, nullptr, 0, skip,
-                                          "k_same_spin<float>[bb]")))
+                                          "k_same_spin<float>[bb]", win_bb)))
             return rc;
         written = true;
     }
-    if ((mask & SQD_TERM_AA) && aa_in_place(ctx, nb, na, norb, 4)) {
+    if ((mask & SQD_TERM_AA) && aa_in_place(ctx, nb, na, norb, 4, win_aa)) {
         if ((rc = launch_same_spin<float>(ctx, sp, Cin, S32, nb, na, A, B, ctx->jk32, norb, nullptr, written ? 1 : 0,
-                                          skip, "k_same_spin<float>[aa]", 1)))
+                                          skip, "k_same_spin<float>[aa]", win_aa, 1)))
             return rc;
         written = true;
     } else if (mask & SQD_TERM_AA) {
@@ -840,7 +963,7 @@ int sqd_sigma_impl(sqd_ctx* ctx, sqd_space* sp, const double* c, double* sigma, 
                                skip);
         }
         if ((rc = launch_same_spin<float>(ctx, sp, Ct32, Yt32, nb, na, A, B, ctx->jk32, norb, nullptr, 0, skip,
-                                              "k_same_spin<float>[aa]"))) return rc;
+                                              "k_same_spin<float>[aa]", win_aa))) return rc;
         {
             prof_scope pt(ctx, "k_transpose<float>");
             if (written)

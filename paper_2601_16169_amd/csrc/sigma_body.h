@@ -136,14 +136,8 @@ struct ss_args {
     const T* X;            // nrows x ncols
     T* Y;
     int64_t nrows, ncols;
-    const int* perm;       // sliced table of the column spin
-    int nslices;
-    const int* sl_s_off;
-    const int* sl_d_off;
-    const uint32_t* s_pk;
-    const T* s_val;
-    const int* d_nbr;
-    const T* d_val;
+    sell_table<T> tab;     // sliced table of the column spin
+    const T* ws;           // cross-spin sums of the row spin's strings, string-major (null: summed here)
     const uint64_t* row_str;   // strings of the row spin (cross-spin term), nw words each
     int nw;
     const double* diag;        // fused DIAG term (or null)
@@ -163,6 +157,35 @@ __device__ __forceinline__ void ss_block(const ss_args<T>& a, const T* __restric
     const int64_t row0 = blk * R;
     const int nthr = blockDim.x;
     const int tid = threadIdx.x;
+    // Each wave walks its bins' blocks (sell_table) as one stream, two blocks
+    // (eight entries) ahead: what bounds the walk is the LDS, 64-byte pieces
+    // at random columns, as long as the table's loads are in flight early
+    // enough and the waves end together.  The first blocks load before the rows
+    // are staged.
+    const sell_table<T>& tab = a.tab;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int per = kBins / (nthr >> 6);
+    int sl = tab.bin[wave * per];
+    const int sl_end = tab.bin[(wave + 1) * per];
+    int b = tab.bin[kBins + 1 + wave * per];
+    const int b_last = max(tab.bin[kBins + 1 + (wave + 1) * per] - 1, 0);   // (the arrays hold one block past the last)
+    struct block { uint32_t e[4]; T v[4]; };
+    auto load = [&](int q) {
+        block x;
+        const int64_t at = (int64_t)min(q, b_last) * 256;
+        const uint4 e = *reinterpret_cast<const uint4*>(tab.ent + at + lane * 4);
+        x.e[0] = e.x, x.e[1] = e.y, x.e[2] = e.z, x.e[3] = e.w;
+        if constexpr (sizeof(T) == 8) {
+            const double2 v0 = *reinterpret_cast<const double2*>(tab.val + at + lane * 2);
+            const double2 v1 = *reinterpret_cast<const double2*>(tab.val + at + 128 + lane * 2);
+            x.v[0] = v0.x, x.v[1] = v0.y, x.v[2] = v1.x, x.v[3] = v1.y;
+        } else {
+            const float4 v = *reinterpret_cast<const float4*>(tab.val + at + lane * 4);
+            x.v[0] = v.x, x.v[1] = v.y, x.v[2] = v.z, x.v[3] = v.w;
+        }
+        return x;
+    };
+    block x0 = load(b), x1 = load(b + 1);
     if (a.colmajor) {
         stage_cols<T, R>(xs, a.X, nrows, row0, ncols);
     } else {
@@ -172,134 +195,81 @@ __device__ __forceinline__ void ss_block(const ss_args<T>& a, const T* __restric
         stage_rows<T, R>(xs, rows, (int)ncols);
     }
     // cross-spin term of the staged rows: ws[pq][r] = sum_{k in row string} (pq|kk),
-    // summed over k in increasing order; every (pq|kk) is loaded (no load
-    // behind a branch) and unoccupied k contribute an exact zero
-    for (int idx = tid; idx < R * norb2; idx += nthr) {
-        const int r = idx / norb2, pq = idx - r * norb2;
-        const int64_t row = row0 + r;
-        T acc = (T)0;
-        for (int q = 0; q < a.nw; ++q) {
-            const uint64_t x = (row < nrows) ? a.row_str[row * a.nw + q] : 0ull;
-            const int kend = min(norb - 64 * q, 64);
-            const T* jq = jk + (int64_t)(64 * q) * norb2 + pq;
-            int k = 0;
-            for (; k + 4 <= kend; k += 4) {
-                T v[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = jq[(int64_t)(k + u) * norb2];
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if ((x >> (k + u)) & 1ull) acc += v[u];
-            }
-            for (; k < kend; ++k)
-                if ((x >> k) & 1ull) acc += jq[(int64_t)k * norb2];
+    // from the per-string table, or summed over k in increasing order: every
+    // (pq|kk) is loaded (no load behind a branch) and unoccupied k contribute
+    // an exact zero
+    if (a.ws) {
+        for (int idx = tid; idx < R * norb2; idx += nthr) {
+            const int r = idx / norb2, pq = idx - r * norb2;
+            const int64_t row = row0 + r < nrows ? row0 + r : nrows - 1;
+            ws[lds_cols<T, R>::idx(pq, r)] = a.ws[row * norb2 + pq];
         }
-        ws[lds_cols<T, R>::idx(pq, r)] = acc;
+    } else {
+        for (int idx = tid; idx < R * norb2; idx += nthr) {
+            const int r = idx / norb2, pq = idx - r * norb2;
+            const int64_t row = row0 + r;
+            T acc = (T)0;
+            for (int q = 0; q < a.nw; ++q) {
+                const uint64_t x = (row < nrows) ? a.row_str[row * a.nw + q] : 0ull;
+                const int kend = min(norb - 64 * q, 64);
+                const T* jq = jk + (int64_t)(64 * q) * norb2 + pq;
+                int k = 0;
+                for (; k + 4 <= kend; k += 4) {
+                    T v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = jq[(int64_t)(k + u) * norb2];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if ((x >> (k + u)) & 1ull) acc += v[u];
+                }
+                for (; k < kend; ++k)
+                    if ((x >> k) & 1ull) acc += jq[(int64_t)k * norb2];
+            }
+            ws[lds_cols<T, R>::idx(pq, r)] = acc;
+        }
     }
     __syncthreads();
-    const int wave = tid >> 6, lane = tid & 63, nw = nthr >> 6;
-    for (int sl = wave; sl < a.nslices; sl += nw) {
+    if (sl == sl_end) return;
+    for (; sl < sl_end; ++sl) {
+        const int b_end = tab.blk[sl + 1], s_end = b + tab.s_blk[sl];
+        const int split = tab.split ? tab.split[sl] : 0;
+        const int t = tab.perm[sl * 64 + lane];
         T acc[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) acc[r] = (T)0;
-        const int s0 = a.sl_s_off[sl], s1 = a.sl_s_off[sl + 1];
-        const int d0 = a.sl_d_off[sl], d1 = a.sl_d_off[sl + 1];
-        // table entries in flight: sixteen for FP32, whose entries are half
-        // the bytes and whose LDS reads are cheaper; eight for FP64 (measured
-        // on MI355X: sixteen is slower there, with one row or eight)
-        constexpr int kD = sizeof(T) == 4 ? 16 : 8;
-        // with one or two staged rows (long rows: the table streams from
-        // beyond the L2) the first batch of doubles loads while the singles
-        // run (2.56e8 workload, FP32 same-spin: 16.0 -> 14.7 ms; with eight
-        // rows it only costs registers: FP32 90 -> 106 us on the 4.0e6 one)
-        constexpr bool kPre = R <= 2;
-        int nbP[kPre ? kD : 1];
-        T vP[kPre ? kD : 1];
-        const bool pre = kPre && d0 + kD <= d1;
-        if constexpr (kPre) {
-            if (pre) {
+        auto use = [&](const block& x, bool single) {
+            if (single) {
 #pragma unroll
-                for (int u = 0; u < kD; ++u) {
-                    nbP[u] = a.d_nbr[(int64_t)(d0 + u) * 64 + lane];
-                    vP[u] = a.d_val[(int64_t)(d0 + u) * 64 + lane];
+                for (int u = 0; u < 4; ++u) {
+                    const int pair = (int)((x.e[u] >> SQD_PAIR_SHIFT) & SQD_PAIR_MASK);
+                    T xr[R], wr[R];
+                    lds_cols<T, R>::load(xs, (int)(x.e[u] & SQD_NBR_MASK), xr);
+                    lds_cols<T, R>::load(ws, pair, wr);
+                    const bool neg = (x.e[u] >> 31) != 0;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) acc[r] += (x.v[u] + (neg ? -wr[r] : wr[r])) * xr[r];
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    T xr[R];
+                    lds_cols<T, R>::load(xs, (int)x.e[u], xr);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) acc[r] += x.v[u] * xr[r];
                 }
             }
-        }
-        auto single = [&](uint32_t e, T v) {
-            const int nbr = (int)(e & SQD_NBR_MASK);
-            const int pair = (int)((e >> SQD_PAIR_SHIFT) & SQD_PAIR_MASK);
-            T xr[R], wr[R];
-            lds_cols<T, R>::load(xs, nbr, xr);
-            lds_cols<T, R>::load(ws, pair, wr);
-            const bool neg = (e >> 31) != 0;
-#pragma unroll
-            for (int r = 0; r < R; ++r) acc[r] += (v + (neg ? -wr[r] : wr[r])) * xr[r];
         };
-        int k = s0;
-        for (; k + 4 <= s1; k += 4) {   // four table entries in flight
-            uint32_t e[4];
-            T v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                e[u] = a.s_pk[(int64_t)(k + u) * 64 + lane];
-                v[u] = a.s_val[(int64_t)(k + u) * 64 + lane];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) single(e[u], v[u]);
+        for (; b < b_end; b += 2) {   // an even number of blocks
+            use(x0, b < s_end);
+            x0 = load(b + 2);
+            use(x1, b + 1 < s_end);
+            x1 = load(b + 3);
         }
-        for (; k < s1; ++k) single(a.s_pk[(int64_t)k * 64 + lane], a.s_val[(int64_t)k * 64 + lane]);
-        auto dbl = [&](int nbr, T v) {
-            T xr[R];
-            lds_cols<T, R>::load(xs, nbr, xr);
+        // the sums of a row held by several lanes, added across them
+        for (int o = 1; o < (1 << split); o <<= 1) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) acc[r] += v * xr[r];
-        };
-        k = d0;
-        if constexpr (kPre) {
-            if (pre) {
-#pragma unroll
-                for (int u = 0; u < kD; ++u) dbl(nbP[u], vP[u]);
-                k += kD;
-            }
+            for (int r = 0; r < R; ++r) acc[r] += __shfl_xor(acc[r], o);
         }
-        for (; k + kD <= d1; k += kD) {
-            int nbd[kD];
-            T v[kD];
-#pragma unroll
-            for (int u = 0; u < kD; ++u) {
-                nbd[u] = a.d_nbr[(int64_t)(k + u) * 64 + lane];
-                v[u] = a.d_val[(int64_t)(k + u) * 64 + lane];
-            }
-#pragma unroll
-            for (int u = 0; u < kD; ++u) dbl(nbd[u], v[u]);
-        }
-        if constexpr (kD > 8) {
-            if (k + 8 <= d1) {
-                int nb8[8];
-                T v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    nb8[u] = a.d_nbr[(int64_t)(k + u) * 64 + lane];
-                    v[u] = a.d_val[(int64_t)(k + u) * 64 + lane];
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) dbl(nb8[u], v[u]);
-                k += 8;
-            }
-        }
-        for (; k + 4 <= d1; k += 4) {
-            int nb4[4];
-            T v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                nb4[u] = a.d_nbr[(int64_t)(k + u) * 64 + lane];
-                v[u] = a.d_val[(int64_t)(k + u) * 64 + lane];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) dbl(nb4[u], v[u]);
-        }
-        for (; k < d1; ++k) dbl(a.d_nbr[(int64_t)k * 64 + lane], a.d_val[(int64_t)k * 64 + lane]);
-        const int t = a.perm[sl * 64 + lane];
         if constexpr (R * sizeof(T) % 16 == 0) {
             // column-major output of a whole row block: R consecutive values
             // of the target's column in 16-byte pieces
@@ -348,23 +318,79 @@ __device__ __forceinline__ void ss_block(const ss_args<T>& a, const T* __restric
 // in LDS (lds_cols layout) and the row (ai|..) of the (pq|rs) matrix, then
 // walks the sliced beta singles table once for all G rows:
 //   Y[e][slot(jb')] = s(e) * sum_{beta singles jb' <- jb (pair bj, s_b)} s_b (ai|bj) C[src(e)][jb]
-// Y is written in slot order (slice * 64 + lane), so each wave stores 64
-// consecutive values, with non-temporal stores (read once, by the gather);
-// the gather maps slots back to beta strings.
+// Y is written in slot order (ab_table), so each wave stores consecutive
+// values, with non-temporal stores (read once, by the gather); the gather maps
+// slots back to beta strings.
 template <typename T>
 struct abg_args {
     const T* C;
     T* Y;                     // nnz_alpha_singles x ldy, columns in sliced (slot) order
     int64_t nb;
-    int64_t ldy;              // 64 x number of beta slices
-    const int* grp;           // chunks x G CSR positions (-1 = padding)
+    const int2* grp;          // chunks x G alpha singles: CSR position (-1 = padding), gather form
     const int* chunk_pair;
-    const uint32_t* a_pk;     // alpha singles (gather form)
-    const int* bperm;         // sliced beta singles
-    int nbslices;
-    const int* bsl_off;
-    const uint32_t* bs_pk;
+    ab_table tab;             // sliced beta singles; Y has tab.nslots columns
 };
+
+// The calling wave's walk over its bins of a sliced singles table.  The first
+// blocks are loaded at construction (before the rows are staged, so that the
+// two waits run together), the others three blocks ahead.  run() calls begin(),
+// each(entry) for every entry of the lane and end(split, slot) for each slice.
+struct ab_walk {
+    const ab_table& tab;
+    int lane, sl, sl_end, b = 0, b_last = 0;
+    uint4 x0, x1, x2;
+    __device__ __forceinline__ uint4 load(int q) const {
+        return *reinterpret_cast<const uint4*>(tab.ent + (int64_t)min(q, b_last) * 256 + lane * 4);
+    }
+    __device__ __forceinline__ explicit ab_walk(const ab_table& t) : tab(t), lane(threadIdx.x & 63) {
+        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        const int per = kBins / ((int)blockDim.x >> 6);
+        sl = tab.bin[wave * per];
+        sl_end = tab.bin[(wave + 1) * per];
+        b = tab.bin[kBins + 1 + wave * per];
+        b_last = max(tab.bin[kBins + 1 + (wave + 1) * per] - 1, 0);   // (the table holds one block past the last)
+        x0 = load(b);
+        x1 = load(b + 1);
+        x2 = load(b + 2);
+    }
+    template <typename B, typename F, typename E>
+    __device__ __forceinline__ void run(B&& begin, F&& each, E&& end) {
+        for (; sl < sl_end; ++sl) {
+            int left = tab.cols[sl];
+            const int split = tab.split ? tab.split[sl] : 0, slot = tab.slot[sl];
+            begin();
+            for (; left > 0; left -= 4) {
+                const uint4 x = x0;
+                x0 = x1;
+                x1 = x2;
+                x2 = load(b + 3);
+                ++b;
+                each(x.x);
+                if (left > 1) each(x.y);
+                if (left > 2) each(x.z);
+                if (left > 3) each(x.w);
+            }
+            end(split, slot);
+        }
+    }
+};
+
+// The sums of one slice for G alpha singles (CSR positions e, -1: none): added
+// across the lanes of each row, times the sign, into Y.
+template <typename T, int G>
+__device__ __forceinline__ void put_y(const abg_args<T>& a, const int (&e)[G], const T (&sgn)[G], T (&acc)[G], int lane,
+                                      int split, int slot) {
+    for (int o = 1; o < (1 << split); o <<= 1) {
+#pragma unroll
+        for (int r = 0; r < G; ++r) acc[r] += __shfl_xor(acc[r], o);
+    }
+    if (lane & ((1 << split) - 1)) return;
+    // lanes without a row read only the zero column: their value is zero
+    T* y = a.Y + slot + (lane >> split);
+#pragma unroll
+    for (int r = 0; r < G; ++r)
+        if (e[r] >= 0) __builtin_nontemporal_store(sgn[r] * acc[r], y + (int64_t)e[r] * a.tab.nslots);
+}
 
 template <typename T, int G>
 __device__ __forceinline__ void abg_block(const abg_args<T>& a, const T* __restrict__ V, int norb, int64_t chunk,
@@ -375,28 +401,30 @@ __device__ __forceinline__ void abg_block(const abg_args<T>& a, const T* __restr
     T* vrow = xs + (nb + 1) * G;
     const int tid = threadIdx.x, nthr = blockDim.x;
     const int pair = a.chunk_pair[chunk];
+    ab_walk walk(a.tab);
     int e[G];
     T sgn[G];
-#pragma unroll
-    for (int r = 0; r < G; ++r) {
-        e[r] = a.grp[chunk * G + r];
-        sgn[r] = (e[r] >= 0 && (a.a_pk[e[r]] >> 31)) ? (T)-1 : (T)1;
-    }
     {
         const T* rows[G];
 #pragma unroll
-        for (int r = 0; r < G; ++r) rows[r] = (e[r] >= 0) ? a.C + (int64_t)(a.a_pk[e[r]] & SQD_NBR_MASK) * nb : nullptr;
+        for (int r = 0; r < G; ++r) {
+            const int2 x = a.grp[chunk * G + r];
+            e[r] = x.x;
+            sgn[r] = ((uint32_t)x.y >> 31) ? (T)-1 : (T)1;
+            rows[r] = e[r] >= 0 ? a.C + (int64_t)((uint32_t)x.y & SQD_NBR_MASK) * nb : nullptr;
+        }
         stage_rows<T, G>(xs, rows, (int)nb);
     }
     for (int q = tid; q < norb2; q += nthr) vrow[q] = V[(int64_t)pair * norb2 + q];
     __syncthreads();
-    const int wave = tid >> 6, lane = tid & 63, nw = nthr >> 6;
-    for (int sl = wave; sl < a.nbslices; sl += nw) {
-        T acc[G];
+    const int lane = tid & 63;
+    T acc[G];
+    walk.run(
+        [&] {
 #pragma unroll
-        for (int r = 0; r < G; ++r) acc[r] = (T)0;
-        const int c0 = a.bsl_off[sl], c1 = a.bsl_off[sl + 1];
-        auto one = [&](uint32_t b) {
+            for (int r = 0; r < G; ++r) acc[r] = (T)0;
+        },
+        [&](uint32_t b) {
             const int nbr = (int)(b & SQD_NBR_MASK);
             const int pb = (int)((b >> SQD_PAIR_SHIFT) & SQD_PAIR_MASK);
             T v = vrow[pb];
@@ -405,41 +433,8 @@ __device__ __forceinline__ void abg_block(const abg_args<T>& a, const T* __restr
             lds_cols<T, G>::load(xs, nbr, xr);
 #pragma unroll
             for (int r = 0; r < G; ++r) acc[r] += v * xr[r];
-        };
-        int col = c0;
-        constexpr int kD = G <= 2 ? 16 : 8;   // table entries in flight (more when few rows share each)
-        for (; col + kD <= c1; col += kD) {
-            uint32_t bd[kD];
-#pragma unroll
-            for (int u = 0; u < kD; ++u) bd[u] = a.bs_pk[(int64_t)(col + u) * 64 + lane];
-#pragma unroll
-            for (int u = 0; u < kD; ++u) one(bd[u]);
-        }
-        if constexpr (kD > 8) {
-            if (col + 8 <= c1) {
-                uint32_t b8[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) b8[u] = a.bs_pk[(int64_t)(col + u) * 64 + lane];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) one(b8[u]);
-                col += 8;
-            }
-        }
-        if (col + 4 <= c1) {
-            uint32_t b4[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) b4[u] = a.bs_pk[(int64_t)(col + u) * 64 + lane];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) one(b4[u]);
-            col += 4;
-        }
-        for (; col < c1; ++col) one(a.bs_pk[(int64_t)col * 64 + lane]);
-        // padding lanes read only the zero column: their value is zero
-        const int64_t slot = (int64_t)sl * 64 + lane;
-#pragma unroll
-        for (int r = 0; r < G; ++r)
-            if (e[r] >= 0) __builtin_nontemporal_store(sgn[r] * acc[r], a.Y + (int64_t)e[r] * a.ldy + slot);
-    }
+        },
+        [&](int split, int slot) { put_y<T, G>(a, e, sgn, acc, lane, split, slot); });
 }
 
 // The same Y from chunks of up to GS alpha singles that share their source
@@ -458,12 +453,14 @@ __device__ __forceinline__ void abs_block(const abg_args<T>& a, const int* __res
     T* vrows = xs + (nb + 1);                // GS rows of (ai|..), row g at g * norb2
     const int tid = threadIdx.x, nthr = blockDim.x;
     const int64_t src = chunk_src[chunk];
+    ab_walk walk(a.tab);
     int e[GS], pr[GS];
     T sgn[GS];
 #pragma unroll
     for (int g = 0; g < GS; ++g) {
-        e[g] = a.grp[chunk * GS + g];
-        const uint32_t x = e[g] >= 0 ? a.a_pk[e[g]] : 0u;
+        const int2 y = a.grp[chunk * GS + g];
+        e[g] = y.x;
+        const uint32_t x = (uint32_t)y.y;   // 0 where none
         sgn[g] = (x >> 31) ? (T)-1 : (T)1;
         pr[g] = (int)((x >> SQD_PAIR_SHIFT) & SQD_PAIR_MASK);
     }
@@ -475,100 +472,102 @@ __device__ __forceinline__ void abs_block(const abg_args<T>& a, const int* __res
         vrows[q] = e[g] >= 0 ? V[(int64_t)pr[g] * norb2 + r] : (T)0;
     }
     __syncthreads();
-    const int wave = tid >> 6, lane = tid & 63, nw = nthr >> 6;
-    for (int sl = wave; sl < a.nbslices; sl += nw) {
-        T acc[GS];
+    const int lane = tid & 63;
+    T acc[GS];
+    walk.run(
+        [&] {
 #pragma unroll
-        for (int g = 0; g < GS; ++g) acc[g] = (T)0;
-        const int c0 = a.bsl_off[sl], c1 = a.bsl_off[sl + 1];
-        auto one = [&](uint32_t b) {
+            for (int g = 0; g < GS; ++g) acc[g] = (T)0;
+        },
+        [&](uint32_t b) {
             const int nbr = (int)(b & SQD_NBR_MASK);
             const int pb = (int)((b >> SQD_PAIR_SHIFT) & SQD_PAIR_MASK);
             T x = xs[nbr];
             if (b >> 31) x = -x;   // (-v) x = v (-x) exactly
 #pragma unroll
             for (int g = 0; g < GS; ++g) acc[g] += vrows[g * norb2 + pb] * x;
-        };
-        int col = c0;
-        // table entries in flight: sixteen while GS rows leave the registers
-        // for them (with GS = 8 FP64 sixteen entries spilled)
-        constexpr int kD = GS <= 3 ? 16 : 8;
-        for (; col + kD <= c1; col += kD) {
-            uint32_t bd[kD];
-#pragma unroll
-            for (int u = 0; u < kD; ++u) bd[u] = a.bs_pk[(int64_t)(col + u) * 64 + lane];
-#pragma unroll
-            for (int u = 0; u < kD; ++u) one(bd[u]);
-        }
-        if (kD > 8 && col + 8 <= c1) {
-            uint32_t b8[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) b8[u] = a.bs_pk[(int64_t)(col + u) * 64 + lane];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) one(b8[u]);
-            col += 8;
-        }
-        if (col + 4 <= c1) {
-            uint32_t b4[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) b4[u] = a.bs_pk[(int64_t)(col + u) * 64 + lane];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) one(b4[u]);
-            col += 4;
-        }
-        for (; col < c1; ++col) one(a.bs_pk[(int64_t)col * 64 + lane]);
-        // padding lanes read only the zero column: their value is zero
-        const int64_t slot = (int64_t)sl * 64 + lane;
-#pragma unroll
-        for (int g = 0; g < GS; ++g)
-            if (e[g] >= 0) __builtin_nontemporal_store(sgn[g] * acc[g], a.Y + (int64_t)e[g] * a.ldy + slot);
-    }
+        },
+        [&](int split, int slot) { put_y<T, GS>(a, e, sgn, acc, lane, split, slot); });
 }
 
-// sigma[ia][perm(p)] += sum_{e in row ia} Y[e][p] over all slots p of row ia,
-// one workgroup per row: each thread reads two adjacent slots with
-// one vector load (ldy is a multiple of 64), eight rows of Y in flight.  Y is
-// written once and read once, so both sides bypass the caches' retention
-// (non-temporal accesses): the tables and C of the next kernels stay cached
-// (4.0e6-determinant workload, same box: gather 142 -> 103 us, the beta-beta
-// kernel after it 192 -> 176 us).  With `row` (LDS, nb values) the sums are
-// placed by target first and the row of sigma is then updated with coalesced
-// accesses; without it (rows too long for LDS) each sum is added in place.
+// What the gather adds to a row of sigma, and where the row goes.
 template <typename T>
-__device__ __forceinline__ void gather_row(const T* __restrict__ Y, T* __restrict__ S, int64_t nb, int64_t ldy,
-                                           const int* __restrict__ bperm, const int* __restrict__ a_off, int64_t ia,
-                                           T* row) {
+struct gather_args {
+    const T* Y;
+    int64_t nb;
+    int64_t nslots;           // columns of Y
+    const int* perm;          // string of each slot
+    const int* a_off;
+    T* S;                     // rows of sigma: read and, without out64, written
+    const T* S2;              // added too, or null
+    const double* diag;       // diag * c added too (FP64 or into out64), or null
+    const double* c;
+    double* out64;            // FP32 sums: the row goes here in FP64 (S is only read)
+};
+
+// Row ia of sigma: S + S2 + sum_{e in row ia} Y[e][slot] (+ diag c), one
+// workgroup per row.  A thread reads two adjacent slots with one vector load,
+// eight rows of Y in flight; Y is written once and read once, so both sides
+// bypass the caches' retention (non-temporal accesses): the tables and C of
+// the next kernels stay cached (4.0e6-determinant workload, same box: gather
+// 142 -> 103 us, the beta-beta kernel after it 192 -> 176 us).  Rows of Y
+// shorter than the workgroup are read by ng groups of threads, each taking
+// every ng-th single, whose sums are added in order.  With `row` (LDS, ng x nb
+// values) the sums are placed by target first and sigma is updated with
+// coalesced accesses; without it (rows too long for the LDS; one group) each
+// sum is added in place.
+template <typename T>
+__device__ __forceinline__ void gather_row(const gather_args<T>& a, int64_t ia, int ng, T* row) {
     typedef T T2 __attribute__((ext_vector_type(2)));
     constexpr int kU = 8;
-    const int e0 = a_off[ia], e1 = a_off[ia + 1];
-    T* srow = S + ia * nb;
-    for (int64_t p = 2 * (int64_t)threadIdx.x; p < ldy; p += 2 * (int64_t)blockDim.x) {
+    const int64_t nb = a.nb, nslots = a.nslots;
+    const int per = (int)blockDim.x / ng, grp = (int)threadIdx.x / per, t = (int)threadIdx.x - grp * per;
+    const int e0 = a.a_off[ia] + grp, e1 = a.a_off[ia + 1];
+    auto put = [&](int64_t j, T v) {                 // sum v of target j of the row
+        const int64_t o = ia * nb + j;
+        v += a.S2 ? a.S[o] + a.S2[o] : a.S[o];
+        if constexpr (sizeof(T) == 8) {
+            if (a.diag) v += a.diag[o] * a.c[o];
+            a.S[o] = v;
+        } else if (a.out64) {
+            double d = (double)v;
+            if (a.diag) d += a.diag[o] * a.c[o];
+            a.out64[o] = d;
+        } else {
+            a.S[o] = v;
+        }
+    };
+    T* mine = row + grp * nb;
+    for (int64_t p = 2 * (int64_t)t; p < nslots; p += 2 * (int64_t)per) {
         T a0 = (T)0, a1 = (T)0;
-        for (int e = e0; e < e1; e += kU) {
+        for (int e = e0; e < e1; e += kU * ng) {
             T2 v[kU];
 #pragma unroll
             for (int u = 0; u < kU; ++u)
-                v[u] = (e + u < e1) ? __builtin_nontemporal_load(reinterpret_cast<const T2*>(Y + (int64_t)(e + u) * ldy + p))
-                                    : T2{(T)0, (T)0};
+                v[u] = (e + u * ng < e1) ? __builtin_nontemporal_load(
+                                                 reinterpret_cast<const T2*>(a.Y + (int64_t)(e + u * ng) * nslots + p))
+                                           : T2{(T)0, (T)0};
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
                 a0 += v[u].x;
                 a1 += v[u].y;
             }
         }
-        const int t0 = bperm[p], t1 = bperm[p + 1];
+        const int t0 = a.perm[p], t1 = a.perm[p + 1];
         if (row) {
-            if (t0 < nb) row[t0] = a0;
-            if (t1 < nb) row[t1] = a1;
+            if (t0 < nb) mine[t0] = a0;
+            if (t1 < nb) mine[t1] = a1;
         } else {
-            if (t0 < nb) srow[t0] += a0;
-            if (t1 < nb) srow[t1] += a1;
+            if (t0 < nb) put(t0, a0);
+            if (t1 < nb) put(t1, a1);
         }
     }
-    if (row) {
-        __syncthreads();
-        for (int64_t j = threadIdx.x; j < nb; j += blockDim.x) srow[j] += row[j];
-        __syncthreads();
+    if (!row) return;
+    __syncthreads();
+    for (int64_t j = threadIdx.x; j < nb; j += blockDim.x) {
+        T v = row[j];
+        for (int q = 1; q < ng; ++q) v += row[q * nb + j];
+        put(j, v);
     }
 }
 

@@ -93,6 +93,51 @@ struct prof_scope {
     }
 };
 
+// A sliced copy (SELL-64) of a spin's tables: slices of 64 lanes, one row or
+// part of a row per lane, stored in blocks of four entries per lane, so that a
+// wavefront reads 256 entries with one 16-byte load per lane (their values
+// with one or two); padding points at the zero column and every slice has an
+// even number of blocks.  A slice lists its rows' singles first, then their
+// doubles.  The entries of a row go to 2^k adjacent lanes in turn (k per
+// slice; one lane without `split`), whose sums the kernel adds across the
+// lanes.  The slices are dealt into sixteen bins of about equal length, bin k
+// being slices bin[k] .. bin[k + 1]: a workgroup of sixteen, eight or four
+// waves gives each wave one, two or four adjacent bins, whose blocks are
+// contiguous in memory.
+constexpr int kBins = 16;
+template <typename T>
+struct sell_table {
+    int nslices = 0;
+    const int* perm = nullptr;    // nslices*64: row at the first lane of its group, else n
+    const int* split = nullptr;   // log2 of the lanes per row of each slice (null: 0)
+    const int* blk = nullptr;     // nslices+1 block offsets
+    const int* s_blk = nullptr;   // blocks of singles of each slice
+    const int* bin = nullptr;     // kBins+1 slice offsets, then the block offsets of the same slices
+    int64_t slots = 0;            // 256 x blocks
+    uint32_t* ent = nullptr;      // entry q of lane l of block b at 256 b + 4 l + q: packed single, or neighbour
+    T* val = nullptr;             // FP32 at the same place; FP64 at 256 b + 128 (q / 2) + 2 l + q % 2
+    int* csr = nullptr;           // CSR entry e of each slot: e of a single, -2 - e of a double, -1 padding
+};
+
+// The sliced copy of a spin's singles for the alpha-beta kernels: slices, lanes
+// per row and bins as in sell_table, entries four to a block in the order of
+// their orbital pairs (lanes reading one column then look up nearby, often
+// equal, integrals); the last block of a slice is used up to its column
+// count.  Rows have output slots: slice by slice, one per row (whole rows) or
+// 64 >> k (rows over 2^k lanes).
+struct ab_table {
+    int nslices = 0;
+    int64_t nslots = 0;           // a multiple of 64
+    const int* perm = nullptr;    // nslots: string of each slot, n where none
+    const int* split = nullptr;   // null: 0
+    const int* blk = nullptr;     // nslices+1 block offsets
+    const int* cols = nullptr;    // columns of each slice
+    const int* slot = nullptr;    // first slot of each slice
+    const int* bin = nullptr;     // kBins+1 slice offsets, then the block offsets of the same slices
+    uint32_t* ent = nullptr;      // entry q of lane l of block b at 256 b + 4 l + q: packed single
+    int64_t nblk = 0;
+};
+
 // Per-spin tables of one string set (Sec. V-A flattened lists).
 struct spin_tables {
     int64_t n = 0;                // strings
@@ -112,34 +157,27 @@ struct spin_tables {
     double* s_val64 = nullptr; float* s_val32 = nullptr;
     double* d_val64 = nullptr; float* d_val32 = nullptr;
     double* e_same = nullptr;     // same-spin diagonal energy per string
-    // sliced (SELL-64) copies for the same-spin kernel, rows sorted by length
-    int nslices = 0;
-    int* perm_ss = nullptr;       // nslices*64, padded with n
-    int* sl_s_off = nullptr;      // nslices+1 (units of 64 entries)
-    int* sl_d_off = nullptr;
-    uint32_t* sell_s_pk = nullptr;
-    double* sell_s_v64 = nullptr; float* sell_s_v32 = nullptr;
-    int* sell_d_nbr = nullptr;
-    double* sell_d_v64 = nullptr; float* sell_d_v32 = nullptr;
-    // sliced singles for the alpha-beta kernel (rows sorted by singles count)
-    int* perm_ab = nullptr;
-    int* sl_ab_off = nullptr;
-    uint32_t* sell_ab_pk = nullptr;
-    int* sell_csr_s = nullptr;    // CSR index of each sliced slot (-1 = padding)
-    int* sell_csr_d = nullptr;
-    int64_t sell_ss_entries = 0, sell_ab_entries = 0;
+    // sliced (SELL-64) copies for the same-spin kernel, rows sorted by length:
+    // ss32 one lane per row (FP32 products), ss64 long rows over several lanes
+    // (FP64 products)
+    sell_table<float> ss32;
+    sell_table<double> ss64;
+    // sliced singles for the alpha-beta kernels, rows sorted by their count:
+    // whole rows (FP32), long rows over several lanes (FP64)
+    ab_table ab32, ab64;
+    int* sell_index = nullptr;    // one allocation: the perms and offsets of the sliced tables
     int max_singles = 0, max_doubles = 0;
     bool alias = false;           // arrays owned by the other spin
     // windowed sliced tables for rows too long to stage whole (window.hip):
     // the source strings are dealt into win_W interleaved windows (source j in
     // window j mod W, local index j / W, at most win_width per window); part w
-    // lists, per target in the perm_ss order, the entries of window w
+    // lists, per target in the order of ss32.perm, the entries of window w
     int win_W = 0, win_width = 0, win_values_version = -1;
     int* win_s_off = nullptr;     // win_W * (nslices + 1) slot-column offsets (units of 64)
     int* win_d_off = nullptr;
     uint32_t* win_s_pk = nullptr; // local source | pair << 17 | negative << 31
     uint16_t* win_d_nbr = nullptr; // local source (below the window width)
-    int* win_islot = nullptr;     // n: slot of each target in the perm_ss order
+    int* win_islot = nullptr;     // n: slot of each target in ss32.perm
     int* win_s_csr = nullptr;     // CSR index of each slot (-1: padding)
     int* win_d_csr = nullptr;
     double* win_s_v64 = nullptr; float* win_s_v32 = nullptr;
@@ -150,6 +188,10 @@ struct spin_tables {
     // past n), per Hamiltonian version
     double* wg64 = nullptr; float* wg32 = nullptr;
     int wg_version = -1;
+    // the same sums string-major, ws[s * norb^2 + pq], in the arithmetic of
+    // each precision, for the row-staged kernel (null where no precision's
+    // rows are staged whole, or the table would be large)
+    double* ws64 = nullptr; float* ws32 = nullptr;
 };
 
 struct sqd_space {
@@ -168,7 +210,7 @@ struct sqd_space {
     // alpha singles grouped by orbital pair for the grouped alpha-beta kernel
     int ab_G = 0;                 // entries per chunk (0 = not built)
     int ab_nchunks = 0;
-    int* ab_grp = nullptr;        // ab_nchunks * ab_G CSR positions (-1 = padding)
+    int2* ab_grp = nullptr;       // ab_nchunks * ab_G alpha singles: CSR position (-1 = padding), gather form
     int* ab_chunk_pair = nullptr; // pair index of each chunk
     int* ab_rev = nullptr;        // alpha singles: entry of the neighbour's row pointing back
     int* ab_row_order = nullptr;  // alpha rows by decreasing number of singles (gather order)
@@ -176,7 +218,7 @@ struct sqd_space {
     // staged sources: one staged source row serves several pairs)
     int abs_G = 0;
     int abs_nchunks = 0;
-    int* abs_grp = nullptr;       // abs_nchunks * abs_G CSR positions (-1 = padding)
+    int2* abs_grp = nullptr;      // abs_nchunks * abs_G alpha singles, as ab_grp
     int* abs_src = nullptr;       // source alpha string of each chunk
     // Knowles-Handy beta tiles (64 targets each): the union of the pair columns
     // their singles use, and for every (target, column) the source of that
@@ -195,6 +237,7 @@ struct sqd_space {
     int64_t h_bytes = 0;
     int h_version = -1;
     int64_t h_xcd_rows[9] = {};   // row ranges of equal element counts, one per XCD
+    unsigned fused_terms[2] = {};   // terms of the products run in one launch (FP64, FP32)
     // partial sums of the windowed same-spin kernel (rows x slots, FP64-sized)
     void* win_P = nullptr;
     size_t win_P_bytes = 0;
@@ -219,6 +262,7 @@ int sqd_noalloc_init(int device);   // device address of the static product scra
 // ---- tables.hip ----
 int sqd_build_spin_tables(sqd_ctx* ctx, sqd_space* sp, int spin, const uint64_t* host_str,
                           int64_t n, int nel);   // host_str: n x sp->nw words
+int sqd_alloc_cross_tables(sqd_ctx* ctx, sqd_space* sp);   // spin_tables::ws64, ws32 (both spins built)
 int sqd_build_values(sqd_ctx* ctx, sqd_space* sp);   // integral-dependent parts
 void sqd_free_spin_tables(spin_tables* t);
 

@@ -8,6 +8,8 @@
 // each row by target index (canonical order) and packed.  The integral-
 // dependent same-spin values are computed per entry afterwards, so that a new
 // Hamiltonian does not rebuild the structure.
+#include <algorithm>
+
 #include <rocprim/device/device_radix_sort.hpp>
 
 #include "sqd_internal.h"
@@ -244,111 +246,57 @@ __global__ void k_pack(const uint64_t* __restrict__ keys, const uint32_t* __rest
     }
 }
 
-// Row lengths -> sort keys for the sliced layouts (longest rows first).
-__global__ void k_len_keys(const int* __restrict__ off_a, const int* __restrict__ off_b, int64_t n,
-                           uint32_t* __restrict__ keys, int* __restrict__ rows) {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    int len = off_a[r + 1] - off_a[r];
-    if (off_b) len += off_b[r + 1] - off_b[r];
-    keys[r] = 0x7FFFFFFFu - (uint32_t)len;
-    rows[r] = (int)r;
-}
-
-// Per-slice maximum row lengths; perm is padded to nslices*64 with n.
-__global__ void k_slice_max(const int* __restrict__ perm, int64_t n, int nslices,
-                            const int* __restrict__ off_a, const int* __restrict__ off_b,
-                            int* __restrict__ max_a, int* __restrict__ max_b) {
-    const int sl = blockIdx.x;
-    const int lane = threadIdx.x;
-    const int r = perm[sl * 64 + lane];
-    int la = 0, lb = 0;
-    if (r < n) {
-        la = off_a[r + 1] - off_a[r];
-        if (off_b) lb = off_b[r + 1] - off_b[r];
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        la = max(la, __shfl_xor(la, o));
-        lb = max(lb, __shfl_xor(lb, o));
-    }
-    if (lane == 0) {
-        max_a[sl] = la;
-        if (max_b) max_b[sl] = lb;
-    }
-}
-
-__global__ void k_pad_perm(const int* __restrict__ sorted_rows, int64_t n, int total, int* __restrict__ perm) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= total) return;
-    perm[k] = (k < n) ? sorted_rows[k] : (int)n;
-}
-
-// Fill a sliced table: slot (slice, col, lane) takes CSR entry col of row
-// perm[slice*64+lane] or a padding entry pointing at the zero slot n.
-__global__ void k_sell_fill_pk(const int* __restrict__ perm, int64_t n, int nslices,
-                               const int* __restrict__ sl_off, const int* __restrict__ off,
-                               const uint32_t* __restrict__ pk, uint32_t* __restrict__ sell_pk,
-                               int* __restrict__ sell_csr) {
+// Fill a sliced same-spin table (layout: sell_table): column c of a lane that
+// is the i-th of g = 2^split lanes of its row takes CSR entry c * g + i, the
+// columns of the singles' blocks from the singles, the others from the doubles.
+template <typename T>
+__global__ void __launch_bounds__(256) k_sell_fill(sell_table<T> L, int64_t n, const int* __restrict__ s_off,
+                                                   const uint32_t* __restrict__ s_pk, const int* __restrict__ d_off,
+                                                   const int* __restrict__ d_nbr) {
     const int sl = blockIdx.x;
     const int lane = threadIdx.x & 63;
-    const int r = perm[sl * 64 + lane];
-    const int ncol = sl_off[sl + 1] - sl_off[sl];
-    const int len = (r < n) ? off[r + 1] - off[r] : 0;
-    for (int col = threadIdx.x >> 6; col < ncol; col += blockDim.x >> 6) {
-        const int64_t pos = ((int64_t)sl_off[sl] + col) * 64 + lane;
-        if (col < len) {
-            const int src = off[r] + col;
-            sell_pk[pos] = pk[src];
-            if (sell_csr) sell_csr[pos] = src;
-        } else {
-            sell_pk[pos] = (uint32_t)n;   // neighbour = zero slot, pair 0, positive
-            if (sell_csr) sell_csr[pos] = -1;
+    const int k = L.split ? L.split[sl] : 0;
+    const int sub = lane & ((1 << k) - 1);
+    const int r = L.perm[sl * 64 + lane - sub];
+    const int b0 = L.blk[sl], nb = L.blk[sl + 1] - b0, sb = L.s_blk[sl];
+    const int s0 = r < n ? s_off[r] : 0, s1 = r < n ? s_off[r + 1] : 0;
+    const int d0 = r < n ? d_off[r] : 0, d1 = r < n ? d_off[r + 1] : 0;
+    for (int b = threadIdx.x >> 6; b < nb; b += blockDim.x >> 6) {
+        const bool single = b < sb;
+        const int from = single ? s0 : d0, to = single ? s1 : d1;
+        const int64_t pos = (int64_t)(b0 + b) * 256 + lane * 4;
+        for (int q = 0; q < 4; ++q) {
+            const int e = from + (((single ? b : b - sb) * 4 + q) << k) + sub;
+            const bool in = e < to;
+            L.ent[pos + q] = !in ? (uint32_t)n : single ? s_pk[e] : (uint32_t)d_nbr[e];
+            L.csr[pos + q] = !in ? -1 : single ? e : -2 - e;
         }
     }
 }
 
-// Order each target's entries in the sliced alpha-beta table by pair index,
-// so that lanes reading column k of a slice tend to look up nearby (often
-// equal) integrals.  Padding stays at the end of each lane's column list.
-__global__ void k_sell_sort_pairs(const int* __restrict__ perm, int64_t n, int nslices,
-                                  const int* __restrict__ sl_off, const int* __restrict__ off,
-                                  uint32_t* __restrict__ sell_pk) {
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= (int64_t)nslices * 64) return;
-    const int sl = (int)(q >> 6), lane = (int)(q & 63);
-    const int r = perm[q];
-    if (r >= n) return;
-    const int len = off[r + 1] - off[r];
-    uint32_t* col = sell_pk + (int64_t)sl_off[sl] * 64 + lane;
-    auto key = [](uint32_t x) { return (x >> SQD_PAIR_SHIFT) & SQD_PAIR_MASK; };
-    for (int i = 1; i < len; ++i) {   // insertion sort over the lane's entries (strided by 64)
-        const uint32_t x = col[(int64_t)i * 64];
-        int j = i - 1;
-        while (j >= 0 && key(col[(int64_t)j * 64]) > key(x)) {
-            col[(int64_t)(j + 1) * 64] = col[(int64_t)j * 64];
-            --j;
-        }
-        col[(int64_t)(j + 1) * 64] = x;
-    }
-}
-
-__global__ void k_sell_fill_nbr(const int* __restrict__ perm, int64_t n, int nslices,
-                                const int* __restrict__ sl_off, const int* __restrict__ off,
-                                const int* __restrict__ nbr, int* __restrict__ sell_nbr,
-                                int* __restrict__ sell_csr) {
+// Fill the alpha-beta table (layout: ab_table), one workgroup per slice.  An
+// entry's place in its row is the number of the row's singles with a smaller
+// pair (the pairs of one row are distinct); the place p of a row over g lanes
+// is column p / g of its lane p % g.
+__global__ void __launch_bounds__(256) k_ab_fill(ab_table L, int64_t n, const int* __restrict__ off,
+                                                 const uint32_t* __restrict__ pk) {
     const int sl = blockIdx.x;
-    const int lane = threadIdx.x & 63;
-    const int r = perm[sl * 64 + lane];
-    const int ncol = sl_off[sl + 1] - sl_off[sl];
-    const int len = (r < n) ? off[r + 1] - off[r] : 0;
-    for (int col = threadIdx.x >> 6; col < ncol; col += blockDim.x >> 6) {
-        const int64_t pos = ((int64_t)sl_off[sl] + col) * 64 + lane;
-        if (col < len) {
-            sell_nbr[pos] = nbr[off[r] + col];
-            sell_csr[pos] = off[r] + col;
-        } else {
-            sell_nbr[pos] = (int)n;
-            sell_csr[pos] = -1;
+    const int b0 = L.blk[sl], nb = L.blk[sl + 1] - b0;
+    uint32_t* out = L.ent + (int64_t)b0 * 256;
+    for (int q = threadIdx.x; q < nb * 256; q += 256) out[q] = (uint32_t)n;   // padding: zero column, pair 0
+    __syncthreads();
+    auto pair = [](uint32_t x) { return (x >> SQD_PAIR_SHIFT) & SQD_PAIR_MASK; };
+    const int k = L.split ? L.split[sl] : 0;
+    const int wave = threadIdx.x >> 6;
+    for (int row = wave; row < (64 >> k); row += 4) {
+        const int r = L.perm[L.slot[sl] + row];
+        if (r >= n) continue;
+        for (int e = off[r] + (threadIdx.x & 63); e < off[r + 1]; e += 64) {
+            const uint32_t x = pk[e];
+            int place = 0;
+            for (int f = off[r]; f < off[r + 1]; ++f) place += pair(pk[f]) < pair(x);
+            const int col = place >> k, lane = (row << k) + (place & ((1 << k) - 1));
+            out[(col >> 2) * 256 + lane * 4 + (col & 3)] = x;
         }
     }
 }
@@ -414,12 +362,29 @@ __global__ void k_double_values(const uint64_t* __restrict__ ent, int64_t nnz, i
 }
 
 template <typename T>
-__global__ void k_sell_values(const int* __restrict__ sell_csr, int64_t m, const T* __restrict__ v,
-                              T* __restrict__ out) {
+__global__ void k_sell_values(const int* __restrict__ csr, int64_t m, const T* __restrict__ s_val,
+                              const T* __restrict__ d_val, T* __restrict__ out) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= m) return;
-    const int src = sell_csr[k];
-    out[k] = (src >= 0) ? v[src] : (T)0;
+    const int e = csr[k];
+    const T v = e >= 0 ? s_val[e] : e == -1 ? (T)0 : d_val[-2 - e];
+    // FP64: the four values of a lane as two planes of 16-byte pieces
+    const int64_t q = k & 3, lane = (k >> 2) & 63;
+    out[sizeof(T) == 8 ? (k & ~(int64_t)255) + 128 * (q >> 1) + 2 * lane + (q & 1) : k] = v;
+}
+
+// ws[s * norb2 + pq] = sum over occupied k of s (ascending) of jk[k * norb2 + pq]
+template <typename T>
+__global__ void k_cross_table(const uint64_t* __restrict__ str, int nw, int64_t n, int norb,
+                              const T* __restrict__ jk, T* __restrict__ ws) {
+    const int norb2 = norb * norb;
+    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= n * norb2) return;
+    const int64_t s = idx / norb2;
+    const int pq = (int)(idx - s * norb2);
+    T acc = (T)0;
+    str_for_each(str + s * nw, nw, [&](int k) { acc += jk[(int64_t)k * norb2 + pq]; });
+    ws[idx] = acc;
 }
 
 inline unsigned nblocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
@@ -508,41 +473,173 @@ int build_kind(sqd_ctx* ctx, sqd_space* sp, spin_tables& t, int** off_out, uint6
     return SQD_OK;
 }
 
-// Sorted row order (longest first) padded to whole 64-row slices.
-int make_perm(sqd_ctx* ctx, sqd_space* sp, spin_tables& t, const int* off_a, const int* off_b,
-              int** perm_out) {
-    const int nslices = (int)((t.n + 63) / 64);
-    uint32_t* keys = nullptr; int* rows = nullptr; int* perm = nullptr;
-    SQD_HIP(ctx, hipMalloc(&keys, sizeof(uint32_t) * t.n));
-    SQD_HIP(ctx, hipMalloc(&rows, sizeof(int) * t.n));
-    int rc = sqd_alloc(ctx, (void**)&perm, sizeof(int) * nslices * 64, &sp->bytes);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_len_keys, dim3(nblocks(t.n, 256)), dim3(256), 0, ctx->stream, off_a, off_b, t.n, keys, rows);
-    rc = radix_sort(ctx, keys, rows, t.n, 32);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_pad_perm, dim3(nblocks(nslices * 64, 256)), dim3(256), 0, ctx->stream, rows, t.n,
-                       nslices * 64, perm);
+// Rows by decreasing length (ties by index): a counting sort.
+std::vector<int> rows_longest_first(const std::vector<int>& len) {
+    const int most = len.empty() ? 0 : *std::max_element(len.begin(), len.end());
+    std::vector<int> at(most + 2, 0), rows(len.size());
+    for (int l : len) at[most - l + 1] += 1;
+    for (int k = 0; k <= most; ++k) at[k + 1] += at[k];
+    for (size_t r = 0; r < len.size(); ++r) rows[at[most - len[r]]++] = (int)r;
+    return rows;
+}
+
+// Lanes per row (log2): the fewest that keep a lane's entries at or below cap.
+inline int split_of(int len, int cap) {
+    int k = 0;
+    while (k < 6 && ((len + (1 << k) - 1) >> k) > cap) ++k;
+    return k;
+}
+
+// Slices dealt into bins, the costliest into the lightest bin; the heaviest
+// bins are placed beside the lightest, so that pairs and fours of adjacent
+// bins are even too.
+std::vector<std::vector<int>> deal_bins(const std::vector<int>& cost) {
+    std::vector<int> order(cost.size()), load(kBins, 0), rank(kBins);
+    for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost[x] > cost[y]; });
+    std::vector<std::vector<int>> in(kBins), out(kBins);
+    for (int k : order) {
+        const int q = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+        in[q].push_back(k);
+        load[q] += cost[k];
+    }
+    for (int q = 0; q < kBins; ++q) rank[q] = q;
+    std::stable_sort(rank.begin(), rank.end(), [&](int x, int y) { return load[x] > load[y]; });
+    static constexpr int kPlace[kBins] = {0, 15, 7, 8, 3, 12, 4, 11, 1, 14, 6, 9, 2, 13, 5, 10};
+    for (int q = 0; q < kBins; ++q) out[q] = in[rank[kPlace[q]]];
+    return out;
+}
+
+// Slices of a sliced table over rows sorted by length, the longest remaining
+// row setting the lanes per row of the next slice; then dealt into bins.
+struct sell_plan {
+    std::vector<int> perm, split, blk{0}, s_blk, bin;
+};
+sell_plan plan_slices(const std::vector<int>& rows, const int* s_off, const int* d_off, int cap) {
+    struct slice { int split, s_blk, nblk; std::vector<int> perm; };
+    std::vector<slice> sl;
+    const int n = (int)rows.size();
+    auto cols = [](const int* off, int r, int k) { return (off[r + 1] - off[r] + (1 << k) - 1) >> k; };
+    for (int at = 0; at < n;) {
+        slice x;
+        x.split = split_of(cols(s_off, rows[at], 0) + cols(d_off, rows[at], 0), cap);
+        int ms = 0, md = 0;
+        for (int lane = 0; lane < 64; ++lane) {
+            const bool first = (lane & ((1 << x.split) - 1)) == 0;
+            const int r = first && at < n ? rows[at++] : n;
+            x.perm.push_back(r);
+            if (r == n) continue;
+            ms = std::max(ms, cols(s_off, r, x.split));
+            md = std::max(md, cols(d_off, r, x.split));
+        }
+        x.s_blk = (ms + 3) / 4;
+        x.nblk = (x.s_blk + (md + 3) / 4 + 1) & ~1;
+        sl.push_back(std::move(x));
+    }
+    // a single costs about two doubles (two LDS columns), a slice about one block
+    std::vector<int> cost;
+    for (const slice& x : sl) cost.push_back(x.nblk + x.s_blk + 1);
+    const auto in = deal_bins(cost);
+    sell_plan p;
+    for (int q = 0; q < kBins; ++q) {
+        p.bin.push_back((int)p.split.size());
+        for (int k : in[q]) {
+            p.perm.insert(p.perm.end(), sl[k].perm.begin(), sl[k].perm.end());
+            p.split.push_back(sl[k].split);
+            p.s_blk.push_back(sl[k].s_blk);
+            p.blk.push_back(p.blk.back() + sl[k].nblk);
+        }
+    }
+    p.bin.push_back((int)p.split.size());
+    for (int q = 0; q <= kBins; ++q) p.bin.push_back(p.blk[p.bin[q]]);
+    return p;
+}
+
+// The same for the singles alone (ab_table).
+struct ab_plan {
+    std::vector<int> perm, split, blk{0}, cols, slot, bin;
+};
+ab_plan plan_ab(const std::vector<int>& rows, const int* off, int cap) {
+    const int n = (int)rows.size();
+    struct slice { int split, at, cols; };
+    std::vector<slice> sl;
+    std::vector<int> cost;
+    for (int at = 0; at < n;) {
+        const int len = off[rows[at] + 1] - off[rows[at]];   // the longest of the slice
+        const int k = split_of(len, cap);
+        sl.push_back({k, at, (len + (1 << k) - 1) >> k});
+        cost.push_back(sl.back().cols + 2);
+        at += 64 >> k;
+    }
+    const auto in = deal_bins(cost);
+    ab_plan p;
+    for (int q = 0; q < kBins; ++q) {
+        p.bin.push_back((int)p.split.size());
+        for (int k : in[q]) {
+            p.slot.push_back((int)p.perm.size());
+            for (int j = 0; j < (64 >> sl[k].split); ++j)
+                p.perm.push_back(sl[k].at + j < n ? rows[sl[k].at + j] : n);
+            p.split.push_back(sl[k].split);
+            p.cols.push_back(sl[k].cols);
+            p.blk.push_back(p.blk.back() + (sl[k].cols + 3) / 4);
+        }
+    }
+    p.bin.push_back((int)p.split.size());
+    for (int q = 0; q <= kBins; ++q) p.bin.push_back(p.blk[p.bin[q]]);
+    while (p.perm.size() % 64) p.perm.push_back(n);
+    return p;
+}
+
+// Entries a lane of the FP64 same-spin table takes at most.  A wavefront walks
+// a slice at the pace of its longest lane, and the rows of sampled sets are
+// uneven: the Hartree-Fock string reaches half of the set, the mean row a
+// tenth.  A thirty-second of all columns leaves each of sixteen waves about
+// two slices of that length, so the waves of a workgroup end together, and
+// only the long rows pay for the sums across lanes.
+inline int split_cap(int64_t entries, int least) { return (int)std::max<int64_t>(least, (entries + 2047) / 2048); }
+
+// Arrays of a sliced same-spin table whose plan is on the device.
+template <typename T>
+int fill_sell(sqd_ctx* ctx, sqd_space* sp, const spin_tables& t, const sell_plan& p, sell_table<T>& L) {
+    L.nslices = (int)p.split.size();
+    L.slots = (int64_t)p.blk.back() * 256;
+    if (L.slots >= (1LL << 31)) return sqd_fail(ctx, SQD_E_LIMIT, "sliced table exceeds 2^31 slots");
+    int rc;
+    if ((rc = sqd_alloc(ctx, (void**)&L.ent, sizeof(uint32_t) * (L.slots + 256), &sp->bytes)) ||
+        (rc = sqd_alloc(ctx, (void**)&L.csr, sizeof(int) * (L.slots + 256), &sp->bytes)) ||
+        (rc = sqd_alloc(ctx, (void**)&L.val, sizeof(T) * (L.slots + 256), &sp->bytes)))
+        return rc;
+    hipLaunchKernelGGL(k_sell_fill<T>, dim3(L.nslices), dim3(256), 0, ctx->stream, L, t.n, t.s_off, t.s_pk, t.d_off,
+                       t.d_nbr);
     SQD_HIP(ctx, hipGetLastError());
-    SQD_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    hipFree(keys); hipFree(rows);
-    *perm_out = perm;
     return SQD_OK;
 }
 
-// Slice offsets (units of 64 entries) from per-slice maxima.
-int slice_offsets(sqd_ctx* ctx, sqd_space* sp, int nslices, const int* maxes, int** sl_off, int64_t* total) {
-    long long* dtot = nullptr;
-    SQD_HIP(ctx, hipMalloc(&dtot, sizeof(long long)));
-    int rc = sqd_alloc(ctx, (void**)sl_off, sizeof(int) * (nslices + 1), &sp->bytes);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, ctx->stream, maxes, (int64_t)nslices, *sl_off, dtot);
-    long long tot = 0;
-    SQD_HIP(ctx, hipMemcpyAsync(&tot, dtot, sizeof(long long), hipMemcpyDeviceToHost, ctx->stream));
-    SQD_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    hipFree(dtot);
-    if (tot * 64 >= (1LL << 31)) return sqd_fail(ctx, SQD_E_LIMIT, "sliced table exceeds 2^31 slots");
-    *total = tot;
+int fill_ab(sqd_ctx* ctx, sqd_space* sp, const spin_tables& t, const ab_plan& p, ab_table& L) {
+    L.nslices = (int)p.split.size();
+    L.nslots = (int64_t)p.perm.size();
+    L.nblk = p.blk.back();
+    if (L.nblk * 256 >= (1LL << 31)) return sqd_fail(ctx, SQD_E_LIMIT, "sliced table exceeds 2^31 slots");
+    int rc;
+    if ((rc = sqd_alloc(ctx, (void**)&L.ent, sizeof(uint32_t) * (L.nblk + 1) * 256, &sp->bytes))) return rc;
+    hipLaunchKernelGGL(k_ab_fill, dim3(L.nslices), dim3(256), 0, ctx->stream, L, t.n, t.s_off, t.s_pk);
+    SQD_HIP(ctx, hipGetLastError());
     return SQD_OK;
+}
+
+template <typename T>
+void free_sell(sell_table<T>& L) {   // the plan's arrays belong to spin_tables::sell_index
+    if (L.ent) (void)hipFree(L.ent);
+    if (L.csr) (void)hipFree(L.csr);
+    if (L.val) (void)hipFree(L.val);
+    L = sell_table<T>();
+}
+
+template <typename T>
+void sell_values(sqd_ctx* ctx, const sell_table<T>& L, const T* s_val, const T* d_val) {
+    if (L.slots > 0)
+        hipLaunchKernelGGL(k_sell_values<T>, dim3(nblocks(L.slots, 256)), dim3(256), 0, ctx->stream, L.csr, L.slots,
+                           s_val, d_val, L.val);
 }
 
 }  // namespace
@@ -559,48 +656,44 @@ int sqd_build_spin_tables(sqd_ctx* ctx, sqd_space* sp, int spin, const uint64_t*
     if ((rc = build_kind<0>(ctx, sp, t, &t.s_off, &t.s_ent, &t.s_pk, &dummy_nbr, &t.nnz_s))) return rc;
     if ((rc = build_kind<1>(ctx, sp, t, &t.d_off, &t.d_ent, &dummy_pk, &t.d_nbr, &t.nnz_d))) return rc;
 
-    // same-spin sliced layout: rows sorted by singles + doubles
-    t.nslices = (int)((n + 63) / 64);
-    if ((rc = make_perm(ctx, sp, t, t.s_off, t.d_off, &t.perm_ss))) return rc;
-    int *mx_s = nullptr, *mx_d = nullptr;
-    SQD_HIP(ctx, hipMalloc(&mx_s, sizeof(int) * (t.nslices + 1)));
-    SQD_HIP(ctx, hipMalloc(&mx_d, sizeof(int) * (t.nslices + 1)));
-    hipLaunchKernelGGL(k_slice_max, dim3(t.nslices), dim3(64), 0, ctx->stream, t.perm_ss, n, t.nslices, t.s_off,
-                       t.d_off, mx_s, mx_d);
-    int64_t tot_s = 0, tot_d = 0;
-    if ((rc = slice_offsets(ctx, sp, t.nslices, mx_s, &t.sl_s_off, &tot_s))) return rc;
-    if ((rc = slice_offsets(ctx, sp, t.nslices, mx_d, &t.sl_d_off, &tot_d))) return rc;
-    t.sell_ss_entries = (tot_s + tot_d) * 64;
-    int* csr_s = nullptr; int* csr_d = nullptr;
-    if ((rc = sqd_alloc(ctx, (void**)&t.sell_s_pk, sizeof(uint32_t) * (tot_s * 64 + 1), &sp->bytes))) return rc;
-    if ((rc = sqd_alloc(ctx, (void**)&t.sell_d_nbr, sizeof(int) * (tot_d * 64 + 1), &sp->bytes))) return rc;
-    if ((rc = sqd_alloc(ctx, (void**)&csr_s, sizeof(int) * (tot_s * 64 + 1), &sp->bytes))) return rc;
-    if ((rc = sqd_alloc(ctx, (void**)&csr_d, sizeof(int) * (tot_d * 64 + 1), &sp->bytes))) return rc;
-    if ((rc = sqd_alloc(ctx, (void**)&t.sell_s_v64, sizeof(double) * (tot_s * 64 + 1), &sp->bytes))) return rc;
-    if ((rc = sqd_alloc(ctx, (void**)&t.sell_s_v32, sizeof(float) * (tot_s * 64 + 1), &sp->bytes))) return rc;
-    if ((rc = sqd_alloc(ctx, (void**)&t.sell_d_v64, sizeof(double) * (tot_d * 64 + 1), &sp->bytes))) return rc;
-    if ((rc = sqd_alloc(ctx, (void**)&t.sell_d_v32, sizeof(float) * (tot_d * 64 + 1), &sp->bytes))) return rc;
-    hipLaunchKernelGGL(k_sell_fill_pk, dim3(t.nslices), dim3(256), 0, ctx->stream, t.perm_ss, n, t.nslices,
-                       t.sl_s_off, t.s_off, t.s_pk, t.sell_s_pk, csr_s);
-    hipLaunchKernelGGL(k_sell_fill_nbr, dim3(t.nslices), dim3(256), 0, ctx->stream, t.perm_ss, n, t.nslices,
-                       t.sl_d_off, t.d_off, t.d_nbr, t.sell_d_nbr, csr_d);
-    SQD_HIP(ctx, hipGetLastError());
-
-    // alpha-beta sliced singles: rows sorted by singles count
-    if ((rc = make_perm(ctx, sp, t, t.s_off, nullptr, &t.perm_ab))) return rc;
-    hipLaunchKernelGGL(k_slice_max, dim3(t.nslices), dim3(64), 0, ctx->stream, t.perm_ab, n, t.nslices, t.s_off,
-                       nullptr, mx_s, nullptr);
-    int64_t tot_ab = 0;
-    if ((rc = slice_offsets(ctx, sp, t.nslices, mx_s, &t.sl_ab_off, &tot_ab))) return rc;
-    t.sell_ab_entries = tot_ab * 64;
-    if ((rc = sqd_alloc(ctx, (void**)&t.sell_ab_pk, sizeof(uint32_t) * (tot_ab * 64 + 1), &sp->bytes))) return rc;
-    hipLaunchKernelGGL(k_sell_fill_pk, dim3(t.nslices), dim3(256), 0, ctx->stream, t.perm_ab, n, t.nslices,
-                       t.sl_ab_off, t.s_off, t.s_pk, t.sell_ab_pk, nullptr);
-    hipLaunchKernelGGL(k_sell_sort_pairs, dim3((unsigned)(((int64_t)t.nslices * 64 + 255) / 256)), dim3(256), 0,
-                       ctx->stream, t.perm_ab, n, t.nslices, t.sl_ab_off, t.s_off, t.sell_ab_pk);
-    SQD_HIP(ctx, hipGetLastError());
-    SQD_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    hipFree(mx_s); hipFree(mx_d);
+    // sliced layouts, planned on the host from the row lengths: same-spin rows
+    // by singles + doubles, alpha-beta rows by singles
+    std::vector<int> so(n + 1), dof(n + 1), len(n);
+    SQD_HIP(ctx, hipMemcpy(so.data(), t.s_off, sizeof(int) * (n + 1), hipMemcpyDeviceToHost));
+    SQD_HIP(ctx, hipMemcpy(dof.data(), t.d_off, sizeof(int) * (n + 1), hipMemcpyDeviceToHost));
+    t.max_singles = t.max_doubles = 0;
+    for (int64_t r = 0; r < n; ++r) {
+        len[r] = so[r + 1] - so[r];
+        t.max_singles = std::max(t.max_singles, len[r]);
+        t.max_doubles = std::max(t.max_doubles, dof[r + 1] - dof[r]);
+    }
+    constexpr int kWhole = 1 << 30;
+    const std::vector<int> rows_s = rows_longest_first(len);
+    const ab_plan a32 = plan_ab(rows_s, so.data(), kWhole);
+    const ab_plan a64 = plan_ab(rows_s, so.data(), split_cap(t.nnz_s, 8));
+    for (int64_t r = 0; r < n; ++r) len[r] += dof[r + 1] - dof[r];
+    const std::vector<int> rows = rows_longest_first(len);
+    const sell_plan p32 = plan_slices(rows, so.data(), dof.data(), kWhole);
+    const sell_plan p64 = plan_slices(rows, so.data(), dof.data(), split_cap(t.nnz_s + t.nnz_d, 12));
+    {
+        const std::pair<const std::vector<int>*, const int**> parts[] = {
+            {&p32.perm, &t.ss32.perm}, {&p32.blk, &t.ss32.blk},   {&p32.s_blk, &t.ss32.s_blk}, {&p32.bin, &t.ss32.bin},
+            {&p64.perm, &t.ss64.perm}, {&p64.blk, &t.ss64.blk},   {&p64.s_blk, &t.ss64.s_blk}, {&p64.bin, &t.ss64.bin},
+            {&p64.split, &t.ss64.split}, {&a32.perm, &t.ab32.perm}, {&a32.blk, &t.ab32.blk},   {&a32.cols, &t.ab32.cols},
+            {&a32.slot, &t.ab32.slot}, {&a32.bin, &t.ab32.bin},   {&a64.perm, &t.ab64.perm},   {&a64.blk, &t.ab64.blk},
+            {&a64.cols, &t.ab64.cols}, {&a64.slot, &t.ab64.slot}, {&a64.bin, &t.ab64.bin},     {&a64.split, &t.ab64.split}};
+        std::vector<int> all;
+        for (const auto& q : parts) all.insert(all.end(), q.first->begin(), q.first->end());
+        if ((rc = sqd_alloc(ctx, (void**)&t.sell_index, sizeof(int) * (all.size() + 1), &sp->bytes))) return rc;
+        SQD_HIP(ctx, hipMemcpy(t.sell_index, all.data(), sizeof(int) * all.size(), hipMemcpyHostToDevice));
+        const int* at = t.sell_index;
+        for (const auto& q : parts) {
+            *q.second = at;
+            at += q.first->size();
+        }
+    }
+    if ((rc = fill_sell(ctx, sp, t, p32, t.ss32)) || (rc = fill_sell(ctx, sp, t, p64, t.ss64))) return rc;
+    if ((rc = fill_ab(ctx, sp, t, a32, t.ab32)) || (rc = fill_ab(ctx, sp, t, a64, t.ab64))) return rc;
 
     // value arrays (CSR order)
     if ((rc = sqd_alloc(ctx, (void**)&t.s_val64, sizeof(double) * (t.nnz_s + 1), &sp->bytes))) return rc;
@@ -608,16 +701,32 @@ int sqd_build_spin_tables(sqd_ctx* ctx, sqd_space* sp, int spin, const uint64_t*
     if ((rc = sqd_alloc(ctx, (void**)&t.d_val64, sizeof(double) * (t.nnz_d + 1), &sp->bytes))) return rc;
     if ((rc = sqd_alloc(ctx, (void**)&t.d_val32, sizeof(float) * (t.nnz_d + 1), &sp->bytes))) return rc;
     if ((rc = sqd_alloc(ctx, (void**)&t.e_same, sizeof(double) * (n + 1), &sp->bytes))) return rc;
-    t.sell_csr_s = csr_s;
-    t.sell_csr_d = csr_d;
-    // host-side maxima for kernel launch shapes
-    std::vector<int> off_h(n + 1);
-    SQD_HIP(ctx, hipMemcpy(off_h.data(), t.s_off, sizeof(int) * (n + 1), hipMemcpyDeviceToHost));
-    t.max_singles = 0;
-    for (int64_t r = 0; r < n; ++r) t.max_singles = std::max(t.max_singles, off_h[r + 1] - off_h[r]);
-    SQD_HIP(ctx, hipMemcpy(off_h.data(), t.d_off, sizeof(int) * (n + 1), hipMemcpyDeviceToHost));
-    t.max_doubles = 0;
-    for (int64_t r = 0; r < n; ++r) t.max_doubles = std::max(t.max_doubles, off_h[r + 1] - off_h[r]);
+    return SQD_OK;
+}
+
+// Cross-spin tables of the spins whose rows of C are staged whole (four rows
+// in LDS, as the same-spin dispatch wants), up to 256 MiB; elsewhere the
+// row-staged kernel sums them itself (norb reads per value and workgroup) and
+// the windowed kernel has its own.
+int sqd_alloc_cross_tables(sqd_ctx* ctx, sqd_space* sp) {
+    const size_t n2 = (size_t)sp->norb * sp->norb;
+    int rc;
+    for (int spin = 0; spin < 2; ++spin) {
+        spin_tables& t = sp->sp[spin];
+        if (t.alias) {
+            t.ws64 = sp->sp[0].ws64;
+            t.ws32 = sp->sp[0].ws32;
+            continue;
+        }
+        const size_t lds4 = ((size_t)sp->sp[1 - spin].n + 1 + n2) * 4;   // four rows, elements
+        const size_t m = (size_t)t.n * n2;
+        if (lds4 * sizeof(double) <= (size_t)ctx->max_lds && m * sizeof(double) <= (256u << 20) &&
+            (rc = sqd_alloc(ctx, (void**)&t.ws64, sizeof(double) * m, &sp->bytes)))
+            return rc;
+        if (lds4 * sizeof(float) <= (size_t)ctx->max_lds && m * sizeof(float) <= (256u << 20) &&
+            (rc = sqd_alloc(ctx, (void**)&t.ws32, sizeof(float) * m, &sp->bytes)))
+            return rc;
+    }
     return SQD_OK;
 }
 
@@ -636,22 +745,15 @@ int sqd_build_values(sqd_ctx* ctx, sqd_space* sp) {
         if (t.nnz_d > 0)
             hipLaunchKernelGGL(k_double_values, dim3(nblocks(t.nnz_d, 256)), dim3(256), 0, ctx->stream, t.d_ent,
                                t.nnz_d, norb, ctx->eri, t.d_val64, t.d_val32);
-        int s_slots = 0, d_slots = 0;
-        SQD_HIP(ctx, hipMemcpy(&s_slots, t.sl_s_off + t.nslices, sizeof(int), hipMemcpyDeviceToHost));
-        SQD_HIP(ctx, hipMemcpy(&d_slots, t.sl_d_off + t.nslices, sizeof(int), hipMemcpyDeviceToHost));
-        const int64_t S = (int64_t)s_slots * 64, D = (int64_t)d_slots * 64;
-        if (S > 0) {
-            hipLaunchKernelGGL(k_sell_values<double>, dim3(nblocks(S, 256)), dim3(256), 0, ctx->stream, t.sell_csr_s, S,
-                               t.s_val64, t.sell_s_v64);
-            hipLaunchKernelGGL(k_sell_values<float>, dim3(nblocks(S, 256)), dim3(256), 0, ctx->stream, t.sell_csr_s, S,
-                               t.s_val32, t.sell_s_v32);
-        }
-        if (D > 0) {
-            hipLaunchKernelGGL(k_sell_values<double>, dim3(nblocks(D, 256)), dim3(256), 0, ctx->stream, t.sell_csr_d, D,
-                               t.d_val64, t.sell_d_v64);
-            hipLaunchKernelGGL(k_sell_values<float>, dim3(nblocks(D, 256)), dim3(256), 0, ctx->stream, t.sell_csr_d, D,
-                               t.d_val32, t.sell_d_v32);
-        }
+        sell_values(ctx, t.ss64, t.s_val64, t.d_val64);
+        sell_values(ctx, t.ss32, t.s_val32, t.d_val32);
+        const int64_t m = t.n * (int64_t)norb * norb;
+        if (t.ws64)
+            hipLaunchKernelGGL(k_cross_table<double>, dim3(nblocks(m, 256)), dim3(256), 0, ctx->stream, t.str, t.nw,
+                               t.n, norb, ctx->jk64, t.ws64);
+        if (t.ws32)
+            hipLaunchKernelGGL(k_cross_table<float>, dim3(nblocks(m, 256)), dim3(256), 0, ctx->stream, t.str, t.nw,
+                               t.n, norb, ctx->jk32, t.ws32);
         SQD_HIP(ctx, hipGetLastError());
     }
     SQD_HIP(ctx, hipStreamSynchronize(ctx->stream));
@@ -662,10 +764,10 @@ int sqd_build_values(sqd_ctx* ctx, sqd_space* sp) {
 void sqd_free_spin_tables(spin_tables* t) {
     if (t->alias) { *t = spin_tables(); return; }
     sqd_free_window_tables(t);
+    free_sell(t->ss32);
+    free_sell(t->ss64);
     void* ptrs[] = {t->str, t->s_off, t->s_ent, t->d_off, t->d_ent, t->s_pk, t->d_nbr, t->s_val64, t->s_val32,
-                    t->d_val64, t->d_val32, t->e_same, t->perm_ss, t->sl_s_off, t->sl_d_off, t->sell_s_pk,
-                    t->sell_s_v64, t->sell_s_v32, t->sell_d_nbr, t->sell_d_v64, t->sell_d_v32, t->perm_ab,
-                    t->sl_ab_off, t->sell_ab_pk, t->sell_csr_s, t->sell_csr_d};
+                    t->d_val64, t->d_val32, t->e_same, t->sell_index, t->ab32.ent, t->ab64.ent, t->ws64, t->ws32};
     for (void* p : ptrs)
         if (p) hipFree(p);
     *t = spin_tables();

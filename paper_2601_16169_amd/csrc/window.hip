@@ -70,6 +70,7 @@ struct win_args {
     int64_t nrows, ncols;
     int W, width, nslices;
     const int* perm;            // nslices * 64: target of each slot (n = padding)
+    const int* bin;             // kBins + 1 slice offsets: the slices of each wave
     const int* s_off;           // W x (nslices + 1)
     const int* d_off;
     const uint32_t* s_pk;
@@ -100,10 +101,11 @@ __global__ void __launch_bounds__(1024) k_same_spin_win(win_args<T> a, const int
     using L = lds_cols<T, R>;
     constexpr int kD = 8;   // doubles per batch
     const int tid = threadIdx.x, nthr = blockDim.x;
-    const int wave = tid >> 6, lane = tid & 63, nw = nthr >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int64_t row0 = (int64_t)blockIdx.x * R;
     const int norb2 = a.norb * a.norb;
     const int64_t ldp = (int64_t)a.nslices * 64;
+    const int sl0 = a.bin[wave], sl1 = a.bin[wave + 1];   // kBins waves
     // rows past the end read the last row (their results are not stored)
     auto rowc = [&](int r) -> int64_t { return row0 + r < a.nrows ? row0 + r : a.nrows - 1; };
     for (int w = 0; w < a.W; ++w) {
@@ -134,7 +136,7 @@ __global__ void __launch_bounds__(1024) k_same_spin_win(win_args<T> a, const int
         const int* so = a.s_off + (int64_t)w * (a.nslices + 1);
         const int* dof = a.d_off + (int64_t)w * (a.nslices + 1);
         const bool first = (w == 0), last = (w == a.W - 1);
-        for (int sl = wave; sl < a.nslices; sl += nw) {
+        for (int sl = sl0; sl < sl1; ++sl) {
             const int64_t slot = (int64_t)sl * 64 + lane;
             T acc[R], prev[R];
 #pragma unroll
@@ -343,21 +345,21 @@ __global__ void __launch_bounds__(256) k_win_unperm_t(const T* __restrict__ P, i
 
 // Build the windowed tables of spin t for W interleaved windows (host pass
 // over the canonical CSR, which lists for every string its in-set
-// neighbours); targets in the order of the whole sliced table (perm_ss).
+// neighbours); targets in the order of the whole sliced table (ss32.perm).
 int build_window_tables(sqd_ctx* ctx, sqd_space* sp, spin_tables& t, int W) {
     sqd_free_window_tables(&t);
     const int64_t n = t.n;
-    const int ns = t.nslices;
+    const int ns = t.ss32.nslices;
     const int width = (int)((n + W - 1) / W);
     std::vector<int> soff(n + 1), doff(n + 1), dnbr(t.nnz_d > 0 ? t.nnz_d : 1), perm((size_t)ns * 64);
     std::vector<uint32_t> spk(t.nnz_s > 0 ? t.nnz_s : 1);
     SQD_HIP(ctx, hipStreamSynchronize(ctx->stream));
     SQD_HIP(ctx, hipMemcpy(soff.data(), t.s_off, sizeof(int) * (n + 1), hipMemcpyDeviceToHost));
     SQD_HIP(ctx, hipMemcpy(doff.data(), t.d_off, sizeof(int) * (n + 1), hipMemcpyDeviceToHost));
-    SQD_HIP(ctx, hipMemcpy(perm.data(), t.perm_ss, sizeof(int) * perm.size(), hipMemcpyDeviceToHost));
+    SQD_HIP(ctx, hipMemcpy(perm.data(), t.ss32.perm, sizeof(int) * perm.size(), hipMemcpyDeviceToHost));
     if (t.nnz_s > 0) SQD_HIP(ctx, hipMemcpy(spk.data(), t.s_pk, sizeof(uint32_t) * t.nnz_s, hipMemcpyDeviceToHost));
     if (t.nnz_d > 0) SQD_HIP(ctx, hipMemcpy(dnbr.data(), t.d_nbr, sizeof(int) * t.nnz_d, hipMemcpyDeviceToHost));
-    // slot of every target (perm_ss lists each target once, padding = n)
+    // slot of every target (ss32.perm lists each target once, padding = n)
     std::vector<int> islot(n > 0 ? n : 1, -1);
     for (size_t q = 0; q < perm.size(); ++q)
         if (perm[q] >= 0 && perm[q] < n) {
@@ -463,9 +465,9 @@ int build_window_tables(sqd_ctx* ctx, sqd_space* sp, spin_tables& t, int W) {
 int window_values(sqd_ctx* ctx, spin_tables& t) {
     if (t.win_values_version == ctx->ham_version) return SQD_OK;
     int s_cols = 0, d_cols = 0;
-    SQD_HIP(ctx, hipMemcpy(&s_cols, t.win_s_off + (size_t)t.win_W * (t.nslices + 1) - 1, sizeof(int),
+    SQD_HIP(ctx, hipMemcpy(&s_cols, t.win_s_off + (size_t)t.win_W * (t.ss32.nslices + 1) - 1, sizeof(int),
                            hipMemcpyDeviceToHost));
-    SQD_HIP(ctx, hipMemcpy(&d_cols, t.win_d_off + (size_t)t.win_W * (t.nslices + 1) - 1, sizeof(int),
+    SQD_HIP(ctx, hipMemcpy(&d_cols, t.win_d_off + (size_t)t.win_W * (t.ss32.nslices + 1) - 1, sizeof(int),
                            hipMemcpyDeviceToHost));
     const int64_t S = (int64_t)s_cols * 64, D = (int64_t)d_cols * 64;
     hipStream_t s = ctx->stream;
@@ -523,24 +525,24 @@ int launch_win(sqd_ctx* ctx, sqd_space* sp, spin_tables& col, spin_tables& row, 
     // the output goes through P in slot order (P exists when W > 1) and a
     // coalesced pass places it
     const int slot_out = col.win_W > 1 ? 1 : 0;
-    win_args<T> a{X, Y, (T*)sp->win_P, nrows, ncols, col.win_W, col.win_width, col.nslices, col.perm_ss,
-                  col.win_s_off, col.win_d_off, col.win_s_pk, sv, col.win_d_nbr, dv, wg, sqd_wtable_ld(row.n),
+    win_args<T> a{X, Y, (T*)sp->win_P, nrows, ncols, col.win_W, col.win_width, col.ss32.nslices, col.ss32.perm,
+                  col.ss32.bin, col.win_s_off, col.win_d_off, col.win_s_pk, sv, col.win_d_nbr, dv, wg, sqd_wtable_ld(row.n),
                   sp->norb, colmajor, accumulate, slot_out};
     const size_t lds = (size_t)(col.win_width + 1) * R * sizeof(T);
     set_lds_attr(k_same_spin_win<T, R>, (int)lds);
     {
         prof_scope ps(ctx, timer);
-        hipLaunchKernelGGL((k_same_spin_win<T, R>), dim3(nblk(nrows, R)), dim3(1024), lds, ctx->stream, a, skip);
+        hipLaunchKernelGGL((k_same_spin_win<T, R>), dim3(nblk(nrows, R)), dim3(64 * kBins), lds, ctx->stream, a, skip);
     }
     if (slot_out && colmajor) {
         prof_scope pu(ctx, "k_win_unperm");
-        const dim3 tg((unsigned)col.nslices, nblk(nrows, 64));
+        const dim3 tg((unsigned)col.ss32.nslices, nblk(nrows, 64));
         hipLaunchKernelGGL((k_win_unperm_t<T>), tg, dim3(256), 0, ctx->stream, (const T*)sp->win_P,
-                           (int64_t)col.nslices * 64, col.perm_ss, Y, nrows, ncols, accumulate, skip);
+                           (int64_t)col.ss32.nslices * 64, col.ss32.perm, Y, nrows, ncols, accumulate, skip);
     } else if (slot_out) {
         const double* dg = sizeof(T) == 8 ? diag : nullptr;
         prof_scope pu(ctx, "k_win_unperm");
-        const int64_t ldp = (int64_t)col.nslices * 64;
+        const int64_t ldp = (int64_t)col.ss32.nslices * 64;
         const size_t rb = (size_t)ldp * sizeof(T);
         if (rb <= (size_t)ctx->max_lds) {
             set_lds_attr(k_win_unperm_lds<T>, (int)rb);
@@ -599,7 +601,7 @@ size_t sqd_window_scratch_bytes(const sqd_space* sp) {
     size_t b = 0;
     for (int spin = 0; spin < 2; ++spin) {   // rows of one spin x slots of the other
         const spin_tables& col = sp->sp[spin].alias ? sp->sp[0] : sp->sp[spin];
-        b = std::max(b, (size_t)sp->sp[1 - spin].n * (size_t)col.nslices * 64 * sizeof(double));
+        b = std::max(b, (size_t)sp->sp[1 - spin].n * (size_t)col.ss32.nslices * 64 * sizeof(double));
     }
     return b;
 }
