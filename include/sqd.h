@@ -406,8 +406,10 @@ int sqd_davidson_batched(sqd_ctx* ctx, int nspace, const sqd_space* const* space
  *   rdm2_dev[((p*n+q)*n+r)*n+s] = sum_st <c| a+_ps a+_rt a_st a_qs |c>
  * so that E = ecore + sum h.rdm1 + 1/2 sum (pq|rs) rdm2, dE/dh_pq = rdm1_pq and
  * dE/d(pq|rs) = rdm2_pqrs / 2 (per element).  rdm1_dev has norb^2 doubles,
- * rdm2_dev norb^4 (NULL skips it).  The alpha-beta part of rdm2 is a
- * D_alpha^T D_beta product over all determinants on FP64 MFMA. */
+ * rdm2_dev norb^4 (NULL skips it).  The alpha-beta part of rdm2 sums over the
+ * pairs of in-set alpha and beta singles; its tables are built by the space's
+ * first call with rdm2_dev (a copy and an allocation, so not under capture)
+ * and kept. */
 int sqd_rdm(sqd_ctx* ctx, const sqd_space* space, const double* c_dev,
             double* rdm1_dev, double* rdm2_dev);
 

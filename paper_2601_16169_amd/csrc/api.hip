@@ -114,7 +114,7 @@ static void space_release_device(sqd_space* sp) {
     sqd_free_spin_tables(&sp->sp[1]);
     sqd_free_spin_tables(&sp->sp[0]);
     void* ptrs[] = {sp->diag, sp->ua, sp->ab_grp, sp->ab_chunk_pair, sp->ab_rev, sp->kh_tile_off, sp->kh_pairs,
-                    sp->kh_map, sp->ab_row_order, sp->win_P, sp->abs_grp, sp->abs_src};
+                    sp->kh_map, sp->ab_row_order, sp->win_P, sp->abs_grp, sp->abs_src, sp->rdm_mem};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     sp->diag = sp->ua = nullptr;
@@ -122,6 +122,7 @@ static void space_release_device(sqd_space* sp) {
     sp->ab_chunk_pair = sp->ab_rev = sp->kh_tile_off = sp->kh_pairs = sp->kh_map = nullptr;
     sp->ab_row_order = nullptr;
     sp->abs_grp = nullptr;
+    sp->rdm_mem = nullptr;
     sp->abs_src = nullptr;
     sp->abs_G = sp->abs_nchunks = 0;
     sp->win_P = nullptr;

@@ -449,8 +449,7 @@ int ab_group_size(sqd_ctx* ctx, const sqd_space* sp) {
 int ensure_ab_row_order(sqd_ctx* ctx, sqd_space* sp) {
     if (sp->ab_row_order) return SQD_OK;
     const spin_tables& A = sp->sp[0];
-    std::vector<int> off(A.n + 1);
-    SQD_HIP(ctx, hipMemcpy(off.data(), A.s_off, sizeof(int) * (A.n + 1), hipMemcpyDeviceToHost));
+    const std::vector<int>& off = A.s_off_host;
     std::vector<int> order(A.n);
     for (int64_t r = 0; r < A.n; ++r) order[r] = (int)r;
     std::stable_sort(order.begin(), order.end(),
@@ -465,10 +464,10 @@ int ensure_ab_row_order(sqd_ctx* ctx, sqd_space* sp) {
 int ensure_ab_groups_impl(sqd_ctx* ctx, sqd_space* sp, int G) {
     if (sp->ab_G == G && sp->ab_grp) return SQD_OK;
     if (G <= 0) return sqd_fail(ctx, SQD_E_LIMIT, "alpha-beta group does not fit in LDS");
-    const spin_tables& A = sp->sp[0];
-    std::vector<uint32_t> pk(A.nnz_s);
-    if (A.nnz_s > 0)
-        SQD_HIP(ctx, hipMemcpy(pk.data(), A.s_pk, sizeof(uint32_t) * A.nnz_s, hipMemcpyDeviceToHost));
+    spin_tables& A = sp->sp[0];
+    int rc;
+    if ((rc = sqd_host_singles(ctx, A))) return rc;
+    const std::vector<uint32_t>& pk = A.s_pk_host;
     const int npair = sp->norb * sp->norb;
     std::vector<std::vector<int>> by(npair);
     for (int64_t e = 0; e < A.nnz_s; ++e) by[(pk[e] >> SQD_PAIR_SHIFT) & SQD_PAIR_MASK].push_back((int)e);
@@ -484,7 +483,6 @@ int ensure_ab_groups_impl(sqd_ctx* ctx, sqd_space* sp, int G) {
     }
     if (sp->ab_grp) { (void)hipFree(sp->ab_grp); sp->ab_grp = nullptr; }
     if (sp->ab_chunk_pair) { (void)hipFree(sp->ab_chunk_pair); sp->ab_chunk_pair = nullptr; }
-    int rc;
     if ((rc = ensure_ab_row_order(ctx, sp))) return rc;
     if ((rc = sqd_alloc(ctx, (void**)&sp->ab_grp, sizeof(int2) * (grp.size() + 1), &sp->bytes))) return rc;
     if ((rc = sqd_alloc(ctx, (void**)&sp->ab_chunk_pair, sizeof(int) * (cp.size() + 1), &sp->bytes))) return rc;
@@ -526,10 +524,10 @@ bool ab_use_source_groups(sqd_ctx* ctx, const sqd_space* sp) {
 // Group the alpha singles (CSR positions) by source string, padded to chunks of G.
 int ensure_ab_source_groups(sqd_ctx* ctx, sqd_space* sp, int G) {
     if (sp->abs_G == G && sp->abs_grp) return SQD_OK;
-    const spin_tables& A = sp->sp[0];
-    std::vector<uint32_t> pk(A.nnz_s);
-    if (A.nnz_s > 0)
-        SQD_HIP(ctx, hipMemcpy(pk.data(), A.s_pk, sizeof(uint32_t) * A.nnz_s, hipMemcpyDeviceToHost));
+    spin_tables& A = sp->sp[0];
+    int rc;
+    if ((rc = sqd_host_singles(ctx, A))) return rc;
+    const std::vector<uint32_t>& pk = A.s_pk_host;
     std::vector<std::vector<int>> by(A.n);
     for (int64_t e = 0; e < A.nnz_s; ++e) by[pk[e] & SQD_NBR_MASK].push_back((int)e);
     std::vector<int2> grp;
@@ -544,7 +542,6 @@ int ensure_ab_source_groups(sqd_ctx* ctx, sqd_space* sp, int G) {
     }
     if (sp->abs_grp) { (void)hipFree(sp->abs_grp); sp->abs_grp = nullptr; }
     if (sp->abs_src) { (void)hipFree(sp->abs_src); sp->abs_src = nullptr; }
-    int rc;
     if ((rc = sqd_alloc(ctx, (void**)&sp->abs_grp, sizeof(int2) * (grp.size() + 1), &sp->bytes))) return rc;
     if ((rc = sqd_alloc(ctx, (void**)&sp->abs_src, sizeof(int) * (cs.size() + 1), &sp->bytes))) return rc;
     if (!grp.empty()) {

@@ -167,6 +167,11 @@ struct spin_tables {
     ab_table ab32, ab64;
     int* sell_index = nullptr;    // one allocation: the perms and offsets of the sliced tables
     int max_singles = 0, max_doubles = 0;
+    // host copies for the schedules that are planned there: strings and row
+    // offsets from the build, the gather form on demand (sqd_host_singles)
+    std::vector<uint64_t> str_host;
+    std::vector<int> s_off_host;
+    std::vector<uint32_t> s_pk_host;
     bool alias = false;           // arrays owned by the other spin
     // windowed sliced tables for rows too long to stage whole (window.hip):
     // the source strings are dealt into win_W interleaved windows (source j in
@@ -237,6 +242,13 @@ struct sqd_space {
     int64_t h_bytes = 0;
     int h_version = -1;
     int64_t h_xcd_rows[9] = {};   // row ranges of equal element counts, one per XCD
+    // alpha-beta part of the 2-RDM (rdm.hip; built by the first call): one
+    // allocation with the beta pair table, the alpha pairs and their chunks
+    void* rdm_mem = nullptr;
+    size_t rdm_off[7] = {};
+    int rdm_nslices = 0, rdm_nchunks = 0;
+    int rdm_G = 0;                // rows of C staged per batch (0: read from memory)
+    bool rdm_keep = false;        // the sums stay in LDS across a chunk's batches
     unsigned fused_terms[2] = {};   // terms of the products run in one launch (FP64, FP32)
     // partial sums of the windowed same-spin kernel (rows x slots, FP64-sized)
     void* win_P = nullptr;
@@ -262,6 +274,7 @@ int sqd_noalloc_init(int device);   // device address of the static product scra
 // ---- tables.hip ----
 int sqd_build_spin_tables(sqd_ctx* ctx, sqd_space* sp, int spin, const uint64_t* host_str,
                           int64_t n, int nel);   // host_str: n x sp->nw words
+int sqd_host_singles(sqd_ctx* ctx, spin_tables& t);   // fills t.s_pk_host (synchronous)
 int sqd_alloc_cross_tables(sqd_ctx* ctx, sqd_space* sp);   // spin_tables::ws64, ws32 (both spins built)
 int sqd_build_values(sqd_ctx* ctx, sqd_space* sp);   // integral-dependent parts
 void sqd_free_spin_tables(spin_tables* t);

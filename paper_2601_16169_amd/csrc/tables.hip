@@ -12,6 +12,7 @@
 
 #include <rocprim/device/device_radix_sort.hpp>
 
+#include "slices.h"
 #include "sqd_internal.h"
 
 namespace {
@@ -473,43 +474,6 @@ int build_kind(sqd_ctx* ctx, sqd_space* sp, spin_tables& t, int** off_out, uint6
     return SQD_OK;
 }
 
-// Rows by decreasing length (ties by index): a counting sort.
-std::vector<int> rows_longest_first(const std::vector<int>& len) {
-    const int most = len.empty() ? 0 : *std::max_element(len.begin(), len.end());
-    std::vector<int> at(most + 2, 0), rows(len.size());
-    for (int l : len) at[most - l + 1] += 1;
-    for (int k = 0; k <= most; ++k) at[k + 1] += at[k];
-    for (size_t r = 0; r < len.size(); ++r) rows[at[most - len[r]]++] = (int)r;
-    return rows;
-}
-
-// Lanes per row (log2): the fewest that keep a lane's entries at or below cap.
-inline int split_of(int len, int cap) {
-    int k = 0;
-    while (k < 6 && ((len + (1 << k) - 1) >> k) > cap) ++k;
-    return k;
-}
-
-// Slices dealt into bins, the costliest into the lightest bin; the heaviest
-// bins are placed beside the lightest, so that pairs and fours of adjacent
-// bins are even too.
-std::vector<std::vector<int>> deal_bins(const std::vector<int>& cost) {
-    std::vector<int> order(cost.size()), load(kBins, 0), rank(kBins);
-    for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost[x] > cost[y]; });
-    std::vector<std::vector<int>> in(kBins), out(kBins);
-    for (int k : order) {
-        const int q = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-        in[q].push_back(k);
-        load[q] += cost[k];
-    }
-    for (int q = 0; q < kBins; ++q) rank[q] = q;
-    std::stable_sort(rank.begin(), rank.end(), [&](int x, int y) { return load[x] > load[y]; });
-    static constexpr int kPlace[kBins] = {0, 15, 7, 8, 3, 12, 4, 11, 1, 14, 6, 9, 2, 13, 5, 10};
-    for (int q = 0; q < kBins; ++q) out[q] = in[rank[kPlace[q]]];
-    return out;
-}
-
 // Slices of a sliced table over rows sorted by length, the longest remaining
 // row setting the lanes per row of the next slice; then dealt into bins.
 struct sell_plan {
@@ -590,14 +554,6 @@ ab_plan plan_ab(const std::vector<int>& rows, const int* off, int cap) {
     return p;
 }
 
-// Entries a lane of the FP64 same-spin table takes at most.  A wavefront walks
-// a slice at the pace of its longest lane, and the rows of sampled sets are
-// uneven: the Hartree-Fock string reaches half of the set, the mean row a
-// tenth.  A thirty-second of all columns leaves each of sixteen waves about
-// two slices of that length, so the waves of a workgroup end together, and
-// only the long rows pay for the sums across lanes.
-inline int split_cap(int64_t entries, int least) { return (int)std::max<int64_t>(least, (entries + 2047) / 2048); }
-
 // Arrays of a sliced same-spin table whose plan is on the device.
 template <typename T>
 int fill_sell(sqd_ctx* ctx, sqd_space* sp, const spin_tables& t, const sell_plan& p, sell_table<T>& L) {
@@ -658,7 +614,10 @@ int sqd_build_spin_tables(sqd_ctx* ctx, sqd_space* sp, int spin, const uint64_t*
 
     // sliced layouts, planned on the host from the row lengths: same-spin rows
     // by singles + doubles, alpha-beta rows by singles
-    std::vector<int> so(n + 1), dof(n + 1), len(n);
+    t.str_host.assign(host_str, host_str + n * t.nw);
+    std::vector<int>& so = t.s_off_host;
+    so.resize(n + 1);
+    std::vector<int> dof(n + 1), len(n);
     SQD_HIP(ctx, hipMemcpy(so.data(), t.s_off, sizeof(int) * (n + 1), hipMemcpyDeviceToHost));
     SQD_HIP(ctx, hipMemcpy(dof.data(), t.d_off, sizeof(int) * (n + 1), hipMemcpyDeviceToHost));
     t.max_singles = t.max_doubles = 0;
@@ -701,6 +660,14 @@ int sqd_build_spin_tables(sqd_ctx* ctx, sqd_space* sp, int spin, const uint64_t*
     if ((rc = sqd_alloc(ctx, (void**)&t.d_val64, sizeof(double) * (t.nnz_d + 1), &sp->bytes))) return rc;
     if ((rc = sqd_alloc(ctx, (void**)&t.d_val32, sizeof(float) * (t.nnz_d + 1), &sp->bytes))) return rc;
     if ((rc = sqd_alloc(ctx, (void**)&t.e_same, sizeof(double) * (n + 1), &sp->bytes))) return rc;
+    return SQD_OK;
+}
+
+int sqd_host_singles(sqd_ctx* ctx, spin_tables& t) {
+    if ((int64_t)t.s_pk_host.size() == t.nnz_s) return SQD_OK;
+    std::vector<uint32_t> pk(t.nnz_s);
+    SQD_HIP(ctx, hipMemcpy(pk.data(), t.s_pk, sizeof(uint32_t) * t.nnz_s, hipMemcpyDeviceToHost));
+    t.s_pk_host.swap(pk);
     return SQD_OK;
 }
 
