@@ -199,15 +199,14 @@ __global__ void __launch_bounds__(kThreads) kb_res_fin(const bdesc* __restrict__
     const bdesc& d = D[blockIdx.x];
     f_res_fin<MT>(partial + (size_t)d.part0 * kPstride, d.nblk, d.st, prm);
 }
-// force: 0 pending restarts; 1 spaces at their precision switch
-template <int MT, typename VT>
+// Spaces at their precision switch: the Ritz vector into cin (an FP32 basis).
+template <int MT>
 __global__ void __launch_bounds__(kThreads) kb_collapse(const bdesc* __restrict__ D, const int2* __restrict__ units,
-                                                        int nunits, int force) {
+                                                        int nunits) {
     for (int u = blockIdx.x; u < nunits; u += gridDim.x) {
         const bdesc& d = D[units[u].x];
-        if (force && d.st->done != DONE_SWITCH) continue;
-        d_collapse<MT, VT>(reinterpret_cast<VT*>(d.V), reinterpret_cast<VT*>(d.AV), d.n, d.st, force,
-                           force ? d.cin : nullptr, units[u].y, d.nblk);
+        if (d.st->done != DONE_SWITCH) continue;
+        d_collapse<MT, float>(reinterpret_cast<float*>(d.V), d.n, d.st, d.cin, units[u].y, d.nblk);
     }
 }
 // Spaces at their switch: V[0] = cin (the Ritz vector formed from an FP32
@@ -227,23 +226,19 @@ __global__ void __launch_bounds__(kThreads) kb_copy_norm(const bdesc* __restrict
         __syncthreads();
     }
 }
-__global__ void kb_collapse_fin(const bdesc* __restrict__ D, int force) {
+__global__ void kb_collapse_fin(const bdesc* __restrict__ D) {
     const bdesc& d = D[blockIdx.x];
-    if (force) {
-        if (d.st->done != DONE_SWITCH) return;
-        f_collapse_fin(d.st, 1);
-        f_set_phase(d.st, 1, DONE_RUNNING);
-        return;
-    }
-    f_collapse_fin(d.st, 0);
+    if (d.st->done != DONE_SWITCH) return;
+    f_collapse_fin(d.st);
+    f_set_phase(d.st, 1, DONE_RUNNING);
 }
 template <int MT, typename VT>
 __global__ void __launch_bounds__(kThreads) kb_orth1(const bdesc* __restrict__ D, const int2* __restrict__ units,
                                                      int nunits, double* __restrict__ partial) {
     for (int u = blockIdx.x; u < nunits; u += gridDim.x) {
         const bdesc& d = D[units[u].x];
-        d_orth1<MT, VT>(reinterpret_cast<const VT*>(d.V), d.n, d.st, d.T, partial + (size_t)d.part0 * kPstride,
-                        units[u].y, d.nblk);
+        d_orth1<MT, VT>(reinterpret_cast<VT*>(d.V), reinterpret_cast<VT*>(d.AV), d.n, d.st, d.T,
+                        partial + (size_t)d.part0 * kPstride, units[u].y, d.nblk);
         __syncthreads();
     }
 }
@@ -552,8 +547,6 @@ int batched_run(sqd_ctx* ctx, batch_plan& p, const sqd_davidson_opts* o, double*
         hipLaunchKernelGGL((kb_residual<MT, VT>), sgrid(p.vec.n), dim3(kThreads), 0, s, p.D, p.vec.dev, p.vec.n,
                            p.partial);
         hipLaunchKernelGGL((kb_res_fin<MT>), dim3(ns), dim3(kThreads), 0, s, p.D, p.partial, prm);
-        hipLaunchKernelGGL((kb_collapse<MT, VT>), sgrid(p.vec.n), dim3(kThreads), 0, s, p.D, p.vec.dev, p.vec.n, 0);
-        hipLaunchKernelGGL(kb_collapse_fin, dim3(ns), dim3(64), 0, s, p.D, 0);
         hipLaunchKernelGGL((kb_orth1<MT, VT>), sgrid(p.vec.n), dim3(kThreads), 0, s, p.D, p.vec.dev, p.vec.n,
                            p.partial);
         hipLaunchKernelGGL((kb_orth1_fin<MT, VT>), dim3(ns), dim3(kThreads), 0, s, p.D, p.partial);
@@ -607,13 +600,12 @@ int batched_run(sqd_ctx* ctx, batch_plan& p, const sqd_davidson_opts* o, double*
                 if (h[b].done == DONE_SWITCH) switch_iter[b] = h[b].iter;
             // the Ritz vector from the FP32 basis into cin, then V[0] = it,
             // normalised in FP64
-            hipLaunchKernelGGL((kb_collapse<MT, float>), sgrid(p.vec.n), dim3(kThreads), 0, s, p.D, p.vec.dev, p.vec.n,
-                               1);
+            hipLaunchKernelGGL(kb_collapse<MT>, sgrid(p.vec.n), dim3(kThreads), 0, s, p.D, p.vec.dev, p.vec.n);
             hipLaunchKernelGGL(kb_copy_norm, sgrid(p.vec.n), dim3(kThreads), 0, s, p.D, p.vec.dev, p.vec.n, p.partial);
             hipLaunchKernelGGL(kb_norm_fin, dim3(ns), dim3(kThreads), 0, s, p.D, p.partial, 1);
             hipLaunchKernelGGL(kb_scale_copy<double>, sgrid(p.vec.n), dim3(kThreads), 0, s, p.D, p.vec.dev, p.vec.n,
                                0, 1);
-            hipLaunchKernelGGL(kb_collapse_fin, dim3(ns), dim3(64), 0, s, p.D, 1);
+            hipLaunchKernelGGL(kb_collapse_fin, dim3(ns), dim3(64), 0, s, p.D);
             batched_sigma<R, G, RF>(ctx, p, s, SQD_FP64, nw_ss, nw_ab);
             hipLaunchKernelGGL((kb_dots<MT, double>), sgrid(p.vec.n), dim3(kThreads), 0, s, p.D, p.vec.dev, p.vec.n,
                                p.partial);

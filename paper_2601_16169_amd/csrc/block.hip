@@ -7,9 +7,9 @@
 // single-root solver keeps its current and previous Ritz vectors).
 //
 // One iteration (basis V of m orthonormal vectors, AV = H V, G = V^T H V):
-//   eigh       the m x m projected matrix in one workgroup (cyclic Jacobi,
-//              round-robin pairs): theta_0 <= ... <= theta_{k-1}, Y = their
-//              eigenvectors (m x k).
+//   eigh       the k lowest eigenpairs of the m x m projected matrix in one
+//              wavefront (small_eig.h): theta_0 <= ... <= theta_{k-1}, Y =
+//              their eigenvectors (m x k).
 //   residual   r_j = AV y_j - theta_j V y_j, |r_j|, t_j = r_j / (theta_j - H_II)
 //              (|den| < 1e-8 replaced by +-1e-8).
 //   host       reads theta and |r_j|: stop when every |r_j| <= tol; restart
@@ -97,17 +97,22 @@ __global__ void __launch_bounds__(kThreads) k_bargmin(const double* __restrict__
     }
 }
 
-__global__ void __launch_bounds__(kThreads) k_bargmin_fin(const double* __restrict__ partial, int nrows,
-                                                          blk_state* st, int j) {
-    if (threadIdx.x != 0) return;
+// one wavefront: a thread walking the blocks' results alone took 90 us over 512
+__global__ void __launch_bounds__(64) k_bargmin_fin(const double* __restrict__ partial, int nrows, blk_state* st,
+                                                    int j) {
     double b = INFINITY;
     long long k = -1;
-    for (int q = 0; q < nrows; ++q) {
-        const double v = partial[(size_t)q * 2];
-        const long long i = (long long)partial[(size_t)q * 2 + 1];
+    auto take = [&](double v, long long i) {
         if (i >= 0 && (k < 0 || v < b || (v == b && i < k))) { b = v; k = i; }
+    };
+    for (int q = threadIdx.x; q < nrows; q += 64)
+        take(partial[(size_t)q * 2], (long long)partial[(size_t)q * 2 + 1]);
+    for (int mask = 32; mask > 0; mask >>= 1) {
+        const double v = __shfl_xor(b, mask);
+        const long long i = __shfl_xor(k, mask);
+        take(v, i);
     }
-    st->kmin[j] = (int)(k < 0 ? 0 : k);
+    if (threadIdx.x == 0) st->kmin[j] = (int)(k < 0 ? 0 : k);
 }
 
 // T[j] = e_kmin[j] + start noise (counter stream j + 1), j < k
@@ -237,17 +242,32 @@ __global__ void __launch_bounds__(kThreads) k_bo3(double* __restrict__ V, const 
     });
 }
 
+// The finishing workgroup blockIdx.x adds kFinCols of the columns that k_bgcols
+// leaves (one workgroup for the 32 of a chunk took 18 us, most of it the wait
+// for 512 x 32 partials; four of them side by side 5).  Thread t < kFinCols
+// returns the sum of its column, a product of basis rows (or of row a and
+// correction b).
+constexpr int kFinCols = 8;
+template <int NB>
+__device__ __forceinline__ double column_sum(const double* __restrict__ partial, int nrows, int& a, int& b) {
+    static_assert(kGB * NB % kFinCols == 0, "whole groups of columns");
+    __shared__ double out[kFinCols];
+    const int first = blockIdx.x * kFinCols;
+    reduce_rows<kFinCols>(partial + (size_t)first * nrows, nrows, out);
+    const int q = first + (threadIdx.x & (kFinCols - 1));
+    a = q / NB;   // chunks of kGB rows follow each other
+    b = q % NB;
+    return out[threadIdx.x & (kFinCols - 1)];
+}
+
 // Block projection of the k candidate rows of T against V[0..m): P = V^T T
 // (partials by k_bgcols, stored by k_bpfin), then T -= V P.
 template <int NB>
 __global__ void __launch_bounds__(kThreads) k_bpfin(const double* __restrict__ partial, int nrows, blk_state* st,
-                                                    int l0, int nl, int nc) {
-    __shared__ double out[8 * NB];
-    reduce_rows<8 * NB>(partial, nrows, out);
-    for (int q = threadIdx.x; q < 8 * NB; q += kThreads) {
-        const int a = q / NB, b = q % NB;
-        if (a < nl && b < nc) st->P[(l0 + a) * KB + b] = out[q];
-    }
+                                                    int m, int nc) {
+    int a, b;
+    const double v = column_sum<NB>(partial, nrows, a, b);
+    if (threadIdx.x < kFinCols && a < m && b < nc) st->P[a * KB + b] = v;
 }
 
 template <int NK>
@@ -272,12 +292,15 @@ __global__ void __launch_bounds__(kThreads) k_bproj(const double* __restrict__ V
 }
 
 // ---------------------------------------------------------------- projected matrix
-// partials of V[l0 + a]^T AV[c0 + b] for a < kGB, b < NB (rows and columns
-// past the counts read the last valid ones and are dropped by the finisher)
+// partials of V[l0 + a]^T AV[c0 + b] for a < kGB, b < NB, l0 = kGB * blockIdx.y
+// (rows and columns past the counts read the last valid ones and are dropped by
+// the finisher).  All chunks of rows are one launch: the launches of a solve of
+// half a million elements cost more than their work.
 template <int NB>
 __global__ void __launch_bounds__(kThreads) k_bgcols(const double* __restrict__ V, const double* __restrict__ AV,
-                                                     int64_t n, int l0, int nl, int c0, int nc,
+                                                     int64_t n, int m, int c0, int nc,
                                                      double* __restrict__ partial) {
+    const int l0 = blockIdx.y * kGB, nl = m - l0 < kGB ? m - l0 : kGB;
     double acc[kGB * NB];
 #pragma unroll
     for (int q = 0; q < kGB * NB; ++q) acc[q] = 0.0;
@@ -292,142 +315,44 @@ __global__ void __launch_bounds__(kThreads) k_bgcols(const double* __restrict__ 
 #pragma unroll
             for (int b = 0; b < NB; ++b) acc[a * NB + b] += v[a] * w[b];
     }
-    block_to_partial<kGB * NB>(acc, partial, blockIdx.x, gridDim.x);
+    block_to_partial<kGB * NB>(acc, partial + (size_t)blockIdx.y * kGB * NB * gridDim.x, blockIdx.x, gridDim.x);
 }
 
 template <int NB>
 __global__ void __launch_bounds__(kThreads) k_bgcols_fin(const double* __restrict__ partial, int nrows, blk_state* st,
-                                                         int l0, int nl, int c0, int nc) {
-    __shared__ double out[kGB * NB];
-    reduce_rows<kGB * NB>(partial, nrows, out);
-    for (int q = threadIdx.x; q < kGB * NB; q += kThreads) {
-        const int a = q / NB, b = q % NB;
-        if (a < nl && b < nc) {
-            const int r = l0 + a, c = c0 + b;
-            st->G[r * MM + c] = out[q];
-            st->G[c * MM + r] = out[q];
-        }
+                                                         int m, int c0, int nc) {
+    int r, b;
+    const double v = column_sum<NB>(partial, nrows, r, b);
+    if (threadIdx.x < kFinCols && r < m && b < nc) {
+        const int c = c0 + b;
+        st->G[r * MM + c] = v;
+        st->G[c * MM + r] = v;
     }
 }
 
-// Lowest k eigenpairs of the m x m matrix G (cyclic Jacobi, round-robin
-// pairs; one workgroup).  theta ascending; Y columns normalised.
-__global__ void __launch_bounds__(kThreads) k_beigh(blk_state* st) {
-    constexpr int LS = MM + 1;
-    __shared__ double A[MM * LS];
-    __shared__ double Q[MM * LS];
-    __shared__ double rc[MM / 2], rs[MM / 2];
-    __shared__ int rp[MM / 2], rq[MM / 2];
-    __shared__ double red[2 * kWaves];
-    __shared__ int order[MM];
-    const int t = threadIdx.x;
+// Lowest k <= K eigenpairs of the m x m matrix G (one wavefront).  theta
+// ascending; Y columns normalised.
+template <int K>
+__global__ void __launch_bounds__(64) k_beigh(blk_state* st) {
+    __shared__ eig_work<MM, K> work;
+    const int lane = threadIdx.x;
     const int m = st->m, k = st->k;
-    for (int q = t; q < MM * KB; q += kThreads) st->Yp[q] = st->Y[q];
-    for (int q = t; q < MM * MM; q += kThreads) {
-        const int i = q / MM, j = q % MM;
-        A[i * LS + j] = (i < m && j < m) ? st->G[q] : 0.0;
-        Q[i * LS + j] = (i == j) ? 1.0 : 0.0;
+    double a[MM];
+#pragma unroll
+    for (int j = 0; j < MM; ++j) {   // exact symmetry of the stored matrix
+        const int i = lane & (MM - 1);
+        const double v = 0.5 * (st->G[i * MM + j] + st->G[j * MM + i]);
+        a[j] = (lane < m && j < m) ? v : 0.0;
     }
-    __syncthreads();
-    // exact symmetry of the stored matrix
-    for (int q = t; q < MM * MM; q += kThreads) {
-        const int i = q / MM, j = q % MM;
-        if (i < j && j < m) {
-            const double v = 0.5 * (A[i * LS + j] + A[j * LS + i]);
-            A[i * LS + j] = v;
-            A[j * LS + i] = v;
-        }
+    for (int q = lane; q < MM * KB; q += 64) st->Yp[q] = st->Y[q];
+    double theta[K], y[K];
+    lowest_pairs<MM, K>(a, m, k < m ? k : m, work, theta, y);
+    for (int q = lane; q < MM * KB; q += 64) st->Y[q] = 0.0;
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        if (lane < MM && j < k) st->Y[lane * KB + j] = y[j];
+        if (lane == j) st->theta[j] = (j < k && j < m) ? theta[j] : 0.0;
     }
-    __syncthreads();
-    if (m > 1) {
-        const int n2 = (m + 1) & ~1;
-        const int npair = n2 / 2;
-        const int lane = t & 63, w = t >> 6;
-        for (int sweep = 0; sweep < 60; ++sweep) {
-            double off = 0.0, tot = 0.0;
-            for (int q = t; q < MM * MM; q += kThreads) {
-                const int i = q / MM, j = q % MM;
-                if (i < m && j < m) {
-                    const double v = A[i * LS + j];
-                    tot += v * v;
-                    if (i != j) off += v * v;
-                }
-            }
-            for (int o = 32; o > 0; o >>= 1) {
-                off += __shfl_xor(off, o);
-                tot += __shfl_xor(tot, o);
-            }
-            if (lane == 0) { red[w] = off; red[kWaves + w] = tot; }
-            __syncthreads();
-            off = 0.0; tot = 0.0;
-            for (int q = 0; q < kWaves; ++q) { off += red[q]; tot += red[kWaves + q]; }
-            __syncthreads();
-            if (off <= 1e-30 * tot || off == 0.0) break;
-            for (int step = 0; step < n2 - 1; ++step) {
-                if (t < npair) {
-                    // round-robin: slot 0 fixed, the other n2 - 1 rotate by `step`
-                    int a = t == 0 ? 0 : 1 + (t - 1 + step) % (n2 - 1);
-                    int b = 1 + (n2 - 2 - t + step) % (n2 - 1);
-                    if (a > b) { const int x = a; a = b; b = x; }
-                    double c = 1.0, s = 0.0;
-                    if (b < m) {
-                        const double apq = A[a * LS + b];
-                        if (apq != 0.0) jacobi_rotation(A[a * LS + a], A[b * LS + b], apq, c, s);
-                    }
-                    rc[t] = c; rs[t] = s; rp[t] = a; rq[t] = b;
-                }
-                __syncthreads();
-                for (int q = t; q < (MM / 2) * (MM / 2); q += kThreads) {
-                    const int b1 = q / (MM / 2), b2 = q % (MM / 2);
-                    if (b1 >= npair || b2 >= npair) continue;
-                    const int p1 = rp[b1], q1 = rq[b1], p2 = rp[b2], q2 = rq[b2];
-                    const bool v1 = q1 < m, v2 = q2 < m;
-                    const double c1 = rc[b1], s1 = rs[b1], c2 = rc[b2], s2 = rs[b2];
-                    if (s1 == 0.0 && s2 == 0.0) continue;
-                    const double app = A[p1 * LS + p2];
-                    const double apq = v2 ? A[p1 * LS + q2] : 0.0;
-                    const double aqp = v1 ? A[q1 * LS + p2] : 0.0;
-                    const double aqq = (v1 && v2) ? A[q1 * LS + q2] : 0.0;
-                    const double rpp = c1 * app - s1 * aqp, rpq = c1 * apq - s1 * aqq;
-                    const double rqp = s1 * app + c1 * aqp, rqq = s1 * apq + c1 * aqq;
-                    A[p1 * LS + p2] = c2 * rpp - s2 * rpq;
-                    if (v2) A[p1 * LS + q2] = s2 * rpp + c2 * rpq;
-                    if (v1) A[q1 * LS + p2] = c2 * rqp - s2 * rqq;
-                    if (v1 && v2) A[q1 * LS + q2] = s2 * rqp + c2 * rqq;
-                }
-                for (int q = t; q < (MM / 2) * MM; q += kThreads) {
-                    const int pr = q / MM, i = q % MM;
-                    if (pr >= npair || i >= m) continue;
-                    const int p = rp[pr], qq = rq[pr];
-                    if (qq >= m || rs[pr] == 0.0) continue;
-                    const double c = rc[pr], s = rs[pr];
-                    const double qp = Q[i * LS + p], qv = Q[i * LS + qq];
-                    Q[i * LS + p] = c * qp - s * qv;
-                    Q[i * LS + qq] = s * qp + c * qv;
-                }
-                __syncthreads();
-            }
-        }
-    }
-    if (t == 0) {
-        // eigenvalues ascending (stable: lowest index on ties)
-        for (int i = 0; i < m; ++i) order[i] = i;
-        for (int i = 1; i < m; ++i) {
-            const int x = order[i];
-            const double v = A[x * LS + x];
-            int j = i - 1;
-            while (j >= 0 && A[order[j] * LS + order[j]] > v) { order[j + 1] = order[j]; --j; }
-            order[j + 1] = x;
-        }
-    }
-    __syncthreads();
-    for (int q = t; q < MM * KB; q += kThreads) {
-        const int l = q / KB, j = q % KB;
-        double v = 0.0;
-        if (l < m && j < k && j < m) v = Q[l * LS + order[j]];
-        st->Y[q] = v;
-    }
-    if (t < KB) st->theta[t] = (t < k && t < m) ? A[order[t] * LS + order[t]] : 0.0;
 }
 
 // ---------------------------------------------------------------- residuals, corrections, Ritz vectors
@@ -494,31 +419,32 @@ __global__ void __launch_bounds__(kThreads) k_bzq(blk_state* st, int kr) {
     __shared__ double GZ[MM * 2 * KB];
     __shared__ int nk;
     const int m = st->m, k = st->k;
-    if (threadIdx.x == 0) {
-        for (int q = 0; q < MM * 2 * KB; ++q) Zs[q] = 0.0;
+    for (int q = threadIdx.x; q < MM * 2 * KB; q += kThreads) Zs[q] = 0.0;
+    __syncthreads();
+    if (threadIdx.x < 64) {   // one wavefront, a lane for each row (one thread alone took 110 us)
+        const int l = threadIdx.x;
+        const bool row = l < m;
         int nc = 0;
         for (int j = 0; j < k && nc < kr; ++j, ++nc)
-            for (int l = 0; l < m; ++l) Zs[l * 2 * KB + nc] = st->Y[l * KB + j];
+            if (row) Zs[l * 2 * KB + nc] = st->Y[l * KB + j];
+        __threadfence_block();
         for (int j = 0; j < k && nc < kr; ++j) {
-            double z[MM];
-            for (int l = 0; l < MM; ++l) z[l] = l < m ? st->Yp[l * KB + j] : 0.0;
-            double n0 = 0.0;
-            for (int l = 0; l < m; ++l) n0 += z[l] * z[l];
+            double z = row ? st->Yp[l * KB + j] : 0.0;
+            const double n0 = sum32(z * z);
             if (!(n0 > 0.0)) continue;
             for (int pass = 0; pass < 2; ++pass)
                 for (int c = 0; c < nc; ++c) {
-                    double d = 0.0;
-                    for (int l = 0; l < m; ++l) d += Zs[l * 2 * KB + c] * z[l];
-                    for (int l = 0; l < m; ++l) z[l] -= d * Zs[l * 2 * KB + c];
+                    const double zc = row ? Zs[l * 2 * KB + c] : 0.0;
+                    z -= sum32(zc * z) * zc;
                 }
-            double n1 = 0.0;
-            for (int l = 0; l < m; ++l) n1 += z[l] * z[l];
+            const double n1 = sum32(z * z);
             if (n1 <= 1e-6 * n0) continue;
             const double inv = 1.0 / sqrt(n1);
-            for (int l = 0; l < m; ++l) Zs[l * 2 * KB + nc] = z[l] * inv;
+            if (row) Zs[l * 2 * KB + nc] = z * inv;
+            __threadfence_block();
             ++nc;
         }
-        nk = nc;
+        if (l == 0) nk = nc;
     }
     __syncthreads();
     const int nc = nk;
@@ -652,19 +578,28 @@ __global__ void __launch_bounds__(kThreads) k_bfinal(const double* __restrict__ 
     }
 }
 
+// one wavefront for each root (one thread each took 139 us over 512 blocks)
 template <int K>
-__global__ void k_bfinal_fin(const double* __restrict__ partial, int nrows, const double* __restrict__ out,
-                             int64_t n, blk_state* st) {
-    const int j = threadIdx.x;
-    if (j >= K) return;
+__global__ void __launch_bounds__(64) k_bfinal_fin(const double* __restrict__ partial, int nrows,
+                                                   const double* __restrict__ out, int64_t n, blk_state* st) {
+    const int j = blockIdx.x;
     double b = -1.0, s = 0.0;
     long long k = -1;
-    for (int q = 0; q < nrows; ++q) {
-        const double v = partial[((size_t)q * K + j) * 3 + 0];
-        const long long i = (long long)partial[((size_t)q * K + j) * 3 + 1];
-        s += partial[((size_t)q * K + j) * 3 + 2];
+    auto take = [&](double v, long long i) {
         if (i >= 0 && (k < 0 || v > b || (v == b && i < k))) { b = v; k = i; }
+    };
+    for (int q = threadIdx.x; q < nrows; q += 64) {
+        const double* p = partial + ((size_t)q * K + j) * 3;
+        take(p[0], (long long)p[1]);
+        s += p[2];
     }
+    for (int mask = 32; mask > 0; mask >>= 1) {
+        const double v = __shfl_xor(b, mask);
+        const long long i = __shfl_xor(k, mask);
+        s += __shfl_xor(s, mask);
+        take(v, i);
+    }
+    if (threadIdx.x != 0) return;
     const double sc = 1.0 / sqrt(s);
     st->fidx[j] = (int)(k < 0 ? 0 : k);
     st->fscale[j] = (k >= 0 && out[(int64_t)j * n + k] < 0.0) ? -sc : sc;
@@ -705,7 +640,17 @@ void launch_restart(int g, hipStream_t s, double* V, double* AV, int64_t n, blk_
 template <int K>
 void launch_final(int g, hipStream_t s, const double* V, int64_t n, blk_state* st, double* out, double* part) {
     hipLaunchKernelGGL((k_bfinal<K>), dim3(g), dim3(kThreads), 0, s, V, n, st, out, part);
-    hipLaunchKernelGGL((k_bfinal_fin<K>), dim3(1), dim3(64), 0, s, part, g, out, n, st);
+    hipLaunchKernelGGL((k_bfinal_fin<K>), dim3(K), dim3(64), 0, s, part, g, out, n, st);
+}
+
+// Products of the rows V[0..m) with W[c0..c0+nc): partials, then `fin` on the
+// grid that covers their columns.
+template <int NB, typename F>
+void gram_columns(int g, hipStream_t s, const double* V, const double* W, int64_t n, int m, int c0, int nc,
+                  double* part, F&& fin) {
+    const int chunks = (m + kGB - 1) / kGB;
+    hipLaunchKernelGGL((k_bgcols<NB>), dim3(g, chunks), dim3(kThreads), 0, s, V, W, n, m, c0, nc, part);
+    fin(dim3(chunks * kGB * NB / kFinCols));
 }
 
 template <typename F>
@@ -738,7 +683,7 @@ int sqd_davidson_block_impl(sqd_ctx* ctx, sqd_space* sp, const sqd_davidson_opts
         {(void**)&T, sizeof(double) * (size_t)n * kk},
         {(void**)&X, sizeof(double) * (size_t)n * 2 * kk},
         {(void**)&AX, sizeof(double) * (size_t)n * 2 * kk},
-        {(void**)&part, sizeof(double) * kMaxBlocks * (kGB * KB + 8)},
+        {(void**)&part, sizeof(double) * kMaxBlocks * (MM * KB)},
         {(void**)&st, sizeof(blk_state)},
     };
     size_t total = 0;
@@ -786,19 +731,21 @@ int sqd_davidson_block_impl(sqd_ctx* ctx, sqd_space* sp, const sqd_davidson_opts
     // two block Gram-Schmidt passes of the kk rows of T against V[0..m)
     auto block_project = [&](int m) {
         for (int pass = 0; pass < 2; ++pass) {
-            for (int l0 = 0; l0 < m; l0 += kGB) {
-                const int nl = std::min(kGB, m - l0);
-                if (kk <= 4) {
-                    hipLaunchKernelGGL((k_bgcols<4>), dim3(g), dim3(kThreads), 0, s, V, T, n, l0, nl, 0, kk, part);
-                    hipLaunchKernelGGL((k_bpfin<4>), dim3(1), dim3(kThreads), 0, s, part, g, st, l0, nl, kk);
-                } else {
-                    hipLaunchKernelGGL((k_bgcols<8>), dim3(g), dim3(kThreads), 0, s, V, T, n, l0, nl, 0, kk, part);
-                    hipLaunchKernelGGL((k_bpfin<8>), dim3(1), dim3(kThreads), 0, s, part, g, st, l0, nl, kk);
-                }
-            }
+            if (kk <= 4) gram_columns<4>(g, s, V, T, n, m, 0, kk, part, [&](dim3 f) {
+                hipLaunchKernelGGL((k_bpfin<4>), f, dim3(kThreads), 0, s, part, g, st, m, kk);
+            });
+            else gram_columns<8>(g, s, V, T, n, m, 0, kk, part, [&](dim3 f) {
+                hipLaunchKernelGGL((k_bpfin<8>), f, dim3(kThreads), 0, s, part, g, st, m, kk);
+            });
             if (kk <= 4) hipLaunchKernelGGL((k_bproj<4>), dim3(g), dim3(kThreads), 0, s, V, T, n, m, kk, st);
             else hipLaunchKernelGGL((k_bproj<8>), dim3(g), dim3(kThreads), 0, s, V, T, n, m, kk, st);
         }
+    };
+    auto g_columns = [&](auto nbc, int m, int c0, int nc) {
+        constexpr int NB = decltype(nbc)::value;
+        gram_columns<NB>(g, s, V, AV, n, m, c0, nc, part, [&](dim3 f) {
+            hipLaunchKernelGGL((k_bgcols_fin<NB>), f, dim3(kThreads), 0, s, part, g, st, m, c0, nc);
+        });
     };
     // products of the basis rows [m0, m1) and G's columns m0..m1-1 against rows [0, m1)
     auto products = [&](int m0, int m1, int prec) -> int {
@@ -811,19 +758,9 @@ int sqd_davidson_block_impl(sqd_ctx* ctx, sqd_space* sp, const sqd_davidson_opts
         }
         for (int c0 = m0; c0 < m1; c0 += KB) {
             const int nc = std::min(KB, m1 - c0);
-            for (int l0 = 0; l0 < m1; l0 += kGB) {
-                const int nl = std::min(kGB, m1 - l0);
-                if (nc <= 1) {
-                    hipLaunchKernelGGL((k_bgcols<1>), dim3(g), dim3(kThreads), 0, s, V, AV, n, l0, nl, c0, nc, part);
-                    hipLaunchKernelGGL((k_bgcols_fin<1>), dim3(1), dim3(kThreads), 0, s, part, g, st, l0, nl, c0, nc);
-                } else if (nc <= 4) {
-                    hipLaunchKernelGGL((k_bgcols<4>), dim3(g), dim3(kThreads), 0, s, V, AV, n, l0, nl, c0, nc, part);
-                    hipLaunchKernelGGL((k_bgcols_fin<4>), dim3(1), dim3(kThreads), 0, s, part, g, st, l0, nl, c0, nc);
-                } else {
-                    hipLaunchKernelGGL((k_bgcols<8>), dim3(g), dim3(kThreads), 0, s, V, AV, n, l0, nl, c0, nc, part);
-                    hipLaunchKernelGGL((k_bgcols_fin<8>), dim3(1), dim3(kThreads), 0, s, part, g, st, l0, nl, c0, nc);
-                }
-            }
+            if (nc <= 1) g_columns(std::integral_constant<int, 1>{}, m1, c0, nc);
+            else if (nc <= 4) g_columns(std::integral_constant<int, 4>{}, m1, c0, nc);
+            else g_columns(std::integral_constant<int, 8>{}, m1, c0, nc);
         }
         return hipGetLastError() == hipSuccess ? SQD_OK : SQD_E_HIP;
     };
@@ -852,7 +789,9 @@ int sqd_davidson_block_impl(sqd_ctx* ctx, sqd_space* sp, const sqd_davidson_opts
     // vectors a restart keeps: the k Ritz vectors and up to k previous ones
     const int kr = std::min(2 * k, mmax - k);
     while (true) {
-        hipLaunchKernelGGL(k_beigh, dim3(1), dim3(kThreads), 0, s, st);
+        with_k(kk, [&](auto kc) {
+            hipLaunchKernelGGL((k_beigh<decltype(kc)::value>), dim3(1), dim3(64), 0, s, st);
+        });
         // a restart follows when the corrections could overflow m_max
         const bool restart = m + k > mmax;
         with_k(kk, [&](auto kc) {

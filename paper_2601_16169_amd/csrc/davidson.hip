@@ -15,13 +15,15 @@
 //              (|den| < 1e-8 replaced by +-1e-8); partials of |r|^2, |t|^2 and
 //              h = V^T t (first classical Gram-Schmidt pass) in the same sweep.
 //              Last block: convergence / cap / phase-switch decisions.
-//   collapse   (only when m == m_max) V[0] = V y, AV[0] = AV y in place.
-//   orth1      t1 = t - V h, partials of h2 = V^T t1 and |t1|^2 (second pass).
+//   orth1      t1 = t - V h, partials of h2 = V^T t1 and |t1|^2 (second pass);
+//              when m == m_max the basis is collapsed in place on the way:
+//              V[0..1] = V qc, AV[0..1] = AV qc (current and previous Ritz
+//              vectors).
 //   orth2      v = (t1 - V h2) / |t1 - V h2| -> V[m] and the product input.
 //   sigma      AV[m] = H v (FP64, or FP32 off-diagonal terms in mixed mode,
 //              whose FP32 phase keeps V and AV in FP32).
-//   dots       G[:, m] = V^T AV[m]; last block: m += 1 and a parallel cyclic
-//              Jacobi eigen-solve of G for the next (theta, y).
+//   dots       G[:, m] = V^T AV[m]; finishing kernel: m += 1 and the lowest
+//              eigenpair of G for the next (theta, y) (small_eig.h).
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -80,15 +82,16 @@ __global__ void __launch_bounds__(kThreads) k_res_fin(const double* __restrict__
     f_res_fin<MT>(partial, nrows, st, prm);
 }
 template <int MT, typename VT>
-__global__ void __launch_bounds__(kThreads) k_collapse(VT* __restrict__ V, VT* __restrict__ AV, int64_t n,
-                                                       const dav_state* st, int force, double* __restrict__ cin) {
-    d_collapse<MT, VT>(V, AV, n, st, force, cin, blockIdx.x, gridDim.x);
+__global__ void __launch_bounds__(kThreads) k_collapse(VT* __restrict__ V, int64_t n, const dav_state* st,
+                                                       double* __restrict__ cin) {
+    d_collapse<MT, VT>(V, n, st, cin, blockIdx.x, gridDim.x);
 }
-__global__ void k_collapse_fin(dav_state* st, int force) { f_collapse_fin(st, force); }
+__global__ void k_collapse_fin(dav_state* st) { f_collapse_fin(st); }
 template <int MT, typename VT>
-__global__ void __launch_bounds__(kThreads) k_orth1(const VT* __restrict__ V, int64_t n, const dav_state* st,
-                                                    double* __restrict__ T, double* __restrict__ partial) {
-    d_orth1<MT, VT>(V, n, st, T, partial, blockIdx.x, gridDim.x);
+__global__ void __launch_bounds__(kThreads) k_orth1(VT* __restrict__ V, VT* __restrict__ AV, int64_t n,
+                                                    const dav_state* st, double* __restrict__ T,
+                                                    double* __restrict__ partial) {
+    d_orth1<MT, VT>(V, AV, n, st, T, partial, blockIdx.x, gridDim.x);
 }
 template <int MT, typename VT>
 __global__ void __launch_bounds__(kThreads) k_orth1_fin(const double* __restrict__ partial, int nrows, dav_state* st) {
@@ -164,12 +167,12 @@ struct dav_launch {
         hipLaunchKernelGGL((k_residual<MT, VT>), dim3(g), dim3(kThreads), 0, s, V, AV, d, n, st, T, part);
         hipLaunchKernelGGL((k_res_fin<MT>), dim3(1), dim3(kThreads), 0, s, part, g, st, p);
     }
-    static void collapse(int g, hipStream_t s, VT* V, VT* AV, int64_t n, dav_state* st, int force, double* cin) {
-        hipLaunchKernelGGL((k_collapse<MT, VT>), dim3(g), dim3(kThreads), 0, s, V, AV, n, st, force, cin);
-        hipLaunchKernelGGL(k_collapse_fin, dim3(1), dim3(64), 0, s, st, force);
+    static void collapse(int g, hipStream_t s, VT* V, int64_t n, dav_state* st, double* cin) {
+        hipLaunchKernelGGL((k_collapse<MT, VT>), dim3(g), dim3(kThreads), 0, s, V, n, st, cin);
+        hipLaunchKernelGGL(k_collapse_fin, dim3(1), dim3(64), 0, s, st);
     }
-    static void orth1(int g, hipStream_t s, const VT* V, int64_t n, dav_state* st, double* T, double* part) {
-        hipLaunchKernelGGL((k_orth1<MT, VT>), dim3(g), dim3(kThreads), 0, s, V, n, st, T, part);
+    static void orth1(int g, hipStream_t s, VT* V, VT* AV, int64_t n, dav_state* st, double* T, double* part) {
+        hipLaunchKernelGGL((k_orth1<MT, VT>), dim3(g), dim3(kThreads), 0, s, V, AV, n, st, T, part);
         hipLaunchKernelGGL((k_orth1_fin<MT, VT>), dim3(1), dim3(kThreads), 0, s, part, g, st);
     }
     static void orth2(int g, hipStream_t s, VT* V, int64_t n, dav_state* st, const double* T, double* cin, float* c32) {
@@ -270,15 +273,13 @@ static int davidson_run(sqd_ctx* ctx, sqd_space* sp, const sqd_davidson_opts* o,
         for (int k = 0; k < o->check_every; ++k) {
             if (basis32) {
                 L32::residual(g, s, V32, AV32, diag, n, w.st, prm, w.T, w.partial);
-                L32::collapse(g, s, V32, AV32, n, w.st, 0, nullptr);
-                L32::orth1(g, s, V32, n, w.st, w.T, w.partial);
+                L32::orth1(g, s, V32, AV32, n, w.st, w.T, w.partial);
                 L32::orth2(g, s, V32, n, w.st, w.T, w.cin, w.c32);
                 if ((rc = product(prec))) return rc;
                 L32::dots(g, s, V32, AV32, w.sout, n, w.st, w.partial);
             } else {
                 L::residual(g, s, w.V, w.AV, diag, n, w.st, prm, w.T, w.partial);
-                L::collapse(g, s, w.V, w.AV, n, w.st, 0, nullptr);
-                L::orth1(g, s, w.V, n, w.st, w.T, w.partial);
+                L::orth1(g, s, w.V, w.AV, n, w.st, w.T, w.partial);
                 L::orth2(g, s, w.V, n, w.st, w.T, w.cin, prec == SQD_FP32 ? w.c32 : nullptr);
                 if (nx > 0)
                     lock_project(g, s, X, nx, w.V, 1, n, w.st, w.cin, prec == SQD_FP32 ? w.c32 : nullptr, w.partial);
@@ -304,14 +305,14 @@ static int davidson_run(sqd_ctx* ctx, sqd_space* sp, const sqd_davidson_opts* o,
             if (basis32) {
                 // x = V y from the FP32 basis into cin, then V[0] = x / |x|
                 // in FP64 (the FP32 rows are not orthonormal to FP64 accuracy)
-                L32::collapse(g, s, V32, AV32, n, w.st, 1, w.cin);
+                L32::collapse(g, s, V32, n, w.st, w.cin);
                 hipLaunchKernelGGL(k_copy_norm, dim3(g), dim3(kThreads), 0, s, w.cin, w.V, n, w.partial);
                 hipLaunchKernelGGL(k_norm_fin, dim3(1), dim3(kThreads), 0, s, w.partial, g, w.st);
                 hipLaunchKernelGGL(k_scale_copy<double>, dim3(g), dim3(kThreads), 0, s, w.V, n, w.st, w.cin,
                                    nullptr);
                 basis32 = false;
             } else {
-                L::collapse(g, s, w.V, w.AV, n, w.st, 1, w.cin);
+                L::collapse(g, s, w.V, n, w.st, w.cin);
             }
             hipLaunchKernelGGL(k_set_phase, dim3(1), dim3(64), 0, s, w.st, 1, DONE_RUNNING);
             if ((rc = product(SQD_FP64))) return rc;

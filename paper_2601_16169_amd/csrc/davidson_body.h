@@ -7,6 +7,7 @@
 #include <cmath>
 #include <type_traits>
 
+#include "small_eig.h"
 #include "sqd_internal.h"
 
 namespace dav {
@@ -75,12 +76,10 @@ struct dav_state {
     double hc[2];         // Gram-Schmidt coefficients after a collapse
     double hist_r[SQD_HIST];
     double hist_e[SQD_HIST];
-    int qn;               // Qp holds the eigenvectors of the leading qn x qn block of G (0: none)
     int xredo;            // locked-vector projection needs a second pass
     double best_r;        // smallest residual of the current phase
     double xc[SQD_MAXLOCK];   // X^T v of the vector being projected
     double xscale;        // scale applied after the projection (1 / |v - X xc|, or 1)
-    double Qp[MM * MM];
 };
 
 struct dav_params {
@@ -91,54 +90,46 @@ struct dav_params {
     int mixed;
 };
 
-// 1/x and 1/sqrt(x) from the hardware estimates refined by two Newton steps
-// (each squares the relative error, so two reach FP64 rounding); a dependent
-// chain far shorter than IEEE division and square root.
-__device__ __forceinline__ double rcp_refined(double x) {
-    double r = __builtin_amdgcn_rcp(x);
+// Sums of v[0..N) over the 64 lanes of a wavefront, by recursive halving: at
+// each step a lane hands the half of its columns that its partner keeps to the
+// partner and adds the other half's, so N - 1 + 6 - log2 N exchanges instead of 6 N
+// (26 columns: 31 instead of 156).  The lane ends with the sum of column `col`
+// (when there are fewer columns than lanes some end with none: col = -1).
+template <int N, int MASK>
+__device__ __forceinline__ double halve_sum(const double (&v)[N], int base, int size, int lane, int& col) {
+    if constexpr (MASK == 0) {
+        static_assert(N == 1, "more columns than lanes");
+        col = size > 0 ? base : -1;
+        return v[0];
+    } else {
+        constexpr int H = (N + 1) / 2;
+        const bool up = (lane & MASK) != 0;
+        double k[H];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) r = fma(r, fma(-x, r, 1.0), r);
-    return r;
-}
-__device__ __forceinline__ double rsqrt_refined(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    const double h = 0.5 * x;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) y = fma(y, fma(-h * y, y, 0.5), y);
-    return y;
-}
-
-// Rotation (c, s) that zeroes the (p, q) entry of a symmetric 2 x 2 block
-// [[app, apq], [apq, aqq]] (Rutishauser's smaller-angle choice, written with
-// d = aqq - app and e = 2 apq: t = sign(d) e / (|d| + hypot(d, e)), c =
-// 1/sqrt(1 + t^2), s = t c; sign(0) = +1).
-__device__ __forceinline__ void jacobi_rotation(double app, double aqq, double apq, double& c, double& s) {
-    const double d = aqq - app, e = 2.0 * apq;
-    const double h2 = d * d + e * e;
-    if (!(h2 > 1e-300)) {   // an entry this small is below any convergence test: leave it
-        c = 1.0;
-        s = 0.0;
-        return;
+        for (int j = 0; j < H; ++j) {
+            const double lo = v[j], hi = j + H < N ? v[j + H] : 0.0;
+            k[j] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, MASK);
+        }
+        // of `size` columns in use the lower lane keeps H, the upper the rest
+        const int low = size < H ? size : H;
+        return halve_sum<H, MASK / 2>(k, up ? base + H : base, up ? size - low : low, lane, col);
     }
-    const double hyp = h2 * rsqrt_refined(h2);
-    const double t = (d >= 0.0 ? e : -e) * rcp_refined(fabs(d) + hyp);
-    c = rsqrt_refined(1.0 + t * t);
-    s = t * c;
 }
 
-// Block-wide sums of acc[0..NV) (wave shuffles, then one LDS slot per wave);
-// written to partial row `row`.  All NV entries are reduced so that every
-// register index is static.
+// Block-wide sums of acc[0..NV) in wred (a slot per wave).
+template <int NV>
+__device__ __forceinline__ void wave_sums(const double (&acc)[NV], double (*wred)[NV]) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int col;
+    const double v = halve_sum<NV, 32>(acc, 0, NV, lane, col);
+    if (col >= 0) wred[w][col] = v;   // lanes that share a column hold the same sum
+}
+
+// Block-wide sums of acc[0..NV); written to partial row `row`.
 template <int NV>
 __device__ void block_to_partial(const double (&acc)[NV], double* __restrict__ partial, int64_t row, int64_t nrows) {
     __shared__ double wred[kWaves][NV];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-        double v = acc[j];
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-        if (lane == 0) wred[w][j] = v;
-    }
+    wave_sums<NV>(acc, wred);
     __syncthreads();
     if (threadIdx.x < NV) {
         double s = 0.0;
@@ -160,13 +151,7 @@ __device__ void reduce_rows(const double* __restrict__ partial, int nrows, doubl
         for (int j = 0; j < NV; ++j) acc[j] += partial[(size_t)j * nrows + b];
     }
     __shared__ double wred[kWaves][NV];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-        double v = acc[j];
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-        if (lane == 0) wred[w][j] = v;
-    }
+    wave_sums<NV>(acc, wred);
     __syncthreads();
     if (threadIdx.x < NV) {
         double s = 0.0;
@@ -354,16 +339,18 @@ __device__ __forceinline__ void d_residual(const VT* __restrict__ V, const VT* _
 // Convergence / cap / phase-switch decisions and the collapse plan.
 template <int MT>
 __device__ __forceinline__ void f_res_fin(const double* __restrict__ partial, int nrows, dav_state* st, dav_params prm) {
-    if (st->done) return;
+    // (the state's loads go out with the partials')
+    const int over = st->done;
     __shared__ double out[MT + 2];
     reduce_rows<MT + 2>(partial, nrows, out);
+    if (over) return;
+    if (threadIdx.x < st->m) st->h[threadIdx.x] = out[threadIdx.x];
     if (threadIdx.x != 0) return;
     const int m = st->m;
     const double theta = st->theta;
     const double rn = sqrt(out[MT]);
     st->rnorm = rn;
     st->tt0 = out[MT + 1];
-    for (int j = 0; j < m; ++j) st->h[j] = out[j];
     const int it = st->iter;
     if (it < SQD_HIST) {
         st->hist_r[it] = rn;
@@ -441,107 +428,105 @@ __device__ __forceinline__ void f_res_fin(const double* __restrict__ partial, in
     }
 }
 
-// In-place collapse: V[a] = V qc[a], AV[a] = AV qc[a] for the kept columns a.
-// force = 1 (switch to FP64 refinement): keep x = V y only, AV not kept.
+// x = V y into cin and, from an FP64 basis, V[0] (the FP64 refinement's first
+// vector; an FP32 basis leaves V[0] to the caller, which it overlaps).
 template <int MT, typename VT = double>
-__device__ __forceinline__ void d_collapse(VT* __restrict__ V, VT* __restrict__ AV, int64_t n, const dav_state* st, int force,
-           double* __restrict__ cin, int64_t bid, int64_t nblk) {
-    int keep;
-    if (force) {
-        keep = 1;
-    } else {
-        if (st->done || !st->collapse) return;
-        keep = st->collapse;
-    }
+__device__ __forceinline__ void d_collapse(VT* __restrict__ V, int64_t n, const dav_state* st,
+                                           double* __restrict__ cin, int64_t bid, int64_t nblk) {
     const int m = st->m;
-    // an FP32 basis leaves the FP64 refinement's first vector to the caller
-    // (it overlaps the FP32 rows still being read): only cin is written
-    const bool wv = !(force && sizeof(VT) < sizeof(double));
-    const double* q1p = force ? st->y : st->qc[0];
-    const double* q2p = st->qc[1];
     with_rows<MT>(m, [&](auto nr_) {
         constexpr int NR = decltype(nr_)::value;
-        double q1[NR], q2[NR];
+        double y[NR];
         const VT* vr[NR];
-        const VT* ar[NR];
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
-            q1[k] = (k < m) ? q1p[k] : 0.0;
-            q2[k] = (k < m) ? q2p[k] : 0.0;
+            y[k] = (k < m) ? st->y[k] : 0.0;
             vr[k] = row_ptr(V, k, m, n);
-            ar[k] = row_ptr(AV, k, m, n);
         }
-        // every row is read before row 0 or 1 is written: the loads of one
-        // element precede its stores, and elements are independent
         for (int64_t i = (int64_t)bid * kThreads + threadIdx.x; i < n; i += (int64_t)nblk * kThreads) {
             double v[NR];
 #pragma unroll
             for (int k = 0; k < NR; ++k) v[k] = __builtin_nontemporal_load(vr[k] + i);
-            double x1 = 0.0, x2 = 0.0;
+            double x = 0.0;
 #pragma unroll
-            for (int k = 0; k < NR; ++k) {
-                x1 += q1[k] * v[k];
-                x2 += q2[k] * v[k];
-            }
-            if (!force) {
-                double a[NR];
-#pragma unroll
-                for (int k = 0; k < NR; ++k) a[k] = __builtin_nontemporal_load(ar[k] + i);
-                double a1 = 0.0, a2 = 0.0;
-#pragma unroll
-                for (int k = 0; k < NR; ++k) {
-                    a1 += q1[k] * a[k];
-                    a2 += q2[k] * a[k];
-                }
-                AV[i] = (VT)a1;
-                if (keep == 2) AV[n + i] = (VT)a2;
-            }
-            if (wv) {
-                V[i] = (VT)x1;
-                if (keep == 2) V[n + i] = (VT)x2;
-            }
-            if (cin) cin[i] = x1;
+            for (int k = 0; k < NR; ++k) x += y[k] * v[k];
+            if (sizeof(VT) == sizeof(double)) V[i] = (VT)x;
+            cin[i] = x;
         }
     });
 }
 
-// State after a collapse (force: m = 0, the next dots pass rebuilds G[0][0]).
-__device__ __forceinline__ void f_collapse_fin(dav_state* st, int force) {
+// State after it: m = 0, the next dots pass rebuilds G[0][0].
+__device__ __forceinline__ void f_collapse_fin(dav_state* st) {
     if (threadIdx.x != 0) return;
-    if (force) {
-        st->m = 0;
-        st->collapse = 0;
-        st->qn = 0;
-        return;
-    }
-    if (st->done || !st->collapse) return;
-    const int keep = st->collapse;
-    st->m = keep;
-    st->qn = 0;
-    for (int k = 0; k < MM * MM; ++k) st->G[k] = 0.0;
-    st->G[0] = st->Gc[0];
-    if (keep == 2) {
-        st->G[1] = st->Gc[1];
-        st->G[MM] = st->Gc[2];
-        st->G[MM + 1] = st->Gc[3];
-    }
-    for (int k = 0; k < MM; ++k) {
-        st->h[k] = (k < keep) ? st->hc[k] : 0.0;
-        st->y[k] = (k == 0) ? 1.0 : 0.0;
-        st->y_prev[k] = st->y[k];
-    }
+    st->m = 0;
     st->collapse = 0;
 }
 
-// t1 = t - V h; partial columns 0..MT-1: V^T t1; MT: |t1|^2.
+// t1 = t - V h; partial columns 0..MT-1: V^T t1; MT: |t1|^2.  With a restart
+// pending the basis is collapsed in place on the way: V[a] = V qc[a], AV[a] =
+// AV qc[a] for the kept columns a (every row of an element is read before its
+// row 0 or 1 is written, and elements are independent), and h is hc over those
+// columns.
 template <int MT, typename VT = double>
-__device__ __forceinline__ void d_orth1(const VT* __restrict__ V, int64_t n, const dav_state* st, double* __restrict__ T,
-        double* __restrict__ partial, int64_t bid, int64_t nblk) {
+__device__ __forceinline__ void d_orth1(VT* __restrict__ V, VT* __restrict__ AV, int64_t n, const dav_state* st,
+        double* __restrict__ T, double* __restrict__ partial, int64_t bid, int64_t nblk) {
     if (st->done) return;
     const int m = st->m;
     double acc[MT + 1];
 #pragma unroll
     for (int k = 0; k < MT + 1; ++k) acc[k] = 0.0;
+    if (st->collapse) {
+        const bool two = st->collapse == 2;
+        const double h0 = st->hc[0], h1 = two ? st->hc[1] : 0.0;
+        with_rows<MT>(m, [&](auto nr_) {
+            constexpr int NR = decltype(nr_)::value;
+            double q1[NR], q2[NR];
+            const VT* vr[NR];
+            const VT* ar[NR];
+#pragma unroll
+            for (int k = 0; k < NR; ++k) {
+                q1[k] = (k < m) ? st->qc[0][k] : 0.0;
+                q2[k] = (k < m) ? st->qc[1][k] : 0.0;
+                vr[k] = row_ptr(V, k, m, n);
+                ar[k] = row_ptr(AV, k, m, n);
+            }
+            for (int64_t i = (int64_t)bid * kThreads + threadIdx.x; i < n; i += (int64_t)nblk * kThreads) {
+                double v[NR];
+#pragma unroll
+                for (int k = 0; k < NR; ++k) v[k] = __builtin_nontemporal_load(vr[k] + i);
+                double x1 = 0.0, x2 = 0.0;
+#pragma unroll
+                for (int k = 0; k < NR; ++k) {
+                    x1 += q1[k] * v[k];
+                    x2 += q2[k] * v[k];
+                }
+#pragma unroll
+                for (int k = 0; k < NR; ++k) v[k] = __builtin_nontemporal_load(ar[k] + i);
+                double a1 = 0.0, a2 = 0.0;
+#pragma unroll
+                for (int k = 0; k < NR; ++k) {
+                    a1 += q1[k] * v[k];
+                    a2 += q2[k] * v[k];
+                }
+                AV[i] = (VT)a1;
+                V[i] = (VT)x1;
+                if (two) {
+                    AV[n + i] = (VT)a2;
+                    V[n + i] = (VT)x2;
+                }
+                // the projection uses the rows as stored
+                const double w1 = (double)(VT)x1, w2 = (double)(VT)x2;
+                const double t = T[i] - h0 * w1 - h1 * w2;
+                T[i] = t;
+                acc[MT] += t * t;
+                acc[0] += w1 * t;
+                if (two) acc[1] += w2 * t;
+            }
+        });
+        block_to_partial<MT + 1>(acc, partial, bid, nblk);
+        return;
+    }
     with_rows<MT>(m, [&](auto nr_) {
         constexpr int NR = decltype(nr_)::value;
         double h[NR];
@@ -549,7 +534,7 @@ __device__ __forceinline__ void d_orth1(const VT* __restrict__ V, int64_t n, con
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
             h[k] = (k < m) ? st->h[k] : 0.0;
-            vr[k] = row_ptr(V, k, m, n);
+            vr[k] = row_ptr((const VT*)V, k, m, n);
         }
         for (int64_t i = (int64_t)bid * kThreads + threadIdx.x; i < n; i += (int64_t)nblk * kThreads) {
             double v[NR];
@@ -569,16 +554,29 @@ __device__ __forceinline__ void d_orth1(const VT* __restrict__ V, int64_t n, con
 
 template <int MT, typename VT = double>
 __device__ __forceinline__ void f_orth1_fin(const double* __restrict__ partial, int nrows, dav_state* st) {
-    if (st->done) return;
+    const int over = st->done, keep = st->collapse, m = keep ? keep : st->m;
     __shared__ double out[MT + 1];
     reduce_rows<MT + 1>(partial, nrows, out);
-    if (threadIdx.x != 0) return;
-    const int m = st->m;
-    double hh = 0.0;
-    for (int j = 0; j < m; ++j) {
-        st->h[j] = out[j];
-        hh += out[j] * out[j];
+    if (over) return;
+    __syncthreads();   // every thread has read the state that changes below
+    if (keep) {        // the basis was collapsed by the pass
+        for (int k = threadIdx.x; k < MM * MM; k += kThreads) {
+            const int i = k / MM, j = k % MM;
+            st->G[k] = (i < keep && j < keep) ? st->Gc[i * 2 + j] : 0.0;
+        }
+        if (threadIdx.x < MM) {
+            st->y[threadIdx.x] = threadIdx.x == 0 ? 1.0 : 0.0;
+            st->y_prev[threadIdx.x] = threadIdx.x == 0 ? 1.0 : 0.0;
+        }
     }
+    if (threadIdx.x < MM) st->h[threadIdx.x] = threadIdx.x < m ? out[threadIdx.x] : 0.0;
+    if (threadIdx.x != 0) return;
+    if (keep) {
+        st->m = keep;
+        st->collapse = 0;
+    }
+    double hh = 0.0;
+    for (int j = 0; j < m; ++j) hh += out[j] * out[j];
     const double t1 = out[MT];
     const double nrm2 = t1 - hh;
     // a second projection only when the first left an overlap above what
@@ -665,163 +663,38 @@ __device__ __forceinline__ void d_dots(const VT* __restrict__ V, VT* __restrict_
     block_to_partial<MT + 1>(acc, partial, bid, nblk);
 }
 
-// G[:, m] from the partials, m += 1, then the lowest eigenpair of G by
-// parallel cyclic Jacobi (round-robin pairs): theta, y (y_prev keeps the old y).
+// G[:, m] from the partials, m += 1, then the lowest eigenpair of G: theta, y
+// (y_prev keeps the old y).
 template <int MT>
 __device__ __forceinline__ void f_dots_fin(const double* __restrict__ partial, int nrows, dav_state* st) {
-    if (st->done) return;
+    const int over = st->done, m0 = st->m, m = m0 + 1;
     __shared__ double out[MT + 1];
+    __shared__ eig_work<MT, 1> work;
+    const int lane = threadIdx.x;
+    double a[MT];
+#pragma unroll
+    for (int j = 0; j < MT; ++j) a[j] = st->G[(lane & (MM - 1)) * MM + j];
+    const double yp = lane < MM ? st->y[lane] : 0.0;
     reduce_rows<MT + 1>(partial, nrows, out);
-    // row stride LS = MM + 1: rows of A, Q and B start in different LDS banks,
-    // so the column accesses of the rotations do not all hit one bank
-    constexpr int LS = MM + 1;
-    __shared__ double A[MM * LS];
-    __shared__ double Q[MM * LS];
-    __shared__ double B[MM * LS];
-    __shared__ double rc[MM / 2], rs[MM / 2];
-    __shared__ int rp[MM / 2], rq[MM / 2];
-    __shared__ double red[2 * kWaves];
-    const int t = threadIdx.x;
-    const int m0 = st->m;
-    const int m = m0 + 1;
-    for (int j = t; j <= m0; j += kThreads) {
-        st->G[j * MM + m0] = out[j];
-        st->G[m0 * MM + j] = out[j];
+    if (over || lane >= 64) return;   // one wavefront
+#pragma unroll
+    for (int j = 0; j < MT; ++j)      // row and column m0 are new
+        a[j] = (lane < m && j < m) ? (lane == m0 ? out[j] : j == m0 ? out[lane] : a[j]) : 0.0;
+    if (lane < m) {
+        st->G[lane * MM + m0] = out[lane];
+        st->G[m0 * MM + lane] = out[lane];
     }
-    for (int k = t; k < MM; k += kThreads) st->y_prev[k] = st->y[k];
-    // Warm start: when Qp diagonalises the leading m0 x m0 block, rotate G by
-    // diag(Qp, 1) first; the result is diagonal but for its last row and
-    // column, and the sweeps below converge in two or three passes.
-    const bool warm = (st->qn == m0) && m0 > 0;
-    __syncthreads();
-    for (int k = t; k < MM * MM; k += kThreads) {
-        const int i = k / MM, j = k % MM;
-        double q = (i == j) ? 1.0 : 0.0;
-        if (warm && i < m0 && j < m0) q = st->Qp[k];
-        Q[i * LS + j] = q;
-        A[i * LS + j] = st->G[k];
+    double theta[1], y[1];
+    lowest_pairs<MT, 1>(a, m, 1, work, theta, y);
+    // sign: keep continuity with the previous Ritz vector
+    const double dp = sum32(lane < m ? y[0] * yp : 0.0);
+    if (lane < MM) {
+        st->y_prev[lane] = yp;
+        st->y[lane] = lane < m ? (dp < 0.0 ? -y[0] : y[0]) : 0.0;
     }
-    if (t == 0) st->m = m;
-    __syncthreads();
-    if (warm) {
-        for (int k = t; k < MM * MM; k += kThreads) {   // B = G Q
-            const int i = k / MM, j = k % MM;
-            double v = 0.0;
-            if (i < m && j < m)
-                for (int l = 0; l < m; ++l) v += A[i * LS + l] * Q[l * LS + j];
-            B[i * LS + j] = v;
-        }
-        __syncthreads();
-        for (int k = t; k < MM * MM; k += kThreads) {   // A = Q^T B
-            const int i = k / MM, j = k % MM;
-            double v = 0.0;
-            if (i < m && j < m)
-                for (int l = 0; l < m; ++l) v += Q[l * LS + i] * B[l * LS + j];
-            A[i * LS + j] = v;
-        }
-        __syncthreads();
-        for (int k = t; k < MM * MM; k += kThreads) {   // exact symmetry
-            const int i = k / MM, j = k % MM;
-            if (i < j && j < m) {
-                const double v = 0.5 * (A[i * LS + j] + A[j * LS + i]);
-                A[i * LS + j] = v;
-                A[j * LS + i] = v;
-            }
-        }
-        __syncthreads();
-    }
-    if (m > 1) {
-        const int n2 = (m + 1) & ~1;
-        const int npair = n2 / 2;
-        const int lane = t & 63, w = t >> 6;
-        for (int sweep = 0; sweep < 50; ++sweep) {
-            double off = 0.0, tot = 0.0;
-            for (int k = t; k < MM * MM; k += kThreads) {
-                const int i = k / MM, j = k % MM;
-                if (i < m && j < m) {
-                    const double v = A[i * LS + j];
-                    tot += v * v;
-                    if (i != j) off += v * v;
-                }
-            }
-            for (int o = 32; o > 0; o >>= 1) {
-                off += __shfl_xor(off, o);
-                tot += __shfl_xor(tot, o);
-            }
-            if (lane == 0) { red[w] = off; red[kWaves + w] = tot; }
-            __syncthreads();
-            off = 0.0; tot = 0.0;
-            for (int q = 0; q < kWaves; ++q) { off += red[q]; tot += red[kWaves + q]; }
-            __syncthreads();
-            if (off <= 1e-28 * tot || off == 0.0) break;
-            for (int step = 0; step < n2 - 1; ++step) {
-                // round-robin pairing: index 0 fixed, the others rotate
-                if (t < npair) {
-                    const int pa = t, pb = n2 - 1 - t;
-                    int ia = pa - 1 + step, ib = pb - 1 + step;
-                    if (ia >= n2 - 1) ia -= n2 - 1;
-                    if (ib >= n2 - 1) ib -= n2 - 1;
-                    int p = pa == 0 ? 0 : ia + 1;
-                    int q = pb == 0 ? 0 : ib + 1;
-                    if (p > q) { const int x = p; p = q; q = x; }
-                    double c = 1.0, s = 0.0;
-                    if (q < m) {
-                        const double apq = A[p * LS + q];
-                        if (apq != 0.0) jacobi_rotation(A[p * LS + p], A[q * LS + q], apq, c, s);
-                    }
-                    rc[t] = c; rs[t] = s; rp[t] = p; rq[t] = q;
-                }
-                __syncthreads();
-                // A <- J^T A J one 2 x 2 block per thread: the pairs are
-                // disjoint, so block (P1, P2) depends only on itself
-                for (int k = t; k < (MM / 2) * (MM / 2); k += kThreads) {
-                    const int b1 = k / (MM / 2), b2 = k % (MM / 2);
-                    if (b1 >= npair || b2 >= npair) continue;
-                    const int p1 = rp[b1], q1 = rq[b1], p2 = rp[b2], q2 = rq[b2];
-                    const bool v1 = q1 < m, v2 = q2 < m;
-                    const double c1 = rc[b1], s1 = rs[b1], c2 = rc[b2], s2 = rs[b2];
-                    if (s1 == 0.0 && s2 == 0.0) continue;
-                    const double app = A[p1 * LS + p2];
-                    const double apq = v2 ? A[p1 * LS + q2] : 0.0;
-                    const double aqp = v1 ? A[q1 * LS + p2] : 0.0;
-                    const double aqq = (v1 && v2) ? A[q1 * LS + q2] : 0.0;
-                    const double rpp = c1 * app - s1 * aqp, rpq = c1 * apq - s1 * aqq;
-                    const double rqp = s1 * app + c1 * aqp, rqq = s1 * apq + c1 * aqq;
-                    A[p1 * LS + p2] = c2 * rpp - s2 * rpq;
-                    if (v2) A[p1 * LS + q2] = s2 * rpp + c2 * rpq;
-                    if (v1) A[q1 * LS + p2] = c2 * rqp - s2 * rqq;
-                    if (v1 && v2) A[q1 * LS + q2] = s2 * rqp + c2 * rqq;
-                }
-                // Q <- Q J
-                for (int k = t; k < (MM / 2) * MM; k += kThreads) {
-                    const int pr = k / MM, i = k % MM;
-                    if (pr >= npair || i >= m) continue;
-                    const int p = rp[pr], q = rq[pr];
-                    if (q >= m || rs[pr] == 0.0) continue;
-                    const double c = rc[pr], s = rs[pr];
-                    const double qp = Q[i * LS + p], qq = Q[i * LS + q];
-                    Q[i * LS + p] = c * qp - s * qq;
-                    Q[i * LS + q] = s * qp + c * qq;
-                }
-                __syncthreads();
-            }
-        }
-    }
-    for (int k = t; k < MM * MM; k += kThreads) st->Qp[k] = Q[(k / MM) * LS + k % MM];
-    if (t == 0) st->qn = m;
-    if (t == 0) {
-        int kmin = 0;
-        for (int k = 1; k < m; ++k)
-            if (A[k * LS + k] < A[kmin * LS + kmin]) kmin = k;
-        st->theta = A[kmin * LS + kmin];
-        double nrm = 0.0;
-        for (int k = 0; k < m; ++k) nrm += Q[k * LS + kmin] * Q[k * LS + kmin];
-        nrm = 1.0 / sqrt(nrm);
-        // sign: keep continuity with the previous Ritz vector
-        double dp = 0.0;
-        for (int k = 0; k < m; ++k) dp += Q[k * LS + kmin] * st->y_prev[k];
-        if (dp < 0.0) nrm = -nrm;
-        for (int k = 0; k < MM; ++k) st->y[k] = (k < m) ? Q[k * LS + kmin] * nrm : 0.0;
+    if (lane == 0) {
+        st->m = m;
+        st->theta = theta[0];
     }
 }
 
