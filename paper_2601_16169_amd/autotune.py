@@ -121,6 +121,19 @@ def _search(ctx, groups, measure, log) -> Dict:
     return result
 
 
+def _best(ctx, groups, measure, log) -> Dict:
+    """The fastest forced settings, or none where the library's automatic
+    choice is as fast: all terms in one launch, which no forced setting
+    reaches."""
+    reset(ctx)
+    automatic = measure()
+    result = _search(ctx, groups, measure, log)
+    if automatic <= result["ab"][1]:
+        reset(ctx)
+        result = {"ss": ([], automatic), "ab": ([], automatic)}
+    return result
+
+
 def tune(space: "sqd.Space", precision: int = sqd.FP64, reps: int = 10, use_cache: bool = True,
          log=None) -> Dict:
     """Tune the context of ``space`` for its full sigma product; returns
@@ -151,12 +164,7 @@ def tune(space: "sqd.Space", precision: int = sqd.FP64, reps: int = 10, use_cach
         e1.synchronize()
         return e0.elapsed_time(e1) / reps
 
-    reset(ctx)
-    automatic = measure()   # all terms in one launch, where the library takes it: no forced setting reaches it
-    result = _search(ctx, (("ss", SS_KNOBS), ("ab", AB_KNOBS)), measure, log)
-    if automatic <= result["ab"][1]:
-        reset(ctx)
-        result = {"ss": ([], automatic), "ab": ([], automatic)}
+    result = _best(ctx, (("ss", SS_KNOBS), ("ab", AB_KNOBS)), measure, log)
     if use_cache:
         _store(key, result)
     return result
@@ -189,8 +197,7 @@ def tune_batched(ctx, spaces: Sequence["sqd.Space"], mode: int = sqd.DAV_MIXED, 
         # difference of two lengths removes the plan and graph set-up
         return 1e3 * (run(iterations + 2) - run(2)) / iterations
 
-    reset(ctx)
-    result = _search(ctx, (("ss", SS_KNOBS), ("ab", AB_KNOBS_BATCHED)), measure, log)
+    result = _best(ctx, (("ss", SS_KNOBS), ("ab", AB_KNOBS_BATCHED)), measure, log)
     if use_cache:
         _store(key, result)
     return result

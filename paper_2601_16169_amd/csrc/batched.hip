@@ -2,11 +2,12 @@
 // counts that the sampling loop of Sec. I produces; load balance across task
 // groups is the paper's scaling limiter, Sec. VI).
 //
-// * Every sigma term of every space runs in ONE launch: the work units are
-//   (space, tile) pairs -- row blocks for the same-spin kernel, pair chunks for
-//   the alpha-beta kernel -- ordered longest-first and pulled by persistent
-//   workgroups from an atomic queue; the cheaper uniform passes (transposes,
-//   gathers, vector kernels) stride over their unit lists statically.
+// * All sigma terms of all spaces run in one launch for each class of row
+//   lengths (kb_terms), whose work units are (space, tile) pairs ordered by the
+//   spaces' work, and one gather; rows too long for that, and kernels chosen by
+//   the caller, take a launch for each term, pulled by persistent workgroups from
+//   an atomic queue.  The cheaper uniform passes (transposes, gathers, vector
+//   kernels) stride over their unit lists statically.
 // * The Davidson state of each space stays on the device; the vector kernels
 //   of all spaces run in one launch each and the small per-space work runs in
 //   one workgroup per space.  A space that has converged (or reached its cap
@@ -56,6 +57,7 @@ struct bdesc {
     float* Y32;
     const int* a_off;
     const int* a_order;   // alpha rows, heaviest first (gather order)
+    int ng;               // groups of threads of the gather of one row
     const int* abs_src;   // source string of each alpha-beta chunk (source-grouped spaces)
     ss_args<double> bb64, aa64;
     ss_args<float> bb32, aa32;
@@ -95,6 +97,27 @@ __global__ void __launch_bounds__(1024) kb_same_spin(const bdesc* __restrict__ D
         ss_block<T, R>(ssa(d, which, T()), jk, norb, units[u].y, lds_raw);
         __syncthreads();
     }
+}
+
+// All terms of all spaces of a class in one launch: unit (space, kind << 28 |
+// block), kind 0 the rows of the beta-beta term (into sout / S32), 1 those of the
+// alpha-alpha term, read from the columns of C (into Yt), 2 the alpha-beta chunks
+// (into Y); kb_gather adds the three.  The separate launches left the chip half
+// empty at the end of each and moved C and the alpha-alpha term through two
+// transposes.  Sixteen spaces of 200 to 1200 strings (norb 24), the products of an
+// iteration of all: FP64 650 -> 455 us, FP32 900 -> 420 us (there also by the
+// tables whose long rows are spread over several lanes).
+constexpr int kUnitShift = 28;
+template <typename T, int R>
+__global__ void __launch_bounds__(1024) kb_terms(const bdesc* __restrict__ D, const int2* __restrict__ units,
+                                                 const T* __restrict__ jk, const T* __restrict__ V, int norb) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const int2 u = units[blockIdx.x];
+    const bdesc& d = D[u.x];
+    if (d.st->done) return;
+    const int kind = u.y >> kUnitShift, k = u.y & ((1 << kUnitShift) - 1);
+    if (kind == 2) abg_block<T, R>(aba(d, T()), V, norb, k, lds_raw);
+    else ss_block<T, R>(ssa(d, kind, T()), jk, norb, k, lds_raw);
 }
 
 template <typename T, int G>
@@ -154,7 +177,9 @@ __global__ void __launch_bounds__(256) kb_transpose(const bdesc* __restrict__ D,
 }
 
 // One unit per (space, alpha row); STAGED: rows assembled in LDS (gather_row).
-template <typename T, bool STAGED>
+// ALL: the alpha-alpha term and the diagonal are added too, and the row goes to
+// sout (kb_terms).
+template <typename T, bool STAGED, bool ALL>
 __global__ void __launch_bounds__(256) kb_gather(const bdesc* __restrict__ D, const int2* __restrict__ units, int nunits) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     T* row = STAGED ? reinterpret_cast<T*>(lds_raw) : nullptr;
@@ -163,9 +188,11 @@ __global__ void __launch_bounds__(256) kb_gather(const bdesc* __restrict__ D, co
         if (d.st->done) continue;
         const T* Y = (const T*)(sizeof(T) == 8 ? (const void*)d.Y64 : (const void*)d.Y32);
         T* S = (T*)(sizeof(T) == 8 ? (void*)d.sout : (void*)d.S32);
+        const T* S2 = (const T*)(sizeof(T) == 8 ? (const void*)d.Yt : (const void*)d.Yt32);
         const ab_table& tab = aba(d, T()).tab;
-        const gather_args<T> a{Y, d.nb, tab.nslots, tab.perm, d.a_off, S, nullptr, nullptr, nullptr, nullptr};
-        gather_row<T>(a, d.a_order[units[u].y], 1, row);
+        gather_args<T> a{Y, d.nb, tab.nslots, tab.perm, d.a_off, S, nullptr, nullptr, nullptr, nullptr};
+        if (ALL) a.S2 = S2, a.diag = d.diag, a.c = d.cin, a.out64 = d.sout;
+        gather_row<T>(a, d.a_order[units[u].y], STAGED ? d.ng : 1, row);
         if (STAGED) __syncthreads();
     }
 }
@@ -377,6 +404,15 @@ struct batch_plan {
     size_t lds_ss64 = 0, lds_ss32 = 0, lds_ab64 = 0, lds_ab32 = 0, lds_ab64_2 = 0, lds_ab32_2 = 0;
     size_t gather_lds64 = 0;   // FP64 row bytes of the staged gather (0: in-place gather)
     int grid_persist = 0;
+    // one launch for the terms of a class (kb_terms): R rows or singles per
+    // workgroup, for FP64 and FP32 (0 classes: the separate launches)
+    struct term_class {
+        int R = 0, waves64 = 0, waves32 = 0;
+        size_t lds64 = 0;
+        unit_list units;
+        std::vector<int2> list;
+    };
+    std::vector<term_class> classes;
 };
 
 template <typename F>
@@ -385,6 +421,7 @@ void lds_attr(F f, size_t bytes) {
 }
 
 constexpr int kGridCap = 4096;
+constexpr int kGatherThreads = 256;
 
 // The alpha-beta chunks of the second class (spaces whose rows allow a
 // larger pair group than the longest rows of the batch).
@@ -423,13 +460,35 @@ void launch_ab_src(batch_plan& p, hipStream_t s, dim3 gp, int nw_ab, const T* V,
 #undef SQD_ABS_LAUNCH
 }
 
+// The products of every running space in one launch per class, and the gather.
+template <typename T>
+void launch_terms(sqd_ctx* ctx, batch_plan& p, hipStream_t s, const T* jk, const T* V) {
+    for (const auto& c : p.classes) {
+        const size_t lds = c.lds64 * sizeof(T) / 8;
+        const dim3 grid(c.units.n), block(64 * (sizeof(T) == 8 ? c.waves64 : c.waves32));
+        if (c.R == 4) hipLaunchKernelGGL((kb_terms<T, 4>), grid, block, lds, s, p.D, c.units.dev, jk, V, ctx->norb);
+        else hipLaunchKernelGGL((kb_terms<T, 2>), grid, block, lds, s, p.D, c.units.dev, jk, V, ctx->norb);
+    }
+    const dim3 grid((unsigned)p.gath.n);
+    if (p.gather_lds64)
+        hipLaunchKernelGGL((kb_gather<T, true, true>), grid, dim3(kGatherThreads), p.gather_lds64 * sizeof(T) / 8, s,
+                           p.D, p.gath.dev, p.gath.n);
+    else
+        hipLaunchKernelGGL((kb_gather<T, false, true>), grid, dim3(kGatherThreads), 0, s, p.D, p.gath.dev, p.gath.n);
+}
+
 // Launch the sigma of every running space (precision prec) into its sout.
 template <int R, int G, int RF>
 int batched_sigma(sqd_ctx* ctx, batch_plan& p, hipStream_t s, int prec, int nw_ss, int nw_ab) {
     const int norb = ctx->norb;
     const dim3 gp(p.grid_persist);
-    hipLaunchKernelGGL(kb_reset, dim3(1), dim3(64), 0, s, p.counters, 8);
     auto sgrid = [&](int n) { return dim3((unsigned)std::max(1, std::min(n, kGridCap))); };
+    if (!p.classes.empty()) {
+        if (prec == SQD_FP64) launch_terms<double>(ctx, p, s, ctx->jk64, ctx->eri);
+        else launch_terms<float>(ctx, p, s, ctx->jk32, ctx->eri32);
+        return SQD_OK;
+    }
+    hipLaunchKernelGGL(kb_reset, dim3(1), dim3(64), 0, s, p.counters, 8);
     if (prec == SQD_FP64) {
         hipLaunchKernelGGL((kb_transpose<double>), sgrid(p.tr.n), dim3(256), 0, s, p.D, 0, p.tr.dev, p.tr.n);
         hipLaunchKernelGGL((kb_same_spin<double, R>), gp, dim3(64 * nw_ss), p.lds_ss64, s, p.D, 1, p.ss_aa.dev, p.ss_aa.n,
@@ -443,10 +502,10 @@ int batched_sigma(sqd_ctx* ctx, batch_plan& p, hipStream_t s, int prec, int nw_s
                                p.abg.n, p.counters + 2, ctx->eri, norb);
         launch_ab_class2<double>(p, s, gp, nw_ab, ctx->eri, norb, p.counters + 6);
         if (p.gather_lds64)
-            hipLaunchKernelGGL((kb_gather<double, true>), sgrid(p.gath.n), dim3(256), p.gather_lds64, s, p.D,
+            hipLaunchKernelGGL((kb_gather<double, true, false>), sgrid(p.gath.n), dim3(256), p.gather_lds64, s, p.D,
                                p.gath.dev, p.gath.n);
         else
-            hipLaunchKernelGGL((kb_gather<double, false>), sgrid(p.gath.n), dim3(256), 0, s, p.D, p.gath.dev,
+            hipLaunchKernelGGL((kb_gather<double, false, false>), sgrid(p.gath.n), dim3(256), 0, s, p.D, p.gath.dev,
                                p.gath.n);
     } else {
         hipLaunchKernelGGL((kb_transpose<float>), sgrid(p.tr.n), dim3(256), 0, s, p.D, 0, p.tr.dev, p.tr.n);
@@ -461,10 +520,10 @@ int batched_sigma(sqd_ctx* ctx, batch_plan& p, hipStream_t s, int prec, int nw_s
                                p.abg.n, p.counters + 5, ctx->eri32, norb);
         launch_ab_class2<float>(p, s, gp, nw_ab, ctx->eri32, norb, p.counters + 7);
         if (p.gather_lds64)
-            hipLaunchKernelGGL((kb_gather<float, true>), sgrid(p.gath.n), dim3(256), p.gather_lds64 / 2, s, p.D,
+            hipLaunchKernelGGL((kb_gather<float, true, false>), sgrid(p.gath.n), dim3(256), p.gather_lds64 / 2, s, p.D,
                                p.gath.dev, p.gath.n);
         else
-            hipLaunchKernelGGL((kb_gather<float, false>), sgrid(p.gath.n), dim3(256), 0, s, p.D, p.gath.dev,
+            hipLaunchKernelGGL((kb_gather<float, false, false>), sgrid(p.gath.n), dim3(256), 0, s, p.D, p.gath.dev,
                                p.gath.n);
         hipLaunchKernelGGL(kb_combine, sgrid(p.vec.n), dim3(256), 0, s, p.D, p.vec.dev, p.vec.n);
     }
@@ -486,6 +545,10 @@ int batched_run(sqd_ctx* ctx, batch_plan& p, const sqd_davidson_opts* o, double*
                                                    : ((R == 8 || p.lds_ss64 > (size_t)ctx->max_lds / 2) ? 16 : 8);
     // measured on MI355X (the batched tuner's choice on 64 spaces of 200-3000 strings)
     const int nw_ab = ctx->tune[SQD_TUNE_AB_WAVES] ? ctx->tune[SQD_TUNE_AB_WAVES] : 8;
+    for (const auto& c : p.classes) {
+        if (c.R == 4) { lds_attr(kb_terms<double, 4>, c.lds64); lds_attr(kb_terms<float, 4>, c.lds64 / 2); }
+        else { lds_attr(kb_terms<double, 2>, c.lds64); lds_attr(kb_terms<float, 2>, c.lds64 / 2); }
+    }
     lds_attr(kb_same_spin<double, R>, p.lds_ss64);
     lds_attr(kb_same_spin<float, RF>, p.lds_ss32);
     lds_attr(kb_ab_grouped<double, G>, p.lds_ab64);
@@ -689,6 +752,39 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
         if ((rc = sqd_ensure_diag(ctx, spaces[b]))) return rc;
     }
     const int64_t max_cols = std::max(max_na, max_nb);
+    // One launch for all terms where two rows of every space fit the LDS and no
+    // kernel is chosen by the caller: the spaces by what fits, so that short rows
+    // keep two workgroups on a compute unit beside long ones (R rows or singles
+    // per workgroup, as in the single-space product).
+    std::vector<int> cls(nspace, -1);
+    {
+        const size_t n2 = (size_t)norb * norb, lim = (size_t)ctx->max_lds;
+        bool one = true;
+        for (int key : {SQD_TUNE_SS_ROWS, SQD_TUNE_SS_WAVES, SQD_TUNE_AB_VARIANT, SQD_TUNE_AB_GROUP, SQD_TUNE_AB_WAVES})
+            one = one && !ctx->tune[key];
+        batch_plan::term_class c[3];
+        const size_t bound[3] = {lim / 2, lim, lim};
+        for (int k = 0; k < 3; ++k) c[k].R = k < 2 ? 4 : 2;
+        for (int b = 0; b < nspace && one; ++b) {
+            const size_t cols = (size_t)std::max(spaces[b]->sp[0].n, spaces[b]->sp[1].n) + 1;
+            auto bytes = [&](int R) { return std::max((cols + n2) * R, ((size_t)spaces[b]->sp[1].n + 1) * R + n2) * 8; };
+            int k = 0;
+            while (k < 3 && bytes(c[k].R) > bound[k]) ++k;
+            if (k == 3) one = false;
+            else c[cls[b] = k].lds64 = std::max(c[k].lds64, bytes(c[k].R));
+        }
+        if (one) {
+            for (int k = 0; k < 3; ++k) {
+                if (!c[k].lds64) continue;
+                c[k].waves64 = c[k].lds64 <= lim / 2 ? 8 : 16;
+                c[k].waves32 = c[k].lds64 / 2 <= lim / 4 ? 8 : 16;
+                for (int& q : cls) if (q == k) q = 16 + (int)p.classes.size();
+                p.classes.push_back(c[k]);
+            }
+            for (int& q : cls) q -= 16;
+        }
+    }
+    const bool one = !p.classes.empty();
     p.R = pick_R(ctx, max_cols, norb, 8, ctx->tune[SQD_TUNE_SS_ROWS]);
     p.Rf = p.R;
     p.G = pick_G(ctx, max_nb, norb);
@@ -724,6 +820,8 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
     p.lds_abs32 = ((size_t)(max_nb + 1) + (size_t)p.GS * norb * norb) * 4;
     p.lds_ab32_2 = ((size_t)(max_nb2 + 1) * p.G2 + (size_t)norb * norb) * 4;
     p.gather_lds64 = (size_t)max_nb * 8 <= (size_t)(64 * 1024) ? (size_t)max_nb * 8 : 0;
+    // (ng groups of threads hold a row each, of at most 2 kGatherThreads / ng slots)
+    if (one && p.gather_lds64) p.gather_lds64 = std::max(p.gather_lds64, (size_t)kGatherThreads * 2 * 8);
     p.grid_persist = ctx->num_cu * 2;
     const bool mixed = o->mode == SQD_DAV_MIXED;
     const int mmax = o->m_max;
@@ -742,7 +840,11 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
         sqd_space* sp = spaces[b];
         const spin_tables& A = sp->sp[0];
         const spin_tables& B = sp->sp[1];
-        if (cls2[b]) rc = sqd_ensure_ab_groups(ctx, sp, p.G2);
+        if (one) {
+            rc = sqd_ensure_ab_groups(ctx, sp, p.classes[cls[b]].R);
+            if (!rc && mixed) rc = sqd_ensure_split32(ctx, sp);
+        }
+        else if (cls2[b]) rc = sqd_ensure_ab_groups(ctx, sp, p.G2);
         else rc = p.GS ? sqd_ensure_ab_source_groups(ctx, sp, p.GS) : sqd_ensure_ab_groups(ctx, sp, p.G);
         if (rc) return rc;
         bdesc& d = p.host[b];
@@ -760,15 +862,15 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
         want((void**)&d.T, sizeof(double) * d.n);
         want((void**)&d.cin, sizeof(double) * d.n);
         want((void**)&d.sout, sizeof(double) * d.n);
-        want((void**)&d.Ct, sizeof(double) * d.n);
+        if (!one) want((void**)&d.Ct, sizeof(double) * d.n);
         want((void**)&d.Yt, sizeof(double) * d.n);
         want((void**)&d.Y64, sizeof(double) * (A.nnz_s * B.ab64.nslots + 1));
         if (mixed) {
             want((void**)&d.c32, sizeof(float) * d.n);
-            want((void**)&d.Ct32, sizeof(float) * d.n);
+            if (!one) want((void**)&d.Ct32, sizeof(float) * d.n);
             want((void**)&d.Yt32, sizeof(float) * d.n);
             want((void**)&d.S32, sizeof(float) * d.n);
-            want((void**)&d.Y32, sizeof(float) * (A.nnz_s * B.ab32.nslots + 1));
+            want((void**)&d.Y32, sizeof(float) * (A.nnz_s * (one ? B.ab64 : B.ab32).nslots + 1));
         }
         for (int j = 0; j < d.nblk; ++j) vec.push_back(make_int2(b, j));
         for (int t = 0; t < d.ntx * d.nty; ++t) tr.push_back(make_int2(b, t));
@@ -782,6 +884,16 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
     for (auto& ob : order) {
         const int b = ob.second;
         const bdesc& d = p.host[b];
+        if (one) {
+            batch_plan::term_class& c = p.classes[cls[b]];
+            auto add = [&](int kind, int64_t count) {
+                for (int64_t k = 0; k < count; ++k) c.list.push_back(make_int2(b, (int)((kind << kUnitShift) | k)));
+            };
+            add(2, spaces[b]->ab_nchunks);
+            add(0, (d.na + c.R - 1) / c.R);
+            add(1, (d.nb + c.R - 1) / c.R);
+            continue;
+        }
         for (int64_t r = 0; r < (d.na + p.R - 1) / p.R; ++r) ssbb.push_back(make_int2(b, (int)r));
         for (int64_t r = 0; r < (d.nb + p.R - 1) / p.R; ++r) ssaa.push_back(make_int2(b, (int)r));
         const int nch = (!cls2[b] && p.GS) ? spaces[b]->abs_nchunks : spaces[b]->ab_nchunks;
@@ -792,9 +904,10 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
     want((void**)&p.counters, sizeof(int) * 8);
     want((void**)&p.count_dev, sizeof(int));
     want((void**)&p.D, sizeof(bdesc) * nspace);
-    std::pair<std::vector<int2>*, unit_list*> lists[7] = {{&vec, &p.vec}, {&tr, &p.tr}, {&ssbb, &p.ss_bb},
-                                                          {&ssaa, &p.ss_aa}, {&abg, &p.abg}, {&abg2, &p.abg2},
-                                                          {&gath, &p.gath}};
+    std::vector<std::pair<std::vector<int2>*, unit_list*>> lists = {{&vec, &p.vec}, {&gath, &p.gath}};
+    for (auto& c : p.classes) lists.push_back({&c.list, &c.units});
+    if (!one)
+        lists.insert(lists.end(), {{&tr, &p.tr}, {&ssbb, &p.ss_bb}, {&ssaa, &p.ss_aa}, {&abg, &p.abg}, {&abg2, &p.abg2}});
     for (auto& l : lists) {
         l.second->n = (int)l.first->size();
         if (l.first->empty()) l.first->push_back(make_int2(0, 0));
@@ -832,6 +945,19 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
         d.a_order = sp->ab_row_order;
         d.st = p.states + b;
         // same-spin: BB on C (rows alpha, columns beta, diagonal fused), AA on C^T
+        if (one) {
+            d.aa64 = ss_args<double>{d.cin, d.Yt, B.n, A.n, A.ss64, B.ws64, B.str, B.nw, nullptr, 0, 1};
+            d.bb64 = ss_args<double>{d.cin, d.sout, A.n, B.n, B.ss64, A.ws64, A.str, A.nw, nullptr, 0, 0};
+            d.aa32 = ss_args<float>{d.c32, d.Yt32, B.n, A.n, A.split32, B.ws32, B.str, B.nw, nullptr, 0, 1};
+            d.bb32 = ss_args<float>{d.c32, d.S32, A.n, B.n, B.split32, A.ws32, A.str, A.nw, nullptr, 0, 0};
+            d.ab64 = abg_args<double>{d.cin, d.Y64, B.n, sp->ab_grp, sp->ab_chunk_pair, B.ab64};
+            d.ab32 = abg_args<float>{d.c32, d.Y32, B.n, sp->ab_grp, sp->ab_chunk_pair, B.ab64};
+            // as many groups of threads of the gather as read a row of Y side by side
+            const int per = (int)((B.ab64.nslots / 2 + 63) / 64 * 64);
+            d.ng = p.gather_lds64 ? std::max(1, std::min(kGatherThreads / std::max(per, 64), 4)) : 1;
+            continue;
+        }
+        d.ng = 1;
         d.aa64 = ss_args<double>{d.Ct, d.Yt, B.n, A.n, A.ss64, B.ws64, B.str, B.nw, nullptr, 0};
         d.bb64 = ss_args<double>{d.cin, d.sout, A.n, B.n, B.ss64, A.ws64, A.str, A.nw, sp->diag, 1};
         d.aa32 = ss_args<float>{d.Ct32, d.Yt32, B.n, A.n, A.ss32, B.ws32, B.str, B.nw, nullptr, 0};
@@ -879,7 +1005,11 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
             default: return with_g(std::integral_constant<int, 1>());
         }
     };
+    // (m_max 24 is the default; with 32 columns of sums the kernels took, 24 / 32
+    // columns: kb_orth1 FP32 83 / 125 us, FP64 87 / 111, kb_dots_fin 37 / 43,
+    // kb_res_fin 12 / 21)
     if (mmax <= 16) rc = run(std::integral_constant<int, 16>());
+    else if (mmax <= 24) rc = run(std::integral_constant<int, 24>());
     else rc = run(std::integral_constant<int, 32>());
     (void)hipStreamSynchronize(s);
     (void)hipEventDestroy(ev);

@@ -753,7 +753,7 @@ int sqd_davidson_block_impl(sqd_ctx* ctx, sqd_space* sp, const sqd_davidson_opts
             int r = (o->product == SQD_PRODUCT_STORED)
                         ? sqd_spmv_impl(ctx, sp, V + (int64_t)l * n, AV + (int64_t)l * n, nullptr)
                         : sqd_sigma_impl(ctx, sp, V + (int64_t)l * n, AV + (int64_t)l * n, prec, SQD_TERM_ALL,
-                                         o->ab_path, nullptr, nullptr);
+                                         o->ab_path, nullptr, nullptr, nullptr, 0, true);
             if (r) return r;
         }
         for (int c0 = m0; c0 < m1; c0 += KB) {

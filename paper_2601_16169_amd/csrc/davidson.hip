@@ -257,7 +257,7 @@ static int davidson_run(sqd_ctx* ctx, sqd_space* sp, const sqd_davidson_opts* o,
     auto product = [&](int p) -> int {
         if (o->product == SQD_PRODUCT_STORED) return sqd_spmv_impl(ctx, sp, w.cin, w.sout, skip);
         return sqd_sigma_impl(ctx, sp, w.cin, w.sout, p, SQD_TERM_ALL, o->ab_path,
-                              p == SQD_FP32 ? w.c32 : nullptr, skip);
+                              p == SQD_FP32 ? w.c32 : nullptr, skip, nullptr, 0, true);
     };
     if ((rc = product(prec))) return rc;
     if (basis32) L32::dots(g, s, V32, AV32, w.sout, n, w.st, w.partial);

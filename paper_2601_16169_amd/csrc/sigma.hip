@@ -322,9 +322,9 @@ bool use_window(sqd_ctx* ctx, int64_t nrows, int64_t ncols, int norb, size_t es)
 }
 
 template <typename T>
-const sell_table<T>& same_spin_table(const spin_tables& t) {
+const sell_table<T>& same_spin_table(const spin_tables& t, bool any_order = false) {
     if constexpr (sizeof(T) == 8) return t.ss64;
-    else return t.ss32;
+    else return any_order ? t.split32 : t.ss32;
 }
 template <typename T>
 const T* cross_table(const spin_tables& t) {
@@ -557,11 +557,11 @@ int ensure_ab_source_groups(sqd_ctx* ctx, sqd_space* sp, int G) {
 const ab_table& ab_tab(const spin_tables& t, size_t es) { return es == sizeof(double) ? t.ab64 : t.ab32; }
 
 // Y bytes of the grouped alpha-beta path (0 if it is not to be used).
-size_t ab_grouped_bytes(sqd_ctx* ctx, const sqd_space* sp, size_t es) {
+size_t ab_grouped_bytes(sqd_ctx* ctx, const sqd_space* sp, size_t es, bool any_order = false) {
     const int variant = ctx->tune[SQD_TUNE_AB_VARIANT];
     if (variant == 2) return 0;
     if (ab_group_size(ctx, sp) == 0 && !ab_use_source_groups(ctx, sp)) return 0;
-    const size_t bytes = (size_t)sp->sp[0].nnz_s * (size_t)ab_tab(sp->sp[1], es).nslots * es;
+    const size_t bytes = (size_t)sp->sp[0].nnz_s * (size_t)(any_order ? sp->sp[1].ab64 : ab_tab(sp->sp[1], es)).nslots * es;
     const size_t cap = (size_t)64 << 30;   // keep the intermediate below 64 GiB
     if (variant == 0 && bytes > cap) return 0;
     return bytes + 256;
@@ -609,8 +609,13 @@ struct fused_shape { int R = 0, G = 0, waves = 0; size_t lds = 0; };
 // 1093, 4300: 2413 / 2171 with four rows, eight waves while four workgroups fit
 // (2000: 391 against 419; 2600: 540 against 508); beyond 100 KiB the separate
 // launches win (5500: 3523 against 3486, 5500 x 300: 348 against 595, 7000:
-// 5443 against 6775 with two rows).
-fused_shape fused_pick(sqd_ctx* ctx, const sqd_space* sp, size_t es, unsigned mask, int ab_path) {
+// 5443 against 6775 with two rows).  FP32 sums in any order (the solvers' FP32
+// phases) take the FP64 products' tables, long rows over several lanes, and are
+// faster in one launch as far as four rows fit: n = 600 x 500: 49 / 45, 2000: 315
+// / 296, 3000: 767 / 677, 4200: 2180 / 1472, 5500: 3826 / 2601 (rows as above /
+// over several lanes; eight rows 49, 307, 726, 2310, 3830).
+fused_shape fused_pick(sqd_ctx* ctx, const sqd_space* sp, size_t es, unsigned mask, int ab_path,
+                       bool any_order = false) {
     fused_shape f;
     constexpr unsigned kOff = SQD_TERM_AA | SQD_TERM_BB | SQD_TERM_AB;
     if ((mask & kOff) != kOff || ab_path != SQD_AB_DIRECT) return f;
@@ -620,7 +625,7 @@ fused_shape fused_pick(sqd_ctx* ctx, const sqd_space* sp, size_t es, unsigned ma
     const size_t n2 = (size_t)sp->norb * sp->norb, lim = (size_t)ctx->max_lds;
     const size_t cols = (size_t)std::max(sp->sp[0].n, sp->sp[1].n) + 1;
     auto bytes = [&](int k) { return std::max((cols + n2) * k, ((size_t)sp->sp[1].n + 1) * k + n2) * es; };
-    if (bytes(4) <= (es == sizeof(double) ? lim : lim * 5 / 8)) f.R = 4;
+    if (bytes(4) <= (es == sizeof(double) || any_order ? lim : lim * 5 / 8)) f.R = 4;
     else if (es == sizeof(double) && bytes(2) <= lim) f.R = 2;
     f.G = f.R;
     f.lds = f.R ? bytes(f.R) : 0;
@@ -630,14 +635,16 @@ fused_shape fused_pick(sqd_ctx* ctx, const sqd_space* sp, size_t es, unsigned ma
 
 template <typename T>
 int launch_fused(sqd_ctx* ctx, sqd_space* sp, const fused_shape& f, const T* C, T* S, T* S2, T* Y, const T* jk,
-                 const T* V, const double* diag, const double* c64, double* out64, const int* skip) {
+                 const T* V, const double* diag, const double* c64, double* out64, const int* skip,
+                 bool any_order = false) {
     const spin_tables& A = sp->sp[0];
     const spin_tables& B = sp->sp[1];
     int rc;
     if ((rc = ensure_ab_groups_impl(ctx, sp, f.G))) return rc;
-    const ab_table& tab = ab_tab(B, sizeof(T));
-    ss_args<T> bb{C, S, A.n, B.n, same_spin_table<T>(B), cross_table<T>(A), A.str, A.nw, nullptr, 0, 0};
-    ss_args<T> aa{C, S2, B.n, A.n, same_spin_table<T>(A), cross_table<T>(B), B.str, B.nw, nullptr, 0, 1};
+    if (any_order && (rc = sqd_ensure_split32(ctx, sp))) return rc;
+    const ab_table& tab = any_order ? B.ab64 : ab_tab(B, sizeof(T));
+    ss_args<T> bb{C, S, A.n, B.n, same_spin_table<T>(B, any_order), cross_table<T>(A), A.str, A.nw, nullptr, 0, 0};
+    ss_args<T> aa{C, S2, B.n, A.n, same_spin_table<T>(A, any_order), cross_table<T>(B), B.str, B.nw, nullptr, 0, 1};
     abg_args<T> ab{C, Y, B.n, sp->ab_grp, sp->ab_chunk_pair, tab};
     const int n_bb = (int)nblk(A.n, f.R), n_aa = (int)nblk(B.n, f.R);
     {
@@ -825,7 +832,8 @@ static int space_scratch_get(sqd_ctx* ctx, sqd_space* sp, size_t bytes, void** o
 }
 
 int sqd_sigma_impl(sqd_ctx* ctx, sqd_space* sp, const double* c, double* sigma, int precision, unsigned mask,
-                   int ab_path, const float* c32_in, const int* skip, void* ext_scratch, size_t ext_bytes) {
+                   int ab_path, const float* c32_in, const int* skip, void* ext_scratch, size_t ext_bytes,
+                   bool any_order) {
     int rc = sqd_ensure_diag(ctx, sp);
     if (rc) return rc;
     // a caller-provided scratch: the row-staged alpha-beta kernel (no
@@ -844,7 +852,7 @@ int sqd_sigma_impl(sqd_ctx* ctx, sqd_space* sp, const double* c, double* sigma, 
     const int norb = sp->norb;
     if (ab_path == SQD_AB_AUTO) ab_path = sqd_sigma_auto_path(ctx, sp, precision);
     const double* diag = (mask & SQD_TERM_DIAG) ? sp->diag : nullptr;
-    const fused_shape fused = fused_pick(ctx, sp, precision == SQD_FP64 ? 8 : 4, mask, ab_path);
+    const fused_shape fused = fused_pick(ctx, sp, precision == SQD_FP64 ? 8 : 4, mask, ab_path, any_order);
     // the windowed same-spin kernel, where the dispatch takes it; without an
     // allocation only on tables that exist
     auto win = [&](int spin) {
@@ -925,7 +933,8 @@ int sqd_sigma_impl(sqd_ctx* ctx, sqd_space* sp, const double* c, double* sigma, 
     // FP32 off-diagonal terms
     void* scr = nullptr;
     const size_t ybytes = (!(mask & SQD_TERM_AB) || ext_scratch) ? 0
-                          : (ab_path == SQD_AB_KH ? sqd_kh_bytes(sp, 4) : ab_grouped_bytes(ctx, sp, 4));
+                          : (ab_path == SQD_AB_KH ? sqd_kh_bytes(sp, 4)
+                                                  : ab_grouped_bytes(ctx, sp, 4, any_order && fused.R));
     if ((rc = scratch_get(sizeof(float) * 4 * (dim + 64) + ybytes, &scr))) return rc;
     float* C32 = (float*)scr;
     float* Ct32 = C32 + dim + 64;
@@ -939,7 +948,8 @@ int sqd_sigma_impl(sqd_ctx* ctx, sqd_space* sp, const double* c, double* sigma, 
     }
     if (fused.R && ybytes) {
         sp->fused_terms[1] |= mask;
-        return launch_fused<float>(ctx, sp, fused, Cin, S32, Ct32, Yab, ctx->jk32, ctx->eri32, diag, c, sigma, skip);
+        return launch_fused<float>(ctx, sp, fused, Cin, S32, Ct32, Yab, ctx->jk32, ctx->eri32, diag, c, sigma, skip,
+                                   any_order);
     }
     bool written = false;
     if (mask & SQD_TERM_BB) {

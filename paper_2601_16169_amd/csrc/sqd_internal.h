@@ -162,6 +162,10 @@ struct spin_tables {
     // (FP64 products)
     sell_table<float> ss32;
     sell_table<double> ss64;
+    // ss64's layout with FP32 values, for the solvers' FP32 phases, whose sums
+    // may be taken in any order (sqd_ensure_split32; its other arrays are ss64's)
+    sell_table<float> split32;
+    int split32_version = -1;
     // sliced singles for the alpha-beta kernels, rows sorted by their count:
     // whole rows (FP32), long rows over several lanes (FP64)
     ab_table ab32, ab64;
@@ -277,13 +281,15 @@ int sqd_build_spin_tables(sqd_ctx* ctx, sqd_space* sp, int spin, const uint64_t*
 int sqd_host_singles(sqd_ctx* ctx, spin_tables& t);   // fills t.s_pk_host (synchronous)
 int sqd_alloc_cross_tables(sqd_ctx* ctx, sqd_space* sp);   // spin_tables::ws64, ws32 (both spins built)
 int sqd_build_values(sqd_ctx* ctx, sqd_space* sp);   // integral-dependent parts
+int sqd_ensure_split32(sqd_ctx* ctx, sqd_space* sp);   // spin_tables::split32 of both spins, current values
 void sqd_free_spin_tables(spin_tables* t);
 
 // ---- sigma.hip ----
 int sqd_ensure_diag(sqd_ctx* ctx, sqd_space* sp);
 int sqd_sigma_impl(sqd_ctx* ctx, sqd_space* sp, const double* c, double* sigma,
                    int precision, unsigned mask, int ab_path, const float* c32_in,
-                   const int* skip_flag, void* ext_scratch = nullptr, size_t ext_bytes = 0);
+                   const int* skip_flag, void* ext_scratch = nullptr, size_t ext_bytes = 0,
+                   bool any_order = false);   // FP32 sums in any order (solvers)
 int sqd_sigma_auto_path(sqd_ctx* ctx, const sqd_space* sp, int precision);
 bool sqd_sigma_prepared(sqd_ctx* ctx, const sqd_space* sp, int precision, unsigned mask, int ab_path);
 int sqd_ensure_ab_groups(sqd_ctx* ctx, sqd_space* sp, int G);

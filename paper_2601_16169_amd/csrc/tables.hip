@@ -663,6 +663,30 @@ int sqd_build_spin_tables(sqd_ctx* ctx, sqd_space* sp, int spin, const uint64_t*
     return SQD_OK;
 }
 
+int sqd_ensure_split32(sqd_ctx* ctx, sqd_space* sp) {
+    int rc = sqd_build_values(ctx, sp);
+    if (rc) return rc;
+    for (int spin = 0; spin < 2; ++spin) {
+        spin_tables& t = sp->sp[spin];
+        if (t.alias) {
+            t.split32 = sp->sp[0].split32;
+            continue;
+        }
+        if (t.split32_version == ctx->ham_version) continue;
+        sell_table<float>& L = t.split32;
+        const sell_table<double>& D = t.ss64;
+        if (!L.val && (rc = sqd_alloc(ctx, (void**)&L.val, sizeof(float) * (D.slots + 256), &sp->bytes))) return rc;
+        L.nslices = D.nslices;
+        L.perm = D.perm, L.split = D.split, L.blk = D.blk, L.s_blk = D.s_blk, L.bin = D.bin;
+        L.slots = D.slots;
+        L.ent = D.ent, L.csr = D.csr;
+        sell_values(ctx, L, t.s_val32, t.d_val32);
+        SQD_HIP(ctx, hipGetLastError());
+        t.split32_version = ctx->ham_version;
+    }
+    return SQD_OK;
+}
+
 int sqd_host_singles(sqd_ctx* ctx, spin_tables& t) {
     if ((int64_t)t.s_pk_host.size() == t.nnz_s) return SQD_OK;
     std::vector<uint32_t> pk(t.nnz_s);
@@ -733,7 +757,7 @@ void sqd_free_spin_tables(spin_tables* t) {
     sqd_free_window_tables(t);
     free_sell(t->ss32);
     free_sell(t->ss64);
-    void* ptrs[] = {t->str, t->s_off, t->s_ent, t->d_off, t->d_ent, t->s_pk, t->d_nbr, t->s_val64, t->s_val32,
+    void* ptrs[] = {t->split32.val, t->str, t->s_off, t->s_ent, t->d_off, t->d_ent, t->s_pk, t->d_nbr, t->s_val64, t->s_val32,
                     t->d_val64, t->d_val32, t->e_same, t->sell_index, t->ab32.ent, t->ab64.ent, t->ws64, t->ws32};
     for (void* p : ptrs)
         if (p) hipFree(p);
