@@ -246,6 +246,8 @@ struct sqd_space {
     int64_t h_bytes = 0;
     int h_version = -1;
     int64_t h_xcd_rows[9] = {};   // row ranges of equal element counts, one per XCD
+    int2* h_units = nullptr;      // work units of the staged product (none: rows from the L2)
+    int h_nunits = 0, h_step = 0, h_cap = 0, h_list = 0;   // the rows of a unit, the values and list entries it stages
     // alpha-beta part of the 2-RDM (rdm.hip; built by the first call): one
     // allocation with the beta pair table, the alpha pairs and their chunks
     void* rdm_mem = nullptr;

@@ -15,8 +15,9 @@
 // matrix-free kernels: same-spin singles add the cross-spin term
 // sum_{k in other string} (pq|kk), alpha-beta pairs are s_a s_b (ai|bj).
 //
-// The product y = H x streams 12 bytes per stored element (int32 column and
-// FP64 value) from HBM: a plain bandwidth-bound kernel, one wavefront per row.
+// The product y = H x streams the values from HBM with the parts of x that a
+// block of rows reads staged in the LDS (k_spmv_staged), or, for few, short or
+// very long rows, values and columns with a wavefront per row (k_spmv).
 #include <algorithm>
 
 #include "sqd_internal.h"
@@ -165,6 +166,184 @@ __global__ void __launch_bounds__(256) k_spmv(const int64_t* __restrict__ rp, co
     }
 }
 
+// The same product with the parts of x that a block of rows reads staged in the
+// LDS.  What bounds k_spmv is the gathers from x: 64-byte requests to the L2 for
+// eight bytes each (1001 x 903 strings, 3.1e8 elements: 1.61 ms; keeping twice the
+// matrix stream in flight changed it by 2%).  The columns of a row follow from
+// the lists of its two strings, in the order in which the row was filled, so a
+// workgroup takes kSpmvRows rows (ia, ib0 ..), stages for the alpha part the kSpmvRows
+// values of each neighbour of ia, for the beta part the row ia of x and for the
+// alpha-beta part the rows of the alpha singles, as many at a time as fit, and
+// streams the values alone (8 bytes an element): 0.87 ms.  A wavefront holds the
+// sums of its eight rows, a lane taking every 64th element.
+constexpr int kSpmvWaves = 16, kSpmvPer = 8;
+constexpr int kSpmvRows = kSpmvWaves * kSpmvPer;
+constexpr int kSpmvCap = 64 * (kSpmvRows + 1);   // values of x staged at a time
+
+struct staged_args {
+    int64_t nb;
+    const int *as_off, *ad_off, *ad_nbr, *bs_off, *bd_off, *bd_nbr;
+    const uint32_t *as_pk, *bs_pk;
+    const int64_t* rp;
+    const double* val;
+    const double* x;
+    double* y;
+    const int2* units;   // (ia, ib0); ia < 0: none
+    int cap, step;       // values staged at a time; rows of a unit
+};
+
+// v[0..N) summed over the lanes: lane l returns the sum of value l >> (6 - log2 N)
+// (the exchanges halve the values)
+template <int N, int MASK>
+__device__ __forceinline__ double lane_sums(const double (&v)[N], int lane) {
+    if constexpr (N > 1) {
+        double h[N / 2];
+        const bool up = (lane & MASK) != 0;
+#pragma unroll
+        for (int j = 0; j < N / 2; ++j) h[j] = (up ? v[j + N / 2] : v[j]) + __shfl_xor(up ? v[j] : v[j + N / 2], MASK);
+        return lane_sums<N / 2, MASK / 2>(h, lane);
+    } else {
+        double s = v[0];
+#pragma unroll
+        for (int m = MASK; m > 0; m >>= 1) s += __shfl_xor(s, m);
+        return s;
+    }
+}
+
+__global__ void __launch_bounds__(64 * kSpmvWaves, 8) k_spmv_staged(staged_args a, const int* __restrict__ skip) {
+    if (skip && *skip) return;
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const int2 unit = a.units[blockIdx.x];
+    if (unit.x < 0) return;
+    double* xs = reinterpret_cast<double*>(lds_raw);
+    int* list = reinterpret_cast<int*>(xs + a.cap);   // beta singles of the rows, as neighbours
+    const int64_t nb = a.nb, ia = unit.x;
+    const int ib0 = unit.y, rows = (int)min((int64_t)a.step, nb - ib0);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int sa0 = a.as_off[ia], nsa = a.as_off[ia + 1] - sa0;
+    const int da0 = a.ad_off[ia], nA = nsa + a.ad_off[ia + 1] - da0;
+    const int list0 = a.bs_off[ib0], nlist = a.bs_off[ib0 + rows] - list0;
+    for (int q = threadIdx.x; q < nlist; q += 64 * kSpmvWaves) list[q] = (int)(a.bs_pk[list0 + q] & SQD_NBR_MASK);
+    // the wavefront's rows (those past the end repeat the last and are not stored)
+    const int each = (rows + kSpmvWaves - 1) / kSpmvWaves;
+    const int r0 = wave * each, mine = max(0, min(each, rows - r0));
+    double acc[kSpmvPer];
+    // lane j holds what the walks need of row j (read from lanes: scalars for every
+    // row would not stay in registers): its next value, from val; the first of its
+    // beta singles in list, and their number; its number of beta entries, and the
+    // first double less the singles
+    const int64_t first = ia * nb + ib0 + min(r0, rows - 1);
+    const double* val = a.val + a.rp[first];
+    const int mr = min(r0 + (lane & (kSpmvPer - 1)), rows - 1);
+    const int at_v = (int)(a.rp[ia * nb + ib0 + mr] - a.rp[first]);
+    const int sb_v = a.bs_off[ib0 + mr] - list0, nsb_v = a.bs_off[ib0 + mr + 1] - list0 - sb_v;
+    const int db_v = a.bd_off[ib0 + mr] - nsb_v, nB_v = a.bd_off[ib0 + mr + 1] - db_v;
+    auto of = [](int v, int j) { return __builtin_amdgcn_readlane(v, j); };
+    {
+        const double t = lane < mine ? val[at_v] * a.x[ia * nb + ib0 + mr] : 0.0;   // the diagonal
+#pragma unroll
+        for (int j = 0; j < kSpmvPer; ++j) acc[j] = lane == j ? t : 0.0;
+    }
+    // alpha part: 64 neighbours at a time, neighbour e of row q at e * (kSpmvRows + 1) + q
+    for (int e0 = 0; e0 < nA; e0 += 64) {
+        const int ne = min(64, nA - e0);
+        double v[kSpmvPer];
+#pragma unroll
+        for (int j = 0; j < kSpmvPer; ++j)
+            v[j] = (lane < ne && j < mine) ? __builtin_nontemporal_load(val + of(at_v, j) + 1 + e0 + lane) : 0.0;
+        __syncthreads();
+        for (int e = wave; e < ne; e += kSpmvWaves) {
+            const int p = e0 + e;
+            const int64_t src = p < nsa ? (int64_t)(a.as_pk[sa0 + p] & SQD_NBR_MASK) : (int64_t)a.ad_nbr[da0 + p - nsa];
+            const double* xr = a.x + src * nb + ib0;
+#pragma unroll
+            for (int u = 0; u < kSpmvRows / 64; ++u)
+                if (lane + 64 * u < rows) xs[e * (kSpmvRows + 1) + lane + 64 * u] = xr[lane + 64 * u];
+        }
+        __syncthreads();
+        if (lane < ne) {
+#pragma unroll
+            for (int j = 0; j < kSpmvPer; ++j)
+                if (j < mine) acc[j] += v[j] * xs[lane * (kSpmvRows + 1) + r0 + j];
+        }
+    }
+    // beta part: row ia of x; then alpha-beta part: the rows of the alpha singles.
+    // The first values of four rows at a time load ahead of their use.
+    constexpr int kH = kSpmvPer / 2;
+    __syncthreads();
+    for (int64_t q = threadIdx.x; q < nb; q += 64 * kSpmvWaves) xs[q] = a.x[ia * nb + q];
+    __syncthreads();
+    const double* bval = val + 1 + nA;
+#pragma unroll
+    for (int h = 0; h < kSpmvPer; h += kH) {
+        int most = 0;
+#pragma unroll
+        for (int j = 0; j < kH; ++j)
+            if (h + j < mine) most = max(most, of(nB_v, h + j));
+        for (int k = lane; k < most; k += 64) {
+            double v[kH];
+            int c[kH];
+#pragma unroll
+            for (int j = 0; j < kH; ++j) {
+                const bool in = k < of(nB_v, h + j) && h + j < mine;
+                v[j] = in ? __builtin_nontemporal_load(bval + of(at_v, h + j) + k) : 0.0;
+                c[j] = (in && k >= of(nsb_v, h + j)) ? a.bd_nbr[of(db_v, h + j) + k] : -1;
+            }
+#pragma unroll
+            for (int j = 0; j < kH; ++j)
+                if (k < of(nB_v, h + j) && h + j < mine) acc[h + j] += v[j] * xs[c[j] < 0 ? list[of(sb_v, h + j) + k] : c[j]];
+        }
+    }
+    const int ab_v = at_v + nB_v;
+    const int per = (int)(a.cap / nb);
+    for (int ka0 = 0; ka0 < nsa; ka0 += per) {
+        const int nka = min(per, nsa - ka0);
+        __syncthreads();
+        for (int e = 0; e < nka; ++e) {
+            const double* xr = a.x + (int64_t)(a.as_pk[sa0 + ka0 + e] & SQD_NBR_MASK) * nb;
+            for (int q = threadIdx.x; q < (int)nb; q += 64 * kSpmvWaves) xs[e * (int)nb + q] = xr[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < kSpmvPer; h += kH) {
+            // the first 128 values of four rows in flight, then the rest of long rows
+            // 256 at a time
+            double v[kH][2];
+#pragma unroll
+            for (int j = 0; j < kH; ++j)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int k = 64 * u + lane, n = of(nsb_v, h + j);
+                    v[j][u] = (k < nka * n && h + j < mine)
+                                  ? __builtin_nontemporal_load(bval + of(ab_v, h + j) + (ka0 * n + k)) : 0.0;
+                }
+#pragma unroll
+            for (int j = 0; j < kH; ++j) {
+                const int n = of(nsb_v, h + j), len = h + j < mine ? nka * n : 0;
+                const int* l = list + of(sb_v, h + j);
+                const float inv = 1.0f / (float)max(n, 1);
+                auto use = [&](double y, int k) {   // (k below 2^22: exact)
+                    const int ka = (int)(((float)k + 0.5f) * inv), kb = k - ka * n;
+                    if (k < len) acc[h + j] += y * xs[ka * (int)nb + l[kb]];
+                };
+#pragma unroll
+                for (int u = 0; u < 2; ++u) use(v[j][u], 64 * u + lane);
+                const double* row = bval + of(ab_v, h + j) + ka0 * n;
+                for (int k0 = 128 + lane; k0 < len; k0 += 256) {
+                    double w[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) w[u] = k0 + 64 * u < len ? __builtin_nontemporal_load(row + k0 + 64 * u) : 0.0;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) use(w[u], k0 + 64 * u);
+                }
+            }
+        }
+    }
+    const double s = lane_sums<kSpmvPer, 32>(acc, lane);
+    const int j = lane >> 3;
+    if ((lane & 7) == 0 && j < mine) a.y[ia * nb + ib0 + r0 + j] = s;
+}
+
 unsigned fill_grid(int64_t rows) {
     const int64_t b = (rows + kRowsPerBlock - 1) / kRowsPerBlock;
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(b, 1 << 16));
@@ -173,16 +352,68 @@ unsigned fill_grid(int64_t rows) {
 }  // namespace
 
 void sqd_release_stored_h(sqd_space* sp) {
-    void* ptrs[] = {sp->h_rowptr, sp->h_col, sp->h_val};
+    void* ptrs[] = {sp->h_rowptr, sp->h_col, sp->h_val, sp->h_units};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     sp->bytes -= sp->h_bytes;
     sp->h_rowptr = nullptr;
     sp->h_col = nullptr;
     sp->h_val = nullptr;
+    sp->h_units = nullptr;
+    sp->h_nunits = sp->h_list = 0;
     sp->h_nnz = 0;
     sp->h_bytes = 0;
     sp->h_version = -1;
+}
+
+// Units of the staged product, or none where it is not taken: a row of x and the
+// lists have to fit the LDS, two units are wanted for every compute unit, a unit
+// of few rows leaves most of its lanes without work, and each staged value has to
+// serve at least one element.  Measured on MI355X, us, rows from the L2 / staged:
+// 252 x 252 strings 212 / 93, 400 x 300: 226 / 119, 2000 x 64: 156 / 105, 2000 x
+// 130: 276 / 195, 20 x 5000: 124 / 86, 1500 x 700: 1752 / 879, 1500 x 1500: 3640 /
+// 1940; not taken: 128 x 128 (128 units) 8 / 15, 3 x 12000 (282 units) 101 / 136,
+// 5000 x 20 (20 rows) 208 / 296, 300 x 3000 (1.4 staged for an element) 1308 / 1392.
+static int plan_staged(sqd_ctx* ctx, sqd_space* sp, const std::vector<int>& as, const std::vector<int>& ad,
+                       const std::vector<int>& bs, const std::vector<int64_t>& PB, int64_t nnz) {
+    const int64_t na = sp->sp[0].n, nb = sp->sp[1].n, nblk = (nb + kSpmvRows - 1) / kSpmvRows, step = (nb + nblk - 1) / nblk;
+    int most = 0;
+    for (int64_t b = 0; b < nb; b += step) most = std::max(most, bs[std::min(nb, b + step)] - bs[b]);
+    const size_t cap = (size_t)std::max<int64_t>(kSpmvCap, nb);
+    if (cap * 8 + (size_t)most * 4 > (size_t)ctx->max_lds) return SQD_OK;
+    const int64_t per_string = (nb + step - 1) / step;   // units of an alpha string
+    const int64_t staged = per_string * nb * (as[na] + na) + nb * (as[na] + ad[na]);
+    if (na * per_string < 2 * ctx->num_cu || step < 32 || staged > nnz) return SQD_OK;
+    // units of one alpha string on one XCD (they stage the same rows of x), the
+    // strings dealt by their elements, heaviest first
+    std::vector<std::pair<int64_t, int>> order(na);
+    for (int64_t i = 0; i < na; ++i) {
+        const int64_t sa = as[i + 1] - as[i], nA = sa + ad[i + 1] - ad[i];
+        order[i] = {-(nb * (1 + nA) + PB[nb] + sa * bs[nb]), (int)i};
+    }
+    std::sort(order.begin(), order.end());
+    std::vector<int2> per[8];
+    int64_t load[8] = {};
+    for (const auto& o : order) {
+        const int q = (int)(std::min_element(load, load + 8) - load);
+        load[q] -= o.first;
+        for (int64_t b = 0; b < nb; b += step) per[q].push_back(make_int2(o.second, (int)b));
+    }
+    size_t longest = 0;
+    for (const auto& p : per) longest = std::max(longest, p.size());
+    std::vector<int2> units(longest * 8, make_int2(-1, 0));
+    for (int q = 0; q < 8; ++q)
+        for (size_t k = 0; k < per[q].size(); ++k) units[8 * k + q] = per[q][k];
+    int rc;
+    if ((rc = sqd_alloc(ctx, (void**)&sp->h_units, sizeof(int2) * (units.size() + 1), nullptr))) return rc;
+    sp->h_bytes += (int64_t)(sizeof(int2) * (units.size() + 1));
+    sp->bytes += (int64_t)(sizeof(int2) * (units.size() + 1));
+    SQD_HIP(ctx, hipMemcpy(sp->h_units, units.data(), sizeof(int2) * units.size(), hipMemcpyHostToDevice));
+    sp->h_nunits = (int)units.size();
+    sp->h_list = most;
+    sp->h_cap = (int)cap;
+    sp->h_step = (int)step;
+    return SQD_OK;
 }
 
 int sqd_store_h_impl(sqd_ctx* ctx, sqd_space* sp, int64_t* nnz_out) {
@@ -273,6 +504,10 @@ int sqd_store_h_impl(sqd_ctx* ctx, sqd_space* sp, int64_t* nnz_out) {
         }
         sp->h_xcd_rows[q] = lo;
     }
+    if ((rc = plan_staged(ctx, sp, as, ad, bs, PB, nnz))) {
+        sqd_release_stored_h(sp);
+        return rc;
+    }
     sp->h_version = ctx->ham_version;
     if (nnz_out) *nnz_out = nnz;
     return SQD_OK;
@@ -282,6 +517,18 @@ int sqd_spmv_impl(sqd_ctx* ctx, sqd_space* sp, const double* x, double* y, const
     if (!sp->h_val || sp->h_version != ctx->ham_version)
         return sqd_fail(ctx, SQD_E_STATE, "no current stored H on this space (call sqd_store_hamiltonian)");
     prof_scope ps(ctx, "k_spmv");
+    if (sp->h_nunits) {
+        const spin_tables& A = sp->sp[0];
+        const spin_tables& B = sp->sp[1];
+        const size_t lds = (size_t)sp->h_cap * sizeof(double) + (size_t)sp->h_list * sizeof(int);
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_spmv_staged),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        staged_args a{B.n, A.s_off, A.d_off, A.d_nbr, B.s_off, B.d_off, B.d_nbr, A.s_pk, B.s_pk,
+                      sp->h_rowptr, sp->h_val, x, y, sp->h_units, sp->h_cap, sp->h_step};
+        hipLaunchKernelGGL(k_spmv_staged, dim3(sp->h_nunits), dim3(64 * kSpmvWaves), lds, ctx->stream, a, skip);
+        SQD_HIP(ctx, hipGetLastError());
+        return SQD_OK;
+    }
     // eight workgroups of four rows per CU, a multiple of the 8 XCDs
     const int64_t want = std::max<int64_t>(1, (sp->dim + kRowsPerBlock - 1) / kRowsPerBlock);
     const unsigned grid = (unsigned)(8 * std::max<int64_t>(1, std::min<int64_t>(ctx->num_cu, (want + 7) / 8)));
