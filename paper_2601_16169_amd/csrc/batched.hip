@@ -63,12 +63,17 @@ struct bdesc {
     ss_args<float> bb32, aa32;
     abg_args<double> ab64;
     abg_args<float> ab32;
+    abb_args<double> abb64;
+    abb_args<float> abb32;
 };
 
 __device__ __forceinline__ const ss_args<double>& ssa(const bdesc& d, int which, double) { return which ? d.aa64 : d.bb64; }
 __device__ __forceinline__ const ss_args<float>& ssa(const bdesc& d, int which, float) { return which ? d.aa32 : d.bb32; }
 __device__ __forceinline__ const abg_args<double>& aba(const bdesc& d, double) { return d.ab64; }
 __device__ __forceinline__ const abg_args<float>& aba(const bdesc& d, float) { return d.ab32; }
+
+__device__ __forceinline__ const abb_args<double>& abb(const bdesc& d, double) { return d.abb64; }
+__device__ __forceinline__ const abb_args<float>& abb(const bdesc& d, float) { return d.abb32; }
 
 __global__ void kb_reset(int* counters, int n) {
     if (threadIdx.x < n) counters[threadIdx.x] = 0;
@@ -116,7 +121,7 @@ __global__ void __launch_bounds__(1024) kb_terms(const bdesc* __restrict__ D, co
     const bdesc& d = D[u.x];
     if (d.st->done) return;
     const int kind = u.y >> kUnitShift, k = u.y & ((1 << kUnitShift) - 1);
-    if (kind == 2) abg_block<T, R>(aba(d, T()), V, norb, k, lds_raw);
+    if (kind == 2) abb_block<T, R>(abb(d, T()), V, norb, k, lds_raw);
     else ss_block<T, R>(ssa(d, kind, T()), jk, norb, k, lds_raw);
 }
 
@@ -189,7 +194,7 @@ __global__ void __launch_bounds__(256) kb_gather(const bdesc* __restrict__ D, co
         const T* Y = (const T*)(sizeof(T) == 8 ? (const void*)d.Y64 : (const void*)d.Y32);
         T* S = (T*)(sizeof(T) == 8 ? (void*)d.sout : (void*)d.S32);
         const T* S2 = (const T*)(sizeof(T) == 8 ? (const void*)d.Yt : (const void*)d.Yt32);
-        const ab_table& tab = aba(d, T()).tab;
+        const ab_table& tab = ALL ? abb(d, T()).tab : aba(d, T()).tab;
         gather_args<T> a{Y, d.nb, tab.nslots, tab.perm, d.a_off, S, nullptr, nullptr, nullptr, nullptr};
         if (ALL) a.S2 = S2, a.diag = d.diag, a.c = d.cin, a.out64 = d.sout;
         gather_row<T>(a, d.a_order[units[u].y], STAGED ? d.ng : 1, row);
@@ -767,7 +772,7 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
         for (int k = 0; k < 3; ++k) c[k].R = k < 2 ? 4 : 2;
         for (int b = 0; b < nspace && one; ++b) {
             const size_t cols = (size_t)std::max(spaces[b]->sp[0].n, spaces[b]->sp[1].n) + 1;
-            auto bytes = [&](int R) { return std::max((cols + n2) * R, ((size_t)spaces[b]->sp[1].n + 1) * R + n2) * 8; };
+            auto bytes = [&](int R) { return std::max((cols + n2) * R, ((size_t)spaces[b]->sp[1].n + 1) * R + 2 * n2) * 8; };
             int k = 0;
             while (k < 3 && bytes(c[k].R) > bound[k]) ++k;
             if (k == 3) one = false;
@@ -841,7 +846,7 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
         const spin_tables& A = sp->sp[0];
         const spin_tables& B = sp->sp[1];
         if (one) {
-            rc = sqd_ensure_ab_groups(ctx, sp, p.classes[cls[b]].R);
+            rc = sqd_ensure_ab_blocks(ctx, sp, p.classes[cls[b]].R);
             if (!rc && mixed) rc = sqd_ensure_split32(ctx, sp);
         }
         else if (cls2[b]) rc = sqd_ensure_ab_groups(ctx, sp, p.G2);
@@ -889,7 +894,7 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
             auto add = [&](int kind, int64_t count) {
                 for (int64_t k = 0; k < count; ++k) c.list.push_back(make_int2(b, (int)((kind << kUnitShift) | k)));
             };
-            add(2, spaces[b]->ab_nchunks);
+            add(2, spaces[b]->abb_nchunks);
             add(0, (d.na + c.R - 1) / c.R);
             add(1, (d.nb + c.R - 1) / c.R);
             continue;
@@ -950,8 +955,8 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
             d.bb64 = ss_args<double>{d.cin, d.sout, A.n, B.n, B.ss64, A.ws64, A.str, A.nw, nullptr, 0, 0};
             d.aa32 = ss_args<float>{d.c32, d.Yt32, B.n, A.n, A.split32, B.ws32, B.str, B.nw, nullptr, 0, 1};
             d.bb32 = ss_args<float>{d.c32, d.S32, A.n, B.n, B.split32, A.ws32, A.str, A.nw, nullptr, 0, 0};
-            d.ab64 = abg_args<double>{d.cin, d.Y64, B.n, sp->ab_grp, sp->ab_chunk_pair, B.ab64};
-            d.ab32 = abg_args<float>{d.c32, d.Y32, B.n, sp->ab_grp, sp->ab_chunk_pair, B.ab64};
+            d.abb64 = abb_args<double>{d.cin, d.Y64, B.n, sp->abb_grp, sp->abb_pair, B.ab64};
+            d.abb32 = abb_args<float>{d.c32, d.Y32, B.n, sp->abb_grp, sp->abb_pair, B.ab64};
             // as many groups of threads of the gather as read a row of Y side by side
             const int per = (int)((B.ab64.nslots / 2 + 63) / 64 * 64);
             d.ng = p.gather_lds64 ? std::max(1, std::min(kGatherThreads / std::max(per, 64), 4)) : 1;

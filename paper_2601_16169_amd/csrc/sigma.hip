@@ -20,6 +20,7 @@
 //         lane reads all KC values of a column with wide loads), lanes own
 //         beta targets and accumulate in registers across all alpha sources.
 #include "sigma_body.h"
+#include "slices.h"
 
 namespace {
 
@@ -230,14 +231,14 @@ k_ab_srcgrouped(abg_args<T> a, const int* __restrict__ chunk_src, const T* __res
 // write buffers of their own and run together; the gather adds them.
 template <typename T, int R, int G>
 __global__ void __launch_bounds__(1024)
-k_sigma_terms(ss_args<T> bb, ss_args<T> aa, abg_args<T> ab, int n_bb, int n_aa, const T* __restrict__ jk,
+k_sigma_terms(ss_args<T> bb, ss_args<T> aa, abb_args<T> ab, int n_bb, int n_aa, const T* __restrict__ jk,
               const T* __restrict__ V, int norb, const int* __restrict__ skip) {
     if (skip && *skip) return;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int k = blockIdx.x;
     if (k < n_bb) ss_block<T, R>(bb, jk, norb, k, lds_raw);
     else if (k < n_bb + n_aa) ss_block<T, R>(aa, jk, norb, k - n_bb, lds_raw);
-    else abg_block<T, G>(ab, V, norb, k - n_bb - n_aa, lds_raw);
+    else abb_block<T, G>(ab, V, norb, k - n_bb - n_aa, lds_raw);
 }
 
 // Rows of sigma from Y (gather_row), heaviest first; STAGED: assembled in LDS.
@@ -495,6 +496,32 @@ int ensure_ab_groups_impl(sqd_ctx* ctx, sqd_space* sp, int G) {
     return SQD_OK;
 }
 
+}  // namespace
+
+int sqd_ensure_ab_blocks(sqd_ctx* ctx, sqd_space* sp, int G) {
+    if (sp->abb_G == G && sp->abb_grp) return SQD_OK;
+    if (G <= 0) return sqd_fail(ctx, SQD_E_LIMIT, "alpha-beta block does not fit in LDS");
+    spin_tables& A = sp->sp[0];
+    int rc;
+    if ((rc = sqd_host_singles(ctx, A))) return rc;
+    std::vector<int2> grp, pairs;
+    plan_ab_blocks(A.s_pk_host, A.n, sp->norb, G, grp, pairs);
+    if (sp->abb_grp) { (void)hipFree(sp->abb_grp); sp->abb_grp = nullptr; }
+    if (sp->abb_pair) { (void)hipFree(sp->abb_pair); sp->abb_pair = nullptr; }
+    if ((rc = ensure_ab_row_order(ctx, sp))) return rc;
+    if ((rc = sqd_alloc(ctx, (void**)&sp->abb_grp, sizeof(int2) * (grp.size() + 1), &sp->bytes))) return rc;
+    if ((rc = sqd_alloc(ctx, (void**)&sp->abb_pair, sizeof(int2) * (pairs.size() + 1), &sp->bytes))) return rc;
+    if (!grp.empty()) {
+        SQD_HIP(ctx, hipMemcpy(sp->abb_grp, grp.data(), sizeof(int2) * grp.size(), hipMemcpyHostToDevice));
+        SQD_HIP(ctx, hipMemcpy(sp->abb_pair, pairs.data(), sizeof(int2) * pairs.size(), hipMemcpyHostToDevice));
+    }
+    sp->abb_G = G;
+    sp->abb_nchunks = (int)pairs.size();
+    return SQD_OK;
+}
+
+namespace {
+
 // Singles per chunk of the source-grouped kernel: the most (ai|..) rows that
 // fit in LDS beside one FP64 source row (0: fewer than two).
 int ab_source_group_size(sqd_ctx* ctx, const sqd_space* sp) {
@@ -599,21 +626,23 @@ struct fused_shape { int R = 0, G = 0, waves = 0; size_t lds = 0; };
 // Separate launches leave the chip half empty at the end of each (a term of
 // sigma on 1200 strings per spin has 300 row blocks for 256 compute units) and
 // cost a launch and its latency each, and the alpha-alpha term two transposes.
-// Measured on MI355X, whole sigma, us, before / now with n strings per spin
-// (norb 8 to 36): FP64 n = 70: 39 / 11, 1237 x 731: 229 / 109, 1900: 443 / 403,
-// 2600: 965 / 785, 3600: 1870 / 1504 (four rows and singles per workgroup, with
-// eight waves while two workgroups fit a compute unit, else sixteen: 1500: 254
-// against 273, 2600: 826 against 785); 4300: 3704 / 2712, 5500: 6097 / 4478,
-// 8800: 14836 / 12844 (two rows; the windowed kernel before).  FP32, whose
-// rows are half as long: n = 1500: 218 / 149, 2000: 423 / 389, 3600: 1463 /
-// 1093, 4300: 2413 / 2171 with four rows, eight waves while four workgroups fit
-// (2000: 391 against 419; 2600: 540 against 508); beyond 100 KiB the separate
-// launches win (5500: 3523 against 3486, 5500 x 300: 348 against 595, 7000:
-// 5443 against 6775 with two rows).  FP32 sums in any order (the solvers' FP32
-// phases) take the FP64 products' tables, long rows over several lanes, and are
-// faster in one launch as far as four rows fit: n = 600 x 500: 49 / 45, 2000: 315
-// / 296, 3000: 767 / 677, 4200: 2180 / 1472, 5500: 3826 / 2601 (rows as above /
-// over several lanes; eight rows 49, 307, 726, 2310, 3830).
+// Measured on MI355X, whole sigma, us, separate launches / one with n strings per
+// spin (norb 8 to 36; pairs of four-row workgroups of eight waves while two fit a
+// compute unit, else sixteen waves): FP64 n = 70: 39 / 11, 1237 x 731: 229 / 105,
+// 2000: 747 / 653, 3000 x 300: 490 / 218, 4000 x 2000: 1648 / 1428, 4500 x 4000:
+// 3815 / 3012; with two rows 6000 x 5500: 6757 / 5791, 9000 x 2000: 4305 / 3053
+// (the windowed kernel before).  FP32, whose rows are half as long, with eight
+// waves while four workgroups fit: 1237 x 731: 150 / 90, 2000: 467 / 389, 3000 x
+// 300: 322 / 218, 4000 x 3000: 1501 / 1031, 4500 x 4000: 2454 / 2104, 5500: 3796 / 3269, 8800: 9726 / 7999;
+// but a few beta strings' rows of many alpha strings leave most of the chip idle
+// while the longest of them, a lane each, are walked: 4000 x 400: 296 / 521, 4000
+// x 1000: 455 / 825, 4000 x 2000: 909 / 1210, 5000 x 1200: 794 / 1169, 6000 x
+// 4000: 2786 / 2814, so those take the one launch only while their rows are short
+// (2000 x 1000: 229 / 216, 3000 x 1000: 395 / 411).  FP32 sums in any order (the
+// solvers' FP32 phases) take the FP64 products' tables, long rows over several
+// lanes, and are faster in one launch as far as four rows fit: n = 600 x 500: 49 /
+// 45, 2000: 315 / 296, 3000: 767 / 677, 4200: 2180 / 1472, 5500: 3826 / 2601 (rows
+// as above / over several lanes; eight rows 49, 307, 726, 2310, 3830).
 fused_shape fused_pick(sqd_ctx* ctx, const sqd_space* sp, size_t es, unsigned mask, int ab_path,
                        bool any_order = false) {
     fused_shape f;
@@ -624,8 +653,9 @@ fused_shape fused_pick(sqd_ctx* ctx, const sqd_space* sp, size_t es, unsigned ma
         if (ctx->tune[key]) return f;   // a kernel chosen by the caller
     const size_t n2 = (size_t)sp->norb * sp->norb, lim = (size_t)ctx->max_lds;
     const size_t cols = (size_t)std::max(sp->sp[0].n, sp->sp[1].n) + 1;
-    auto bytes = [&](int k) { return std::max((cols + n2) * k, ((size_t)sp->sp[1].n + 1) * k + n2) * es; };
-    if (bytes(4) <= (es == sizeof(double) || any_order ? lim : lim * 5 / 8)) f.R = 4;
+    auto bytes = [&](int k) { return std::max((cols + n2) * k, ((size_t)sp->sp[1].n + 1) * k + 2 * n2) * es; };
+    const size_t whole = 2 * sp->sp[0].n <= 3 * sp->sp[1].n ? lim : lim * 3 / 8;   // FP32, whole rows
+    if (bytes(4) <= (es == sizeof(double) || any_order ? lim : whole)) f.R = 4;
     else if (es == sizeof(double) && bytes(2) <= lim) f.R = 2;
     f.G = f.R;
     f.lds = f.R ? bytes(f.R) : 0;
@@ -640,16 +670,16 @@ int launch_fused(sqd_ctx* ctx, sqd_space* sp, const fused_shape& f, const T* C, 
     const spin_tables& A = sp->sp[0];
     const spin_tables& B = sp->sp[1];
     int rc;
-    if ((rc = ensure_ab_groups_impl(ctx, sp, f.G))) return rc;
+    if ((rc = sqd_ensure_ab_blocks(ctx, sp, f.G))) return rc;
     if (any_order && (rc = sqd_ensure_split32(ctx, sp))) return rc;
     const ab_table& tab = any_order ? B.ab64 : ab_tab(B, sizeof(T));
     ss_args<T> bb{C, S, A.n, B.n, same_spin_table<T>(B, any_order), cross_table<T>(A), A.str, A.nw, nullptr, 0, 0};
     ss_args<T> aa{C, S2, B.n, A.n, same_spin_table<T>(A, any_order), cross_table<T>(B), B.str, B.nw, nullptr, 0, 1};
-    abg_args<T> ab{C, Y, B.n, sp->ab_grp, sp->ab_chunk_pair, tab};
+    abb_args<T> ab{C, Y, B.n, sp->abb_grp, sp->abb_pair, tab};
     const int n_bb = (int)nblk(A.n, f.R), n_aa = (int)nblk(B.n, f.R);
     {
         prof_scope ps(ctx, sizeof(T) == 8 ? "k_sigma_terms<double>" : "k_sigma_terms<float>");
-        const dim3 grid(n_bb + n_aa + sp->ab_nchunks), block(64 * f.waves);
+        const dim3 grid(n_bb + n_aa + sp->abb_nchunks), block(64 * f.waves);
         auto launch = [&](auto k) {
             constexpr int K = decltype(k)::value;
             set_lds(k_sigma_terms<T, K, K>, (int)f.lds);
@@ -765,7 +795,7 @@ bool sqd_sigma_prepared(sqd_ctx* ctx, const sqd_space* sp, int precision, unsign
     if (ab_path == SQD_AB_AUTO) ab_path = sqd_sigma_auto_path(ctx, sp, precision);
     const fused_shape fused = fused_pick(ctx, sp, es0, mask, ab_path);
     if (fused.R && ab_grouped_bytes(ctx, sp, es0))
-        return sp->ab_grp != nullptr && sp->ab_G == fused.G && sp->ab_row_order != nullptr;
+        return sp->abb_grp != nullptr && sp->abb_G == fused.G && sp->ab_row_order != nullptr;
     for (int spin = 0; spin < 2; ++spin) {   // windowed same-spin tables of either spin
         if (!(mask & (spin == 0 ? SQD_TERM_AA : SQD_TERM_BB))) continue;
         const spin_tables& col = sp->sp[spin].alias ? sp->sp[0] : sp->sp[spin];

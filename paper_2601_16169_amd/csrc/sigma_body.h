@@ -437,6 +437,92 @@ __device__ __forceinline__ void abg_block(const abg_args<T>& a, const T* __restr
         [&](int split, int slot) { put_y<T, G>(a, e, sgn, acc, lane, split, slot); });
 }
 
+// The same Y from blocks of G sources by one or two pairs (sqd_ensure_ab_blocks):
+// where the G staged rows of C serve two pairs, an entry of the table costs 8 G
+// bytes of LDS for C and 16 for the integrals for 2 G products instead of 8 G + 8
+// for G, and the table is read once for both (2000 strings per spin, norb 24: 6100
+// walks of the beta table in place of 8800, sigma FP64 715 -> 653 us, FP32
+// 411 -> 389).  Same products and summation order as abg_block.
+template <typename T>
+struct abb_args {
+    const T* C;
+    T* Y;
+    int64_t nb;
+    const int2* grp;          // blocks x 2 x G alpha singles: CSR position (-1 = padding), gather form
+    const int2* pair;         // second -1: one pair
+    ab_table tab;
+};
+
+template <typename T, int G, int P>
+__device__ __forceinline__ void abb_walk(const abb_args<T>& a, const T* __restrict__ V, int norb, int64_t chunk, int2 pair,
+                                         unsigned char* lds_raw) {
+    T* xs = reinterpret_cast<T*>(lds_raw);
+    const int norb2 = norb * norb;
+    const int64_t nb = a.nb;
+    T* vrow = xs + (nb + 1) * G;             // the pairs' integrals, P side by side
+    const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
+    ab_walk walk(a.tab);
+    int e[P * G];
+    uint32_t neg = 0;
+    {
+        const T* rows[G];
+#pragma unroll
+        for (int r = 0; r < P * G; ++r) {
+            const int2 x = a.grp[chunk * 2 * G + r];
+            e[r] = x.x;
+            neg |= ((uint32_t)x.y >> 31) << r;
+            if (r < G) rows[r] = e[r] >= 0 ? a.C + (int64_t)((uint32_t)x.y & SQD_NBR_MASK) * nb : nullptr;
+        }
+        stage_rows<T, G>(xs, rows, (int)nb);
+    }
+    for (int q = tid; q < norb2; q += nthr) {
+        vrow[q * P] = V[(int64_t)pair.x * norb2 + q];
+        if (P > 1) vrow[q * P + 1] = V[(int64_t)pair.y * norb2 + q];
+    }
+    __syncthreads();
+    T acc[P * G];
+    walk.run(
+        [&] {
+#pragma unroll
+            for (int r = 0; r < P * G; ++r) acc[r] = (T)0;
+        },
+        [&](uint32_t b) {
+            const int nbr = (int)(b & SQD_NBR_MASK);
+            const int pb = (int)((b >> SQD_PAIR_SHIFT) & SQD_PAIR_MASK);
+            T v[P], xr[G];
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                v[p] = vrow[pb * P + p];
+                if (b >> 31) v[p] = -v[p];
+            }
+            lds_cols<T, G>::load(xs, nbr, xr);
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+#pragma unroll
+                for (int r = 0; r < G; ++r) acc[p * G + r] += v[p] * xr[r];
+        },
+        [&](int split, int slot) {
+            for (int o = 1; o < (1 << split); o <<= 1) {
+#pragma unroll
+                for (int r = 0; r < P * G; ++r) acc[r] += __shfl_xor(acc[r], o);
+            }
+            if (lane & ((1 << split) - 1)) return;
+            T* y = a.Y + slot + (lane >> split);
+#pragma unroll
+            for (int r = 0; r < P * G; ++r)
+                if (e[r] >= 0)
+                    __builtin_nontemporal_store((neg >> r) & 1 ? -acc[r] : acc[r], y + (int64_t)e[r] * a.tab.nslots);
+        });
+}
+
+template <typename T, int G>
+__device__ __forceinline__ void abb_block(const abb_args<T>& a, const T* __restrict__ V, int norb, int64_t chunk,
+                                          unsigned char* lds_raw) {
+    const int2 pair = a.pair[chunk];
+    if (pair.y < 0) abb_walk<T, G, 1>(a, V, norb, chunk, pair, lds_raw);
+    else abb_walk<T, G, 2>(a, V, norb, chunk, pair, lds_raw);
+}
+
 // The same Y from chunks of up to GS alpha singles that share their source
 // string (chunk_src): one staged row of C serves GS pairs, whose (ai|..) rows
 // are staged beside it.  Where a row of C fills most of the LDS (long rows,

@@ -51,3 +51,128 @@ inline std::vector<std::vector<int>> deal_bins(const std::vector<int>& cost) {
 // two slices of that length, so the waves of a workgroup end together, and
 // only the long rows pay for the sums across lanes.
 inline int split_cap(int64_t entries, int least) { return (int)std::max<int64_t>(least, (entries + 2047) / 2048); }
+
+// (counting bits with the instruction: every host of these devices has it)
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+#pragma clang attribute push(__attribute__((target("popcnt"))), apply_to = function)
+#endif
+inline int bits_in_common(const uint64_t* a, const uint64_t* b, size_t words) {
+    int c = 0;
+    for (size_t w = 0; w < words; ++w) c += __builtin_popcountll(a[w] & b[w]);
+    return c;
+}
+
+// Blocks of G alpha singles of one pair, or of G sources by two pairs that both
+// excite, from the singles in gather form (nbr | pair << 19 | negative << 31, in
+// CSR order): grp lists 2 G singles a block (CSR position, gather form; -1 where
+// none), pairs the one or two pairs.  In a round the pairs of each orbital are
+// matched, the one with the most sources left with the one that shares most of
+// them, as long as they fill a block; the rounds go over the created and the
+// annihilated orbital by turns, until one adds less than 4% of the singles (eight
+// at most).  What is left goes to blocks of one pair.  2000 strings of 24
+// orbitals: 62% of the singles in blocks of two pairs and 6100 walks of the beta
+// table instead of 8800, planned in 0.6 ms; choosing the best two of all pairs
+// each time finds 76% in 2.4 ms (5000 strings of 36 orbitals: 3.6 and 38 ms), and
+// four pairs to a block save 2% of the reads more.
+inline void plan_ab_blocks(const std::vector<uint32_t>& pk, int64_t n, int norb, int G, std::vector<int2>& grp,
+                           std::vector<int2>& pairs) {
+    const int npair = norb * norb;
+    const size_t words = (size_t)(n + 63) / 64;
+    auto src_of = [&](int e) { return pk[e] & SQD_NBR_MASK; };
+    auto pair_of = [&](int e) { return (int)((pk[e] >> SQD_PAIR_SHIFT) & SQD_PAIR_MASK); };
+    // the sources of each pair as bits, and its singles by source: the single of
+    // source j is at the rank of its bit
+    std::vector<uint64_t> all((size_t)npair * words, 0);
+    std::vector<int> rank((size_t)npair * words), first(npair + 1, 0), ent(pk.size()), count(npair);
+    for (size_t e = 0; e < pk.size(); ++e) {
+        const uint32_t j = src_of((int)e);
+        all[pair_of((int)e) * words + (j >> 6)] |= 1ull << (j & 63);
+        first[pair_of((int)e) + 1] += 1;
+    }
+    for (int p = 0; p < npair; ++p) {
+        count[p] = first[p + 1];
+        first[p + 1] += first[p];
+        int at = first[p];
+        if (!count[p]) continue;
+        for (size_t w = 0; w < words; ++w) {
+            rank[p * words + w] = at;
+            at += __builtin_popcountll(all[p * words + w]);
+        }
+    }
+    auto place = [&](int p, uint32_t j) {
+        return rank[p * words + (j >> 6)] + __builtin_popcountll(all[p * words + (j >> 6)] & ((1ull << (j & 63)) - 1));
+    };
+    for (size_t e = 0; e < pk.size(); ++e) ent[place(pair_of((int)e), src_of((int)e))] = (int)e;
+    std::vector<uint64_t> left = all;
+    grp.reserve(pk.size() * 2);
+    auto add = [&](int p, int q, const uint32_t* src, int m) {
+        for (int half = 0; half < 2; ++half)
+            for (int r = 0; r < G; ++r) {
+                if (r < m && (half == 0 || q >= 0)) {
+                    const int e = ent[place(half ? q : p, src[r])];
+                    grp.push_back(make_int2(e, (int)pk[e]));
+                } else {
+                    grp.push_back(make_int2(-1, 0));
+                }
+            }
+        pairs.push_back(make_int2(p, q));
+    };
+    std::vector<uint32_t> src(n);
+    std::vector<int> line;
+    size_t before = 0;
+    for (int round = 0; round < 8; ++round) {
+        for (int i = 0; i < norb; ++i) {
+            // the pairs of one orbital: by turns with i created and annihilated
+            line.clear();
+            for (int a = 0; a < norb; ++a) {
+                const int p = round % 2 ? a * norb + i : i * norb + a;
+                if (count[p] >= G) line.push_back(p);
+            }
+            while (line.size() > 1) {
+                size_t at = 0, with = 0;
+                for (size_t k = 1; k < line.size(); ++k)
+                    if (count[line[k]] > count[line[at]]) at = k;
+                const int p = line[at];
+                std::swap(line[at], line.back());
+                line.pop_back();
+                uint64_t* lp = left.data() + p * words;
+                int most = G - 1;
+                for (size_t k = 0; k < line.size(); ++k) {
+                    if (count[line[k]] <= most) continue;
+                    const int c = bits_in_common(lp, left.data() + line[k] * words, words);
+                    if (c > most) most = c, with = k;
+                }
+                if (most < G) continue;
+                const int q = line[with];
+                std::swap(line[with], line.back());
+                line.pop_back();
+                uint64_t* lq = left.data() + q * words;
+                const int m = most / G * G;
+                int got = 0;
+                for (size_t w = 0; w < words && got < m; ++w) {
+                    uint64_t taken = 0;
+                    for (uint64_t x = lp[w] & lq[w]; x && got < m; x &= x - 1) {
+                        src[got++] = (uint32_t)(64 * w + __builtin_ctzll(x));
+                        taken |= x & (~x + 1);
+                    }
+                    lp[w] &= ~taken;
+                    lq[w] &= ~taken;
+                }
+                for (int k = 0; k < m; k += G) add(p, q, src.data() + k, G);
+                count[p] -= m;
+                count[q] -= m;
+            }
+        }
+        if ((grp.size() - before) * 25 < pk.size()) break;
+        before = grp.size();
+    }
+    for (int p = 0; p < npair; ++p) {
+        int got = 0;
+        for (size_t w = 0; w < words && got < count[p]; ++w)
+            for (uint64_t x = left[p * words + w]; x; x &= x - 1) src[got++] = (uint32_t)(64 * w + __builtin_ctzll(x));
+        for (int k = 0; k < got; k += G) add(p, -1, src.data() + k, std::min(G, got - k));
+    }
+}
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+#pragma clang attribute pop
+#endif

@@ -221,6 +221,10 @@ struct sqd_space {
     int ab_nchunks = 0;
     int2* ab_grp = nullptr;       // ab_nchunks * ab_G alpha singles: CSR position (-1 = padding), gather form
     int* ab_chunk_pair = nullptr; // pair index of each chunk
+    // blocks of the one-launch products: abb_G sources by one or two pairs
+    int abb_G = 0, abb_nchunks = 0;
+    int2* abb_grp = nullptr;      // abb_nchunks * 2 * abb_G alpha singles, as ab_grp: of the first pair, of the second
+    int2* abb_pair = nullptr;     // the pairs of each block (second -1: one pair)
     int* ab_rev = nullptr;        // alpha singles: entry of the neighbour's row pointing back
     int* ab_row_order = nullptr;  // alpha rows by decreasing number of singles (gather order)
     // the same singles grouped by source string (rows too long for two
@@ -295,6 +299,7 @@ int sqd_sigma_impl(sqd_ctx* ctx, sqd_space* sp, const double* c, double* sigma,
 int sqd_sigma_auto_path(sqd_ctx* ctx, const sqd_space* sp, int precision);
 bool sqd_sigma_prepared(sqd_ctx* ctx, const sqd_space* sp, int precision, unsigned mask, int ab_path);
 int sqd_ensure_ab_groups(sqd_ctx* ctx, sqd_space* sp, int G);
+int sqd_ensure_ab_blocks(sqd_ctx* ctx, sqd_space* sp, int G);   // sqd_space::abb_*
 // the alpha singles grouped by source string, chunks of G (for the batched solver)
 int sqd_ensure_ab_source_groups(sqd_ctx* ctx, sqd_space* sp, int G);
 
