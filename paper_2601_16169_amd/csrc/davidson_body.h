@@ -339,93 +339,93 @@ __device__ __forceinline__ void d_residual(const VT* __restrict__ V, const VT* _
 // Convergence / cap / phase-switch decisions and the collapse plan.
 template <int MT>
 __device__ __forceinline__ void f_res_fin(const double* __restrict__ partial, int nrows, dav_state* st, dav_params prm) {
-    // (the state's loads go out with the partials')
-    const int over = st->done;
+    // (the state's loads go out with the partials': one after another behind the
+    // sums they took half of the kernel's time)
+    const int over = st->done, m = st->m, it = st->iter, phase = st->phase, phase_start = st->phase_start;
+    const int lane = threadIdx.x;
+    const double theta = st->theta;
+    double best_r = st->best_r;
+    int best_it = st->best_it;
+    const double yk = lane < MM ? st->y[lane] : 0.0, yp = lane < MM ? st->y_prev[lane] : 0.0;
     __shared__ double out[MT + 2];
     reduce_rows<MT + 2>(partial, nrows, out);
-    if (over) return;
-    if (threadIdx.x < st->m) st->h[threadIdx.x] = out[threadIdx.x];
-    if (threadIdx.x != 0) return;
-    const int m = st->m;
-    const double theta = st->theta;
+    if (over || lane >= 64) return;   // one wavefront
+    if (lane < m) st->h[lane] = out[lane];
     const double rn = sqrt(out[MT]);
-    st->rnorm = rn;
-    st->tt0 = out[MT + 1];
-    const int it = st->iter;
-    if (it < SQD_HIST) {
-        st->hist_r[it] = rn;
-        st->hist_e[it] = theta;
-        st->nhist = it + 1;
-    }
-    st->iter = it + 1;
     int done = DONE_RUNNING;
     // smallest residual of this phase (a new best must improve by 10%)
-    if (it == st->phase_start || rn < 0.9 * st->best_r) {
-        st->best_r = rn;
-        st->best_it = it;
+    const bool best = it == phase_start || rn < 0.9 * best_r;
+    if (best) {
+        best_r = rn;
+        best_it = it;
     }
-    if (st->phase == 0) {
+    if (phase == 0) {
         // FP32 phase: hand over to FP64 refinement below switch_tol, on
         // reaching tol, below the FP32 floor (kFloor32 |theta|), or once the
         // residual has not improved for kStallWindow iterations after falling
         // below kStallFrom |theta| (a Davidson residual is not monotone: early
         // plateaus and bumps are not the FP32 floor)
         const double at = fabs(theta);
-        const bool stall = st->best_r < kStallFrom * at && it - st->best_it >= kStallWindow;
+        const bool stall = best_r < kStallFrom * at && it - best_it >= kStallWindow;
         if (rn < prm.switch_tol || rn <= prm.tol || rn < kFloor32 * at || stall) done = DONE_SWITCH;
     } else if (rn <= prm.tol) {
         done = DONE_CONVERGED;
     }
-    if (done == DONE_RUNNING && st->iter >= prm.max_iter) done = DONE_CAP;
-    st->done = done;
-    st->collapse = 0;
+    if (done == DONE_RUNNING && it + 1 >= prm.max_iter) done = DONE_CAP;
+    int keep = 0;
     if (done == DONE_RUNNING && m >= prm.m_max) {
         // keep the Ritz vector and the previous Ritz vector, orthonormalised in
-        // the small space: q1 = y, q2 ~ y_prev - (y . y_prev) y
-        double* q1 = st->qc[0];
-        double* q2 = st->qc[1];
-        double dp = 0.0;
-        for (int k = 0; k < m; ++k) dp += st->y[k] * st->y_prev[k];
-        double nq = 0.0;
-        for (int k = 0; k < MM; ++k) {
-            q1[k] = (k < m) ? st->y[k] : 0.0;
-            q2[k] = (k < m) ? st->y_prev[k] - dp * st->y[k] : 0.0;
-            nq += q2[k] * q2[k];
-        }
-        int keep = 1;
-        if (nq > 1e-20 && prm.m_max >= 3) {
-            double d2 = 0.0;
-            for (int k = 0; k < m; ++k) d2 += q1[k] * q2[k];
-            nq = 0.0;
-            for (int k = 0; k < m; ++k) {
-                q2[k] -= d2 * q1[k];
-                nq += q2[k] * q2[k];
-            }
-            const double inv = 1.0 / sqrt(nq);
-            for (int k = 0; k < m; ++k) q2[k] *= inv;
+        // the small space: q1 = y, q2 ~ y_prev - (y . y_prev) y; a row of G and an
+        // element of each vector per lane (one thread alone walked G four times)
+        __shared__ double qs[2][MM];
+        double q[2] = {lane < m ? yk : 0.0, lane < m ? yp : 0.0};
+        q[1] -= sum32(q[0] * q[1]) * q[0];
+        keep = 1;
+        if (sum32(q[1] * q[1]) > 1e-20 && prm.m_max >= 3) {
+            q[1] -= sum32(q[0] * q[1]) * q[0];
+            q[1] *= 1.0 / sqrt(sum32(q[1] * q[1]));
             keep = 2;
         }
-        for (int a = 0; a < keep; ++a) {
-            double ha = 0.0;
-            for (int k = 0; k < m; ++k) ha += st->qc[a][k] * out[k];
-            st->hc[a] = ha;
-            for (int b = 0; b < keep; ++b) {
-                double g = 0.0;
-                for (int k = 0; k < m; ++k) {
-                    double gk = 0.0;
-                    for (int l = 0; l < m; ++l) gk += st->G[k * MM + l] * st->qc[b][l];
-                    g += st->qc[a][k] * gk;
-                }
-                st->Gc[a * 2 + b] = g;
+        double g[2] = {0.0, 0.0};
+        if (lane < MM) {
+            qs[0][lane] = st->qc[0][lane] = q[0];
+            qs[1][lane] = st->qc[1][lane] = q[1];
+        }
+        __threadfence_block();
+        for (int l = 0; l < m; ++l) {
+            const double x = lane < m ? st->G[lane * MM + l] : 0.0;
+            g[0] += x * qs[0][l];
+            g[1] += x * qs[1][l];
+        }
+        const double o = lane < m ? out[lane] : 0.0;
+        const double h0 = sum32(q[0] * o), h1 = sum32(q[1] * o);
+        const double g00 = sum32(q[0] * g[0]), g11 = sum32(q[1] * g[1]);
+        const double g01 = 0.5 * (sum32(q[0] * g[1]) + sum32(q[1] * g[0]));
+        if (lane == 0) {
+            st->hc[0] = h0;
+            st->Gc[0] = g00;
+            if (keep == 2) {
+                st->hc[1] = h1;
+                st->Gc[1] = st->Gc[2] = g01;
+                st->Gc[3] = g11;
             }
         }
-        if (keep == 2) {
-            const double g = 0.5 * (st->Gc[1] + st->Gc[2]);
-            st->Gc[1] = g;
-            st->Gc[2] = g;
-        }
-        st->collapse = keep;
     }
+    if (lane != 0) return;
+    st->rnorm = rn;
+    st->tt0 = out[MT + 1];
+    if (it < SQD_HIST) {
+        st->hist_r[it] = rn;
+        st->hist_e[it] = theta;
+        st->nhist = it + 1;
+    }
+    st->iter = it + 1;
+    if (best) {
+        st->best_r = best_r;
+        st->best_it = best_it;
+    }
+    st->done = done;
+    st->collapse = keep;
 }
 
 // x = V y into cin and, from an FP64 basis, V[0] (the FP64 refinement's first
@@ -555,6 +555,7 @@ __device__ __forceinline__ void d_orth1(VT* __restrict__ V, VT* __restrict__ AV,
 template <int MT, typename VT = double>
 __device__ __forceinline__ void f_orth1_fin(const double* __restrict__ partial, int nrows, dav_state* st) {
     const int over = st->done, keep = st->collapse, m = keep ? keep : st->m;
+    const double tt0 = st->tt0, rnorm = st->rnorm;
     __shared__ double out[MT + 1];
     reduce_rows<MT + 1>(partial, nrows, out);
     if (over) return;
@@ -570,13 +571,13 @@ __device__ __forceinline__ void f_orth1_fin(const double* __restrict__ partial, 
         }
     }
     if (threadIdx.x < MM) st->h[threadIdx.x] = threadIdx.x < m ? out[threadIdx.x] : 0.0;
+    if (threadIdx.x >= 64) return;
+    const double o = threadIdx.x < m ? out[threadIdx.x] : 0.0, hh = sum32(o * o);
     if (threadIdx.x != 0) return;
     if (keep) {
         st->m = keep;
         st->collapse = 0;
     }
-    double hh = 0.0;
-    for (int j = 0; j < m; ++j) hh += out[j] * out[j];
     const double t1 = out[MT];
     const double nrm2 = t1 - hh;
     // a second projection only when the first left an overlap above what
@@ -584,11 +585,12 @@ __device__ __forceinline__ void f_orth1_fin(const double* __restrict__ partial, 
     // (6e-8), so a second pass there cannot improve the stored vector unless
     // the first left more than 1e-6 of it
     constexpr double kVisible = sizeof(VT) < sizeof(double) ? 1e-12 : 1e-26;
-    st->reortho = (hh > kVisible * t1) ? 1 : 0;
-    if (!(nrm2 > 1e-28 * st->tt0) || !(nrm2 > 0.0)) {
-        st->done = (st->rnorm <= 0.0) ? DONE_CONVERGED : DONE_STALLED;
+    const bool again = hh > kVisible * t1;
+    st->reortho = again ? 1 : 0;
+    if (!(nrm2 > 1e-28 * tt0) || !(nrm2 > 0.0)) {
+        st->done = (rnorm <= 0.0) ? DONE_CONVERGED : DONE_STALLED;
     } else {
-        st->tinv = 1.0 / sqrt(st->reortho ? nrm2 : t1);
+        st->tinv = 1.0 / sqrt(again ? nrm2 : t1);
     }
 }
 
