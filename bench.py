@@ -181,6 +181,7 @@ def main():
     counters = _counters(a.workload)
     # the alpha-alpha term comes back through transposes only when windowed
     info["aa_in_place"] = not any(k.startswith("k_transpose") for k in kernels)
+    info["one_launch"] = any(k.startswith("k_sigma_terms") for k in kernels)
     roofline = _roofline(kernels, info, sp, counters)
     kernel_roofs = [_kernel_roofline(k, v, info, sp, counters) for k, v in kernels.items()]
     conn = info["conn_per_sigma"]
@@ -502,10 +503,12 @@ def _leg(a, ctx, sp, prob, c, out, info):
             torch.cuda.synchronize()
             res[name] = {"seconds": time.perf_counter() - t, "energy": E, "iterations": rep["iterations"],
                          "converged": rep["converged"]}
-        stream_bytes = 12.0 * nnz + 8.0 * (sp.dim + 1) + 16.0 * sp.dim
+        # the values alone: the product derives the columns from the string lists
+        stream_bytes = 8.0 * nnz + 8.0 * (sp.dim + 1) + 16.0 * sp.dim
         # bytes the counters saw leave the L2 (FETCH + WRITE, scaled), from
         # the committed summary while the product's source is unchanged
-        crow = _counters(a.workload, "counters_stored").get("k_spmv", {})
+        rows = _counters(a.workload, "counters_stored")
+        crow = rows.get("k_spmv_staged", rows.get("k_spmv", {}))
         cbytes = crow.get("HBM bytes")
         print(json.dumps({"leg": "stored", "workload": prob.name, "nnz": nnz, "stored_bytes": 12 * nnz + 8 * (sp.dim + 1),
                           "build_seconds": t_build, "spmv_ms": t_spmv * 1e3, "matrix_free_sigma_ms": t_mf * 1e3,
@@ -639,8 +642,14 @@ def _algorithmic(name, info, sp):
         # when the row-staged alpha-alpha kernel adds into sigma in place)
         vec = 2 * es * dim + (es * dim if aa and info.get("aa_in_place") else 0) + (0 if aa else 8 * dim)
         return 2.0 * (t[1] if aa else t[2]), float(vec + tables)
+    if name.startswith("k_sigma_terms"):   # the three off-diagonal terms, each into a buffer of its own
+        tables = (4 + es) * (ns[0] + nd[0] + ns[1] + nd[1]) + 4 * (ns[0] + ns[1])
+        return 2.0 * (t[1] + t[2] + t[3]), float(es * (3 * dim + ns[0] * nb) + tables)
     if name.startswith("k_ab_gather"):
-        return 0.0, float(es * (ns[0] * nb + 2 * dim))
+        # Y and sigma; in the one-launch product the alpha-alpha term, the
+        # diagonal and the input too
+        more = (es + 16) * dim if info.get("one_launch") else 0
+        return 0.0, float(es * (ns[0] * nb + 2 * dim) + more)
     if name.startswith("k_transpose"):
         return 0.0, 2.0 * es * dim
     return None, None
