@@ -330,8 +330,8 @@ int sqd_store_hamiltonian(sqd_ctx* ctx, const sqd_space* space, int64_t* nnz_out
 /* Free the stored H of a space (no-op if none).  Synchronises the stream. */
 int sqd_release_hamiltonian(sqd_ctx* ctx, const sqd_space* space);
 /* sigma_dev = H c_dev from the stored H (all terms, FP64; dim doubles each,
- * distinct caller-owned buffers): a sparse product bound by HBM bandwidth,
- * 12 bytes per stored element.  SQD_E_STATE without a current stored H.
+ * distinct caller-owned buffers): a sparse product that streams the stored
+ * values (and, for few, short or very long rows, their columns).  SQD_E_STATE without a current stored H.
  * Only enqueues work, so it can be captured in a HIP graph. */
 int sqd_spmv(sqd_ctx* ctx, const sqd_space* space, const double* c_dev, double* sigma_dev);
 /* Host copy of the stored H: rowptr_host (dim + 1), cols_host and vals_host
@@ -390,8 +390,8 @@ int sqd_davidson_block(sqd_ctx* ctx, const sqd_space* space, const sqd_davidson_
 /* Many independent spaces built on the same context (same integrals) solved
  * together, each for its lowest root (Sec. I: the sampling loop yields many
  * configuration sets; Sec. II/IV: the same matrix-free product per space;
- * Sec. VI: load imbalance across uneven task groups): one persistent launch per sigma term over a work queue of
- * (space, tile) units ordered longest-first, and the Davidson iteration of all
+ * Sec. VI: load imbalance across uneven task groups): all sigma terms of all
+ * spaces in shared launches of (space, tile) units ordered longest-first, and the Davidson iteration of all
  * spaces captured once in a hipGraph and replayed.  energies_host[nspace],
  * vecs_dev[nspace] (each that space's dim), reps[nspace] optional.
  * Synchronous. */
@@ -408,8 +408,8 @@ int sqd_davidson_batched(sqd_ctx* ctx, int nspace, const sqd_space* const* space
  * dE/d(pq|rs) = rdm2_pqrs / 2 (per element).  rdm1_dev has norb^2 doubles,
  * rdm2_dev norb^4 (NULL skips it).  The alpha-beta part of rdm2 sums over the
  * pairs of in-set alpha and beta singles; its tables are built by the space's
- * first call with rdm2_dev (a copy and an allocation, so not under capture)
- * and kept. */
+ * first call with rdm2_dev (a copy and an allocation, beside the capture if
+ * the call is captured) and kept. */
 int sqd_rdm(sqd_ctx* ctx, const sqd_space* space, const double* c_dev,
             double* rdm1_dev, double* rdm2_dev);
 

@@ -13,7 +13,7 @@ tunes the same-spin knobs with the alpha-beta ones automatic, then the
 alpha-beta knobs with the best same-spin setting applied.  Times are HIP events
 on the context's stream.
 
-``tune`` tunes one space's sigma; ``tune_batched`` tunes the persistent
+``tune`` tunes one space's sigma; ``tune_batched`` tunes the
 batched solver for a list of spaces by timing short batched solves (a fixed
 number of iterations, no convergence test) and applies the same knobs, which
 the batched launch reads.  Results are cached in a JSON file keyed by the

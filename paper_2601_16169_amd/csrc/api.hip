@@ -31,6 +31,17 @@ int sqd_alloc(sqd_ctx* ctx, void** p, size_t bytes, int64_t* counter) {
     return SQD_OK;
 }
 
+hipError_t sqd_copy_now(void* dst, const void* src, size_t bytes, hipMemcpyKind kind) {
+    if (!bytes) return hipSuccess;
+    hipStream_t s = nullptr;
+    hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    if (e != hipSuccess) return e;
+    e = hipMemcpyAsync(dst, src, bytes, kind, s);
+    const hipError_t w = hipStreamSynchronize(s);
+    (void)hipStreamDestroy(s);
+    return e != hipSuccess ? e : w;
+}
+
 bool sqd_capturing(sqd_ctx* ctx) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(ctx->stream, &cs) != hipSuccess) {

@@ -429,7 +429,7 @@ __global__ void __launch_bounds__(256) k_transpose_d(const double* __restrict__ 
 // orbital pair and their chunks.
 int build_rdm_plan(sqd_ctx* ctx, sqd_space* sp) {
     if (sp->rdm_mem) return SQD_OK;
-    if (sqd_capturing(ctx)) return sqd_fail(ctx, SQD_E_STATE, "RDM tables not built before the capture");
+    const sqd_beside_capture beside;   // a first call may be captured
     spin_tables& A = sp->sp[0];
     spin_tables& B = sp->sp[1].alias ? A : sp->sp[1];
     const int norb = sp->norb, n2 = norb * norb;
@@ -550,7 +550,7 @@ int build_rdm_plan(sqd_ctx* ctx, sqd_space* sp) {
         if (parts[k].second) std::memcpy(all.data() + off[k], parts[k].first, parts[k].second);
     void* mem = nullptr;
     if ((rc = sqd_alloc(ctx, &mem, all.size(), &sp->bytes))) return rc;
-    const hipError_t e = hipMemcpy(mem, all.data(), all.size(), hipMemcpyHostToDevice);
+    const hipError_t e = sqd_copy_now(mem, all.data(), all.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         (void)hipFree(mem);
         sp->bytes -= (int64_t)all.size();

@@ -2,17 +2,22 @@
 // three task types of the Slater-Condon rules: alpha-alpha, beta-beta and one
 // alpha plus one beta excitation).
 //
-// Terms and kernels (all owner-computes, no atomics, deterministic):
-//   DIAG  H_II c_I, fused into the beta-beta kernel's epilogue (FP64 always).
+// Terms and kernels (all owner-computes, no atomics, deterministic).  The whole
+// product of all but the longest rows is one launch of the three off-diagonal
+// terms, each into a buffer of its own (k_sigma_terms), and the gather that adds
+// them and the diagonal; single terms, kernels chosen by the caller and the rest
+// take a launch per term:
+//   DIAG  H_II c_I, fused into the beta-beta kernel's epilogue or the gather (FP64
+//         always).
 //   BB    same-spin kernel on C (rows = alpha strings, columns = beta strings):
 //         sigma[ia, jb] += sum over beta singles/doubles (jb <- kb) of
 //         H^bb(jb, kb; Ia) c[ia, kb].  A workgroup stages R rows of C in LDS
 //         (layout [column][row], plus a zero slot for padding) and the
 //         cross-spin term W_a[pq] = sum_{k in Ia} (pq|kk) of those rows; each
-//         lane owns one target column of a 64-row slice of the sliced table
-//         and walks its entries (coalesced 64-wide table reads).
-//   AA    the same kernel on C^T (one tiled transpose each way), i.e. the
-//         beta-beta machinery applied with the spins swapped.
+//         lane owns one target column (or, FP64, a share of one) of a 64-row slice
+//         of the sliced table and walks its entries (16-byte table reads).
+//   AA    the same body on C^T, read from the columns of C (or through one tiled
+//         transpose each way), i.e. the beta-beta machinery with the spins swapped.
 //   AB    sigma[ia', jb'] += sum_{alpha singles ia' <- ia (pair ai, s_a)}
 //         sum_{beta singles jb' <- jb (pair bj, s_b)} s_a s_b (ai|bj) c[ia, jb]:
 //         a workgroup per target alpha row stages KC source rows of C and the
@@ -583,6 +588,18 @@ int ensure_ab_source_groups(sqd_ctx* ctx, sqd_space* sp, int G) {
 // The sliced singles a product of this element size walks.
 const ab_table& ab_tab(const spin_tables& t, size_t es) { return es == sizeof(double) ? t.ab64 : t.ab32; }
 
+// The blocks of the one-launch products exist (of G sources each).
+bool ab_blocks_built(const sqd_space* sp, int G) {
+    return sp->abb_grp && sp->abb_G == G && sp->ab_row_order;
+}
+// ... and serve a product of element size es where a capture began before the
+// separate kernels' schedule was built (0: they do not).
+int ab_blocks_usable(sqd_ctx* ctx, const sqd_space* sp, size_t es) {
+    const size_t n2 = (size_t)sp->norb * sp->norb, k = (size_t)sp->abb_G;
+    if ((k != 2 && k != 4) || !ab_blocks_built(sp, sp->abb_G)) return 0;
+    return (((size_t)sp->sp[1].n + 1) * k + 2 * n2) * es <= (size_t)ctx->max_lds ? (int)k : 0;
+}
+
 // Y bytes of the grouped alpha-beta path (0 if it is not to be used).
 size_t ab_grouped_bytes(sqd_ctx* ctx, const sqd_space* sp, size_t es, bool any_order = false) {
     const int variant = ctx->tune[SQD_TUNE_AB_VARIANT];
@@ -700,7 +717,25 @@ int launch_ab_grouped(sqd_ctx* ctx, sqd_space* sp, const T* C, T* S, T* Y, const
     const spin_tables& B = sp->sp[1];
     const ab_table& tab = ab_tab(B, sizeof(T));
     int rc;
-    if (ab_use_source_groups(ctx, sp)) {
+    const bool by_source = ab_use_source_groups(ctx, sp);
+    const bool built = by_source ? sp->abs_grp && sp->abs_G == ab_source_group_size(ctx, sp)
+                                 : sp->ab_grp && sp->ab_G == ab_group_size(ctx, sp);
+    const int blocks = !built && sqd_capturing(ctx) ? ab_blocks_usable(ctx, sp, sizeof(T)) : 0;
+    if (blocks) {
+        // captured after one-launch products only: their blocks
+        const size_t lds = (((size_t)B.n + 1) * blocks + 2 * (size_t)sp->norb * sp->norb) * sizeof(T);
+        abb_args<T> ab{C, Y, B.n, sp->abb_grp, sp->abb_pair, tab};
+        const ss_args<T> none{};
+        if (sp->abb_nchunks > 0 && blocks == 4) {
+            set_lds(k_sigma_terms<T, 4, 4>, (int)lds);
+            hipLaunchKernelGGL((k_sigma_terms<T, 4, 4>), dim3(sp->abb_nchunks), dim3(1024), lds, ctx->stream, none,
+                               none, ab, 0, 0, (const T*)nullptr, V, sp->norb, skip);
+        } else if (sp->abb_nchunks > 0) {
+            set_lds(k_sigma_terms<T, 2, 2>, (int)lds);
+            hipLaunchKernelGGL((k_sigma_terms<T, 2, 2>), dim3(sp->abb_nchunks), dim3(1024), lds, ctx->stream, none,
+                               none, ab, 0, 0, (const T*)nullptr, V, sp->norb, skip);
+        }
+    } else if (by_source) {
         const int GS = ab_source_group_size(ctx, sp);
         if ((rc = ensure_ab_row_order(ctx, sp)) || (rc = ensure_ab_source_groups(ctx, sp, GS))) return rc;
         if (sp->abs_nchunks > 0) {
@@ -785,6 +820,12 @@ int sqd_sigma_auto_path(sqd_ctx* ctx, const sqd_space* sp, int precision) {
     return SQD_AB_DIRECT;
 }
 
+// The windowed tables, cross-spin table and scratch of a spin exist.
+static bool window_built(sqd_ctx* ctx, const sqd_space* sp, int spin, const spin_tables& col, const spin_tables& row) {
+    const int W = sqd_window_count(ctx, sp->sp[spin].n);
+    return W != 0 && col.win_W == W && row.wg64 && (W == 1 || sp->win_P_bytes >= sqd_window_scratch_bytes(sp));
+}
+
 // True when a product with these arguments would allocate, copy or
 // synchronise nothing: the space's values and diagonal are current and the
 // alpha-beta path's per-space schedule exists.  (The context scratch is
@@ -794,14 +835,17 @@ bool sqd_sigma_prepared(sqd_ctx* ctx, const sqd_space* sp, int precision, unsign
     const size_t es0 = precision == SQD_FP64 ? 8 : 4;
     if (ab_path == SQD_AB_AUTO) ab_path = sqd_sigma_auto_path(ctx, sp, precision);
     const fused_shape fused = fused_pick(ctx, sp, es0, mask, ab_path);
-    if (fused.R && ab_grouped_bytes(ctx, sp, es0))
-        return sp->abb_grp != nullptr && sp->abb_G == fused.G && sp->ab_row_order != nullptr;
+    if (fused.R && ab_grouped_bytes(ctx, sp, es0) && ab_blocks_built(sp, fused.G)) return true;
     for (int spin = 0; spin < 2; ++spin) {   // windowed same-spin tables of either spin
         if (!(mask & (spin == 0 ? SQD_TERM_AA : SQD_TERM_BB))) continue;
         const spin_tables& col = sp->sp[spin].alias ? sp->sp[0] : sp->sp[spin];
         const spin_tables& row = sp->sp[1 - spin].alias ? sp->sp[0] : sp->sp[1 - spin];
         if (use_window(ctx, sp->sp[1 - spin].n, sp->sp[spin].n, sp->norb, es0)) {
             const int W = sqd_window_count(ctx, sp->sp[spin].n);
+            // whole rows instead, which fit where a one-launch product ran
+            if (!window_built(ctx, sp, spin, col, row) &&
+                (sp->fused_terms[es0 == 8 ? 0 : 1] & (spin == 0 ? SQD_TERM_AA : SQD_TERM_BB)))
+                continue;
             if (W == 0 || col.win_W != W || col.win_values_version != ctx->ham_version || !row.wg64 ||
                 row.wg_version != ctx->ham_version || (W > 1 && sp->win_P_bytes < sqd_window_scratch_bytes(sp)))
                 return false;
@@ -812,15 +856,10 @@ bool sqd_sigma_prepared(sqd_ctx* ctx, const sqd_space* sp, int precision, unsign
     if (ab_path == SQD_AB_KH) return sp->kh_map != nullptr && sp->ab_rev != nullptr;
     const size_t es = precision == SQD_FP64 ? 8 : 4;
     if (ab_grouped_bytes(ctx, sp, es) == 0) return true;   // row-staged kernel: nothing per space
+    if (ab_blocks_usable(ctx, sp, es)) return true;
     if (ab_use_source_groups(ctx, sp))
         return sp->abs_grp != nullptr && sp->abs_G == ab_source_group_size(ctx, sp) && sp->ab_row_order != nullptr;
     return sp->ab_grp != nullptr && sp->ab_G == ab_group_size(ctx, sp) && sp->ab_row_order != nullptr;
-}
-
-// The windowed tables, cross-spin table and scratch of a spin exist.
-static bool window_built(sqd_ctx* ctx, const sqd_space* sp, int spin, const spin_tables& col, const spin_tables& row) {
-    const int W = sqd_window_count(ctx, sp->sp[spin].n);
-    return W != 0 && col.win_W == W && row.wg64 && (W == 1 || sp->win_P_bytes >= sqd_window_scratch_bytes(sp));
 }
 
 // True when the arrays that a space's first product builds exist for a
@@ -882,11 +921,14 @@ int sqd_sigma_impl(sqd_ctx* ctx, sqd_space* sp, const double* c, double* sigma, 
     const int norb = sp->norb;
     if (ab_path == SQD_AB_AUTO) ab_path = sqd_sigma_auto_path(ctx, sp, precision);
     const double* diag = (mask & SQD_TERM_DIAG) ? sp->diag : nullptr;
-    const fused_shape fused = fused_pick(ctx, sp, precision == SQD_FP64 ? 8 : 4, mask, ab_path, any_order);
+    fused_shape fused = fused_pick(ctx, sp, precision == SQD_FP64 ? 8 : 4, mask, ab_path, any_order);
+    // captured after products of single terms only: separate launches, on what those built
+    if (fused.R && !ab_blocks_built(sp, fused.G) && sqd_capturing(ctx)) fused.R = 0;
     // the windowed same-spin kernel, where the dispatch takes it; without an
-    // allocation only on tables that exist
+    // allocation, and under capture, only on tables that exist
+    const bool may_build = !ext_scratch && !sqd_capturing(ctx);
     auto win = [&](int spin) {
-        if (!ext_scratch) return true;
+        if (may_build) return true;
         const spin_tables& col = sp->sp[spin].alias ? sp->sp[0] : sp->sp[spin];
         const spin_tables& row = sp->sp[1 - spin].alias ? sp->sp[0] : sp->sp[1 - spin];
         return window_built(ctx, sp, spin, col, row);

@@ -1,5 +1,5 @@
 // Device bodies of the sigma kernels, shared by the single-space launches
-// (sigma.hip) and the batched persistent launches (davidson.hip).  Each body
+// (sigma.hip) and the launches over many spaces (batched.hip).  Each body
 // processes one work unit (a block index of its own launch shape) of one
 // space described by an argument struct.
 #pragma once

@@ -271,6 +271,17 @@ int sqd_hip_fail(sqd_ctx* ctx, hipError_t e, const char* what);
 int sqd_alloc(sqd_ctx* ctx, void** p, size_t bytes, int64_t* counter);
 void* sqd_ctx_scratch(sqd_ctx* ctx, size_t bytes, int* rc);
 bool sqd_capturing(sqd_ctx* ctx);
+// While alive, this thread may allocate and copy (sqd_copy_now) beside a capture.
+struct sqd_beside_capture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    sqd_beside_capture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~sqd_beside_capture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    sqd_beside_capture(const sqd_beside_capture&) = delete;
+    sqd_beside_capture& operator=(const sqd_beside_capture&) = delete;
+};
+// A copy between host and device on a stream of its own, waited for: not part of
+// a capture, and not on the null stream, which a capture may forbid.
+hipError_t sqd_copy_now(void* dst, const void* src, size_t bytes, hipMemcpyKind kind);
 
 #define SQD_HIP(ctx, call)                                              \
     do {                                                                \

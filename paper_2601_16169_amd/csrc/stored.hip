@@ -409,6 +409,8 @@ static int plan_staged(sqd_ctx* ctx, sqd_space* sp, const std::vector<int>& as, 
     sp->h_bytes += (int64_t)(sizeof(int2) * (units.size() + 1));
     sp->bytes += (int64_t)(sizeof(int2) * (units.size() + 1));
     SQD_HIP(ctx, hipMemcpy(sp->h_units, units.data(), sizeof(int2) * units.size(), hipMemcpyHostToDevice));
+    SQD_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(k_spmv_staged),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, ctx->max_lds));
     sp->h_nunits = (int)units.size();
     sp->h_list = most;
     sp->h_cap = (int)cap;
@@ -521,8 +523,6 @@ int sqd_spmv_impl(sqd_ctx* ctx, sqd_space* sp, const double* x, double* y, const
         const spin_tables& A = sp->sp[0];
         const spin_tables& B = sp->sp[1];
         const size_t lds = (size_t)sp->h_cap * sizeof(double) + (size_t)sp->h_list * sizeof(int);
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_spmv_staged),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         staged_args a{B.n, A.s_off, A.d_off, A.d_nbr, B.s_off, B.d_off, B.d_nbr, A.s_pk, B.s_pk,
                       sp->h_rowptr, sp->h_val, x, y, sp->h_units, sp->h_cap, sp->h_step};
         hipLaunchKernelGGL(k_spmv_staged, dim3(sp->h_nunits), dim3(64 * kSpmvWaves), lds, ctx->stream, a, skip);

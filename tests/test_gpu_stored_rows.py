@@ -45,3 +45,41 @@ def test_stored_rows(norb, nel, na, nb):
         sp.close()
     finally:
         ctx.close()
+
+
+def test_stored_rows_graph_replays():
+    """The staged product captured in a HIP graph, without an eager call of it
+    before: every replay equals the eager product, bit for bit, with eager products
+    of another vector between the replays."""
+    torch = need_gpu()
+    banner("stored rows graph capture")
+    from paper_2601_16169_amd import sqd
+    stream = torch.cuda.Stream()
+    ctx = sqd.Context(0, stream)
+    try:
+        ints = I.make_integrals(10, 20, seed=3)
+        every = I.all_strings(10, 5)
+        ctx.set_hamiltonian(ints.h, ints.eri, ints.ecore)
+        sp = ctx.build_space(5, 5, every, every[:130].copy())
+        sp.store_hamiltonian()
+        with torch.cuda.stream(stream):
+            c, c2 = (torch.tensor(I.random_vector(sp.dim, k), device="cuda:0") for k in (23, 24))
+            out, other = torch.empty_like(c), torch.empty_like(c)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            sp.spmv(c, out)
+        with torch.cuda.stream(stream):
+            eager = sp.spmv(c).clone()
+        for rep in range(4):
+            with torch.cuda.stream(stream):
+                out.fill_(float("nan"))
+                graph.replay()
+            stream.synchronize()
+            assert torch.equal(out, eager), f"replay {rep} differs"
+            with torch.cuda.stream(stream):
+                sp.spmv(c2, other)
+            stream.synchronize()
+        sp.close()
+    finally:
+        ctx.close()
