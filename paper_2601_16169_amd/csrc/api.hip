@@ -31,8 +31,9 @@ int sqd_alloc(sqd_ctx* ctx, void** p, size_t bytes, int64_t* counter) {
     return SQD_OK;
 }
 
-hipError_t sqd_copy_now(void* dst, const void* src, size_t bytes, hipMemcpyKind kind) {
+hipError_t sqd_copy_now(sqd_ctx* ctx, void* dst, const void* src, size_t bytes, hipMemcpyKind kind) {
     if (!bytes) return hipSuccess;
+    if (!sqd_capturing(ctx)) return hipMemcpy(dst, src, bytes, kind);
     hipStream_t s = nullptr;
     hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
     if (e != hipSuccess) return e;

@@ -550,7 +550,7 @@ int build_rdm_plan(sqd_ctx* ctx, sqd_space* sp) {
         if (parts[k].second) std::memcpy(all.data() + off[k], parts[k].first, parts[k].second);
     void* mem = nullptr;
     if ((rc = sqd_alloc(ctx, &mem, all.size(), &sp->bytes))) return rc;
-    const hipError_t e = sqd_copy_now(mem, all.data(), all.size(), hipMemcpyHostToDevice);
+    const hipError_t e = sqd_copy_now(ctx, mem, all.data(), all.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         (void)hipFree(mem);
         sp->bytes -= (int64_t)all.size();

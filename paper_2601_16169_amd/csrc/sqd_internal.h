@@ -279,9 +279,9 @@ struct sqd_beside_capture {
     sqd_beside_capture(const sqd_beside_capture&) = delete;
     sqd_beside_capture& operator=(const sqd_beside_capture&) = delete;
 };
-// A copy between host and device on a stream of its own, waited for: not part of
-// a capture, and not on the null stream, which a capture may forbid.
-hipError_t sqd_copy_now(void* dst, const void* src, size_t bytes, hipMemcpyKind kind);
+// A copy between host and device, waited for.  Beside a capture on a stream of its
+// own, not on the null stream, which a capture may forbid (a stream costs 0.2 ms).
+hipError_t sqd_copy_now(sqd_ctx* ctx, void* dst, const void* src, size_t bytes, hipMemcpyKind kind);
 
 #define SQD_HIP(ctx, call)                                              \
     do {                                                                \

@@ -690,10 +690,7 @@ int sqd_ensure_split32(sqd_ctx* ctx, sqd_space* sp) {
 int sqd_host_singles(sqd_ctx* ctx, spin_tables& t) {
     if ((int64_t)t.s_pk_host.size() == t.nnz_s) return SQD_OK;
     std::vector<uint32_t> pk(t.nnz_s);
-    if (sqd_capturing(ctx))
-        SQD_HIP(ctx, sqd_copy_now(pk.data(), t.s_pk, sizeof(uint32_t) * t.nnz_s, hipMemcpyDeviceToHost));
-    else
-        SQD_HIP(ctx, hipMemcpy(pk.data(), t.s_pk, sizeof(uint32_t) * t.nnz_s, hipMemcpyDeviceToHost));
+    SQD_HIP(ctx, sqd_copy_now(ctx, pk.data(), t.s_pk, sizeof(uint32_t) * t.nnz_s, hipMemcpyDeviceToHost));
     t.s_pk_host.swap(pk);
     return SQD_OK;
 }
