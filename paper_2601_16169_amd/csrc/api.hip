@@ -125,22 +125,18 @@ static void space_release_device(sqd_space* sp) {
     sqd_release_stored_h(sp);
     sqd_free_spin_tables(&sp->sp[1]);
     sqd_free_spin_tables(&sp->sp[0]);
-    void* ptrs[] = {sp->diag, sp->ua, sp->ab_grp, sp->ab_chunk_pair, sp->ab_rev, sp->kh_tile_off, sp->kh_pairs,
-                    sp->kh_map, sp->ab_row_order, sp->win_P, sp->abs_grp, sp->abs_src, sp->rdm_mem,
-                    sp->abb_grp, sp->abb_pair};
+    void* ptrs[] = {sp->diag, sp->ua, sp->ab.mem, sp->ab_rev, sp->kh_tile_off, sp->kh_pairs, sp->kh_map,
+                    sp->ab_row_order, sp->win_P, sp->abs.mem, sp->rdm_mem, sp->abb.mem};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     sp->diag = sp->ua = nullptr;
-    sp->ab_grp = nullptr;
-    sp->ab_chunk_pair = sp->ab_rev = sp->kh_tile_off = sp->kh_pairs = sp->kh_map = nullptr;
+    sp->ab = sp->abs = ab_schedule<int>();
+    sp->abb = ab_schedule<int2>();
+    sp->ab_rev = sp->kh_tile_off = sp->kh_pairs = sp->kh_map = nullptr;
     sp->ab_row_order = nullptr;
-    sp->abs_grp = sp->abb_grp = sp->abb_pair = nullptr;
     sp->rdm_mem = nullptr;
-    sp->abs_src = nullptr;
-    sp->abs_G = sp->abs_nchunks = 0;
     sp->win_P = nullptr;
     sp->win_P_bytes = 0;
-    sp->ab_G = sp->abb_G = 0;
     sp->kh_ntiles = 0;
 }
 

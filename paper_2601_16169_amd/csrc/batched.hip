@@ -894,14 +894,14 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
             auto add = [&](int kind, int64_t count) {
                 for (int64_t k = 0; k < count; ++k) c.list.push_back(make_int2(b, (int)((kind << kUnitShift) | k)));
             };
-            add(2, spaces[b]->abb_nchunks);
+            add(2, spaces[b]->abb.n);
             add(0, (d.na + c.R - 1) / c.R);
             add(1, (d.nb + c.R - 1) / c.R);
             continue;
         }
         for (int64_t r = 0; r < (d.na + p.R - 1) / p.R; ++r) ssbb.push_back(make_int2(b, (int)r));
         for (int64_t r = 0; r < (d.nb + p.R - 1) / p.R; ++r) ssaa.push_back(make_int2(b, (int)r));
-        const int nch = (!cls2[b] && p.GS) ? spaces[b]->abs_nchunks : spaces[b]->ab_nchunks;
+        const int nch = (!cls2[b] && p.GS) ? spaces[b]->abs.n : spaces[b]->ab.n;
         for (int c = 0; c < nch; ++c) (cls2[b] ? abg2 : abg).push_back(make_int2(b, c));
     }
     want((void**)&p.partial, sizeof(double) * (size_t)part * kPstride);
@@ -955,8 +955,8 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
             d.bb64 = ss_args<double>{d.cin, d.sout, A.n, B.n, B.ss64, A.ws64, A.str, A.nw, nullptr, 0, 0};
             d.aa32 = ss_args<float>{d.c32, d.Yt32, B.n, A.n, A.split32, B.ws32, B.str, B.nw, nullptr, 0, 1};
             d.bb32 = ss_args<float>{d.c32, d.S32, A.n, B.n, B.split32, A.ws32, A.str, A.nw, nullptr, 0, 0};
-            d.abb64 = abb_args<double>{d.cin, d.Y64, B.n, sp->abb_grp, sp->abb_pair, B.ab64};
-            d.abb32 = abb_args<float>{d.c32, d.Y32, B.n, sp->abb_grp, sp->abb_pair, B.ab64};
+            d.abb64 = abb_args<double>{d.cin, d.Y64, B.n, sp->abb.grp, sp->abb.key, B.ab64};
+            d.abb32 = abb_args<float>{d.c32, d.Y32, B.n, sp->abb.grp, sp->abb.key, B.ab64};
             // as many groups of threads of the gather as read a row of Y side by side
             const int per = (int)((B.ab64.nslots / 2 + 63) / 64 * 64);
             d.ng = p.gather_lds64 ? std::max(1, std::min(kGatherThreads / std::max(per, 64), 4)) : 1;
@@ -968,9 +968,9 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
         d.aa32 = ss_args<float>{d.Ct32, d.Yt32, B.n, A.n, A.ss32, B.ws32, B.str, B.nw, nullptr, 0};
         d.bb32 = ss_args<float>{d.c32, d.S32, A.n, B.n, B.ss32, A.ws32, A.str, A.nw, nullptr, 1};
         const bool src = !cls2[b] && p.GS;
-        const int2* grp = src ? sp->abs_grp : sp->ab_grp;
-        const int* cpair = src ? nullptr : sp->ab_chunk_pair;
-        d.abs_src = src ? sp->abs_src : nullptr;
+        const int2* grp = src ? sp->abs.grp : sp->ab.grp;
+        const int* cpair = src ? nullptr : sp->ab.key;
+        d.abs_src = src ? sp->abs.key : nullptr;
         d.ab64 = abg_args<double>{d.cin, d.Y64, B.n, grp, cpair, B.ab64};
         d.ab32 = abg_args<float>{d.c32, d.Y32, B.n, grp, cpair, B.ab32};
     }

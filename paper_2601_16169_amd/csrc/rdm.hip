@@ -19,7 +19,6 @@
 // (or part of one).  X[qp][sr] = X[pq][rs], so alpha pairs with p > q alone
 // are walked; rdm2 receives X[pq][rs] + X[rs][pq] (the beta-alpha term).
 #include <algorithm>
-#include <cstring>
 #include <type_traits>
 
 #include "sigma_body.h"
@@ -535,32 +534,14 @@ int build_rdm_plan(sqd_ctx* ctx, sqd_space* sp) {
         }
     std::stable_sort(chunks.begin(), chunks.end(), [](const int4& x, const int4& y) { return x.y > y.y; });
     // one allocation
-    const std::pair<const void*, size_t> parts[] = {
+    const host_part parts[] = {
         {ent.data(), sizeof(uint2) * ent.size()},        {units.data(), sizeof(alpha_unit) * units.size()},
         {chunks.data(), sizeof(int4) * chunks.size()},   {perm.data(), sizeof(int) * perm.size()},
         {split.data(), sizeof(int) * split.size()},      {blk.data(), sizeof(int) * blk.size()},
         {bin.data(), sizeof(int) * bin.size()}};
-    size_t total_bytes = 0, off[7];
-    for (int k = 0; k < 7; ++k) {
-        off[k] = total_bytes;
-        total_bytes += (parts[k].second + 255) & ~(size_t)255;
-    }
-    std::vector<char> all(total_bytes + 256);
-    for (int k = 0; k < 7; ++k)
-        if (parts[k].second) std::memcpy(all.data() + off[k], parts[k].first, parts[k].second);
-    void* mem = nullptr;
-    if ((rc = sqd_alloc(ctx, &mem, all.size(), &sp->bytes))) return rc;
-    const hipError_t e = sqd_copy_now(ctx, mem, all.data(), all.size(), hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-        (void)hipFree(mem);
-        sp->bytes -= (int64_t)all.size();
-        return sqd_hip_fail(ctx, e, "RDM tables");
-    }
-    for (int k = 0; k < 7; ++k) sp->rdm_off[k] = off[k];
     sp->rdm_nslices = nslices;
     sp->rdm_nchunks = (int)chunks.size();
-    sp->rdm_mem = mem;
-    return SQD_OK;
+    return upload_parts(ctx, parts, 7, &sp->rdm_mem, sp->rdm_off, &sp->bytes);
 }
 
 }  // namespace

@@ -460,15 +460,14 @@ int ensure_ab_row_order(sqd_ctx* ctx, sqd_space* sp) {
     for (int64_t r = 0; r < A.n; ++r) order[r] = (int)r;
     std::stable_sort(order.begin(), order.end(),
                      [&](int x, int y) { return off[x + 1] - off[x] > off[y + 1] - off[y]; });
-    int rc;
-    if ((rc = sqd_alloc(ctx, (void**)&sp->ab_row_order, sizeof(int) * (A.n + 1), &sp->bytes))) return rc;
-    SQD_HIP(ctx, hipMemcpy(sp->ab_row_order, order.data(), sizeof(int) * A.n, hipMemcpyHostToDevice));
-    return SQD_OK;
+    const host_part part{order.data(), sizeof(int) * order.size()};
+    size_t at;
+    return upload_parts(ctx, &part, 1, (void**)&sp->ab_row_order, &at, &sp->bytes);
 }
 
 // Group the alpha singles (CSR positions) by orbital pair, padded to chunks of G.
 int ensure_ab_groups_impl(sqd_ctx* ctx, sqd_space* sp, int G) {
-    if (sp->ab_G == G && sp->ab_grp) return SQD_OK;
+    if (sp->ab.built(G)) return SQD_OK;
     if (G <= 0) return sqd_fail(ctx, SQD_E_LIMIT, "alpha-beta group does not fit in LDS");
     spin_tables& A = sp->sp[0];
     int rc;
@@ -487,42 +486,22 @@ int ensure_ab_groups_impl(sqd_ctx* ctx, sqd_space* sp, int G) {
             cp.push_back(p);
         }
     }
-    if (sp->ab_grp) { (void)hipFree(sp->ab_grp); sp->ab_grp = nullptr; }
-    if (sp->ab_chunk_pair) { (void)hipFree(sp->ab_chunk_pair); sp->ab_chunk_pair = nullptr; }
     if ((rc = ensure_ab_row_order(ctx, sp))) return rc;
-    if ((rc = sqd_alloc(ctx, (void**)&sp->ab_grp, sizeof(int2) * (grp.size() + 1), &sp->bytes))) return rc;
-    if ((rc = sqd_alloc(ctx, (void**)&sp->ab_chunk_pair, sizeof(int) * (cp.size() + 1), &sp->bytes))) return rc;
-    if (!grp.empty()) {
-        SQD_HIP(ctx, hipMemcpy(sp->ab_grp, grp.data(), sizeof(int2) * grp.size(), hipMemcpyHostToDevice));
-        SQD_HIP(ctx, hipMemcpy(sp->ab_chunk_pair, cp.data(), sizeof(int) * cp.size(), hipMemcpyHostToDevice));
-    }
-    sp->ab_G = G;
-    sp->ab_nchunks = (int)cp.size();
-    return SQD_OK;
+    return upload_schedule(ctx, G, grp, cp, sp->ab, &sp->bytes);
 }
 
 }  // namespace
 
 int sqd_ensure_ab_blocks(sqd_ctx* ctx, sqd_space* sp, int G) {
-    if (sp->abb_G == G && sp->abb_grp) return SQD_OK;
+    if (sp->abb.built(G)) return SQD_OK;
     if (G <= 0) return sqd_fail(ctx, SQD_E_LIMIT, "alpha-beta block does not fit in LDS");
     spin_tables& A = sp->sp[0];
     int rc;
     if ((rc = sqd_host_singles(ctx, A))) return rc;
     std::vector<int2> grp, pairs;
     plan_ab_blocks(A.s_pk_host, A.n, sp->norb, G, grp, pairs);
-    if (sp->abb_grp) { (void)hipFree(sp->abb_grp); sp->abb_grp = nullptr; }
-    if (sp->abb_pair) { (void)hipFree(sp->abb_pair); sp->abb_pair = nullptr; }
     if ((rc = ensure_ab_row_order(ctx, sp))) return rc;
-    if ((rc = sqd_alloc(ctx, (void**)&sp->abb_grp, sizeof(int2) * (grp.size() + 1), &sp->bytes))) return rc;
-    if ((rc = sqd_alloc(ctx, (void**)&sp->abb_pair, sizeof(int2) * (pairs.size() + 1), &sp->bytes))) return rc;
-    if (!grp.empty()) {
-        SQD_HIP(ctx, hipMemcpy(sp->abb_grp, grp.data(), sizeof(int2) * grp.size(), hipMemcpyHostToDevice));
-        SQD_HIP(ctx, hipMemcpy(sp->abb_pair, pairs.data(), sizeof(int2) * pairs.size(), hipMemcpyHostToDevice));
-    }
-    sp->abb_G = G;
-    sp->abb_nchunks = (int)pairs.size();
-    return SQD_OK;
+    return upload_schedule(ctx, G, grp, pairs, sp->abb, &sp->bytes);
 }
 
 namespace {
@@ -555,7 +534,7 @@ bool ab_use_source_groups(sqd_ctx* ctx, const sqd_space* sp) {
 
 // Group the alpha singles (CSR positions) by source string, padded to chunks of G.
 int ensure_ab_source_groups(sqd_ctx* ctx, sqd_space* sp, int G) {
-    if (sp->abs_G == G && sp->abs_grp) return SQD_OK;
+    if (sp->abs.built(G)) return SQD_OK;
     spin_tables& A = sp->sp[0];
     int rc;
     if ((rc = sqd_host_singles(ctx, A))) return rc;
@@ -572,17 +551,7 @@ int ensure_ab_source_groups(sqd_ctx* ctx, sqd_space* sp, int G) {
             cs.push_back((int)j);
         }
     }
-    if (sp->abs_grp) { (void)hipFree(sp->abs_grp); sp->abs_grp = nullptr; }
-    if (sp->abs_src) { (void)hipFree(sp->abs_src); sp->abs_src = nullptr; }
-    if ((rc = sqd_alloc(ctx, (void**)&sp->abs_grp, sizeof(int2) * (grp.size() + 1), &sp->bytes))) return rc;
-    if ((rc = sqd_alloc(ctx, (void**)&sp->abs_src, sizeof(int) * (cs.size() + 1), &sp->bytes))) return rc;
-    if (!grp.empty()) {
-        SQD_HIP(ctx, hipMemcpy(sp->abs_grp, grp.data(), sizeof(int2) * grp.size(), hipMemcpyHostToDevice));
-        SQD_HIP(ctx, hipMemcpy(sp->abs_src, cs.data(), sizeof(int) * cs.size(), hipMemcpyHostToDevice));
-    }
-    sp->abs_G = G;
-    sp->abs_nchunks = (int)cs.size();
-    return SQD_OK;
+    return upload_schedule(ctx, G, grp, cs, sp->abs, &sp->bytes);
 }
 
 // The sliced singles a product of this element size walks.
@@ -590,13 +559,13 @@ const ab_table& ab_tab(const spin_tables& t, size_t es) { return es == sizeof(do
 
 // The blocks of the one-launch products exist (of G sources each).
 bool ab_blocks_built(const sqd_space* sp, int G) {
-    return sp->abb_grp && sp->abb_G == G && sp->ab_row_order;
+    return sp->abb.built(G) && sp->ab_row_order;
 }
 // ... and serve a product of element size es where a capture began before the
 // separate kernels' schedule was built (0: they do not).
 int ab_blocks_usable(sqd_ctx* ctx, const sqd_space* sp, size_t es) {
-    const size_t n2 = (size_t)sp->norb * sp->norb, k = (size_t)sp->abb_G;
-    if ((k != 2 && k != 4) || !ab_blocks_built(sp, sp->abb_G)) return 0;
+    const size_t n2 = (size_t)sp->norb * sp->norb, k = (size_t)sp->abb.G;
+    if ((k != 2 && k != 4) || !ab_blocks_built(sp, sp->abb.G)) return 0;
     return (((size_t)sp->sp[1].n + 1) * k + 2 * n2) * es <= (size_t)ctx->max_lds ? (int)k : 0;
 }
 
@@ -692,11 +661,11 @@ int launch_fused(sqd_ctx* ctx, sqd_space* sp, const fused_shape& f, const T* C, 
     const ab_table& tab = any_order ? B.ab64 : ab_tab(B, sizeof(T));
     ss_args<T> bb{C, S, A.n, B.n, same_spin_table<T>(B, any_order), cross_table<T>(A), A.str, A.nw, nullptr, 0, 0};
     ss_args<T> aa{C, S2, B.n, A.n, same_spin_table<T>(A, any_order), cross_table<T>(B), B.str, B.nw, nullptr, 0, 1};
-    abb_args<T> ab{C, Y, B.n, sp->abb_grp, sp->abb_pair, tab};
+    abb_args<T> ab{C, Y, B.n, sp->abb.grp, sp->abb.key, tab};
     const int n_bb = (int)nblk(A.n, f.R), n_aa = (int)nblk(B.n, f.R);
     {
         prof_scope ps(ctx, sizeof(T) == 8 ? "k_sigma_terms<double>" : "k_sigma_terms<float>");
-        const dim3 grid(n_bb + n_aa + sp->abb_nchunks), block(64 * f.waves);
+        const dim3 grid(n_bb + n_aa + sp->abb.n), block(64 * f.waves);
         auto launch = [&](auto k) {
             constexpr int K = decltype(k)::value;
             set_lds(k_sigma_terms<T, K, K>, (int)f.lds);
@@ -718,36 +687,35 @@ int launch_ab_grouped(sqd_ctx* ctx, sqd_space* sp, const T* C, T* S, T* Y, const
     const ab_table& tab = ab_tab(B, sizeof(T));
     int rc;
     const bool by_source = ab_use_source_groups(ctx, sp);
-    const bool built = by_source ? sp->abs_grp && sp->abs_G == ab_source_group_size(ctx, sp)
-                                 : sp->ab_grp && sp->ab_G == ab_group_size(ctx, sp);
+    const bool built = by_source ? sp->abs.built(ab_source_group_size(ctx, sp)) : sp->ab.built(ab_group_size(ctx, sp));
     const int blocks = !built && sqd_capturing(ctx) ? ab_blocks_usable(ctx, sp, sizeof(T)) : 0;
     if (blocks) {
         // captured after one-launch products only: their blocks
         const size_t lds = (((size_t)B.n + 1) * blocks + 2 * (size_t)sp->norb * sp->norb) * sizeof(T);
-        abb_args<T> ab{C, Y, B.n, sp->abb_grp, sp->abb_pair, tab};
+        abb_args<T> ab{C, Y, B.n, sp->abb.grp, sp->abb.key, tab};
         const ss_args<T> none{};
-        if (sp->abb_nchunks > 0 && blocks == 4) {
+        if (sp->abb.n > 0 && blocks == 4) {
             set_lds(k_sigma_terms<T, 4, 4>, (int)lds);
-            hipLaunchKernelGGL((k_sigma_terms<T, 4, 4>), dim3(sp->abb_nchunks), dim3(1024), lds, ctx->stream, none,
+            hipLaunchKernelGGL((k_sigma_terms<T, 4, 4>), dim3(sp->abb.n), dim3(1024), lds, ctx->stream, none,
                                none, ab, 0, 0, (const T*)nullptr, V, sp->norb, skip);
-        } else if (sp->abb_nchunks > 0) {
+        } else if (sp->abb.n > 0) {
             set_lds(k_sigma_terms<T, 2, 2>, (int)lds);
-            hipLaunchKernelGGL((k_sigma_terms<T, 2, 2>), dim3(sp->abb_nchunks), dim3(1024), lds, ctx->stream, none,
+            hipLaunchKernelGGL((k_sigma_terms<T, 2, 2>), dim3(sp->abb.n), dim3(1024), lds, ctx->stream, none,
                                none, ab, 0, 0, (const T*)nullptr, V, sp->norb, skip);
         }
     } else if (by_source) {
         const int GS = ab_source_group_size(ctx, sp);
         if ((rc = ensure_ab_row_order(ctx, sp)) || (rc = ensure_ab_source_groups(ctx, sp, GS))) return rc;
-        if (sp->abs_nchunks > 0) {
+        if (sp->abs.n > 0) {
             const size_t lds = ((size_t)(B.n + 1) + (size_t)GS * sp->norb * sp->norb) * sizeof(T);
             const int nw = ctx->tune[SQD_TUNE_AB_WAVES] ? ctx->tune[SQD_TUNE_AB_WAVES] : 16;
-            abg_args<T> args{C, Y, B.n, sp->abs_grp, nullptr, tab};
+            abg_args<T> args{C, Y, B.n, sp->abs.grp, nullptr, tab};
             prof_scope ps(ctx, sizeof(T) == 8 ? "k_ab_srcgrouped<double>" : "k_ab_srcgrouped<float>");
 #define SQD_ABS_LAUNCH(GG)                                                                                    \
     case GG:                                                                                                  \
         set_lds(k_ab_srcgrouped<T, GG>, (int)lds);                                                            \
-        hipLaunchKernelGGL((k_ab_srcgrouped<T, GG>), dim3(sp->abs_nchunks), dim3(64 * nw), lds, ctx->stream,    \
-                           args, sp->abs_src, V, sp->norb, skip);                                             \
+        hipLaunchKernelGGL((k_ab_srcgrouped<T, GG>), dim3(sp->abs.n), dim3(64 * nw), lds, ctx->stream, args,     \
+                           sp->abs.key, V, sp->norb, skip);                                                   \
         break;
             switch (GS) {
                 SQD_ABS_LAUNCH(2)
@@ -760,18 +728,18 @@ int launch_ab_grouped(sqd_ctx* ctx, sqd_space* sp, const T* C, T* S, T* Y, const
     } else {
     const int G = ab_group_size(ctx, sp);
     if ((rc = ensure_ab_groups_impl(ctx, sp, G))) return rc;
-    if (sp->ab_nchunks > 0) {
+    if (sp->ab.n > 0) {
         const size_t lds = ((size_t)(B.n + 1) * G + (size_t)sp->norb * sp->norb) * sizeof(T);
         // measured on MI355X: 16 waves for FP64, and for FP32 when few rows
         // share each table entry (G <= 2: the loop is latency-bound)
         const int nw = ctx->tune[SQD_TUNE_AB_WAVES] ? ctx->tune[SQD_TUNE_AB_WAVES]
                                                     : ((sizeof(T) == 8 || G <= 2) ? 16 : 8);
-        abg_args<T> args{C, Y, B.n, sp->ab_grp, sp->ab_chunk_pair, tab};
+        abg_args<T> args{C, Y, B.n, sp->ab.grp, sp->ab.key, tab};
         prof_scope ps(ctx, sizeof(T) == 8 ? "k_ab_grouped<double>" : "k_ab_grouped<float>");
 #define SQD_ABG_LAUNCH(GG)                                                                                   \
     case GG:                                                                                                 \
         set_lds(k_ab_grouped<T, GG>, (int)lds);                                                              \
-        hipLaunchKernelGGL((k_ab_grouped<T, GG>), dim3(sp->ab_nchunks), dim3(64 * nw), lds, ctx->stream, args, \
+        hipLaunchKernelGGL((k_ab_grouped<T, GG>), dim3(sp->ab.n), dim3(64 * nw), lds, ctx->stream, args,       \
                            V, sp->norb, skip);                                                               \
         break;
         switch (G) {
@@ -858,8 +826,8 @@ bool sqd_sigma_prepared(sqd_ctx* ctx, const sqd_space* sp, int precision, unsign
     if (ab_grouped_bytes(ctx, sp, es) == 0) return true;   // row-staged kernel: nothing per space
     if (ab_blocks_usable(ctx, sp, es)) return true;
     if (ab_use_source_groups(ctx, sp))
-        return sp->abs_grp != nullptr && sp->abs_G == ab_source_group_size(ctx, sp) && sp->ab_row_order != nullptr;
-    return sp->ab_grp != nullptr && sp->ab_G == ab_group_size(ctx, sp) && sp->ab_row_order != nullptr;
+        return sp->abs.built(ab_source_group_size(ctx, sp)) && sp->ab_row_order != nullptr;
+    return sp->ab.built(ab_group_size(ctx, sp)) && sp->ab_row_order != nullptr;
 }
 
 // True when the arrays that a space's first product builds exist for a

@@ -3,9 +3,59 @@
 #pragma once
 
 #include <algorithm>
+#include <cstring>
 #include <vector>
 
 #include "sqd_internal.h"
+
+// Arrays planned on the host, side by side in one device allocation.  *mem is set
+// when all of them are there: after a failure nothing is held and *mem is as it was.
+struct host_part {
+    const void* data;
+    size_t bytes;
+};
+inline int upload_parts(sqd_ctx* ctx, const host_part* parts, int n, void** mem, size_t* off, int64_t* counter) {
+    size_t total = 0;
+    for (int k = 0; k < n; ++k) {
+        off[k] = total;
+        total += (parts[k].bytes + 255) & ~(size_t)255;
+    }
+    total += 256;
+    std::vector<char> all(total);
+    for (int k = 0; k < n; ++k)
+        if (parts[k].bytes) std::memcpy(all.data() + off[k], parts[k].data, parts[k].bytes);
+    void* p = nullptr;
+    const int rc = sqd_alloc(ctx, &p, total, nullptr);
+    if (rc) return rc;
+    const hipError_t e = sqd_copy_now(ctx, p, all.data(), total, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        (void)hipFree(p);
+        return sqd_hip_fail(ctx, e, "upload of a host plan");
+    }
+    *mem = p;
+    *counter += (int64_t)total;
+    return SQD_OK;
+}
+
+// The schedule s from chunks of G; the one it replaces is freed once the new one
+// is whole, and stays if that fails.
+template <typename K>
+int upload_schedule(sqd_ctx* ctx, int G, const std::vector<int2>& grp, const std::vector<K>& key, ab_schedule<K>& s,
+                    int64_t* counter) {
+    const host_part parts[] = {{grp.data(), sizeof(int2) * grp.size()}, {key.data(), sizeof(K) * key.size()}};
+    size_t off[2];
+    ab_schedule<K> t;
+    const int rc = upload_parts(ctx, parts, 2, &t.mem, off, &t.bytes);
+    if (rc) return rc;
+    t.G = G;
+    t.n = (int)key.size();
+    t.grp = reinterpret_cast<const int2*>(static_cast<char*>(t.mem) + off[0]);
+    t.key = reinterpret_cast<const K*>(static_cast<char*>(t.mem) + off[1]);
+    if (s.mem) (void)hipFree(s.mem);
+    *counter += t.bytes - s.bytes;
+    s = t;
+    return SQD_OK;
+}
 
 // Rows by decreasing length (ties by index): a counting sort.
 inline std::vector<int> rows_longest_first(const std::vector<int>& len) {

@@ -203,6 +203,18 @@ struct spin_tables {
     double* ws64 = nullptr; float* ws32 = nullptr;
 };
 
+// The alpha singles in chunks for an alpha-beta kernel, planned on the host: one
+// device allocation, set once both arrays are filled.
+template <typename K>
+struct ab_schedule {
+    void* mem = nullptr;          // null: not built
+    int G = 0, n = 0;             // singles (or sources) per chunk, chunks
+    int64_t bytes = 0;
+    const int2* grp = nullptr;    // alpha singles of each chunk: CSR position (-1 = padding), gather form
+    const K* key = nullptr;       // what the singles of a chunk share
+    bool built(int g) const { return mem && G == g; }
+};
+
 struct sqd_space {
     sqd_ctx* ctx = nullptr;       // null once the context was destroyed (orphan)
     int norb = 0;
@@ -217,22 +229,17 @@ struct sqd_space {
     int diag_version = -1;
     double* ua = nullptr;         // na x norb: sum_{p in Ia} (pp|qq)
     // alpha singles grouped by orbital pair for the grouped alpha-beta kernel
-    int ab_G = 0;                 // entries per chunk (0 = not built)
-    int ab_nchunks = 0;
-    int2* ab_grp = nullptr;       // ab_nchunks * ab_G alpha singles: CSR position (-1 = padding), gather form
-    int* ab_chunk_pair = nullptr; // pair index of each chunk
-    // blocks of the one-launch products: abb_G sources by one or two pairs
-    int abb_G = 0, abb_nchunks = 0;
-    int2* abb_grp = nullptr;      // abb_nchunks * 2 * abb_G alpha singles, as ab_grp: of the first pair, of the second
-    int2* abb_pair = nullptr;     // the pairs of each block (second -1: one pair)
+    // (key: the pair of each chunk)
+    ab_schedule<int> ab;
+    // blocks of the one-launch products: G sources by one or two pairs (key: the
+    // pairs, second -1: one pair; grp: G singles of the first pair, G of the second)
+    ab_schedule<int2> abb;
     int* ab_rev = nullptr;        // alpha singles: entry of the neighbour's row pointing back
     int* ab_row_order = nullptr;  // alpha rows by decreasing number of singles (gather order)
     // the same singles grouped by source string (rows too long for two
-    // staged sources: one staged source row serves several pairs)
-    int abs_G = 0;
-    int abs_nchunks = 0;
-    int2* abs_grp = nullptr;      // abs_nchunks * abs_G alpha singles, as ab_grp
-    int* abs_src = nullptr;       // source alpha string of each chunk
+    // staged sources: one staged source row serves several pairs; key: the source
+    // alpha string of each chunk)
+    ab_schedule<int> abs;
     // Knowles-Handy beta tiles (64 targets each): the union of the pair columns
     // their singles use, and for every (target, column) the source of that
     // single (0: none, else source + 1, bit 31 = negative sign)
@@ -310,7 +317,7 @@ int sqd_sigma_impl(sqd_ctx* ctx, sqd_space* sp, const double* c, double* sigma,
 int sqd_sigma_auto_path(sqd_ctx* ctx, const sqd_space* sp, int precision);
 bool sqd_sigma_prepared(sqd_ctx* ctx, const sqd_space* sp, int precision, unsigned mask, int ab_path);
 int sqd_ensure_ab_groups(sqd_ctx* ctx, sqd_space* sp, int G);
-int sqd_ensure_ab_blocks(sqd_ctx* ctx, sqd_space* sp, int G);   // sqd_space::abb_*
+int sqd_ensure_ab_blocks(sqd_ctx* ctx, sqd_space* sp, int G);   // sqd_space::abb
 // the alpha singles grouped by source string, chunks of G (for the batched solver)
 int sqd_ensure_ab_source_groups(sqd_ctx* ctx, sqd_space* sp, int G);
 

@@ -1,0 +1,84 @@
+"""The host side of the kernels' plans (csrc/slices.h), compiled for the host and
+run without a GPU: device memory is host memory, and allocations and copies fail
+where a test wants them to."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2601_16169_amd import build
+
+STUBS = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "slices.h"
+
+static int allocs_left = 1 << 30, copies_left = 1 << 30, held = 0;
+int sqd_fail(sqd_ctx*, int code, const std::string&) { return code; }
+int sqd_hip_fail(sqd_ctx*, hipError_t, const char*) { return SQD_E_HIP; }
+int sqd_alloc(sqd_ctx*, void** p, size_t bytes, int64_t* counter) {
+    if (allocs_left-- <= 0) return SQD_E_OOM;
+    *p = std::malloc(bytes);
+    ++held;
+    if (counter) *counter += (int64_t)bytes;
+    return SQD_OK;
+}
+hipError_t sqd_copy_now(sqd_ctx*, void* dst, const void* src, size_t bytes, hipMemcpyKind) {
+    if (copies_left-- <= 0) return hipErrorUnknown;
+    std::memcpy(dst, src, bytes);
+    return hipSuccess;
+}
+extern "C" hipError_t hipFree(void* p) {
+    std::free(p);
+    --held;
+    return hipSuccess;
+}
+#define REQUIRE(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
+"""
+
+
+def _run(tmp_path, body):
+    src = tmp_path / "main.cpp"
+    src.write_text(STUBS + body)
+    exe = tmp_path / "main"
+    cmd = [build.hipcc(), "--offload-host-only", "-x", "hip", "-O1", "-fPIC", "-std=c++17", "-w", "-I", build.CSRC, "-c",
+           str(src), "-o", str(tmp_path / "main.o")]
+    subprocess.run(cmd, check=True, capture_output=True, text=True, timeout=120)
+    subprocess.run(["g++", str(tmp_path / "main.o"), "-o", str(exe)], check=True, capture_output=True, text=True,
+                   timeout=120)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout
+
+
+def test_schedule_is_whole_or_as_before(tmp_path):
+    """A schedule that cannot be allocated or copied leaves the one before it (or
+    none) in place, and holds no memory."""
+    _run(tmp_path, r"""
+int main() {
+    ab_schedule<int2> s;
+    int64_t bytes = 0;
+    std::vector<int2> grp(16, make_int2(3, 4)), key(2, make_int2(5, -1));
+    for (int which = 0; which < 2; ++which) {          // the first schedule of a space
+        (which ? copies_left : allocs_left) = 0;
+        REQUIRE(upload_schedule(nullptr, 4, grp, key, s, &bytes) != SQD_OK);
+        REQUIRE(!s.mem && !s.built(4) && s.n == 0 && held == 0 && bytes == 0);
+        allocs_left = copies_left = 1 << 30;
+    }
+    REQUIRE(upload_schedule(nullptr, 4, grp, key, s, &bytes) == SQD_OK);
+    REQUIRE(s.built(4) && s.n == 2 && held == 1 && bytes == s.bytes);
+    REQUIRE(s.grp[15].x == 3 && s.key[1].x == 5 && s.key[1].y == -1);
+    const void* mem = s.mem;
+    std::vector<int2> grp2(4, make_int2(7, 8)), key2(1, make_int2(9, 10));
+    for (int which = 0; which < 2; ++which) {          // one that replaces it
+        (which ? copies_left : allocs_left) = 0;
+        REQUIRE(upload_schedule(nullptr, 2, grp2, key2, s, &bytes) != SQD_OK);
+        REQUIRE(s.mem == mem && s.built(4) && s.n == 2 && s.key[1].x == 5 && held == 1 && bytes == s.bytes);
+        allocs_left = copies_left = 1 << 30;
+    }
+    REQUIRE(upload_schedule(nullptr, 2, grp2, key2, s, &bytes) == SQD_OK);
+    REQUIRE(s.built(2) && !s.built(4) && s.n == 1 && s.grp[3].y == 8 && s.key[0].y == 10 && held == 1);
+    REQUIRE(upload_schedule(nullptr, 2, {}, {}, s, &bytes) == SQD_OK);      // no singles: built and empty
+    REQUIRE(s.built(2) && s.n == 0 && held == 1 && bytes == s.bytes);
+    return 0;
+}
+""")
