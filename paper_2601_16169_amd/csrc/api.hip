@@ -126,12 +126,12 @@ static void space_release_device(sqd_space* sp) {
     sqd_free_spin_tables(&sp->sp[1]);
     sqd_free_spin_tables(&sp->sp[0]);
     void* ptrs[] = {sp->diag, sp->ua, sp->ab.mem, sp->ab_rev, sp->kh_tile_off, sp->kh_pairs, sp->kh_map,
-                    sp->ab_row_order, sp->win_P, sp->abs.mem, sp->rdm_mem, sp->abb.mem};
+                    sp->ab_row_order, sp->win_P, sp->abs.mem, sp->rdm_mem, sp->abb[0].mem, sp->abb[1].mem};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     sp->diag = sp->ua = nullptr;
     sp->ab = sp->abs = ab_schedule<int>();
-    sp->abb = ab_schedule<int2>();
+    sp->abb[0] = sp->abb[1] = ab_schedule<int2>();
     sp->ab_rev = sp->kh_tile_off = sp->kh_pairs = sp->kh_map = nullptr;
     sp->ab_row_order = nullptr;
     sp->rdm_mem = nullptr;

@@ -894,7 +894,7 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
             auto add = [&](int kind, int64_t count) {
                 for (int64_t k = 0; k < count; ++k) c.list.push_back(make_int2(b, (int)((kind << kUnitShift) | k)));
             };
-            add(2, spaces[b]->abb.n);
+            add(2, spaces[b]->blocks(c.R).n);
             add(0, (d.na + c.R - 1) / c.R);
             add(1, (d.nb + c.R - 1) / c.R);
             continue;
@@ -955,8 +955,9 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
             d.bb64 = ss_args<double>{d.cin, d.sout, A.n, B.n, B.ss64, A.ws64, A.str, A.nw, nullptr, 0, 0};
             d.aa32 = ss_args<float>{d.c32, d.Yt32, B.n, A.n, A.split32, B.ws32, B.str, B.nw, nullptr, 0, 1};
             d.bb32 = ss_args<float>{d.c32, d.S32, A.n, B.n, B.split32, A.ws32, A.str, A.nw, nullptr, 0, 0};
-            d.abb64 = abb_args<double>{d.cin, d.Y64, B.n, sp->abb.grp, sp->abb.key, B.ab64};
-            d.abb32 = abb_args<float>{d.c32, d.Y32, B.n, sp->abb.grp, sp->abb.key, B.ab64};
+            const ab_schedule<int2>& bl = sp->blocks(p.classes[cls[b]].R);
+            d.abb64 = abb_args<double>{d.cin, d.Y64, B.n, bl.grp, bl.key, B.ab64};
+            d.abb32 = abb_args<float>{d.c32, d.Y32, B.n, bl.grp, bl.key, B.ab64};
             // as many groups of threads of the gather as read a row of Y side by side
             const int per = (int)((B.ab64.nslots / 2 + 63) / 64 * 64);
             d.ng = p.gather_lds64 ? std::max(1, std::min(kGatherThreads / std::max(per, 64), 4)) : 1;

@@ -493,15 +493,15 @@ int ensure_ab_groups_impl(sqd_ctx* ctx, sqd_space* sp, int G) {
 }  // namespace
 
 int sqd_ensure_ab_blocks(sqd_ctx* ctx, sqd_space* sp, int G) {
-    if (sp->abb.built(G)) return SQD_OK;
-    if (G <= 0) return sqd_fail(ctx, SQD_E_LIMIT, "alpha-beta block does not fit in LDS");
+    if (sp->blocks(G).built(G)) return SQD_OK;
+    if (G != 2 && G != 4) return sqd_fail(ctx, SQD_E_LIMIT, "alpha-beta block does not fit in LDS");
     spin_tables& A = sp->sp[0];
     int rc;
     if ((rc = sqd_host_singles(ctx, A))) return rc;
     std::vector<int2> grp, pairs;
     plan_ab_blocks(A.s_pk_host, A.n, sp->norb, G, grp, pairs);
     if ((rc = ensure_ab_row_order(ctx, sp))) return rc;
-    return upload_schedule(ctx, G, grp, pairs, sp->abb, &sp->bytes);
+    return upload_schedule(ctx, G, grp, pairs, sp->blocks(G), &sp->bytes);
 }
 
 namespace {
@@ -559,14 +559,15 @@ const ab_table& ab_tab(const spin_tables& t, size_t es) { return es == sizeof(do
 
 // The blocks of the one-launch products exist (of G sources each).
 bool ab_blocks_built(const sqd_space* sp, int G) {
-    return sp->abb.built(G) && sp->ab_row_order;
+    return sp->blocks(G).built(G) && sp->ab_row_order;
 }
 // ... and serve a product of element size es where a capture began before the
-// separate kernels' schedule was built (0: they do not).
+// separate kernels' schedule was built: the most sources of those built (0: none).
 int ab_blocks_usable(sqd_ctx* ctx, const sqd_space* sp, size_t es) {
-    const size_t n2 = (size_t)sp->norb * sp->norb, k = (size_t)sp->abb.G;
-    if ((k != 2 && k != 4) || !ab_blocks_built(sp, sp->abb.G)) return 0;
-    return (((size_t)sp->sp[1].n + 1) * k + 2 * n2) * es <= (size_t)ctx->max_lds ? (int)k : 0;
+    const size_t n2 = (size_t)sp->norb * sp->norb;
+    for (int k : {4, 2})
+        if (ab_blocks_built(sp, k) && (((size_t)sp->sp[1].n + 1) * k + 2 * n2) * es <= (size_t)ctx->max_lds) return k;
+    return 0;
 }
 
 // Y bytes of the grouped alpha-beta path (0 if it is not to be used).
@@ -661,11 +662,12 @@ int launch_fused(sqd_ctx* ctx, sqd_space* sp, const fused_shape& f, const T* C, 
     const ab_table& tab = any_order ? B.ab64 : ab_tab(B, sizeof(T));
     ss_args<T> bb{C, S, A.n, B.n, same_spin_table<T>(B, any_order), cross_table<T>(A), A.str, A.nw, nullptr, 0, 0};
     ss_args<T> aa{C, S2, B.n, A.n, same_spin_table<T>(A, any_order), cross_table<T>(B), B.str, B.nw, nullptr, 0, 1};
-    abb_args<T> ab{C, Y, B.n, sp->abb.grp, sp->abb.key, tab};
+    const ab_schedule<int2>& blocks = sp->blocks(f.G);
+    abb_args<T> ab{C, Y, B.n, blocks.grp, blocks.key, tab};
     const int n_bb = (int)nblk(A.n, f.R), n_aa = (int)nblk(B.n, f.R);
     {
         prof_scope ps(ctx, sizeof(T) == 8 ? "k_sigma_terms<double>" : "k_sigma_terms<float>");
-        const dim3 grid(n_bb + n_aa + sp->abb.n), block(64 * f.waves);
+        const dim3 grid(n_bb + n_aa + blocks.n), block(64 * f.waves);
         auto launch = [&](auto k) {
             constexpr int K = decltype(k)::value;
             set_lds(k_sigma_terms<T, K, K>, (int)f.lds);
@@ -692,15 +694,16 @@ int launch_ab_grouped(sqd_ctx* ctx, sqd_space* sp, const T* C, T* S, T* Y, const
     if (blocks) {
         // captured after one-launch products only: their blocks
         const size_t lds = (((size_t)B.n + 1) * blocks + 2 * (size_t)sp->norb * sp->norb) * sizeof(T);
-        abb_args<T> ab{C, Y, B.n, sp->abb.grp, sp->abb.key, tab};
+        const ab_schedule<int2>& bl = sp->blocks(blocks);
+        abb_args<T> ab{C, Y, B.n, bl.grp, bl.key, tab};
         const ss_args<T> none{};
-        if (sp->abb.n > 0 && blocks == 4) {
+        if (bl.n > 0 && blocks == 4) {
             set_lds(k_sigma_terms<T, 4, 4>, (int)lds);
-            hipLaunchKernelGGL((k_sigma_terms<T, 4, 4>), dim3(sp->abb.n), dim3(1024), lds, ctx->stream, none,
+            hipLaunchKernelGGL((k_sigma_terms<T, 4, 4>), dim3(bl.n), dim3(1024), lds, ctx->stream, none,
                                none, ab, 0, 0, (const T*)nullptr, V, sp->norb, skip);
-        } else if (sp->abb.n > 0) {
+        } else if (bl.n > 0) {
             set_lds(k_sigma_terms<T, 2, 2>, (int)lds);
-            hipLaunchKernelGGL((k_sigma_terms<T, 2, 2>), dim3(sp->abb.n), dim3(1024), lds, ctx->stream, none,
+            hipLaunchKernelGGL((k_sigma_terms<T, 2, 2>), dim3(bl.n), dim3(1024), lds, ctx->stream, none,
                                none, ab, 0, 0, (const T*)nullptr, V, sp->norb, skip);
         }
     } else if (by_source) {

@@ -232,8 +232,12 @@ struct sqd_space {
     // (key: the pair of each chunk)
     ab_schedule<int> ab;
     // blocks of the one-launch products: G sources by one or two pairs (key: the
-    // pairs, second -1: one pair; grp: G singles of the first pair, G of the second)
-    ab_schedule<int2> abb;
+    // pairs, second -1: one pair; grp: G singles of the first pair, G of the second).
+    // FP64 and FP32 products of one space can take different G: one schedule for
+    // each, kept as long as the space (captured products hold its pointers)
+    ab_schedule<int2> abb[2];
+    ab_schedule<int2>& blocks(int G) { return abb[G == 4]; }   // G: 2 or 4
+    const ab_schedule<int2>& blocks(int G) const { return abb[G == 4]; }
     int* ab_rev = nullptr;        // alpha singles: entry of the neighbour's row pointing back
     int* ab_row_order = nullptr;  // alpha rows by decreasing number of singles (gather order)
     // the same singles grouped by source string (rows too long for two
@@ -317,7 +321,7 @@ int sqd_sigma_impl(sqd_ctx* ctx, sqd_space* sp, const double* c, double* sigma,
 int sqd_sigma_auto_path(sqd_ctx* ctx, const sqd_space* sp, int precision);
 bool sqd_sigma_prepared(sqd_ctx* ctx, const sqd_space* sp, int precision, unsigned mask, int ab_path);
 int sqd_ensure_ab_groups(sqd_ctx* ctx, sqd_space* sp, int G);
-int sqd_ensure_ab_blocks(sqd_ctx* ctx, sqd_space* sp, int G);   // sqd_space::abb
+int sqd_ensure_ab_blocks(sqd_ctx* ctx, sqd_space* sp, int G);   // sqd_space::blocks(G), G 2 or 4
 // the alpha singles grouped by source string, chunks of G (for the batched solver)
 int sqd_ensure_ab_source_groups(sqd_ctx* ctx, sqd_space* sp, int G);
 
