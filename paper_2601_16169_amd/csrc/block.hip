@@ -318,13 +318,16 @@ __global__ void __launch_bounds__(kThreads) k_bgcols(const double* __restrict__ 
     block_to_partial<kGB * NB>(acc, partial + (size_t)blockIdx.y * kGB * NB * gridDim.x, blockIdx.x, gridDim.x);
 }
 
+// Columns c0 .. c0 + nc of G from the partials of V^T AV (m includes them).  Among the
+// new columns both (r, c) and (c, r) are summed, by different workgroups and with
+// different rounding: the one with r <= c writes both places.
 template <int NB>
 __global__ void __launch_bounds__(kThreads) k_bgcols_fin(const double* __restrict__ partial, int nrows, blk_state* st,
                                                          int m, int c0, int nc) {
     int r, b;
     const double v = column_sum<NB>(partial, nrows, r, b);
-    if (threadIdx.x < kFinCols && r < m && b < nc) {
-        const int c = c0 + b;
+    const int c = c0 + b;
+    if (threadIdx.x < kFinCols && b < nc && r <= c) {   // (c < m)
         st->G[r * MM + c] = v;
         st->G[c * MM + r] = v;
     }
