@@ -102,6 +102,43 @@ inline std::vector<std::vector<int>> deal_bins(const std::vector<int>& cost) {
 // only the long rows pay for the sums across lanes.
 inline int split_cap(int64_t entries, int least) { return (int)std::max<int64_t>(least, (entries + 2047) / 2048); }
 
+// Slices of the sliced singles (ab_table) over rows sorted by length, dealt into bins.
+struct ab_plan {
+    std::vector<int> perm, split, blk{0}, cols, slot, bin, order;
+};
+inline ab_plan plan_ab(const std::vector<int>& rows, const int* off, int cap) {
+    const int n = (int)rows.size();
+    struct slice { int split, at, cols; };
+    std::vector<slice> sl;
+    std::vector<int> cost;
+    for (int at = 0; at < n;) {
+        const int len = off[rows[at] + 1] - off[rows[at]];   // the longest of the slice
+        const int k = split_of(len, cap);
+        sl.push_back({k, at, (len + (1 << k) - 1) >> k});
+        cost.push_back(sl.back().cols + 2);
+        at += 64 >> k;
+    }
+    const auto in = deal_bins(cost);
+    ab_plan p;
+    p.order.resize(sl.size());
+    for (int q = 0; q < kBins; ++q) {
+        p.bin.push_back((int)p.split.size());
+        for (int k : in[q]) {
+            p.order[k] = (int)p.split.size();   // (sl: the longest rows first)
+            p.slot.push_back((int)p.perm.size());
+            for (int j = 0; j < (64 >> sl[k].split); ++j)
+                p.perm.push_back(sl[k].at + j < n ? rows[sl[k].at + j] : n);
+            p.split.push_back(sl[k].split);
+            p.cols.push_back(sl[k].cols);
+            p.blk.push_back(p.blk.back() + (sl[k].cols + 3) / 4);
+        }
+    }
+    p.bin.push_back((int)p.split.size());
+    for (int q = 0; q <= kBins; ++q) p.bin.push_back(p.blk[p.bin[q]]);
+    while (p.perm.size() % 64) p.perm.push_back(n);
+    return p;
+}
+
 // (counting bits with the instruction: every host of these devices has it)
 #if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
 #pragma clang attribute push(__attribute__((target("popcnt"))), apply_to = function)

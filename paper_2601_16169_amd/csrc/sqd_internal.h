@@ -134,6 +134,7 @@ struct ab_table {
     const int* cols = nullptr;    // columns of each slice
     const int* slot = nullptr;    // first slot of each slice
     const int* bin = nullptr;     // kBins+1 slice offsets, then the block offsets of the same slices
+    const int* order = nullptr;   // whole rows: the slices, longest first
     uint32_t* ent = nullptr;      // entry q of lane l of block b at 256 b + 4 l + q: packed single
     int64_t nblk = 0;
 };

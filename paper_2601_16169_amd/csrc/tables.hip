@@ -519,41 +519,6 @@ sell_plan plan_slices(const std::vector<int>& rows, const int* s_off, const int*
     return p;
 }
 
-// The same for the singles alone (ab_table).
-struct ab_plan {
-    std::vector<int> perm, split, blk{0}, cols, slot, bin;
-};
-ab_plan plan_ab(const std::vector<int>& rows, const int* off, int cap) {
-    const int n = (int)rows.size();
-    struct slice { int split, at, cols; };
-    std::vector<slice> sl;
-    std::vector<int> cost;
-    for (int at = 0; at < n;) {
-        const int len = off[rows[at] + 1] - off[rows[at]];   // the longest of the slice
-        const int k = split_of(len, cap);
-        sl.push_back({k, at, (len + (1 << k) - 1) >> k});
-        cost.push_back(sl.back().cols + 2);
-        at += 64 >> k;
-    }
-    const auto in = deal_bins(cost);
-    ab_plan p;
-    for (int q = 0; q < kBins; ++q) {
-        p.bin.push_back((int)p.split.size());
-        for (int k : in[q]) {
-            p.slot.push_back((int)p.perm.size());
-            for (int j = 0; j < (64 >> sl[k].split); ++j)
-                p.perm.push_back(sl[k].at + j < n ? rows[sl[k].at + j] : n);
-            p.split.push_back(sl[k].split);
-            p.cols.push_back(sl[k].cols);
-            p.blk.push_back(p.blk.back() + (sl[k].cols + 3) / 4);
-        }
-    }
-    p.bin.push_back((int)p.split.size());
-    for (int q = 0; q <= kBins; ++q) p.bin.push_back(p.blk[p.bin[q]]);
-    while (p.perm.size() % 64) p.perm.push_back(n);
-    return p;
-}
-
 // Arrays of a sliced same-spin table whose plan is on the device.
 template <typename T>
 int fill_sell(sqd_ctx* ctx, sqd_space* sp, const spin_tables& t, const sell_plan& p, sell_table<T>& L) {
@@ -577,7 +542,7 @@ int fill_ab(sqd_ctx* ctx, sqd_space* sp, const spin_tables& t, const ab_plan& p,
     L.nblk = p.blk.back();
     if (L.nblk * 256 >= (1LL << 31)) return sqd_fail(ctx, SQD_E_LIMIT, "sliced table exceeds 2^31 slots");
     int rc;
-    if ((rc = sqd_alloc(ctx, (void**)&L.ent, sizeof(uint32_t) * (L.nblk + 1) * 256, &sp->bytes))) return rc;
+    if ((rc = sqd_alloc(ctx, (void**)&L.ent, sizeof(uint32_t) * (L.nblk + 2) * 256, &sp->bytes))) return rc;
     hipLaunchKernelGGL(k_ab_fill, dim3(L.nslices), dim3(256), 0, ctx->stream, L, t.n, t.s_off, t.s_pk);
     SQD_HIP(ctx, hipGetLastError());
     return SQD_OK;
@@ -639,8 +604,9 @@ int sqd_build_spin_tables(sqd_ctx* ctx, sqd_space* sp, int spin, const uint64_t*
             {&p32.perm, &t.ss32.perm}, {&p32.blk, &t.ss32.blk},   {&p32.s_blk, &t.ss32.s_blk}, {&p32.bin, &t.ss32.bin},
             {&p64.perm, &t.ss64.perm}, {&p64.blk, &t.ss64.blk},   {&p64.s_blk, &t.ss64.s_blk}, {&p64.bin, &t.ss64.bin},
             {&p64.split, &t.ss64.split}, {&a32.perm, &t.ab32.perm}, {&a32.blk, &t.ab32.blk},   {&a32.cols, &t.ab32.cols},
-            {&a32.slot, &t.ab32.slot}, {&a32.bin, &t.ab32.bin},   {&a64.perm, &t.ab64.perm},   {&a64.blk, &t.ab64.blk},
-            {&a64.cols, &t.ab64.cols}, {&a64.slot, &t.ab64.slot}, {&a64.bin, &t.ab64.bin},     {&a64.split, &t.ab64.split}};
+            {&a32.slot, &t.ab32.slot}, {&a32.bin, &t.ab32.bin},   {&a32.order, &t.ab32.order}, {&a64.perm, &t.ab64.perm},
+            {&a64.blk, &t.ab64.blk},   {&a64.cols, &t.ab64.cols}, {&a64.slot, &t.ab64.slot},   {&a64.bin, &t.ab64.bin},
+            {&a64.split, &t.ab64.split}};
         std::vector<int> all;
         for (const auto& q : parts) all.insert(all.end(), q.first->begin(), q.first->end());
         if ((rc = sqd_alloc(ctx, (void**)&t.sell_index, sizeof(int) * (all.size() + 1), &sp->bytes))) return rc;

@@ -82,3 +82,37 @@ int main() {
     return 0;
 }
 """)
+
+
+def test_slices_of_whole_rows_are_listed_longest_first(tmp_path):
+    """The order in which the row-staged alpha-beta kernel deals its slices: every
+    slice once, by decreasing columns, so that eight waves of eight slices each end a
+    pass within one slice of each other.  Uneven rows (the first reaches all others),
+    rows of one length, one string."""
+    _run(tmp_path, r"""
+int main() {
+    for (int n : {1, 64, 65, 700, 5000}) {
+        for (int uneven = 0; uneven < 2; ++uneven) {
+            std::vector<int> len(n), off(n + 1, 0);
+            for (int r = 0; r < n; ++r) len[r] = uneven ? n / (1 + r) : 7;
+            for (int r = 0; r < n; ++r) off[r + 1] = off[r] + len[r];
+            const ab_plan p = plan_ab(rows_longest_first(len), off.data(), 1 << 30);
+            const int ns = (int)p.split.size();
+            REQUIRE((int)p.order.size() == ns && ns == (n + 63) / 64);
+            std::vector<int> seen(ns, 0);
+            for (int k = 0; k < ns; ++k) {
+                REQUIRE(p.order[k] >= 0 && p.order[k] < ns && !seen[p.order[k]]++);
+                REQUIRE(p.split[p.order[k]] == 0);
+                REQUIRE(k == 0 || p.cols[p.order[k]] <= p.cols[p.order[k - 1]]);
+            }
+            const int groups = (ns + 63) / 64;
+            std::vector<int> load(8 * groups, 0);
+            for (int k = 0; k < ns; ++k) load[k % (8 * groups)] += p.cols[p.order[k]];
+            int lo = 1 << 30, hi = 0;
+            for (int x : load) lo = std::min(lo, x), hi = std::max(hi, x);
+            REQUIRE(hi - lo <= p.cols[p.order[0]]);
+        }
+    }
+    return 0;
+}
+""")
