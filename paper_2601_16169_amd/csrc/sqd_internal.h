@@ -170,7 +170,7 @@ struct spin_tables {
     // sliced singles for the alpha-beta kernels, rows sorted by their count:
     // whole rows (FP32), long rows over several lanes (FP64)
     ab_table ab32, ab64;
-    int* sell_index = nullptr;    // one allocation: the perms and offsets of the sliced tables
+    void* table_mem = nullptr;    // one allocation: the sliced tables with their plans, the values, e_same
     int max_singles = 0, max_doubles = 0;
     // host copies for the schedules that are planned there: strings and row
     // offsets from the build, the gather form on demand (sqd_host_singles)
