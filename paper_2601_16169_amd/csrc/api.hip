@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstring>
 
+#include "slices.h"
 #include "sqd_internal.h"
 
 #define SQD_VERSION_STRING "libsqd 0.1 gfx950"
@@ -125,11 +126,12 @@ static void space_release_device(sqd_space* sp) {
     sqd_release_stored_h(sp);
     sqd_free_spin_tables(&sp->sp[1]);
     sqd_free_spin_tables(&sp->sp[0]);
-    void* ptrs[] = {sp->diag, sp->ua, sp->ab.mem, sp->ab_rev, sp->kh_tile_off, sp->kh_pairs, sp->kh_map,
+    void* ptrs[] = {sp->diag, sp->ua, sp->cross_mem, sp->ab.mem, sp->ab_rev, sp->kh_tile_off, sp->kh_pairs, sp->kh_map,
                     sp->ab_row_order, sp->win_P, sp->abs.mem, sp->rdm_mem, sp->abb[0].mem, sp->abb[1].mem};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     sp->diag = sp->ua = nullptr;
+    sp->cross_mem = nullptr;
     sp->ab = sp->abs = ab_schedule<int>();
     sp->abb[0] = sp->abb[1] = ab_schedule<int2>();
     sp->ab_rev = sp->kh_tile_off = sp->kh_pairs = sp->kh_map = nullptr;
@@ -402,7 +404,8 @@ static int build_space_impl(sqd_ctx* ctx, int nalpha, int nbeta, int nw, const u
         return rc;
     }
     ctx->spaces.push_back(sp);
-    if ((rc = sqd_alloc_cross_tables(ctx, sp)) || (rc = sqd_build_values(ctx, sp)) || (rc = sqd_ensure_diag(ctx, sp))) {
+    alloc_cross_tables(ctx, sp);
+    if ((rc = sqd_build_values(ctx, sp)) || (rc = sqd_ensure_diag(ctx, sp))) {
         sqd_space_free(sp);
         return rc;
     }

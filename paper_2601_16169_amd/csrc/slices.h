@@ -139,6 +139,43 @@ inline ab_plan plan_ab(const std::vector<int>& rows, const int* off, int cap) {
     return p;
 }
 
+// Cross-spin tables (spin_tables::ws64, ws32) of the spins whose rows of C fit the
+// LDS four at a time, up to 256 MiB each, in one allocation.  Elsewhere, and where
+// that allocation fails, the row-staged kernel sums them itself (norb reads per value
+// and workgroup); the windowed kernel has its own.
+inline void alloc_cross_tables(sqd_ctx* ctx, sqd_space* sp) {
+    const size_t n2 = (size_t)sp->norb * sp->norb;
+    size_t total = 0, bytes64[2] = {}, bytes32[2] = {};
+    for (int spin = 0; spin < 2; ++spin) {
+        const spin_tables& t = sp->sp[spin];
+        if (t.alias) continue;
+        const size_t lds4 = ((size_t)sp->sp[1 - spin].n + 1 + n2) * 4;   // four rows, elements
+        const size_t m = (size_t)t.n * n2;
+        if (lds4 * sizeof(double) <= (size_t)ctx->max_lds && m * sizeof(double) <= (256u << 20))
+            bytes64[spin] = (m * sizeof(double) + 255) & ~(size_t)255;
+        if (lds4 * sizeof(float) <= (size_t)ctx->max_lds && m * sizeof(float) <= (256u << 20))
+            bytes32[spin] = (m * sizeof(float) + 255) & ~(size_t)255;
+        total += bytes64[spin] + bytes32[spin];
+    }
+    const std::string err = ctx->err;
+    if (!total || sqd_alloc(ctx, &sp->cross_mem, total, &sp->bytes) != SQD_OK) {
+        ctx->err = err;   // no failure of the call
+        return;
+    }
+    char* at = static_cast<char*>(sp->cross_mem);
+    for (int spin = 0; spin < 2; ++spin) {
+        spin_tables& t = sp->sp[spin];
+        if (bytes64[spin]) t.ws64 = reinterpret_cast<double*>(at);
+        at += bytes64[spin];
+        if (bytes32[spin]) t.ws32 = reinterpret_cast<float*>(at);
+        at += bytes32[spin];
+        if (t.alias) {
+            t.ws64 = sp->sp[0].ws64;
+            t.ws32 = sp->sp[0].ws32;
+        }
+    }
+}
+
 // (counting bits with the instruction: every host of these devices has it)
 #if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
 #pragma clang attribute push(__attribute__((target("popcnt"))), apply_to = function)

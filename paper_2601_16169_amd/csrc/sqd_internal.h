@@ -199,8 +199,8 @@ struct spin_tables {
     double* wg64 = nullptr; float* wg32 = nullptr;
     int wg_version = -1;
     // the same sums string-major, ws[s * norb^2 + pq], in the arithmetic of
-    // each precision, for the row-staged kernel (null where no precision's
-    // rows are staged whole, or the table would be large)
+    // each precision, for the row-staged kernel (alloc_cross_tables; null: it sums
+    // them itself)
     double* ws64 = nullptr; float* ws32 = nullptr;
 };
 
@@ -225,6 +225,7 @@ struct sqd_space {
     int values_version = -1;      // ham_version the values were built for
     int64_t dim = 0;
     int64_t bytes = 0;
+    void* cross_mem = nullptr;    // both spins' ws64 and ws32
     // diagonal cache (FP64), per Hamiltonian version
     double* diag = nullptr;
     int diag_version = -1;
@@ -308,7 +309,6 @@ int sqd_noalloc_init(int device);   // device address of the static product scra
 int sqd_build_spin_tables(sqd_ctx* ctx, sqd_space* sp, int spin, const uint64_t* host_str,
                           int64_t n, int nel);   // host_str: n x sp->nw words
 int sqd_host_singles(sqd_ctx* ctx, spin_tables& t);   // fills t.s_pk_host (synchronous)
-int sqd_alloc_cross_tables(sqd_ctx* ctx, sqd_space* sp);   // spin_tables::ws64, ws32 (both spins built)
 int sqd_build_values(sqd_ctx* ctx, sqd_space* sp);   // integral-dependent parts
 int sqd_ensure_split32(sqd_ctx* ctx, sqd_space* sp);   // spin_tables::split32 of both spins, current values
 void sqd_free_spin_tables(spin_tables* t);

@@ -663,32 +663,6 @@ int sqd_host_singles(sqd_ctx* ctx, spin_tables& t) {
     return SQD_OK;
 }
 
-// Cross-spin tables of the spins whose rows of C are staged whole (four rows
-// in LDS, as the same-spin dispatch wants), up to 256 MiB; elsewhere the
-// row-staged kernel sums them itself (norb reads per value and workgroup) and
-// the windowed kernel has its own.
-int sqd_alloc_cross_tables(sqd_ctx* ctx, sqd_space* sp) {
-    const size_t n2 = (size_t)sp->norb * sp->norb;
-    int rc;
-    for (int spin = 0; spin < 2; ++spin) {
-        spin_tables& t = sp->sp[spin];
-        if (t.alias) {
-            t.ws64 = sp->sp[0].ws64;
-            t.ws32 = sp->sp[0].ws32;
-            continue;
-        }
-        const size_t lds4 = ((size_t)sp->sp[1 - spin].n + 1 + n2) * 4;   // four rows, elements
-        const size_t m = (size_t)t.n * n2;
-        if (lds4 * sizeof(double) <= (size_t)ctx->max_lds && m * sizeof(double) <= (256u << 20) &&
-            (rc = sqd_alloc(ctx, (void**)&t.ws64, sizeof(double) * m, &sp->bytes)))
-            return rc;
-        if (lds4 * sizeof(float) <= (size_t)ctx->max_lds && m * sizeof(float) <= (256u << 20) &&
-            (rc = sqd_alloc(ctx, (void**)&t.ws32, sizeof(float) * m, &sp->bytes)))
-            return rc;
-    }
-    return SQD_OK;
-}
-
 int sqd_build_values(sqd_ctx* ctx, sqd_space* sp) {
     if (sp->values_version == ctx->ham_version) return SQD_OK;
     const int norb = sp->norb;
@@ -723,8 +697,7 @@ int sqd_build_values(sqd_ctx* ctx, sqd_space* sp) {
 void sqd_free_spin_tables(spin_tables* t) {
     if (t->alias) { *t = spin_tables(); return; }
     sqd_free_window_tables(t);
-    void* ptrs[] = {t->table_mem, t->split32.val, t->str, t->s_off, t->s_ent, t->d_off, t->d_ent, t->s_pk, t->d_nbr,
-                    t->ws64, t->ws32};
+    void* ptrs[] = {t->table_mem, t->split32.val, t->str, t->s_off, t->s_ent, t->d_off, t->d_ent, t->s_pk, t->d_nbr};
     for (void* p : ptrs)
         if (p) hipFree(p);
     *t = spin_tables();

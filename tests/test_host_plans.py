@@ -116,3 +116,51 @@ int main() {
     return 0;
 }
 """)
+
+
+def test_cross_tables_are_optional(tmp_path):
+    """A space whose cross-spin tables cannot be allocated is built without them (the
+    kernels then sum them), and the call leaves no error; where they can, each spin has
+    its own, aligned, within one allocation."""
+    _run(tmp_path, r"""
+int main() {
+    sqd_ctx ctx;
+    ctx.max_lds = 160 * 1024;
+    ctx.err = "earlier";
+    for (int alias = 0; alias < 2; ++alias) {
+        sqd_space sp;
+        sp.norb = 10;
+        sp.sp[0].n = 77;
+        sp.sp[1].n = alias ? 77 : 4000;      // rows of 4000: four fit, and four of 77
+        sp.sp[1].alias = alias;
+        allocs_left = 0;
+        alloc_cross_tables(&ctx, &sp);
+        REQUIRE(!sp.cross_mem && sp.bytes == 0 && ctx.err == "earlier");
+        for (const auto& t : sp.sp) REQUIRE(!t.ws64 && !t.ws32);
+        allocs_left = 1 << 30;
+        alloc_cross_tables(&ctx, &sp);
+        REQUIRE(sp.cross_mem && held == 1 && ctx.err == "earlier");
+        const char *from = (const char*)sp.cross_mem, *to = from + sp.bytes;
+        for (const auto& t : sp.sp) {
+            REQUIRE((const char*)t.ws64 >= from && (const char*)(t.ws64 + t.n * 100) <= to);
+            REQUIRE((const char*)t.ws32 >= from && (const char*)(t.ws32 + t.n * 100) <= to);
+            REQUIRE(((const char*)t.ws64 - from) % 256 == 0 && ((const char*)t.ws32 - from) % 256 == 0);
+        }
+        REQUIRE((sp.sp[0].ws64 == sp.sp[1].ws64) == (alias == 1));
+        hipFree(sp.cross_mem);
+    }
+    sqd_space sp;                             // rows too long for four: FP32 alone, or none
+    sp.norb = 10;
+    sp.sp[0].n = 6000;
+    sp.sp[1].n = 12000;
+    alloc_cross_tables(&ctx, &sp);
+    REQUIRE(sp.cross_mem && !sp.sp[0].ws64 && !sp.sp[0].ws32 && !sp.sp[1].ws64 && sp.sp[1].ws32);
+    hipFree(sp.cross_mem);
+    sqd_space none;
+    none.norb = 10;
+    none.sp[0].n = none.sp[1].n = 12000;
+    alloc_cross_tables(&ctx, &none);
+    REQUIRE(!none.cross_mem && held == 0);
+    return 0;
+}
+""")
