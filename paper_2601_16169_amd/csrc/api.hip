@@ -127,7 +127,7 @@ static void space_release_device(sqd_space* sp) {
     sqd_free_spin_tables(&sp->sp[1]);
     sqd_free_spin_tables(&sp->sp[0]);
     void* ptrs[] = {sp->diag, sp->ua, sp->cross_mem, sp->ab.mem, sp->ab_rev, sp->kh_tile_off, sp->kh_pairs, sp->kh_map,
-                    sp->ab_row_order, sp->win_P, sp->abs.mem, sp->rdm_mem, sp->abb[0].mem, sp->abb[1].mem};
+                    sp->win_P, sp->abs.mem, sp->rdm_mem, sp->abb[0].mem, sp->abb[1].mem};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     sp->diag = sp->ua = nullptr;
@@ -135,7 +135,6 @@ static void space_release_device(sqd_space* sp) {
     sp->ab = sp->abs = ab_schedule<int>();
     sp->abb[0] = sp->abb[1] = ab_schedule<int2>();
     sp->ab_rev = sp->kh_tile_off = sp->kh_pairs = sp->kh_map = nullptr;
-    sp->ab_row_order = nullptr;
     sp->rdm_mem = nullptr;
     sp->win_P = nullptr;
     sp->win_P_bytes = 0;

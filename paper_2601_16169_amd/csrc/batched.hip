@@ -947,7 +947,7 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
         d.out = vecs[b];
         d.noise = nullptr;
         d.a_off = A.s_off;
-        d.a_order = sp->ab_row_order;
+        d.a_order = A.by_singles;
         d.st = p.states + b;
         // same-spin: BB on C (rows alpha, columns beta, diagonal fused), AA on C^T
         if (one) {
@@ -956,8 +956,8 @@ int sqd_davidson_batched_impl(sqd_ctx* ctx, int nspace, sqd_space* const* spaces
             d.aa32 = ss_args<float>{d.c32, d.Yt32, B.n, A.n, A.split32, B.ws32, B.str, B.nw, nullptr, 0, 1};
             d.bb32 = ss_args<float>{d.c32, d.S32, A.n, B.n, B.split32, A.ws32, A.str, A.nw, nullptr, 0, 0};
             const ab_schedule<int2>& bl = sp->blocks(p.classes[cls[b]].R);
-            d.abb64 = abb_args<double>{d.cin, d.Y64, B.n, bl.grp, bl.key, B.ab64};
-            d.abb32 = abb_args<float>{d.c32, d.Y32, B.n, bl.grp, bl.key, B.ab64};
+            d.abb64 = abb_args<double>{d.cin, d.Y64, B.n, bl.grp, bl.key, bl.n2, B.ab64};
+            d.abb32 = abb_args<float>{d.c32, d.Y32, B.n, bl.grp, bl.key, bl.n2, B.ab64};
             // as many groups of threads of the gather as read a row of Y side by side
             const int per = (int)((B.ab64.nslots / 2 + 63) / 64 * 64);
             d.ng = p.gather_lds64 ? std::max(1, std::min(kGatherThreads / std::max(per, 64), 4)) : 1;

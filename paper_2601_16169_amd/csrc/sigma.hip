@@ -463,21 +463,6 @@ int ab_group_size(sqd_ctx* ctx, const sqd_space* sp) {
     return 0;
 }
 
-// Gather order: heaviest alpha rows first, so that the rows with the most
-// singles start together on different compute units.
-int ensure_ab_row_order(sqd_ctx* ctx, sqd_space* sp) {
-    if (sp->ab_row_order) return SQD_OK;
-    const spin_tables& A = sp->sp[0];
-    const std::vector<int>& off = A.s_off_host;
-    std::vector<int> order(A.n);
-    for (int64_t r = 0; r < A.n; ++r) order[r] = (int)r;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int x, int y) { return off[x + 1] - off[x] > off[y + 1] - off[y]; });
-    const host_part part{order.data(), sizeof(int) * order.size()};
-    size_t at;
-    return upload_parts(ctx, &part, 1, (void**)&sp->ab_row_order, &at, &sp->bytes);
-}
-
 // Group the alpha singles (CSR positions) by orbital pair, padded to chunks of G.
 int ensure_ab_groups_impl(sqd_ctx* ctx, sqd_space* sp, int G) {
     if (sp->ab.built(G)) return SQD_OK;
@@ -499,7 +484,6 @@ int ensure_ab_groups_impl(sqd_ctx* ctx, sqd_space* sp, int G) {
             cp.push_back(p);
         }
     }
-    if ((rc = ensure_ab_row_order(ctx, sp))) return rc;
     return upload_schedule(ctx, G, grp, cp, sp->ab, &sp->bytes);
 }
 
@@ -511,10 +495,8 @@ int sqd_ensure_ab_blocks(sqd_ctx* ctx, sqd_space* sp, int G) {
     spin_tables& A = sp->sp[0];
     int rc;
     if ((rc = sqd_host_singles(ctx, A))) return rc;
-    std::vector<int2> grp, pairs;
-    plan_ab_blocks(A.s_pk_host, A.n, sp->norb, G, grp, pairs);
-    if ((rc = ensure_ab_row_order(ctx, sp))) return rc;
-    return upload_schedule(ctx, G, grp, pairs, sp->blocks(G), &sp->bytes);
+    const ab_block_plan plan = plan_ab_blocks(A.s_pk_host, A.n, sp->norb, G);
+    return upload_schedule(ctx, G, plan.grp.get(), plan.size, plan.n2, plan.pairs, sp->blocks(G), &sp->bytes);
 }
 
 namespace {
@@ -571,9 +553,7 @@ int ensure_ab_source_groups(sqd_ctx* ctx, sqd_space* sp, int G) {
 const ab_table& ab_tab(const spin_tables& t, size_t es) { return es == sizeof(double) ? t.ab64 : t.ab32; }
 
 // The blocks of the one-launch products exist (of G sources each).
-bool ab_blocks_built(const sqd_space* sp, int G) {
-    return sp->blocks(G).built(G) && sp->ab_row_order;
-}
+bool ab_blocks_built(const sqd_space* sp, int G) { return sp->blocks(G).built(G); }
 // ... and serve a product of element size es where a capture began before the
 // separate kernels' schedule was built: the most sources of those built (0: none).
 int ab_blocks_usable(sqd_ctx* ctx, const sqd_space* sp, size_t es) {
@@ -609,10 +589,10 @@ int launch_ab_gather(sqd_ctx* ctx, sqd_space* sp, const gather_args<T>& a, const
         const int ng = sizeof(T) == 8 ? std::min(8, most / per) : 1;
         set_lds(k_ab_gather<T, true>, (int)(ng * row_bytes));
         hipLaunchKernelGGL((k_ab_gather<T, true>), dim3((unsigned)na), dim3(per * ng), (size_t)(ng * row_bytes),
-                           ctx->stream, a, ng, sp->ab_row_order, skip);
+                           ctx->stream, a, ng, sp->sp[0].by_singles, skip);
     } else {
         hipLaunchKernelGGL((k_ab_gather<T, false>), dim3((unsigned)na), dim3(per), 0, ctx->stream, a, 1,
-                           sp->ab_row_order, skip);
+                           sp->sp[0].by_singles, skip);
     }
     SQD_HIP(ctx, hipGetLastError());
     return SQD_OK;
@@ -670,26 +650,34 @@ int launch_fused(sqd_ctx* ctx, sqd_space* sp, const fused_shape& f, const T* C, 
     const spin_tables& A = sp->sp[0];
     const spin_tables& B = sp->sp[1];
     int rc;
-    if ((rc = sqd_ensure_ab_blocks(ctx, sp, f.G))) return rc;
     if (any_order && (rc = sqd_ensure_split32(ctx, sp))) return rc;
     const ab_table& tab = any_order ? B.ab64 : ab_tab(B, sizeof(T));
     ss_args<T> bb{C, S, A.n, B.n, same_spin_table<T>(B, any_order), cross_table<T>(A), A.str, A.nw, nullptr, 0, 0};
     ss_args<T> aa{C, S2, B.n, A.n, same_spin_table<T>(A, any_order), cross_table<T>(B), B.str, B.nw, nullptr, 0, 1};
-    const ab_schedule<int2>& blocks = sp->blocks(f.G);
-    abb_args<T> ab{C, Y, B.n, blocks.grp, blocks.key, tab};
     const int n_bb = (int)nblk(A.n, f.R), n_aa = (int)nblk(B.n, f.R);
-    {
+    auto launch = [&](int bbs, int aas, const ab_schedule<int2>& blocks) -> int {
+        if (bbs + aas + blocks.n == 0) return SQD_OK;
         prof_scope ps(ctx, sizeof(T) == 8 ? "k_sigma_terms<double>" : "k_sigma_terms<float>");
-        const dim3 grid(n_bb + n_aa + blocks.n), block(64 * f.waves);
-        auto launch = [&](auto k) {
+        const abb_args<T> ab{C, Y, B.n, blocks.grp, blocks.key, blocks.n2, tab};
+        auto go = [&](auto k) {
             constexpr int K = decltype(k)::value;
             set_lds(k_sigma_terms<T, K, K>, (int)f.lds);
-            hipLaunchKernelGGL((k_sigma_terms<T, K, K>), grid, block, f.lds, ctx->stream, bb, aa, ab, n_bb, n_aa, jk,
-                               V, sp->norb, skip);
+            hipLaunchKernelGGL((k_sigma_terms<T, K, K>), dim3(bbs + aas + blocks.n), dim3(64 * f.waves), f.lds,
+                               ctx->stream, bb, aa, ab, bbs, aas, jk, V, sp->norb, skip);
         };
-        if (f.R == 4) launch(std::integral_constant<int, 4>());
-        else launch(std::integral_constant<int, 2>());
+        if (f.R == 4) go(std::integral_constant<int, 4>());
+        else go(std::integral_constant<int, 2>());
         SQD_HIP(ctx, hipGetLastError());
+        return SQD_OK;
+    };
+    if (ab_blocks_built(sp, f.G)) {
+        if ((rc = launch(n_bb, n_aa, sp->blocks(f.G)))) return rc;
+    } else {
+        // the first product: the same-spin rows run while the blocks are planned on the
+        // host (2000 strings of 16 orbitals a spin: 1180 us planned before, 790 so, 640 a
+        // repeated product; 4500 x 200: 1610 / 1180 / 500)
+        if ((rc = sqd_host_singles(ctx, sp->sp[0])) || (rc = launch(n_bb, n_aa, ab_schedule<int2>()))) return rc;
+        if ((rc = sqd_ensure_ab_blocks(ctx, sp, f.G)) || (rc = launch(0, 0, sp->blocks(f.G)))) return rc;
     }
     return launch_ab_gather<T>(ctx, sp, gather_args<T>{Y, B.n, tab.nslots, tab.perm, A.s_off, S, S2, diag, c64, out64},
                                skip);
@@ -708,7 +696,7 @@ int launch_ab_grouped(sqd_ctx* ctx, sqd_space* sp, const T* C, T* S, T* Y, const
         // captured after one-launch products only: their blocks
         const size_t lds = (((size_t)B.n + 1) * blocks + 2 * (size_t)sp->norb * sp->norb) * sizeof(T);
         const ab_schedule<int2>& bl = sp->blocks(blocks);
-        abb_args<T> ab{C, Y, B.n, bl.grp, bl.key, tab};
+        abb_args<T> ab{C, Y, B.n, bl.grp, bl.key, bl.n2, tab};
         const ss_args<T> none{};
         if (bl.n > 0 && blocks == 4) {
             set_lds(k_sigma_terms<T, 4, 4>, (int)lds);
@@ -721,7 +709,7 @@ int launch_ab_grouped(sqd_ctx* ctx, sqd_space* sp, const T* C, T* S, T* Y, const
         }
     } else if (by_source) {
         const int GS = ab_source_group_size(ctx, sp);
-        if ((rc = ensure_ab_row_order(ctx, sp)) || (rc = ensure_ab_source_groups(ctx, sp, GS))) return rc;
+        if ((rc = ensure_ab_source_groups(ctx, sp, GS))) return rc;
         if (sp->abs.n > 0) {
             const size_t lds = ((size_t)(B.n + 1) + (size_t)GS * sp->norb * sp->norb) * sizeof(T);
             const int nw = ctx->tune[SQD_TUNE_AB_WAVES] ? ctx->tune[SQD_TUNE_AB_WAVES] : 16;
@@ -775,8 +763,7 @@ int launch_ab_grouped(sqd_ctx* ctx, sqd_space* sp, const T* C, T* S, T* Y, const
 
 int sqd_ensure_ab_groups(sqd_ctx* ctx, sqd_space* sp, int G) { return ensure_ab_groups_impl(ctx, sp, G); }
 int sqd_ensure_ab_source_groups(sqd_ctx* ctx, sqd_space* sp, int G) {
-    int rc = ensure_ab_row_order(ctx, sp);
-    return rc ? rc : ensure_ab_source_groups(ctx, sp, G);
+    return ensure_ab_source_groups(ctx, sp, G);
 }
 
 int sqd_ensure_diag(sqd_ctx* ctx, sqd_space* sp) {
@@ -842,8 +829,8 @@ bool sqd_sigma_prepared(sqd_ctx* ctx, const sqd_space* sp, int precision, unsign
     if (ab_grouped_bytes(ctx, sp, es) == 0) return true;   // row-staged kernel: nothing per space
     if (ab_blocks_usable(ctx, sp, es)) return true;
     if (ab_use_source_groups(ctx, sp))
-        return sp->abs.built(ab_source_group_size(ctx, sp)) && sp->ab_row_order != nullptr;
-    return sp->ab.built(ab_group_size(ctx, sp)) && sp->ab_row_order != nullptr;
+        return sp->abs.built(ab_source_group_size(ctx, sp));
+    return sp->ab.built(ab_group_size(ctx, sp));
 }
 
 // True when the arrays that a space's first product builds exist for a

@@ -448,8 +448,9 @@ struct abb_args {
     const T* C;
     T* Y;
     int64_t nb;
-    const int2* grp;          // blocks x 2 x G alpha singles: CSR position (-1 = padding), gather form
-    const int2* pair;         // second -1: one pair
+    const int2* grp;          // alpha singles: CSR position (-1 = padding), gather form
+    const int2* pair;
+    int n2;                   // the first n2 blocks: G singles of pair.x, G of pair.y; the others G of pair.x
     ab_table tab;
 };
 
@@ -466,9 +467,10 @@ __device__ __forceinline__ void abb_walk(const abb_args<T>& a, const T* __restri
     uint32_t neg = 0;
     {
         const T* rows[G];
+        const int2* grp = a.grp + (chunk + (P > 1 ? chunk : a.n2)) * G;
 #pragma unroll
         for (int r = 0; r < P * G; ++r) {
-            const int2 x = a.grp[chunk * 2 * G + r];
+            const int2 x = grp[r];
             e[r] = x.x;
             neg |= ((uint32_t)x.y >> 31) << r;
             if (r < G) rows[r] = e[r] >= 0 ? a.C + (int64_t)((uint32_t)x.y & SQD_NBR_MASK) * nb : nullptr;
@@ -519,7 +521,7 @@ template <typename T, int G>
 __device__ __forceinline__ void abb_block(const abb_args<T>& a, const T* __restrict__ V, int norb, int64_t chunk,
                                           unsigned char* lds_raw) {
     const int2 pair = a.pair[chunk];
-    if (pair.y < 0) abb_walk<T, G, 1>(a, V, norb, chunk, pair, lds_raw);
+    if (chunk >= a.n2) abb_walk<T, G, 1>(a, V, norb, chunk, pair, lds_raw);
     else abb_walk<T, G, 2>(a, V, norb, chunk, pair, lds_raw);
 }
 

@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <memory>
 #include <vector>
 
 #include "sqd_internal.h"
@@ -21,13 +22,19 @@ inline int upload_parts(sqd_ctx* ctx, const host_part* parts, int n, void** mem,
         total += (parts[k].bytes + 255) & ~(size_t)255;
     }
     total += 256;
-    std::vector<char> all(total);
-    for (int k = 0; k < n; ++k)
-        if (parts[k].bytes) std::memcpy(all.data() + off[k], parts[k].data, parts[k].bytes);
     void* p = nullptr;
     const int rc = sqd_alloc(ctx, &p, total, nullptr);
     if (rc) return rc;
-    const hipError_t e = sqd_copy_now(ctx, p, all.data(), total, hipMemcpyHostToDevice);
+    hipError_t e = hipSuccess;
+    if (total <= 64 * 1024) {   // one copy; of larger arrays gathering them costs more
+        std::vector<char> all(total);
+        for (int k = 0; k < n; ++k)
+            if (parts[k].bytes) std::memcpy(all.data() + off[k], parts[k].data, parts[k].bytes);
+        e = sqd_copy_now(ctx, p, all.data(), total, hipMemcpyHostToDevice);
+    } else {
+        for (int k = 0; k < n && e == hipSuccess; ++k)
+            e = sqd_copy_now(ctx, static_cast<char*>(p) + off[k], parts[k].data, parts[k].bytes, hipMemcpyHostToDevice);
+    }
     if (e != hipSuccess) {
         (void)hipFree(p);
         return sqd_hip_fail(ctx, e, "upload of a host plan");
@@ -37,24 +44,31 @@ inline int upload_parts(sqd_ctx* ctx, const host_part* parts, int n, void** mem,
     return SQD_OK;
 }
 
-// The schedule s from chunks of G; the one it replaces is freed once the new one
-// is whole, and stays if that fails.
+// The schedule s from chunks of G (n2 of them: ab_schedule::n2); the one it replaces
+// is freed once the new one is whole, and stays if that fails.
 template <typename K>
-int upload_schedule(sqd_ctx* ctx, int G, const std::vector<int2>& grp, const std::vector<K>& key, ab_schedule<K>& s,
-                    int64_t* counter) {
-    const host_part parts[] = {{grp.data(), sizeof(int2) * grp.size()}, {key.data(), sizeof(K) * key.size()}};
+int upload_schedule(sqd_ctx* ctx, int G, const int2* grp, size_t size, int n2, const std::vector<K>& key,
+                    ab_schedule<K>& s, int64_t* counter) {
+    const host_part parts[] = {{grp, sizeof(int2) * size}, {key.data(), sizeof(K) * key.size()}};
     size_t off[2];
     ab_schedule<K> t;
     const int rc = upload_parts(ctx, parts, 2, &t.mem, off, &t.bytes);
     if (rc) return rc;
     t.G = G;
     t.n = (int)key.size();
+    t.n2 = n2;
     t.grp = reinterpret_cast<const int2*>(static_cast<char*>(t.mem) + off[0]);
     t.key = reinterpret_cast<const K*>(static_cast<char*>(t.mem) + off[1]);
     if (s.mem) (void)hipFree(s.mem);
     *counter += t.bytes - s.bytes;
     s = t;
     return SQD_OK;
+}
+
+template <typename K>
+int upload_schedule(sqd_ctx* ctx, int G, const std::vector<int2>& grp, const std::vector<K>& key, ab_schedule<K>& s,
+                    int64_t* counter) {
+    return upload_schedule(ctx, G, grp.data(), grp.size(), 0, key, s, counter);
 }
 
 // Rows by decreasing length (ties by index): a counting sort.
@@ -180,71 +194,63 @@ inline void alloc_cross_tables(sqd_ctx* ctx, sqd_space* sp) {
 #if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
 #pragma clang attribute push(__attribute__((target("popcnt"))), apply_to = function)
 #endif
-inline int bits_in_common(const uint64_t* a, const uint64_t* b, size_t words) {
-    int c = 0;
-    for (size_t w = 0; w < words; ++w) c += __builtin_popcountll(a[w] & b[w]);
-    return c;
-}
-
 // Blocks of G alpha singles of one pair, or of G sources by two pairs that both
-// excite, from the singles in gather form (nbr | pair << 19 | negative << 31, in
-// CSR order): grp lists 2 G singles a block (CSR position, gather form; -1 where
-// none), pairs the one or two pairs.  In a round the pairs of each orbital are
-// matched, the one with the most sources left with the one that shares most of
-// them, as long as they fill a block; the rounds go over the created and the
-// annihilated orbital by turns, until one adds less than 4% of the singles (eight
-// at most).  What is left goes to blocks of one pair.  2000 strings of 24
-// orbitals: 62% of the singles in blocks of two pairs and 6100 walks of the beta
-// table instead of 8800, planned in 0.6 ms; choosing the best two of all pairs
-// each time finds 76% in 2.4 ms (5000 strings of 36 orbitals: 3.6 and 38 ms), and
-// four pairs to a block save 2% of the reads more.
-inline void plan_ab_blocks(const std::vector<uint32_t>& pk, int64_t n, int norb, int G, std::vector<int2>& grp,
-                           std::vector<int2>& pairs) {
+// excite, from the singles in gather form (nbr | pair << 17 | negative << 31, in
+// CSR order).  In a round the pairs of each orbital are matched, the one with the
+// most sources left with the one that shares most of them, as long as they fill a
+// block; the rounds go over the created and the annihilated orbital by turns, until
+// one adds less than 4% of the singles (eight at most).  What is left goes to blocks
+// of one pair.  2000 strings of 16 orbitals: 62% of the singles in blocks of two pairs
+// and 6100 walks of the beta table instead of 8800 (24 orbitals: 36%); choosing the
+// best two of all pairs each time finds 76% in four times the time, and four pairs to
+// a block save 2% of the reads more.
+struct ab_block_plan {
+    std::unique_ptr<int2[]> grp;   // 2 G singles of each block of two pairs, then G of each of one (sqd_space::abb)
+    size_t size = 0;
+    int n2 = 0;                    // blocks of two pairs
+    std::vector<int2> pairs;       // the pairs of each block (second -1: one)
+};
+inline ab_block_plan plan_ab_blocks(const std::vector<uint32_t>& pk, int64_t n, int norb, int G) {
     const int npair = norb * norb;
     const size_t words = (size_t)(n + 63) / 64;
-    auto src_of = [&](int e) { return pk[e] & SQD_NBR_MASK; };
-    auto pair_of = [&](int e) { return (int)((pk[e] >> SQD_PAIR_SHIFT) & SQD_PAIR_MASK); };
-    // the sources of each pair as bits, and its singles by source: the single of
-    // source j is at the rank of its bit
-    std::vector<uint64_t> all((size_t)npair * words, 0);
-    std::vector<int> rank((size_t)npair * words), first(npair + 1, 0), ent(pk.size()), count(npair);
-    for (size_t e = 0; e < pk.size(); ++e) {
-        const uint32_t j = src_of((int)e);
-        all[pair_of((int)e) * words + (j >> 6)] |= 1ull << (j & 63);
-        first[pair_of((int)e) + 1] += 1;
-    }
+    // the singles by pair.  The strings of a pair's targets are those of its sources
+    // plus one number, and the strings ascend, so CSR order is the order of the sources
+    std::vector<int> first(npair + 1, 0), count(npair), at(npair);
+    for (uint32_t x : pk) first[((x >> SQD_PAIR_SHIFT) & SQD_PAIR_MASK) + 1] += 1;
+    size_t blocks = 0;   // at most
     for (int p = 0; p < npair; ++p) {
         count[p] = first[p + 1];
+        blocks += (size_t)(count[p] + G - 1) / G;
         first[p + 1] += first[p];
-        int at = first[p];
-        if (!count[p]) continue;
+        at[p] = first[p];
+    }
+    // all: the sources of each pair as bits; left: those not in a block; rank: the
+    // single of the first source of a word
+    std::unique_ptr<int2[]> one(new int2[pk.size() + 1]);
+    std::vector<uint64_t> all((size_t)npair * words, 0);
+    for (size_t e = 0; e < pk.size(); ++e) {
+        const uint32_t x = pk[e], j = x & SQD_NBR_MASK;
+        const int p = (int)((x >> SQD_PAIR_SHIFT) & SQD_PAIR_MASK);
+        one[at[p]++] = make_int2((int)e, (int)x);
+        all[p * words + (j >> 6)] |= 1ull << (j & 63);
+    }
+    std::vector<uint64_t> left = all, any(words), many(words), bits;
+    std::unique_ptr<int[]> rank(new int[(size_t)npair * words]);
+    std::vector<int> line, used, most_of(npair);
+    for (int p = 0; p < npair; ++p) {
+        if (count[p] < G) continue;   // (never matched)
+        int r = first[p];
         for (size_t w = 0; w < words; ++w) {
-            rank[p * words + w] = at;
-            at += __builtin_popcountll(all[p * words + w]);
+            rank[p * words + w] = r;
+            r += __builtin_popcountll(all[p * words + w]);
         }
     }
-    auto place = [&](int p, uint32_t j) {
-        return rank[p * words + (j >> 6)] + __builtin_popcountll(all[p * words + (j >> 6)] & ((1ull << (j & 63)) - 1));
-    };
-    for (size_t e = 0; e < pk.size(); ++e) ent[place(pair_of((int)e), src_of((int)e))] = (int)e;
-    std::vector<uint64_t> left = all;
-    grp.reserve(pk.size() * 2);
-    auto add = [&](int p, int q, const uint32_t* src, int m) {
-        for (int half = 0; half < 2; ++half)
-            for (int r = 0; r < G; ++r) {
-                if (r < m && (half == 0 || q >= 0)) {
-                    const int e = ent[place(half ? q : p, src[r])];
-                    grp.push_back(make_int2(e, (int)pk[e]));
-                } else {
-                    grp.push_back(make_int2(-1, 0));
-                }
-            }
-        pairs.push_back(make_int2(p, q));
-    };
-    std::vector<uint32_t> src(n);
-    std::vector<int> line;
-    size_t before = 0;
-    for (int round = 0; round < 8; ++round) {
+    ab_block_plan plan;
+    plan.grp.reset(new int2[blocks * G + 1]);
+    plan.pairs.reserve(blocks);
+    int2* out = plan.grp.get();
+    int matched = 0;
+    for (int round = 0, before = 0; round < 8; ++round) {
         for (int i = 0; i < norb; ++i) {
             // the pairs of one orbital: by turns with i created and annihilated
             line.clear();
@@ -252,18 +258,50 @@ inline void plan_ab_blocks(const std::vector<uint32_t>& pk, int64_t n, int norb,
                 const int p = round % 2 ? a * norb + i : i * norb + a;
                 if (count[p] >= G) line.push_back(p);
             }
+            if (line.size() < 2) continue;
+            // many: the sources that two pairs or more share; most_of: as many can a
+            // pair share with another
+            std::fill(any.begin(), any.end(), 0);
+            std::fill(many.begin(), many.end(), 0);
+            for (int p : line)
+                for (size_t w = 0; w < words; ++w) {
+                    const uint64_t x = left[p * words + w];
+                    many[w] |= any[w] & x;
+                    any[w] |= x;
+                }
+            size_t keep = 0;
+            for (int p : line) {
+                int c = 0;
+                for (size_t w = 0; w < words; ++w) c += __builtin_popcountll(left[p * words + w] & many[w]);
+                most_of[p] = c;
+                if (c >= G) line[keep++] = p;
+            }
+            line.resize(keep);
             while (line.size() > 1) {
-                size_t at = 0, with = 0;
+                size_t big = 0, with = 0;
                 for (size_t k = 1; k < line.size(); ++k)
-                    if (count[line[k]] > count[line[at]]) at = k;
-                const int p = line[at];
-                std::swap(line[at], line.back());
+                    if (count[line[k]] > count[line[big]]) big = k;
+                const int p = line[big];
+                std::swap(line[big], line.back());
                 line.pop_back();
                 uint64_t* lp = left.data() + p * words;
+                // (a pair of few sources: the words that hold them)
+                const bool few = (size_t)most_of[p] < words;
+                if (few) {
+                    used.clear();
+                    bits.clear();
+                    for (size_t w = 0; w < words; ++w)
+                        if (lp[w] & many[w]) used.push_back((int)w), bits.push_back(lp[w] & many[w]);
+                }
                 int most = G - 1;
                 for (size_t k = 0; k < line.size(); ++k) {
-                    if (count[line[k]] <= most) continue;
-                    const int c = bits_in_common(lp, left.data() + line[k] * words, words);
+                    if (most_of[line[k]] <= most) continue;
+                    const uint64_t* lk = left.data() + line[k] * words;
+                    int c = 0;
+                    if (few)
+                        for (size_t u = 0; u < used.size(); ++u) c += __builtin_popcountll(bits[u] & lk[used[u]]);
+                    else
+                        for (size_t w = 0; w < words; ++w) c += __builtin_popcountll(lp[w] & lk[w]);
                     if (c > most) most = c, with = k;
                 }
                 if (most < G) continue;
@@ -271,31 +309,48 @@ inline void plan_ab_blocks(const std::vector<uint32_t>& pk, int64_t n, int norb,
                 std::swap(line[with], line.back());
                 line.pop_back();
                 uint64_t* lq = left.data() + q * words;
+                const uint64_t *ap = all.data() + p * words, *aq = all.data() + q * words;
+                const int *rp = rank.get() + p * words, *rq = rank.get() + q * words;
                 const int m = most / G * G;
                 int got = 0;
                 for (size_t w = 0; w < words && got < m; ++w) {
-                    uint64_t taken = 0;
-                    for (uint64_t x = lp[w] & lq[w]; x && got < m; x &= x - 1) {
-                        src[got++] = (uint32_t)(64 * w + __builtin_ctzll(x));
-                        taken |= x & (~x + 1);
+                    const uint64_t both = lp[w] & lq[w];
+                    uint64_t x = both;
+                    for (; x && got < m; x &= x - 1) {
+                        const uint64_t below = (x & (~x + 1)) - 1;
+                        out[0] = one[rp[w] + __builtin_popcountll(ap[w] & below)];
+                        out[G] = one[rq[w] + __builtin_popcountll(aq[w] & below)];
+                        ++out;
+                        if (++got % G == 0) out += G;
                     }
-                    lp[w] &= ~taken;
-                    lq[w] &= ~taken;
+                    lp[w] &= ~(both & ~x);
+                    lq[w] &= ~(both & ~x);
                 }
-                for (int k = 0; k < m; k += G) add(p, q, src.data() + k, G);
+                plan.pairs.insert(plan.pairs.end(), m / G, make_int2(p, q));
                 count[p] -= m;
                 count[q] -= m;
+                matched += 2 * m;
             }
         }
-        if ((grp.size() - before) * 25 < pk.size()) break;
-        before = grp.size();
+        if ((matched - before) * (int64_t)25 < (int64_t)pk.size()) break;
+        before = matched;
     }
+    plan.n2 = (int)plan.pairs.size();
     for (int p = 0; p < npair; ++p) {
-        int got = 0;
-        for (size_t w = 0; w < words && got < count[p]; ++w)
-            for (uint64_t x = left[p * words + w]; x; x &= x - 1) src[got++] = (uint32_t)(64 * w + __builtin_ctzll(x));
-        for (int k = 0; k < got; k += G) add(p, -1, src.data() + k, std::min(G, got - k));
+        const int2* from = one.get() + first[p];
+        int2* const to = out;
+        if (count[p] == first[p + 1] - first[p]) {
+            out = std::copy(from, from + count[p], out);
+        } else {
+            for (size_t w = 0; w < words; ++w)
+                for (uint64_t x = left[p * words + w]; x; x &= x - 1)
+                    *out++ = one[rank[p * words + w] + __builtin_popcountll(all[p * words + w] & ((x & (~x + 1)) - 1))];
+        }
+        while ((out - to) % G) *out++ = make_int2(-1, 0);
+        plan.pairs.insert(plan.pairs.end(), (out - to) / G, make_int2(p, -1));
     }
+    plan.size = out - plan.grp.get();
+    return plan;
 }
 #if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
 #pragma clang attribute pop

@@ -171,6 +171,7 @@ struct spin_tables {
     // whole rows (FP32), long rows over several lanes (FP64)
     ab_table ab32, ab64;
     void* table_mem = nullptr;    // one allocation: the sliced tables with their plans, the values, e_same
+    const int* by_singles = nullptr;   // the strings by decreasing number of singles (order of the gather's rows)
     int max_singles = 0, max_doubles = 0;
     // host copies for the schedules that are planned there: strings and row
     // offsets from the build, the gather form on demand (sqd_host_singles)
@@ -210,6 +211,7 @@ template <typename K>
 struct ab_schedule {
     void* mem = nullptr;          // null: not built
     int G = 0, n = 0;             // singles (or sources) per chunk, chunks
+    int n2 = 0;                   // blocks of two pairs, which come first
     int64_t bytes = 0;
     const int2* grp = nullptr;    // alpha singles of each chunk: CSR position (-1 = padding), gather form
     const K* key = nullptr;       // what the singles of a chunk share
@@ -234,14 +236,14 @@ struct sqd_space {
     // (key: the pair of each chunk)
     ab_schedule<int> ab;
     // blocks of the one-launch products: G sources by one or two pairs (key: the
-    // pairs, second -1: one pair; grp: G singles of the first pair, G of the second).
+    // pairs, second -1: one pair; grp: in blocks of two pairs G singles of the first
+    // and G of the second).
     // FP64 and FP32 products of one space can take different G: one schedule for
     // each, kept as long as the space (captured products hold its pointers)
     ab_schedule<int2> abb[2];
     ab_schedule<int2>& blocks(int G) { return abb[G == 4]; }   // G: 2 or 4
     const ab_schedule<int2>& blocks(int G) const { return abb[G == 4]; }
     int* ab_rev = nullptr;        // alpha singles: entry of the neighbour's row pointing back
-    int* ab_row_order = nullptr;  // alpha rows by decreasing number of singles (gather order)
     // the same singles grouped by source string (rows too long for two
     // staged sources: one staged source row serves several pairs; key: the source
     // alpha string of each chunk)

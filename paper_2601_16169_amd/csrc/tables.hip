@@ -589,7 +589,7 @@ int sqd_build_spin_tables(sqd_ctx* ctx, sqd_space* sp, int spin, const uint64_t*
             {&p64.split, &t.ss64.split}, {&a32.perm, &t.ab32.perm}, {&a32.blk, &t.ab32.blk},   {&a32.cols, &t.ab32.cols},
             {&a32.slot, &t.ab32.slot}, {&a32.bin, &t.ab32.bin},   {&a32.order, &t.ab32.order}, {&a64.perm, &t.ab64.perm},
             {&a64.blk, &t.ab64.blk},   {&a64.cols, &t.ab64.cols}, {&a64.slot, &t.ab64.slot},   {&a64.bin, &t.ab64.bin},
-            {&a64.split, &t.ab64.split}};
+            {&a64.split, &t.ab64.split}, {&rows_s, &t.by_singles}};
         std::vector<int> all;
         for (const auto& q : parts) all.insert(all.end(), q.first->begin(), q.first->end());
         // the sliced tables, their plans and the values (CSR order) in one allocation:

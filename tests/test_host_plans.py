@@ -164,3 +164,69 @@ int main() {
     return 0;
 }
 """)
+
+
+@pytest.mark.parametrize("norb", [12, 70])
+def test_blocks_hold_every_single_once(tmp_path, norb):
+    """Blocks of the alpha-beta term: the singles of a block share their pair and, side
+    by side in blocks of two pairs, their source; blocks of two pairs come first; every
+    single is in one block; padding only fills the last block of a pair.  Strings of one
+    and two words, sets from one string to most of all, around the 64 bits of a word."""
+    _run(tmp_path, r"""
+#include <map>
+#include <random>
+typedef unsigned __int128 str;
+int main() {
+    const int norb = NORB, nel = norb > 64 ? 3 : 6;
+    std::mt19937_64 rng(5);
+    for (int n : {1, 3, 63, 64, 65, 129, 500}) {
+        std::map<str, int> at;
+        while ((int)at.size() < n) {      // most from the lowest orbitals: dense in singles
+            str s = 0;
+            for (int left = nel; left;) {
+                const int k = (int)(rng() % (rng() % 4 ? nel + 5 : norb));
+                const int o = norb > 64 && rng() % 2 ? norb - 1 - k : k;
+                if (!(s >> o & 1)) s |= (str)1 << o, --left;
+            }
+            at[s] = 0;
+        }
+        int idx = 0;
+        for (auto& x : at) x.second = idx++;
+        std::vector<uint32_t> pk;
+        for (const auto& t : at) {
+            std::map<int, uint32_t> row;
+            for (int a = 0; a < norb; ++a)
+                for (int i = 0; i < norb; ++i) {
+                    if (!(t.first >> a & 1) || (t.first >> i & 1)) continue;
+                    const auto s = at.find(t.first ^ ((str)1 << a) ^ ((str)1 << i));
+                    if (s == at.end()) continue;
+                    row[s->second] = (uint32_t)s->second | (uint32_t)(a * norb + i) << SQD_PAIR_SHIFT | (uint32_t)(rng() % 2) << 31;
+                }
+            for (const auto& e : row) pk.push_back(e.second);
+        }
+        for (int G : {2, 4}) {
+            const ab_block_plan p = plan_ab_blocks(pk, n, norb, G);
+            REQUIRE(p.size == (size_t)p.n2 * 2 * G + (p.pairs.size() - p.n2) * G);
+            std::vector<int> seen(pk.size(), 0);
+            for (size_t k = 0; k < p.pairs.size(); ++k) {
+                const bool two = k < (size_t)p.n2;
+                const int2* g = p.grp.get() + (k + (two ? k : (size_t)p.n2)) * G;
+                REQUIRE((p.pairs[k].y >= 0) == two);
+                for (int r = 0; r < (two ? 2 * G : G); ++r) {
+                    if (g[r].x < 0) {
+                        REQUIRE(!two && r > 0 && (k + 1 == p.pairs.size() || p.pairs[k + 1].x != p.pairs[k].x));
+                        continue;
+                    }
+                    const uint32_t x = pk[g[r].x];
+                    REQUIRE((uint32_t)g[r].y == x && !seen[g[r].x]++);
+                    REQUIRE((int)((x >> SQD_PAIR_SHIFT) & SQD_PAIR_MASK) == (r < G ? p.pairs[k].x : p.pairs[k].y));
+                    if (r >= G) REQUIRE((x & SQD_NBR_MASK) == ((uint32_t)g[r - G].y & SQD_NBR_MASK));
+                }
+            }
+            for (int s : seen) REQUIRE(s == 1);
+            if (n == 500) REQUIRE(p.n2 > 0);
+        }
+    }
+    return 0;
+}
+""".replace("NORB", str(norb)))
