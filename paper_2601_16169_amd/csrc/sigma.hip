@@ -623,6 +623,31 @@ struct fused_shape { int R = 0, G = 0, waves = 0; size_t lds = 0; };
 // lanes, and are faster in one launch as far as four rows fit: n = 600 x 500: 49 /
 // 45, 2000: 315 / 296, 3000: 767 / 677, 4200: 2180 / 1472, 5500: 3826 / 2601 (rows
 // as above / over several lanes; eight rows 49, 307, 726, 2310, 3830).
+//
+// Products whose time is the walk over the long rows of a dense set (more than 235
+// singles and doubles a string) are an exception where the separate kernels fill the
+// chip with a better form of that walk.  FP64: eight rows by windows instead of two
+// whole ones, and singles grouped by source, where the other spin has strings enough
+// for either; of four whole rows, one round of alpha-alpha workgroups that have a
+// compute unit each, beside which the one launch holds its short beta rows to one
+// workgroup a unit too.  us, separate / one, entries a string: 2000 x 9000 strings, 593:
+// 6080 / 7290, 275: 2940 / 3330, but 191: 2640 / 2820 and 176: equal; 9000 x 2000, 593:
+// 8270 / 9720, 244: 3570 / 4160; 5500 x 5500, 390: 13480 / 14330, 211: 6750 / 6670; 5500
+// x 800, 390: 2110 / 1980, 1040: 2440 / 2560; 1000 x 9000, 593: 3760 / 3040; 4000 x 1000
+// (250 workgroups), 302: 1100 / 1180, 196: equal, 4000 x 1040: 1370 / 1210, 800: 1000 / 950.
+// FP32 in any order: long alpha rows and one or two rounds of workgroups, an iteration of
+// a solve: 9000 x 1000, 593: 2230 / 3070, 324: 1490 / 1800, 189: 1340 / 1210; 9000 x 2000,
+// 593: 4680 / 4960; 5500 x 1000, 390: 1060 / 1450; 5500 x 3500: 5090 / 4140, 9000 x 500:
+// 1810 / 1770; 4000 x 1000, 302: 700 / 800; 1000 x 9000: 2190 / 1710.
+bool fused_slower(sqd_ctx* ctx, const sqd_space* sp, const fused_shape& f, size_t es) {
+    const int64_t na = sp->sp[0].n, nb = sp->sp[1].n, cu = ctx->num_cu;
+    const spin_tables& t = sp->sp[nb > na];
+    if (t.nnz_s + t.nnz_d <= 235 * t.n) return false;
+    const int64_t blocks = (nb + 3) / 4;   // four-row workgroups of the alpha-alpha term
+    if (es == sizeof(float)) return 2 * na > 3 * nb && 10 * blocks >= 9 * cu && blocks <= 2 * cu;
+    if (f.R == 2) return na >= nb ? 2 * nb >= 7 * cu : 10 * na >= 9 * 8 * cu;
+    return f.lds > (size_t)ctx->max_lds / 2 && 10 * blocks >= 9 * cu && blocks <= cu;
+}
 fused_shape fused_pick(sqd_ctx* ctx, const sqd_space* sp, size_t es, unsigned mask, int ab_path,
                        bool any_order = false) {
     fused_shape f;
@@ -639,6 +664,7 @@ fused_shape fused_pick(sqd_ctx* ctx, const sqd_space* sp, size_t es, unsigned ma
     else if (es == sizeof(double) && bytes(2) <= lim) f.R = 2;
     f.G = f.R;
     f.lds = f.R ? bytes(f.R) : 0;
+    if (f.R && (es == sizeof(double) || any_order) && fused_slower(ctx, sp, f, es)) return fused_shape();
     f.waves = f.lds <= lim / (es == sizeof(double) ? 2 : 4) ? 8 : 16;
     return f;
 }
