@@ -31,6 +31,11 @@ from . import sqd
 
 CACHE = os.environ.get("SQD_TUNE_CACHE", os.path.join(os.path.dirname(os.path.abspath(__file__)), "tune_cache.json"))
 
+# Stored with every entry's key: raised when the library's automatic choice changes
+# so that a forced setting found before may be slower than it (2: all terms in one
+# launch).  Entries of another generation are not used.
+GENERATION = 2
+
 Setting = Tuple[int, ...]   # key, value, key, value, ...
 
 # rows staged x waves (whole rows), or windows of source strings (for rows too
@@ -52,6 +57,10 @@ def signature(space: "sqd.Space", precision: int) -> str:
     i = space.info()
     return (f"na{i['na']}_nb{i['nb']}_norb{i['norb']}_e{i['nalpha']}-{i['nbeta']}"
             f"_s{i['nnz_single'][0]}-{i['nnz_single'][1]}_d{i['nnz_double'][0]}-{i['nnz_double'][1]}_p{precision}")
+
+
+def _key(sig: str) -> str:
+    return f"{_device_name()}|g{GENERATION}|{sig}"
 
 
 def batch_signature(spaces: Sequence["sqd.Space"], mode: int) -> str:
@@ -140,7 +149,7 @@ def tune(space: "sqd.Space", precision: int = sqd.FP64, reps: int = 10, use_cach
     {group: (setting, ms)} and leaves the fastest setting applied."""
     import torch
     ctx = space.ctx
-    key = _device_name() + "|" + signature(space, precision)
+    key = _key(signature(space, precision))
     if use_cache:
         cached = _load().get(key)
         if cached:
@@ -177,7 +186,7 @@ def tune_batched(ctx, spaces: Sequence["sqd.Space"], mode: int = sqd.DAV_MIXED, 
     stops early) and the wall time after the first is compared.  Leaves the
     fastest setting applied on ``ctx``."""
     import torch
-    key = _device_name() + "|" + batch_signature(spaces, mode)
+    key = _key(batch_signature(spaces, mode))
     if use_cache:
         cached = _load().get(key)
         if cached:
