@@ -520,7 +520,6 @@ sell_plan plan_slices(const std::vector<int>& rows, const int* s_off, const int*
 }
 
 // Sizes of a sliced table from its plan, and its arrays among those to be allocated.
-using array_list = std::vector<std::pair<void**, size_t>>;
 constexpr int64_t kMaxSlots = (1LL << 31) - 1;
 template <typename T>
 bool size_sell(const sell_plan& p, sell_table<T>& L, array_list& arrays) {
@@ -592,9 +591,7 @@ int sqd_build_spin_tables(sqd_ctx* ctx, sqd_space* sp, int spin, const uint64_t*
             {&a64.split, &t.ab64.split}, {&rows_s, &t.by_singles}};
         std::vector<int> all;
         for (const auto& q : parts) all.insert(all.end(), q.first->begin(), q.first->end());
-        // the sliced tables, their plans and the values (CSR order) in one allocation:
-        // each of some megabytes costs 0.3 ms to make and as much to free (2000 + 2000
-        // strings of 16 orbitals, build and free: 5.6 ms with an allocation an array, 3.4 so)
+        // the sliced tables, their plans and the values (CSR order)
         int* index = nullptr;
         array_list arrays = {{(void**)&index, sizeof(int) * (all.size() + 1)},
                              {(void**)&t.s_val64, sizeof(double) * (t.nnz_s + 1)},
@@ -606,14 +603,7 @@ int sqd_build_spin_tables(sqd_ctx* ctx, sqd_space* sp, int spin, const uint64_t*
                              size_ab(a32, t.ab32, arrays), size_ab(a64, t.ab64, arrays)};
         for (bool f : fits)
             if (!f) return sqd_fail(ctx, SQD_E_LIMIT, "sliced table exceeds 2^31 slots");
-        size_t total = 0;
-        for (const auto& q : arrays) total += (q.second + 255) & ~(size_t)255;
-        if ((rc = sqd_alloc(ctx, &t.table_mem, total, &sp->bytes))) return rc;
-        char* mem = static_cast<char*>(t.table_mem);
-        for (const auto& q : arrays) {
-            *q.first = mem;
-            mem += (q.second + 255) & ~(size_t)255;
-        }
+        if ((rc = alloc_arrays(ctx, arrays, t.table_mem, &sp->bytes))) return rc;
         SQD_HIP(ctx, hipMemcpy(index, all.data(), sizeof(int) * all.size(), hipMemcpyHostToDevice));
         const int* at = index;
         for (const auto& q : parts) {
@@ -697,7 +687,8 @@ int sqd_build_values(sqd_ctx* ctx, sqd_space* sp) {
 void sqd_free_spin_tables(spin_tables* t) {
     if (t->alias) { *t = spin_tables(); return; }
     sqd_free_window_tables(t);
-    void* ptrs[] = {t->table_mem, t->split32.val, t->str, t->s_off, t->s_ent, t->d_off, t->d_ent, t->s_pk, t->d_nbr};
+    for (void* p : t->table_mem) (void)hipFree(p);
+    void* ptrs[] = {t->split32.val, t->str, t->s_off, t->s_ent, t->d_off, t->d_ent, t->s_pk, t->d_nbr};
     for (void* p : ptrs)
         if (p) hipFree(p);
     *t = spin_tables();

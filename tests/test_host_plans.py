@@ -166,6 +166,61 @@ int main() {
 """)
 
 
+def test_arrays_share_few_allocations(tmp_path):
+    """Arrays of a space in few allocations: each in one of them, aligned and clear of
+    the others; small ones in blocks that stay within the size that the runtime keeps at
+    hand, the larger ones in one; where an allocation fails, those made are listed.  Sizes
+    around that limit, none large, none small, empty arrays, no arrays."""
+    _run(tmp_path, r"""
+int main() {
+    const size_t lim = 2000u << 10;
+    const std::vector<std::vector<size_t>> cases = {
+        {}, {0}, {1, 255, 256, 257}, {lim, 1, lim - 256, 256, 1}, {lim + 1}, {5, 3 * lim, lim - 255, lim + 256, 7},
+        {lim / 2, lim / 2 - 256, 256, 256, lim / 2}, {4 * lim, 0, 0, 9}};
+    for (const auto& sizes : cases) {
+        size_t used = 0;
+        for (int fail = 0;; ++fail) {                  // the allocations that succeed first
+            std::vector<void*> at(sizes.size(), nullptr), mem;
+            array_list arrays;
+            for (size_t k = 0; k < sizes.size(); ++k) arrays.push_back({&at[k], sizes[k]});
+            int64_t bytes = 0;
+            allocs_left = fail;
+            const int rc = alloc_arrays(nullptr, arrays, mem, &bytes);
+            allocs_left = 1 << 30;
+            REQUIRE((int)mem.size() == held);
+            if (rc == SQD_OK) {
+                int nlarge = 0, from_block = 0;
+                for (size_t k = 0; k < sizes.size(); ++k) {
+                    const size_t pad = (sizes[k] + 255) / 256 * 256;
+                    nlarge += pad > lim;
+                    int owner = -1;
+                    for (size_t m = 0; m < mem.size(); ++m)
+                        if ((char*)at[k] >= (char*)mem[m] && (owner < 0 || mem[m] > mem[owner])) owner = (int)m;
+                    REQUIRE(owner >= 0 && ((char*)at[k] - (char*)mem[owner]) % 256 == 0);
+                    if (pad <= lim) {
+                        REQUIRE((char*)at[k] + pad <= (char*)mem[owner] + lim);
+                        from_block += (char*)at[k] == (char*)mem[owner];
+                    }
+                    std::memset(at[k], (int)k + 1, sizes[k]);
+                }
+                for (size_t k = 0; k < sizes.size(); ++k)
+                    for (size_t i = 0; i < sizes[k]; ++i) REQUIRE(((unsigned char*)at[k])[i] == k + 1);
+                REQUIRE((int)mem.size() <= from_block + (nlarge > 0) && bytes % 256 == 0);
+                used = mem.size();
+            }
+            for (void* p : mem) hipFree(p);
+            REQUIRE(held == 0);
+            if (rc == SQD_OK) {
+                REQUIRE((size_t)fail == used);
+                break;
+            }
+        }
+    }
+    return 0;
+}
+""")
+
+
 @pytest.mark.parametrize("norb", [12, 70])
 def test_blocks_hold_every_single_once(tmp_path, norb):
     """Blocks of the alpha-beta term: the singles of a block share their pair and, side
