@@ -277,10 +277,12 @@ int sqd_diag(sqd_ctx* ctx, const sqd_space* space, double* diag_dev);
  * shared by the graph and eager calls on the same context (do not run them
  * concurrently); eager calls that need a larger scratch later keep the
  * captured buffer alive until sqd_release_workspace or sqd_destroy, after
- * which the graph must not be replayed.  A later call that changes how the
- * space's alpha singles are grouped (another SQD_TUNE_AB_* setting, or a
- * batched solve that includes the space) rebuilds that schedule: graphs
- * captured on the space before must then not be replayed either. */
+ * which the graph must not be replayed.  Products with a launch per term (single
+ * terms, SQD_TUNE_* settings, long rows) keep one grouping of the space's alpha
+ * singles: a later call that changes it (another SQD_TUNE_AB_* setting, or a batched
+ * solve that includes the space) rebuilds it, and graphs captured of such products
+ * on the space before must then not be replayed either.  Whole products in one
+ * launch keep theirs, of each precision, until the space is destroyed. */
 int sqd_sigma(sqd_ctx* ctx, const sqd_space* space, const double* c_dev,
               double* sigma_dev, int precision, unsigned terms_mask, int ab_path);
 
@@ -296,8 +298,9 @@ int sqd_sigma(sqd_ctx* ctx, const sqd_space* space, const double* c_dev,
  * (as for SQD_TUNE_AB_VARIANT 2); beyond either SQD_E_LIMIT, before anything
  * is enqueued.  Where a same-spin term takes the windowed kernel (rows too
  * long to stage four whole in LDS), its tables are built by the space's first
- * sqd_sigma call with that term and precision; until then SQD_E_STATE, before
- * anything is enqueued.  After a Hamiltonian change the first call refreshes the
+ * sqd_sigma call with that term and precision, or, where that call was a whole
+ * product in one launch, not needed (the term then stages whole rows); until then
+ * SQD_E_STATE, before anything is enqueued.  After a Hamiltonian change the first call refreshes the
  * space's values in place (kernels and a synchronisation; under capture it
  * returns SQD_E_STATE instead).  All calls on one GPU share the array and it
  * keeps the last call's contents (every word the product reads is written by

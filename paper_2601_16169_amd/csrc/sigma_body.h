@@ -440,7 +440,7 @@ __device__ __forceinline__ void abg_block(const abg_args<T>& a, const T* __restr
 // The same Y from blocks of G sources by one or two pairs (sqd_ensure_ab_blocks):
 // where the G staged rows of C serve two pairs, an entry of the table costs 8 G
 // bytes of LDS for C and 16 for the integrals for 2 G products instead of 8 G + 8
-// for G, and the table is read once for both (2000 strings per spin, norb 24: 6100
+// for G, and the table is read once for both (2000 strings per spin, norb 16: 6100
 // walks of the beta table in place of 8800, sigma FP64 715 -> 653 us, FP32
 // 411 -> 389).  Same products and summation order as abg_block.
 template <typename T>

@@ -199,9 +199,10 @@ inline ab_plan plan_ab(const std::vector<int>& rows, const int* off, int cap) {
 }
 
 // Cross-spin tables (spin_tables::ws64, ws32) of the spins whose rows of C fit the
-// LDS four at a time, up to 256 MiB each, in one allocation.  Elsewhere, and where
-// that allocation fails, the row-staged kernel sums them itself (norb reads per value
-// and workgroup); the windowed kernel has its own.
+// LDS four at a time, up to 256 MiB each, in one allocation.  Elsewhere (one-launch
+// products that stage two rows among them), and where that allocation fails, the
+// workgroups sum them themselves (norb reads per value); the windowed kernel has its
+// own.
 inline void alloc_cross_tables(sqd_ctx* ctx, sqd_space* sp) {
     const size_t n2 = (size_t)sp->norb * sp->norb;
     size_t total = 0, bytes64[2] = {}, bytes32[2] = {};

@@ -154,7 +154,7 @@ __device__ __forceinline__ void lowest_pairs(double (&a)[MT], int m, int k, eig_
     constexpr int L = 64 / KR;
     const int r = lane / L, sub = lane - r * L;   // this lane's root and section
     double lo = glo * inv - 4e-16, hi = ghi * inv + 4e-16;
-    constexpr int kRounds = KR == 1 ? 9 : KR == 2 ? 11 : KR == 4 ? 13 : 17;   // (L + 1)^rounds > 2^54
+    constexpr int kRounds = KR == 1 ? 9 : KR == 2 ? 11 : KR == 4 ? 13 : 17;   // (L + 1)^rounds > 2^53
     for (int it = 0; it < kRounds; ++it) {
         const double width = hi - lo;
         const double x = lo + width * ((double)(sub + 1) * (1.0 / (L + 1)));

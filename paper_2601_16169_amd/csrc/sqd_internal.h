@@ -151,7 +151,7 @@ struct spin_tables {
     int* d_off = nullptr;
     uint64_t* d_ent = nullptr;
     int64_t nnz_s = 0, nnz_d = 0;
-    // gather form of the singles: nbr | pair << 19 | negative << 31
+    // gather form of the singles: nbr | pair << SQD_PAIR_SHIFT | negative << 31
     uint32_t* s_pk = nullptr;
     int* d_nbr = nullptr;
     // integral-dependent values (rebuilt when the Hamiltonian changes)
