@@ -326,11 +326,12 @@ spin_tables& owner(sqd_space* sp, const spin_tables& t) {
 // when fewer than four rows fit in one workgroup's LDS.  Measured on MI355X
 // on norb-36 spaces of n strings per spin (same-spin beta-beta / alpha-alpha
 // terms, ms, row-staged against windowed): FP64 with two rows staged, n =
-// 4000: 1.41 / 1.55 against 1.00 / 0.91; n = 8000: 5.75 / 6.18 against 4.64 /
-// 3.99; one row, n = 16000: 48.6 / 50.8 against 23.6 / 21.5.  FP32 with four
-// rows staged, n = 6000: 1.29 / 1.44 against 1.56 / 1.48; n = 8000: 2.25 /
-// 2.50 against 2.53 / 2.35; two rows, n = 10000: 5.41 / 5.82 against 4.65 /
-// 4.23; n = 16000: 15.0 / 16.0 against 12.9 / 11.0.
+// 4000: 0.64 / 0.79 against 0.72 / 0.80; n = 8000: 2.93 / 3.52 against 3.09 /
+// 3.25 (denser sets want the windows: see fused_slower); one row, n = 10000:
+// 9.06 / 9.97 against 5.17 / 5.35; n = 16000: 29.5 / 31.7 against 20.5 / 20.4.
+// FP32 with four rows staged, n = 6000: 1.25 / 1.40 against 1.25 / 1.39; n =
+// 8000: 2.18 / 2.44 against 1.83 / 2.16; two rows, n = 10000: 5.60 / 6.01
+// against 3.54 / 4.00; n = 16000: 14.0 / 15.1 against 10.6 / 10.8.
 bool use_window(sqd_ctx* ctx, int64_t nrows, int64_t ncols, int norb, size_t es) {
     const int mode = ctx->tune[SQD_TUNE_SS_WINDOW];
     if (mode == 1) return false;
