@@ -76,10 +76,10 @@ int upload_schedule(sqd_ctx* ctx, int G, const std::vector<int2>& grp, const std
 // much to unmap.  So arrays below that go side by side into blocks of as much, and the
 // larger ones all into one.  Building and freeing a space of other strings each time,
 // ms, an allocation an array / one for all / so: 1600 + 1600 strings of 16 orbitals
-// 2.1 / 3.2 / 2.1, 2000 + 2000: 3.4 / 4.3 / 3.8, 4000 + 4000 of 20: 10.9 / 6.0 / 5.9.
+// 2.1 / 3.2 / 2.1, 2300 + 2300: 7.0 / 5.6 / 4.7, 4000 + 4000 of 20: 10.9 / 6.0 / 5.9.
 using array_list = std::vector<std::pair<void**, size_t>>;
+constexpr size_t kBlock = 2000u << 10;
 inline int alloc_arrays(sqd_ctx* ctx, const array_list& arrays, std::vector<void*>& mem, int64_t* counter) {
-    constexpr size_t kBlock = 2000u << 10;
     auto padded = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
     auto place = [&](const std::vector<size_t>& which) -> int {
         size_t total = 0;
@@ -114,6 +114,25 @@ inline int alloc_arrays(sqd_ctx* ctx, const array_list& arrays, std::vector<void
     }
     if (!block.empty() && (rc = place(block))) return rc;
     return large.empty() ? SQD_OK : place(large);
+}
+
+// The sliced tables and values of a spin, as above; but the runtime also keeps up to 64
+// MiB of freed larger allocations, by size, and those of a space with up to 18 MiB a spin
+// are found there again if each array has its own.  Build and free, one space after the
+// other, ms, larger arrays in one allocation / in one each: 1800 + 1800 strings of 16
+// orbitals (13 MiB a spin) 3.1 / 2.5, 2000 + 2000 (16) 3.9 / 2.7, 2200 + 2200 (18.5) 4.1 /
+// 4.3, 2400 + 2400 (21) 4.2 / 7.2.
+inline int alloc_tables(sqd_ctx* ctx, const array_list& arrays, std::vector<void*>& mem, int64_t* counter) {
+    size_t total = 0;
+    for (const auto& q : arrays) total += q.second;
+    if (total > (size_t)18 << 20) return alloc_arrays(ctx, arrays, mem, counter);
+    array_list small;
+    for (const auto& q : arrays) {
+        int rc;
+        if (q.second <= kBlock) small.push_back(q);
+        else if ((rc = alloc_arrays(ctx, {q}, mem, counter))) return rc;
+    }
+    return alloc_arrays(ctx, small, mem, counter);
 }
 
 // Rows by decreasing length (ties by index): a counting sort.

@@ -170,7 +170,7 @@ struct spin_tables {
     // sliced singles for the alpha-beta kernels, rows sorted by their count:
     // whole rows (FP32), long rows over several lanes (FP64)
     ab_table ab32, ab64;
-    std::vector<void*> table_mem; // the sliced tables with their plans, the values, e_same (alloc_arrays)
+    std::vector<void*> table_mem; // the sliced tables with their plans, the values, e_same (alloc_tables)
     const int* by_singles = nullptr;   // the strings by decreasing number of singles (order of the gather's rows)
     int max_singles = 0, max_doubles = 0;
     // host copies for the schedules that are planned there: strings and row

@@ -603,7 +603,7 @@ int sqd_build_spin_tables(sqd_ctx* ctx, sqd_space* sp, int spin, const uint64_t*
                              size_ab(a32, t.ab32, arrays), size_ab(a64, t.ab64, arrays)};
         for (bool f : fits)
             if (!f) return sqd_fail(ctx, SQD_E_LIMIT, "sliced table exceeds 2^31 slots");
-        if ((rc = alloc_arrays(ctx, arrays, t.table_mem, &sp->bytes))) return rc;
+        if ((rc = alloc_tables(ctx, arrays, t.table_mem, &sp->bytes))) return rc;
         SQD_HIP(ctx, hipMemcpy(index, all.data(), sizeof(int) * all.size(), hipMemcpyHostToDevice));
         const int* at = index;
         for (const auto& q : parts) {

@@ -221,6 +221,49 @@ int main() {
 """)
 
 
+def test_tables_of_a_spin_are_allocated_once(tmp_path):
+    """The tables of a spin, small and large in all: every array set and clear of the
+    others, the larger ones of small tables each at the start of an allocation, and after
+    a failed allocation those made are listed.  Totals around the limit between the two."""
+    _run(tmp_path, r"""
+int main() {
+    const size_t lim = 2000u << 10, all = (size_t)18 << 20;
+    const std::vector<std::vector<size_t>> cases = {
+        {}, {100, lim, lim + 1, lim + 2, 7}, {3 * lim, 5, all - 3 * lim - 5}, {3 * lim, 6, all - 3 * lim - 5}, {lim, 4096}};
+    for (const auto& sizes : cases) {
+        size_t total = 0;
+        for (size_t b : sizes) total += b;
+        for (int fail = 0;; ++fail) {
+            std::vector<void*> at(sizes.size(), nullptr), mem;
+            array_list arrays;
+            for (size_t k = 0; k < sizes.size(); ++k) arrays.push_back({&at[k], sizes[k]});
+            int64_t bytes = 0;
+            allocs_left = fail;
+            const int rc = alloc_tables(nullptr, arrays, mem, &bytes);
+            allocs_left = 1 << 30;
+            REQUIRE((int)mem.size() == held);
+            if (rc == SQD_OK) {
+                size_t starts = 0;
+                for (size_t k = 0; k < sizes.size(); ++k) {
+                    const bool first = std::find(mem.begin(), mem.end(), at[k]) != mem.end();
+                    starts += first;
+                    REQUIRE(at[k] && (first || sizes[k] <= lim || total > all));
+                    std::memset(at[k], (int)k + 1, sizes[k]);
+                }
+                REQUIRE(mem.size() == starts);
+                for (size_t k = 0; k < sizes.size(); ++k)
+                    for (size_t i = 0; i < sizes[k]; ++i) REQUIRE(((unsigned char*)at[k])[i] == k + 1);
+            }
+            for (void* p : mem) hipFree(p);
+            REQUIRE(held == 0);
+            if (rc == SQD_OK) break;
+        }
+    }
+    return 0;
+}
+""")
+
+
 @pytest.mark.parametrize("norb", [12, 70])
 def test_blocks_hold_every_single_once(tmp_path, norb):
     """Blocks of the alpha-beta term: the singles of a block share their pair and, side
