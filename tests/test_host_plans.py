@@ -166,6 +166,54 @@ int main() {
 """)
 
 
+def test_parts_arrive_whole(tmp_path):
+    """Host arrays side by side on the device, copied singly or gathered: all bytes
+    arrive, aligned, whatever the sizes around the limit of a gathered copy, empty ones
+    among them; where a copy fails nothing is held and the caller's pointer stays."""
+    _run(tmp_path, r"""
+int main() {
+    const size_t lim = 64 << 10;
+    const std::vector<std::vector<size_t>> cases = {
+        {}, {0, 0}, {1}, {lim}, {lim + 1}, {lim - 256, 256}, {lim - 256, 257}, {1, 0, 255, 256, 257, 0},
+        {3 * lim, 5, 0, lim / 2, lim / 2, 7, 2 * lim, 9}, {5, 3 * lim, 8, 8}, {lim / 2, lim / 2, lim / 2, lim / 2, lim / 2}};
+    for (const auto& sizes : cases) {
+        std::vector<std::vector<unsigned char>> data;
+        std::vector<host_part> parts;
+        size_t sum = 0;
+        for (size_t b : sizes) {
+            data.emplace_back(b);
+            for (size_t i = 0; i < b; ++i) data.back()[i] = (unsigned char)(1 + (i * 7 + data.size()) % 251);
+            sum += b;
+        }
+        for (const auto& d : data) parts.push_back({d.data(), d.size()});
+        for (int fail = 0;; ++fail) {
+            std::vector<size_t> off(sizes.size() + 1, 0);
+            void* mem = nullptr;
+            int64_t bytes = 0;
+            copies_left = fail;
+            const int rc = upload_parts(nullptr, parts.data(), (int)parts.size(), &mem, off.data(), &bytes);
+            const int copies = fail - copies_left;
+            copies_left = 1 << 30;
+            if (rc) {
+                REQUIRE(!mem && !held && !bytes);
+                continue;
+            }
+            REQUIRE(mem && held == 1 && bytes >= (int64_t)sum);
+            for (size_t k = 0; k < sizes.size(); ++k) {
+                REQUIRE(off[k] % 256 == 0 && off[k] + sizes[k] <= (size_t)bytes);
+                REQUIRE(!std::memcmp((char*)mem + off[k], data[k].data(), sizes[k]));
+            }
+            if (sizes.empty() || off[sizes.size() - 1] + sizes.back() <= lim) REQUIRE(copies <= 1);
+            hipFree(mem);
+            break;
+        }
+    }
+    REQUIRE(held == 0);
+    return 0;
+}
+""")
+
+
 def test_arrays_share_few_allocations(tmp_path):
     """Arrays of a space in few allocations: each in one of them, aligned and clear of
     the others; small ones in blocks that stay within the size that the runtime keeps at
